@@ -118,6 +118,42 @@ def test_sym_eig_against_oracle(rq, K, r):
     assert np.allclose(p[:, :r] @ p[:, :r].T, p_ref[:, :r] @ p_ref[:, :r].T, atol=1e-4)
 
 
+# orders that take the single-launch kernel (at most 128): the smallest, odd and even numbers of
+# pairs, one more column than a slice of the vectors holds, and the first order beyond it
+@pytest.mark.parametrize("K", [2, 4, 6, 18, 30, 32, 62, 98, 126, 128, 130])
+def test_sym_eig_small_orders(rq, K):
+    g = torch.Generator().manual_seed(K)
+    x = torch.randn(2 * K + 3, K, generator=g, dtype=torch.float64) * torch.exp(-3.0 * torch.arange(K) / K)
+    c = torch.zeros(K, K + 8)
+    c[:, :K] = (x.T @ x).float()
+    buf = torch.full((K, K + 3), 7.0, device="cuda")
+    lam, p = torch.empty(K, device="cuda"), buf[:, :K]
+    rq.resq_sym_eig_static(c.cuda()[:, :K], lam, p)
+    torch.cuda.synchronize()
+    c64 = c[:, :K].double().numpy()
+    lam_ref = np.linalg.eigvalsh(c64)[::-1]
+    lam, p = lam.double().cpu().numpy(), p.double().cpu().numpy()
+    assert torch.all(buf[:, K:] == 7.0)
+    # fp32 outputs of an fp64 iteration: half an fp32 step of the largest value, of each entry of a vector
+    assert np.abs(lam - lam_ref).max() <= 1e-7 * lam_ref[0]
+    assert np.allclose(p.T @ p, np.eye(K), atol=1e-6)
+    assert np.abs(c64 @ p - p * lam).max() <= 1e-6 * lam_ref[0]
+
+
+def test_sym_eig_small_orders_without_rotations(rq):
+    # nothing to rotate, singular and indefinite input
+    lam, p = rq.resq_sym_eig(torch.zeros(64, 64, device="cuda"))
+    assert torch.all(lam == 0) and torch.equal(p, torch.eye(64, device="cuda"))
+    one = torch.ones(16, 16)
+    one[0, 0] = -3.0
+    lam, p = rq.resq_sym_eig(one.cuda())
+    torch.cuda.synchronize()
+    ref = np.linalg.eigvalsh(one.double().numpy())[::-1]
+    assert np.allclose(lam.double().cpu().numpy(), ref, atol=2e-6)
+    pd = p.double().cpu().numpy()
+    assert np.allclose(pd @ np.diag(ref) @ pd.T, one.numpy(), atol=1e-5)
+
+
 def test_sym_eig_repeated_eigenvalues_and_diagonal_input(rq):
     # a matrix that is already diagonal with a repeated value: sorted, vectors a permutation
     d = np.array([3.0, 1.0, 3.0, 2.0, 0.0, 5.0, 1.0, 4.0])
