@@ -12,6 +12,7 @@
 #include "resq_gemm.hip.h"
 #include "resq_gemm_m64.hip.h"
 #include "resq_basis.hip.h"
+#include "resq_project.hip.h"
 #include "resq_hadamard.hip.h"
 #include "resq_headproj.hip.h"
 #include "resq_layout.h"
@@ -788,21 +789,29 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
     if (!aligned(a, 16) || !aligned(u, 16) || !aligned(out, out_is_bf16 ? 2 : 4) || lda % 8 != 0 ||
         ldu % 8 != 0 || J % 8 != 0)
         return RESQ_ERR_ALIGN;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const dim3 grid((unsigned)((J + kBasisTile - 1) / kBasisTile), (unsigned)((rows + kBasisTile - 1) / kBasisTile), 1);
+    // bf16 rows: three exact bf16 products instead of one fp32 product, at every size (same
+    // tiles and grid as the fp32 kernel; PROJFIG); fp32 rows would need at least six, and stay on the fp32 instruction
+    if (a_is_bf16) {
+        ProjectArgs pa;
+        pa.a = static_cast<const uint16_t*>(a);
+        pa.u = u;
+        pa.out = out;
+        pa.lda = lda; pa.ldu = ldu; pa.ldo = ldo;
+        pa.I = rows; pa.J = J; pa.T = K;
+        if (out_is_bf16) launch(project_split_kernel<true>, grid, dim3(kProjThreads), 0, st, pa);
+        else launch(project_split_kernel<false>, grid, dim3(kProjThreads), 0, st, pa);
+        return launch_status();
+    }
     BasisGemmArgs g;
     g.a = a; g.b = u; g.c = out;
     g.lda = lda; g.ldb = ldu; g.ldc = ldo;
     g.I = rows; g.J = J; g.T = K;
     g.accumulate = 0;
     g.t_per_slice = round_up(K, kBasisChunk);
-    const dim3 grid((unsigned)((J + kBasisTile - 1) / kBasisTile), (unsigned)((rows + kBasisTile - 1) / kBasisTile), 1);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (a_is_bf16) {
-        if (out_is_bf16) launch(basis_gemm_kernel<false, true, false, true>, grid, dim3(kBasisThreads), 0, st, g);
-        else launch(basis_gemm_kernel<false, true, false, false>, grid, dim3(kBasisThreads), 0, st, g);
-    } else {
-        if (out_is_bf16) launch(basis_gemm_kernel<false, false, false, true>, grid, dim3(kBasisThreads), 0, st, g);
-        else launch(basis_gemm_kernel<false, false, false, false>, grid, dim3(kBasisThreads), 0, st, g);
-    }
+    if (out_is_bf16) launch(basis_gemm_kernel<false, false, false, true>, grid, dim3(kBasisThreads), 0, st, g);
+    else launch(basis_gemm_kernel<false, false, false, false>, grid, dim3(kBasisThreads), 0, st, g);
     return launch_status();
 }
 

@@ -82,6 +82,27 @@ def test_project_rows(rq, rows, K, J, a_dtype, out_dtype):
         assert np.all(np.abs(got - ref) <= 4 * K * 2.0 ** -24 * mag + 1e-30)
 
 
+# bf16 rows go through the bf16 matrix cores with u in three exact parts: edges of the 128 x 128
+# tiles and of the 32 steps of a chunk
+@pytest.mark.parametrize("rows,K,J", [(1, 1, 8), (128, 32, 128), (129, 33, 136), (127, 31, 120), (40, 64, 1000), (300, 515, 16)])
+def test_project_rows_split(rq, rows, K, J):
+    g = torch.Generator().manual_seed(rows + K + J)
+    ld = (K + 7) // 8 * 8 + 8
+    a = torch.full((rows, ld), float("nan"), dtype=torch.bfloat16)   # what lies behind a row is not read
+    a[:, :K] = torch.randn(rows, K, generator=g).bfloat16()
+    # parts of very different size, exact zeros and bf16 numbers among them
+    u = torch.randn(K, J, generator=g) * torch.exp2(torch.randint(-40, 10, (K, J), generator=g).float())
+    u[::3] = u[::3].bfloat16().float()
+    u[1::5] = 0.0
+    buf = torch.full((rows, J + 3), 7.0, device="cuda")
+    rq.resq_project_rows(a.cuda()[:, :K], u.cuda(), out=buf[:, :J])
+    torch.cuda.synchronize()
+    ad, ud = a[:, :K].double().numpy(), u.double().numpy()
+    assert torch.all(buf[:, J:] == 7.0)
+    # products are exact; 3 K additions in fp32
+    assert np.all(np.abs(buf[:, :J].double().cpu().numpy() - ad @ ud) <= 3 * K * 2.0 ** -24 * (np.abs(ad) @ np.abs(ud)) + 1e-30)
+
+
 def test_project_rows_on_column_blocks(rq):
     # U_h = P_h R_h written into the first r columns of U: sub-blocks in and out
     K, r = 64, 16
