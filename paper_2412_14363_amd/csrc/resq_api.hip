@@ -10,6 +10,7 @@
 #include "resq_decode.hip.h"
 #include "resq_eig.hip.h"
 #include "resq_gemm.hip.h"
+#include "resq_gemm_f8.hip.h"
 #include "resq_gemm_m64.hip.h"
 #include "resq_basis.hip.h"
 #include "resq_project.hip.h"
@@ -440,6 +441,18 @@ static GemmPlan plan_gemm(int64_t M, const WeightLayout& L) {
     return {narrow ? 3 : 2, 0, rings};
 }
 
+// Whether the 128 x 128 tiles take the low group through the fp8 matrix cores (resq_gemm_f8.hip.h).
+// That saves power and issue slots per low stage (5 to 6 % on an all-low layer, 2.5 to 6 % at r = K/8
+// with 28 low stages and more, on more than one round of 512 tiles); it costs 0.3 us per round and 1 to
+// 2 % per high stage.  So not where a single round runs below the power limit (2048 x 4096 -> 4096
+// 31.7 / 32.1 us), where stages are few (2048 x 2048 -> 8192, 14 low: 35.6 / 36.8; 4096 x 1024 -> 8192,
+// 8 low: 46.9 / 48.3) or mostly high (4096 x 4096 -> 8192, r = K/2: 126.4 / 130.2); and not where its
+// sums could leave the whole numbers of fp32.
+static bool use_f8(int64_t M, const WeightLayout& L) {
+    const int64_t tiles = ((M + kBM - 1) / kBM) * ((L.N + kBN - 1) / kBN);
+    return tiles > 512 && L.lo_blocks >= 24 && 2 * L.lo_blocks >= 3 * L.hi_blocks && L.kl_pad <= kF8MaxLoWidth;
+}
+
 // arguments of the weight-streaming kernels; the code pointers are null when the kernel
 // quantizes x itself
 static DecodeArgs make_decode_args(const int8_t* q_hi, const uint8_t* q_lo, const float* s_hi,
@@ -619,6 +632,9 @@ static int gemm_mixed_impl(const int8_t* q_hi, const uint8_t* q_lo, const float*
             if (dbg) launch(gemm_mixed_m64_kernel<true, 1>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
             else launch(gemm_mixed_m64_kernel<false, 1>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
         }
+    } else if (use_f8(M, L)) {
+        if (dbg) launch(gemm_mixed_f8_kernel<true>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
+        else launch(gemm_mixed_f8_kernel<false>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
     } else {
         if (dbg) launch(gemm_mixed_kernel<true>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
         else launch(gemm_mixed_kernel<false>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);

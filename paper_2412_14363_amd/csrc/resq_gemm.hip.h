@@ -275,6 +275,51 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// Write y once: the 128 x 128 bf16 tile sits in LDS; wave w stores rows 32 w .. 32 w + 31, four
+// whole 256-byte row segments per store instruction.
+__device__ __forceinline__ void store_tile(const GemmArgs& a, const uint8_t* lds, int wave, int lane, int64_t m0,
+                                           int64_t n0) {
+    const bool fast = ((reinterpret_cast<uintptr_t>(a.y) & 15) == 0) && (a.ldy % 8 == 0) &&
+                      (n0 + kBN <= a.L.N);
+    if (a.swiglu) {
+        // 64 outputs per row: eight 128-byte row segments per store instruction
+        const int64_t n_out = a.L.N / 2;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int row = wave * 32 + it * 8 + (lane >> 3);
+            const int64_t m = m0 + row;
+            const int64_t n = n0 / 2 + (lane & 7) * 8;
+            const uint4 v = *reinterpret_cast<const uint4*>(lds + row * kOutRowBytes + (lane & 7) * 16);
+            if (m >= a.M) continue;
+            if (fast) {
+                *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
+            } else {
+                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (n + e < n_out) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int it = 0; it < 8; ++it) {
+        const int row = wave * 32 + it * 4 + (lane >> 4);
+        const int64_t m = m0 + row;
+        const int64_t n = n0 + (lane & 15) * 8;
+        const uint4 v = *reinterpret_cast<const uint4*>(lds + row * kOutRowBytes + (lane & 15) * 16);
+        if (m >= a.M) continue;
+        if (fast) {
+            *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
+        } else {
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (n + e < a.L.N) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+        }
+    }
+}
+
 // Second launch bound: two workgroups per compute unit, i.e. two wavefronts per SIMD with
 // 256 registers each (128 vector + 128 accumulation).
 template <bool DBG>
@@ -724,49 +769,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
         }
     }
 
-    // ---- write y once --------------------------------------------------------
-    // The 128 x 128 bf16 tile sits in LDS; wave w stores rows 32 w .. 32 w + 31, four
-    // whole 256-byte row segments per store instruction.
     __syncthreads();
-    const bool fast = ((reinterpret_cast<uintptr_t>(a.y) & 15) == 0) && (a.ldy % 8 == 0) &&
-                      (n0 + kBN <= a.L.N);
-    if (a.swiglu) {
-        // 64 outputs per row: eight 128-byte row segments per store instruction
-        const int64_t n_out = a.L.N / 2;
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const int row = wave * 32 + it * 8 + (lane >> 3);
-            const int64_t m = m0 + row;
-            const int64_t n = n0 / 2 + (lane & 7) * 8;
-            const uint4 v = *reinterpret_cast<const uint4*>(lds + row * kOutRowBytes + (lane & 7) * 16);
-            if (m >= a.M) continue;
-            if (fast) {
-                *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
-            } else {
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (n + e < n_out) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-        const int row = wave * 32 + it * 4 + (lane >> 4);
-        const int64_t m = m0 + row;
-        const int64_t n = n0 + (lane & 15) * 8;
-        const uint4 v = *reinterpret_cast<const uint4*>(lds + row * kOutRowBytes + (lane & 15) * 16);
-        if (m >= a.M) continue;
-        if (fast) {
-            *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (n + e < a.L.N) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-        }
-    }
+    store_tile(a, lds, wave, lane, m0, n0);
 }
 
 }  // namespace resq

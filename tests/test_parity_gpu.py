@@ -291,6 +291,29 @@ def test_layer_tiled_kernel_wide_tiles(oracle, rq, M, K, N, r):
     check_layer(oracle, rq, x, w, r, ldy_extra=8 if N % 4 == 0 else 3)
 
 
+# 128 x 128 tiles in more than one round and 24 low stages or more: the low group on the fp8 matrix
+# cores.  Ragged tiles; 2 and 4 high stages (the first buffer) and none; 24, 26 and 28 low stages (what
+# the four-stage turns of the loop leave over); groups that end inside their padding
+TILED_F8_SHAPES = [(1925, 3200, 4500, 128), (1921, 3584, 4400, 256), (1930, 3072, 4300, 0), (4200, 3450, 2050, 122)]
+
+
+@pytest.mark.parametrize("M,K,N,r", TILED_F8_SHAPES)
+def test_layer_tiled_kernel_fp8_low_group(oracle, rq, M, K, N, r):
+    assert rq.resq_gemm_mixed_plan(M, N, K, r) == (2, 0, 0)
+    x, w = wl.random_small_case(M * 17 + K + 3, M, K, N, r, act="student_t3")
+    check_layer(oracle, rq, x, w, r, ldy_extra=8 if N % 4 == 0 else 3)
+
+
+def test_layer_tiled_kernel_fp8_low_group_asym_and_saturated(oracle, rq):
+    M, K, N, r = TILED_F8_SHAPES[0]
+    x, w = wl.random_small_case(5, M, K, N, r, act="student_t3")
+    check_layer_asym(oracle, rq, (x.float() + 1.5).to(torch.bfloat16), w, r)
+    # every low code at +7 or -7, the same in all columns of a row: the largest sums there are
+    x[:, r:] = torch.where(torch.arange(M) % 2 == 0, 1.0, -1.0)[:, None].to(torch.bfloat16)
+    w[:, r:] = torch.where(torch.arange(N) % 3 == 0, 0.5, -0.5)[:, None].to(torch.bfloat16)
+    check_layer(oracle, rq, x, w, r)
+
+
 @pytest.mark.parametrize("M,K,N,r", [
     (385, 2048, 400, 256), (512, 4096, 272, 512), (1000, 1000, 515, 104), (1024, 3200, 256, 448),
     (700, 256, 256, 0), (640, 256, 64, 256), (1024, 14336, 144, 1792),
@@ -938,6 +961,7 @@ def test_project_heads_no_rows(rq):
     (300, 256, 2050, 32), (130, 520, 4100, 64),                                           # ... and below, on wide layers
     (1153, 256, 1050, 32), (1300, 640, 1150, 128),                                        # ... 257 to 512 such tiles: one ring
     (2100, 256, 1100, 32), (4100, 256, 550, 0), (4100, 256, 550, 256), (1100, 1000, 2100, 104),  # 128 x 128 tiles
+    (1925, 3200, 2250, 128),                                                              # ... with the low group in fp8
 ])
 def test_layer_swiglu(oracle, rq, M, K, F, r):
     x, w = wl.random_small_case(M + K + F, M, K, 2 * F, r, act="student_t3")
