@@ -9,6 +9,7 @@ library cannot be loaded, importing the symbols raises.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 from typing import Optional
 
 import torch
@@ -112,22 +113,34 @@ def _check_layer_buffers(where: str, act: "ActCodes", packed: torch.Tensor, N: i
         raise ValueError(f"{where}: activation code buffers do not match (M, K, r) = ({M}, {K}, {r})")
 
 
+# The raw handle of a device's current stream.  torch.cuda.current_stream() builds a Stream object
+# around it, 2.7 us a call, a third of a small call's host time; asked for on every call all the same,
+# since it is the caller's to change.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or \
+    (lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 # ---- layout queries ---------------------------------------------------------
+# Functions of their arguments alone, asked for by every GEMM call's buffer checks: the last answers
+# are kept (0.1 us instead of 0.9).
 
+@functools.lru_cache(maxsize=1024, typed=True)
 def resq_act_hi_ld(K: int, r: int) -> int:
     return int(lib().resq_act_hi_ld(K, r))
 
 
+@functools.lru_cache(maxsize=1024, typed=True)
 def resq_act_lo_ld(K: int, r: int) -> int:
     return int(lib().resq_act_lo_ld(K, r))
 
 
+@functools.lru_cache(maxsize=1024, typed=True)
 def resq_packed_weight_bytes(N: int, K: int, r: int) -> int:
     return int(lib().resq_packed_weight_bytes(N, K, r))
 
@@ -454,6 +467,7 @@ def resq_project_heads(x: torch.Tensor, packed: torch.Tensor, y: Optional[torch.
     return y
 
 
+@functools.lru_cache(maxsize=1024, typed=True)
 def resq_kv_cache_row_bytes(d_head: int, r: int) -> int:
     return int(lib().resq_kv_cache_row_bytes(d_head, r))
 
