@@ -843,8 +843,8 @@ static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int swee
                                 int64_t ldp, void* workspace, void* stream) {
     const int n = (int)K;
     // one launch on LDS while the matrix and a slice of the vectors fit there, up to 128 columns:
-    // 2.75 ms at n = 128 and 12 sweeps against 10.5 ms in two launches a round (0.24 / 1.69 ms at
-    // n = 32, 0.66 / 4.9 at 64)
+    // 1.06 ms at n = 128 against 6.9 ms in two launches a round (0.15 / 1.69 ms at n = 32, 0.39 / 4.9
+    // at 64)
     if (n <= kEigSmallMax) {
         const int small_lds = eig_small_lds_bytes(n);
         if (small_lds > 64 * 1024 &&

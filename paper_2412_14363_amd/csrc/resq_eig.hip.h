@@ -94,188 +94,234 @@ __global__ void eig_rotations_kernel(EigPlan e, int sweep, int round) {
 //
 // Two launches per round (a rotation kernel of one workgroup, a row kernel) cost
 // more than the rounds themselves at head sizes: 12 sweeps of a 128 x 128 matrix
-// are 3048 launches, 10.5 ms.  Here a workgroup keeps the matrix in LDS (fp64, one
-// copy of each off-diagonal pair: 132 KB at n = 128) and walks all rounds by
-// itself: a round is 2 x 2 blocks (pair k, pair kk) that no two threads share, so
-// it needs two barriers (2.75 ms in all).  The vectors do not fit beside it, but column j of Vt is
-// rotated independently of every other column: each of the ceil(n / 16) workgroups
-// repeats the iteration on the matrix (same arithmetic, same decisions) and carries
-// 16 columns of Vt, so that the workgroups never talk to each other.  The vectors'
+// are 3048 launches, 10.5 ms.  Here a workgroup keeps the matrix in LDS (fp64,
+// one copy of each off-diagonal pair) and walks all rounds by itself.
+//
+// Slots.  What made a first version of this kernel slow (5200 clocks a round) was
+// finding the elements: the pairs change every round.  So the DATA moves instead:
+// pair k owns slots (k, 0) and (k, 1) for good, and after a round the element in a
+// slot moves one place along the tournament's circle (slot (0, 0) stays).  A round
+// reads and writes the same addresses every time, from one buffer into the other;
+// after n - 1 rounds, a sweep, everything is back where it was.  The four elements of
+// the 2 x 2 block of two pairs lie in four planes: no bank is met twice.
+//
+// The vectors do not fit beside the matrix, but column j of Vt is rotated
+// independently of every other column: each of the ceil(n / 8) workgroups repeats
+// the iteration on the matrix (same arithmetic, same decisions) and carries 8
+// columns of Vt, so that the workgroups never talk to each other.  The vectors'
 // rotation of round r runs on wavefronts 1..15 while wavefront 0 computes the
-// angles of round r + 1, a chain of fp64 roots and quotients that is the longest
-// part of a round.
+// angles of round r + 1, a chain of fp64 roots and quotients.  (Wavefront 0 rotating
+// only the blocks that the next angles need, and the others all the rest behind one
+// barrier a round instead of two, measured the same: 1.04 ms at n = 128.)
+//
+// Measured on the covariance of Gaussian rows, 12 sweeps allowed, two launches a round /
+// this kernel: n = 128 6.9 / 1.06 ms (3000 clocks a round), n = 64 4.9 / 0.39, n = 32
+// 1.69 / 0.15.
 constexpr int kEigSmallMax = 128;
 constexpr int kEigSmallThreads = 1024;
-constexpr int kEigSmallCols = 16;  // columns of Vt per workgroup
+constexpr int kEigSmallCols = 8;  // columns of Vt per workgroup
 
-// Bytes of LDS: matrix [n][n + 3], Vt slice [n][16], cosines and sines of two rounds, two flags.
-// The pitch is odd, so that neither a run along a row nor one along a column meets a bank twice,
-// and not n + 1, with which all elements of a round's pairs (p + q is the same for all) would.
+// blocks (k, l), k < l: lanes of `units` rows of n / 2 (see below)
+__host__ __device__ inline int eig_small_units(int half) { return (half + 1) >> 1; }
+// doubles of one of the two buffers: the four planes, the diagonal blocks (three numbers each)
+__host__ __device__ inline int eig_small_buf(int half) { return 4 * eig_small_units(half) * half + 3 * half + (half & 1); }  // even: what lies behind is 16-byte aligned
+// bytes of LDS: both buffers, both buffers of the Vt slice [n][8], cosines and sines of two rounds, two flags
 __host__ __device__ inline int eig_small_lds_bytes(int n) {
-    return (n * (n + 3) + n * kEigSmallCols + 2 * n) * (int)sizeof(double) + 2 * (int)sizeof(int);
+    return (2 * eig_small_buf(n / 2) + 2 * n * kEigSmallCols + 2 * n) * (int)sizeof(double) + 2 * (int)sizeof(int);
 }
 
 __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float* __restrict__ c, int64_t ldc, int n,
                                                                      int sweeps, float* __restrict__ eigvals,
                                                                      float* __restrict__ p, int64_t ldp) {
     extern __shared__ __attribute__((aligned(16))) double lds[];
-    const int pitch = n + 3, half = n >> 1;
-    double* a = lds;                                   // element (i, j), i <= j, at i * pitch + j
-    double* vt = a + n * pitch;                        // [n][16]: columns j0 .. j0 + 15 of Vt
-    double2* cs = reinterpret_cast<double2*>(vt + n * kEigSmallCols);  // [2][half]
+    const int half = n >> 1, units = eig_small_units(half), plane = units * half, bufsz = eig_small_buf(half);
+    const int diag = 4 * plane;                        // a00[half], a11[half], a01[half] of the pairs
+    double* vt = lds + 2 * bufsz;                      // [2][n][8]: columns j0 .. j0 + 7 of Vt, rows by slot 2 k + x
+    double2* cs = reinterpret_cast<double2*>(vt + 2 * n * kEigSmallCols);  // [2][half]
     int* flag = reinterpret_cast<int*>(cs + n);        // [2]: does the round rotate anything
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int j0 = blockIdx.x * kEigSmallCols;
 
-    for (int idx = t; idx < n * n; idx += kEigSmallThreads) {
-        const int i = idx / n, j = idx % n;
-        if (i <= j) a[i * pitch + j] = 0.5 * ((double)c[(int64_t)i * ldc + j] + (double)c[(int64_t)j * ldc + i]);
-    }
-    for (int idx = t; idx < n * kEigSmallCols; idx += kEigSmallThreads)
-        vt[idx] = idx / kEigSmallCols == j0 + idx % kEigSmallCols ? 1.0 : 0.0;
-    __syncthreads();
-
-    auto at = [&](int i, int j) __attribute__((always_inline)) -> double& {
-        return a[i < j ? i * pitch + j : j * pitch + i];
-    };
-    // Vt <- J^T Vt for the round whose rotations are rot, on `threads` threads from `first` on
-    auto rotate_vectors = [&](const double2* rot, int round, int first, int threads) __attribute__((always_inline)) {
-        for (int idx = t - first; idx < half * kEigSmallCols; idx += threads) {
-            const int k = idx / kEigSmallCols, col = idx % kEigSmallCols;
-            const double2 r = rot[k];
-            if (r.y == 0.0) continue;
-            int pp, qq;
-            eig_pair(n, round, k, pp, qq);
-            double* vp = vt + pp * kEigSmallCols + col;
-            double* vq = vt + qq * kEigSmallCols + col;
-            const double x = *vp, y = *vq;
-            *vp = r.x * x - r.y * y;
-            *vq = r.y * x + r.x * y;
+    // the index whose row and column start (and end every sweep) in slot (k, x): eig_pair's round 0
+    auto index_of = [&](int k, int x) { return k == 0 ? (x == 0 ? n - 1 : 0) : (x == 0 ? k : n - 1 - k); };
+    // where the element in slot (k, x) goes after a round
+    auto move = [&](int& k, int& x) {
+        if (half == 1 || (k == 0 && x == 0)) return;
+        if (x == 0) {
+            if (k == 1) { k = 0; x = 1; }
+            else --k;
+        } else {
+            if (k < half - 1) ++k;
+            else x = 0;
         }
     };
+    // Block (k, l), k < l: row k of the units, lane l, for the lower half of the pairs; the rows'
+    // free lanes below k hold, turned round, the blocks of pair half - 1 - k, so that all lanes work.
+    auto block_at = [&](int k, int l) { return k < units ? k * half + l : (half - 1 - k) * half + half - 1 - l; };
+    // offset in a buffer of the element between two slots
+    auto at = [&](int k, int x, int l, int y) {
+        if (k == l) return diag + (x != y ? 2 * half : x * half) + k;
+        if (k > l) {
+            int s = k; k = l; l = s;
+            s = x; x = y; y = s;
+        }
+        return (2 * x + y) * plane + block_at(k, l);
+    };
 
-    int buf = 0, pending = 0, pending_round = 0;  // the vectors are one round behind the matrix
+    for (int idx = t; idx < n * n; idx += kEigSmallThreads) {
+        const int s0 = idx / n, s1 = idx % n;
+        if (s0 > s1) continue;
+        const int i = index_of(s0 >> 1, s0 & 1), j = index_of(s1 >> 1, s1 & 1);
+        lds[at(s0 >> 1, s0 & 1, s1 >> 1, s1 & 1)] =
+            0.5 * ((double)c[(int64_t)i * ldc + j] + (double)c[(int64_t)j * ldc + i]);
+    }
+    for (int idx = t; idx < n * kEigSmallCols; idx += kEigSmallThreads) {
+        const int s0 = idx / kEigSmallCols;
+        vt[idx] = index_of(s0 >> 1, s0 & 1) == j0 + idx % kEigSmallCols ? 1.0 : 0.0;
+    }
+
+    // this thread's blocks (two rows of units at most), their places and where their four elements go
+    bool on[2];
+    int bk[2], bl[2], rd[2], wr[2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int u = wave + h * (kEigSmallThreads / 64);
+        const bool upper = lane > u;
+        // not the diagonal, and not the lower lanes of the middle row of an odd number of pairs
+        on[h] = u < units && lane < half && lane != u && (upper || 2 * u != half - 1);
+        bk[h] = on[h] ? (upper ? u : half - 1 - u) : 0;
+        bl[h] = on[h] ? (upper ? lane : half - 1 - lane) : 0;
+        rd[h] = on[h] ? u * half + lane : 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            int k = bk[h], x = e >> 1, l = bl[h], y = e & 1;
+            move(k, x);
+            move(l, y);
+            wr[h][e] = on[h] ? at(k, x, l, y) : 0;
+        }
+    }
+    // wavefront 0: the diagonal block of pair `lane`
+    int wd[3];
+    {
+        int k0 = lane < half ? lane : 0, x0 = 0, k1 = k0, x1 = 1;
+        move(k0, x0);
+        move(k1, x1);
+        wd[0] = at(k0, x0, k0, x0);
+        wd[1] = at(k1, x1, k1, x1);
+        wd[2] = at(k0, x0, k1, x1);
+    }
+    // the others: two rows of one column of Vt
+    const int vk = (t - 64) / kEigSmallCols, vc = t & (kEigSmallCols - 1);
+    const bool v_on = t >= 64 && vk < half;
+    int vw[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+        int k = v_on ? vk : 0, y = x;
+        move(k, y);
+        vw[x] = (2 * k + y) * kEigSmallCols + vc;
+    }
+    __syncthreads();
+
+    // Vt <- J^T Vt for the round whose rotations are rot, from buffer b of the slice into the other
+    auto rotate_vectors = [&](const double2* rot, int b) __attribute__((always_inline)) {
+        if (!v_on) return;
+        const double* src = vt + b * n * kEigSmallCols + 2 * vk * kEigSmallCols + vc;
+        double* dst = vt + (b ^ 1) * n * kEigSmallCols;
+        const double2 r = rot[vk];
+        const double x = src[0], y = src[kEigSmallCols];
+        dst[vw[0]] = r.x * x - r.y * y;
+        dst[vw[1]] = r.y * x + r.x * y;
+    };
+
+    int buf = 0, rounds = 0;  // the vectors are one round behind the matrix
     for (int sweep = 0; sweep < sweeps; ++sweep) {
         int rotated = 0;
         for (int round = 0; round < n - 1; ++round) {
+            const double* cur = lds + buf * bufsz;
+            double* nxt = lds + (buf ^ 1) * bufsz;
             double2* rot = cs + buf * half;
+            double a00 = 0.0, a11 = 0.0, a01 = 0.0;
+            double2 r = make_double2(1.0, 0.0);
             if (wave == 0) {
                 bool turn = false;
                 if (lane < half) {
-                    int pp, qq;
-                    eig_pair(n, round, lane, pp, qq);
-                    const double app = a[pp * pitch + pp], aqq = a[qq * pitch + qq], apq = a[pp * pitch + qq];
-                    double2 r = make_double2(1.0, 0.0);
-                    turn = fabs(apq) > kEigSkip * sqrt(fabs(app * aqq));
+                    a00 = cur[diag + lane];
+                    a11 = cur[diag + half + lane];
+                    a01 = cur[diag + 2 * half + lane];
+                    // As eig_rotations_kernel has it, |a01| > 2^-40 sqrt(|a00 a11|) and tan of the smaller angle =
+                    // sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with fewer
+                    // roots and quotients in a row.  (The hardware's approximate ones are not enough: the
+                    // signs of some vectors then come out otherwise.)
+                    turn = a01 * a01 > kEigSkip * kEigSkip * fabs(a00 * a11);
                     if (turn) {
-                        // As eig_rotations_kernel has it.  (Approximate quotients and roots shorten this chain to a
-                        // third, and the signs of some vectors then come out otherwise.)
-                        const double tau = (aqq - app) / (2.0 * apq);
-                        const double tn = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-                        r.x = 1.0 / sqrt(1.0 + tn * tn);
+                        const double d = a11 - a00, b = 2.0 * a01;
+                        double tn = fabs(b) / (fabs(d) + sqrt(d * d + b * b));
+                        if (d != 0.0 && (d < 0.0) != (b < 0.0)) tn = -tn;
+                        r.x = rsqrt(1.0 + tn * tn);
                         r.y = tn * r.x;
                     }
                     rot[lane] = r;
                 }
                 const bool any = __ballot(turn) != 0;
                 if (lane == 0) flag[buf] = any ? 1 : 0;
-            } else if (pending) {
-                rotate_vectors(cs + (buf ^ 1) * half, pending_round, 64, kEigSmallThreads - 64);
+            } else if (rounds > 0) {
+                rotate_vectors(cs + (buf ^ 1) * half, buf ^ 1);
             }
             __syncthreads();
-            const int any = flag[buf];
-            if (any) {
-                // Blocks (k, kk), k < kk.  Unit k of half / 2 (rounded up) takes kk > k of pair k on its upper
-                // lanes and, turned round, kk >= k' of pair k' = half - 1 - k on its lower ones, so that all
-                // lanes work and each half runs along one pair of rows.  A wavefront loads the blocks of two
-                // units before it writes the first.  The diagonal blocks (lane k of unit k, and those of the
-                // lower pairs, which no unit meets) are wavefront 0's afterwards.
-                const int mate = half - 1 - lane;
-                const bool live = lane < half;
-                const double2 r_up = rot[live ? lane : 0], r_dn = rot[live ? mate : 0];
-                int up_p, up_q, dn_p, dn_q;
-                eig_pair(n, round, live ? lane : 0, up_p, up_q);
-                eig_pair(n, round, live ? mate : 0, dn_p, dn_q);
-                const int units = (half + 1) >> 1;
-                for (int u0 = wave; u0 < units; u0 += 2 * (kEigSmallThreads / 64)) {
-                    double x[2][4];
-                    double* e[2][4];
-                    double2 ra[2], rb[2];
-                    bool on[2];
+            rotated |= flag[buf];
+            double2 x0[2], x1[2], ra[2], rb[2];
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int k = u0 + h * (kEigSmallThreads / 64);
-                        const bool upper = lane > k;
-                        const int kr = upper ? k : half - 1 - k;
-                        // off the diagonal, and not the lower half of the middle unit of an odd number of pairs
-                        on[h] = k < units && live && lane != k && (upper || 2 * k != half - 1);
-                        ra[h] = rot[on[h] ? kr : 0];
-                        rb[h].x = upper ? r_up.x : r_dn.x;
-                        rb[h].y = upper ? r_up.y : r_dn.y;
-                        on[h] = on[h] && (ra[h].y != 0.0 || rb[h].y != 0.0);
-                        int p1, q1;
-                        eig_pair(n, round, kr < 0 ? 0 : kr, p1, q1);
-                        const int p2 = upper ? up_p : dn_p, q2 = upper ? up_q : dn_q;
-                        e[h][0] = &at(p1, p2);
-                        e[h][1] = &at(p1, q2);
-                        e[h][2] = &at(q1, p2);
-                        e[h][3] = &at(q1, q2);
-                        if (on[h]) {
-#pragma unroll
-                            for (int v = 0; v < 4; ++v) x[h][v] = *e[h][v];
-                        }
-                    }
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        if (!on[h]) continue;
-                        const double y00 = ra[h].x * x[h][0] - ra[h].y * x[h][2], y10 = ra[h].y * x[h][0] + ra[h].x * x[h][2];
-                        const double y01 = ra[h].x * x[h][1] - ra[h].y * x[h][3], y11 = ra[h].y * x[h][1] + ra[h].x * x[h][3];
-                        *e[h][0] = rb[h].x * y00 - rb[h].y * y01;
-                        *e[h][1] = rb[h].y * y00 + rb[h].x * y01;
-                        *e[h][2] = rb[h].x * y10 - rb[h].y * y11;
-                        *e[h][3] = rb[h].y * y10 + rb[h].x * y11;
-                    }
-                }
-                if (wave == 0 && live && r_up.y != 0.0) {
-                    const double2 r = r_up;
-                    double& xpp = a[up_p * pitch + up_p];
-                    double& xqq = a[up_q * pitch + up_q];
-                    double& xpq = a[up_p * pitch + up_q];
-                    const double app = xpp, aqq = xqq, apq = xpq;
-                    const double rpp = r.x * app - r.y * apq, rpq = r.x * apq - r.y * aqq;
-                    const double rqp = r.y * app + r.x * apq, rqq = r.y * apq + r.x * aqq;
-                    xpp = r.x * rpp - r.y * rpq;
-                    xpq = r.y * rpp + r.x * rpq;
-                    xqq = r.y * rqp + r.x * rqq;
-                }
-                __syncthreads();
+            for (int h = 0; h < 2; ++h) {
+                if (!on[h]) continue;
+                ra[h] = rot[bk[h]];
+                rb[h] = rot[bl[h]];
+                x0[h] = make_double2(cur[rd[h]], cur[plane + rd[h]]);
+                x1[h] = make_double2(cur[2 * plane + rd[h]], cur[3 * plane + rd[h]]);
             }
-            rotated |= any;
-            pending = any;
-            pending_round = round;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (!on[h]) continue;
+                const double y00 = ra[h].x * x0[h].x - ra[h].y * x1[h].x, y10 = ra[h].y * x0[h].x + ra[h].x * x1[h].x;
+                const double y01 = ra[h].x * x0[h].y - ra[h].y * x1[h].y, y11 = ra[h].y * x0[h].y + ra[h].x * x1[h].y;
+                nxt[wr[h][0]] = rb[h].x * y00 - rb[h].y * y01;
+                nxt[wr[h][1]] = rb[h].y * y00 + rb[h].x * y01;
+                nxt[wr[h][2]] = rb[h].x * y10 - rb[h].y * y11;
+                nxt[wr[h][3]] = rb[h].y * y10 + rb[h].x * y11;
+            }
+            if (wave == 0 && lane < half) {
+                const double r00 = r.x * a00 - r.y * a01, r01 = r.x * a01 - r.y * a11;
+                const double r10 = r.y * a00 + r.x * a01, r11 = r.y * a01 + r.x * a11;
+                nxt[wd[0]] = r.x * r00 - r.y * r01;
+                nxt[wd[1]] = r.y * r10 + r.x * r11;
+                nxt[wd[2]] = r.y * r00 + r.x * r01;
+            }
+            __syncthreads();
             buf ^= 1;
+            ++rounds;
         }
         if (!rotated) break;  // as every later sweep would find: the same for all threads
     }
-    if (pending) rotate_vectors(cs + (buf ^ 1) * half, pending_round, 0, kEigSmallThreads);
-    __syncthreads();
-    // positions in decreasing order (ties by index), as eig_finish_kernel has them
-    int* rank = reinterpret_cast<int*>(cs);
+    rotate_vectors(cs + (buf ^ 1) * half, buf ^ 1);
+    // positions in decreasing order (ties by index), as eig_finish_kernel has them; rank by slot
+    const double* a = lds + buf * bufsz + diag;
+    vt += buf * n * kEigSmallCols;
+    int* rank = reinterpret_cast<int*>(cs + buf * half);   // not the rotations that are still read
     if (t < n) {
-        const double li = a[t * pitch + t];
+        const double li = a[(t & 1) * half + (t >> 1)];
+        const int i = index_of(t >> 1, t & 1);
         int r = 0;
-        for (int j = 0; j < n; ++j) {
-            const double lj = a[j * pitch + j];
-            r += (lj > li || (lj == li && j < t)) ? 1 : 0;
+        for (int s = 0; s < n; ++s) {
+            const double lj = a[(s & 1) * half + (s >> 1)];
+            r += (lj > li || (lj == li && index_of(s >> 1, s & 1) < i)) ? 1 : 0;
         }
         rank[t] = r;
         if (blockIdx.x == 0) eigvals[r] = (float)li;
     }
     __syncthreads();
     for (int idx = t; idx < n * kEigSmallCols; idx += kEigSmallThreads) {
-        const int col = idx / n, i = idx % n;
-        if (j0 + col < n) p[(int64_t)(j0 + col) * ldp + rank[i]] = (float)vt[i * kEigSmallCols + col];
+        const int col = idx / n, s = idx % n;
+        if (j0 + col < n) p[(int64_t)(j0 + col) * ldp + rank[s]] = (float)vt[s * kEigSmallCols + col];
     }
 }
 
