@@ -473,12 +473,12 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
                 sg += 2;
             };
             // the buffers are in the instructions, so that a read costs no address: four stages a turn
-            for (; sg + 3 + kPrefetch < S;) {
+            while (sg + 3 + kPrefetch < S) {
                 pair(YES{}, IC<0>{});
                 pair(YES{}, IC<2>{});
             }
             buf = 0;
-            for (; sg < S;) pair(NO{}, IC<0>{});
+            while (sg < S) pair(NO{}, IC<0>{});
             // the last stage widened what lies behind it: its h = 0 does not count
             bytes = (uint32_t)wa[0][0][0] + (uint32_t)wa[0][0][2] + (uint32_t)wa[0][0][4] + (uint32_t)wa[0][0][6];
             sum -= __builtin_amdgcn_sad_u8(bytes, 0u, 0u);
