@@ -702,36 +702,57 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_kv_cache_kernel(
     const float mx_h = wave_max<G>(high ? mx : -inf), nmn_h = wave_max<G>(high ? nmn : -inf);
     const float mx_l = wave_max<G>(live && !high ? mx : -inf);
     const float nmn_l = wave_max<G>(live && !high ? nmn : -inf);
-    // an absent group: scale 1, zero-point 0
-    const float zh = r > 0 ? -nmn_h : 0.0f, zl = d - r > 0 ? -nmn_l : 0.0f;
-    const float sh = r > 0 ? asym_scale(zh, mx_h, 255) : 1.0f;
-    const float sl = d - r > 0 ? asym_scale(zl, mx_l, 15) : 1.0f;
-    // the branch on `high` is not wave-uniform, and the quantizer votes across the
-    // wavefront: run both kinds for every lane's vote, keep the own kind's result
-    uint32_t ch[8], cl8[8];
-    float odd_dummy = 0.0f;
-    if (hi_units > 0) quant8_asym<false>(v, zh, sh, 1.0f / sh, ch, odd_dummy);
-    if (nunits > hi_units) quant8_asym<true>(v, zl, sl, 1.0f / sl, cl8, odd_dummy);
-    if (!row_live) return;
+    // A lane's columns are all of one group: it needs one scale, one reciprocal and one pass of the
+    // quantizer, with the constants of its own group (run for both groups on all lanes and
+    // selected afterwards, which the votes across the wavefront suggest, it took 6.3 instead of 4.9 us
+    // for 32768 rows of 128 columns, and 30.9 instead of 22.9, 4.0 TB/s, for 262144).
+    const float levels = high ? 255.0f : 15.0f;
+    const float zero = live ? -(high ? nmn_h : nmn_l) : 0.0f;
+    const float range = live ? (high ? mx_h : mx_l) - zero : 0.0f;
+    const float scale = range == 0.0f ? 1.0f : range / levels;  // asym_scale
+    const float inv = 1.0f / scale;
+    constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: quant8_asym, with the codes themselves
+    const float tie = 0.5f - (levels + 1.0f) * 9.5367431640625e-07f;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    float ds[8];
+    uint32_t u[8];
+    bool near_tie[8], any_tie = false;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        ds[j] = __uint_as_float((j & 1) ? (w[j >> 1] & 0xFFFF0000u) : (w[j >> 1] << 16)) - zero;
+        const float t = ds[j] * inv;
+        const float uf = t + kMagic;
+        near_tie[j] = !(fabsf(t - (uf - kMagic)) <= tie);
+        any_tie |= near_tie[j];
+        u[j] = __float_as_uint(uf);
+    }
+    if (__builtin_amdgcn_ballot_w64(any_tie) != 0) {  // wave-uniform, then per element slot
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            if (__builtin_amdgcn_ballot_w64(near_tie[j]) != 0)
+                u[j] = (uint32_t)(int)fminf(fmaxf(rintf(ds[j] / scale), 0.0f), levels);
+    }
+    if (!row_live || !live) return;
     uint8_t* row = cache + m * row_bytes;
-    if (live && high) {
-        // stored = code - 128 in the low byte: flipping bit 7 gives the code
+    float* par = reinterpret_cast<float*>(row + r + (d - r) / 2);
+    if (high) {
         uint32_t* dst = reinterpret_cast<uint32_t*>(row + gl * 8);   // rows are 4-byte aligned
-        dst[0] = pack_low_bytes(ch[0], ch[1], ch[2], ch[3]) ^ 0x80808080u;
-        dst[1] = pack_low_bytes(ch[4], ch[5], ch[6], ch[7]) ^ 0x80808080u;
-    } else if (live) {
-        // even channels are stored as the code already, odd ones as code - 8 in two's complement
+        dst[0] = pack_low_bytes(u[0], u[1], u[2], u[3]);
+        dst[1] = pack_low_bytes(u[4], u[5], u[6], u[7]);
+    } else {
         uint32_t by[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) by[k] = ((cl8[2 * k + 1] << 4) | (cl8[2 * k] & 0xFu)) ^ 0x80u;
+        for (int k = 0; k < 4; ++k) by[k] = (u[2 * k + 1] << 4) | (u[2 * k] & 0xFu);
         *reinterpret_cast<uint32_t*>(row + r + (gl - hi_units) * 4) = pack_low_bytes(by[0], by[1], by[2], by[3]);
     }
-    if (gl == 0) {
-        float* par = reinterpret_cast<float*>(row + r + (d - r) / 2);
-        par[0] = sh;
-        par[1] = zh;
-        par[2] = sl;
-        par[3] = zl;
+    // the first lane of a group writes its constants; an absent group: scale 1, zero-point 0
+    if (gl == 0 || gl == hi_units) {
+        par[high ? 0 : 2] = scale;
+        par[high ? 1 : 3] = zero;
+        if (gl == 0 && (hi_units == 0 || hi_units == nunits)) {
+            par[high ? 2 : 0] = 1.0f;
+            par[high ? 3 : 1] = 0.0f;
+        }
     }
 }
 
