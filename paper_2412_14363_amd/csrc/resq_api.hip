@@ -134,7 +134,14 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
     const int64_t ld_hi = round_up(r, kHiPad), ld_lo = round_up(K - r, kLoPad) / 2;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint16_t* xp = static_cast<const uint16_t*>(x);
-    const dim3 block(kQuantThreads), grid((unsigned)M);
+    const dim3 block(kQuantThreads), wide(kQuantWideThreads), grid((unsigned)M);
+    // Few long rows: 1024 threads to a row instead of 256 (256 / 1024 threads, us).  Up to one row per
+    // compute unit from two units of eight columns a thread on: 16 rows of 6400 columns 4.56 / 4.08, of 8192
+    // 4.44 / 4.20, of 14336 6.12 / 4.16, transformed ones of 8192 5.76 / 5.00; not below (4096: equal), nor
+    // with the asymmetric quantizer's four maxima (8192: 4.36 / 4.56).  Longer rows keep the gain until
+    // the units are full of wavefronts: 512 x 14336 9.04 / 8.04, transformed 10.44 / 9.48 (1024: equal;
+    // 512 x 8192: 5.48 / 6.64), 1024 x 28672 transformed 24.5 / 23.0 (2048: 38.4 / 41.9).
+    const bool few = M <= (K > 16384 ? 1024 : K > 8192 ? 512 : (rot.log2b ? K - r > 4096 : K > 4096) && !asym ? 256 : 0);
     const bool vec = aligned(x, 16) && ldx % 8 == 0 && K % 8 == 0 && r % 8 == 0 && K <= 16384;
     const bool rotate = rot.log2b > 0;
 #define RESQ_QA_ARGS xp, ldx, (int)K, (int)r, q_hi, ld_hi, q_lo, ld_lo, s_hi, s_lo, lo_sum
@@ -147,10 +154,22 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else                                                                                        \
             launch(hadamard256_quantize_kernel<HI, LO, false>, grid, block, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo); \
     } while (0)
-        if (r <= 2048 && K - r <= 2 * 2048) RESQ_LAUNCH_H256(1, 2);
+#define RESQ_LAUNCH_H256_WIDE(LO)                                                                   \
+    do {                                                                                            \
+        if (asym)                                                                                   \
+            launch(hadamard256_quantize_kernel<1, LO, true, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo);  \
+        else                                                                                        \
+            launch(hadamard256_quantize_kernel<1, LO, false, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo); \
+    } while (0)
+        if (few) {
+            if (K - r <= 8192) RESQ_LAUNCH_H256_WIDE(1);
+            else if (K - r <= 2 * 8192) RESQ_LAUNCH_H256_WIDE(2);
+            else RESQ_LAUNCH_H256_WIDE(4);
+        } else if (r <= 2048 && K - r <= 2 * 2048) RESQ_LAUNCH_H256(1, 2);
         else if (r <= 2048 && K - r <= 7 * 2048) RESQ_LAUNCH_H256(1, 7);
         else RESQ_LAUNCH_H256(2, 13);
 #undef RESQ_LAUNCH_H256
+#undef RESQ_LAUNCH_H256_WIDE
         return launch_status();
     }
     if (rotate && !vec) return RESQ_ERR_ALIGN;
@@ -164,6 +183,13 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
             launch(quantize_act_vec_kernel<ITERS, false, true>, grid, block, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo);  \
         else                                                                                        \
             launch(quantize_act_vec_kernel<ITERS, false, false>, grid, block, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo); \
+    } while (0)
+#define RESQ_LAUNCH_QA_WIDE(ITERS)                                                                  \
+    do {                                                                                            \
+        if (asym)                                                                                   \
+            launch(quantize_act_vec_kernel<ITERS, false, true, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo);  \
+        else                                                                                        \
+            launch(quantize_act_vec_kernel<ITERS, false, false, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo); \
     } while (0)
     if (vec && K <= 512 && !rotate) {
         // short rows (an attention head of a K/V cache entry): 16, 32 or 64 lanes per row
@@ -181,6 +207,9 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else if (K <= 256) RESQ_LAUNCH_SHORT(32);
         else RESQ_LAUNCH_SHORT(64);
 #undef RESQ_LAUNCH_SHORT
+    } else if (vec && !rotate && few) {
+        if (K <= 8192) RESQ_LAUNCH_QA_WIDE(1);
+        else RESQ_LAUNCH_QA_WIDE(2);
     } else if (vec) {
         if (K <= 2048) RESQ_LAUNCH_QA(1);
         else if (K <= 4096) RESQ_LAUNCH_QA(2);
@@ -192,6 +221,7 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         launch(quantize_act_generic_kernel<false>, grid, block, 0, st, RESQ_QA_ARGS, c_hi, c_lo);
     }
 #undef RESQ_LAUNCH_QA
+#undef RESQ_LAUNCH_QA_WIDE
 #undef RESQ_QA_ARGS
     return launch_status();
 }

@@ -20,6 +20,7 @@
 namespace resq {
 
 constexpr int kQuantThreads = 256;
+constexpr int kQuantWideThreads = 1024;  // per row, where rows are few
 
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t b) { return __uint_as_float(b << 16); }
 
@@ -53,32 +54,41 @@ __device__ __forceinline__ int wave_sum(int v) {
     return v;
 }
 
-// max over the 256 threads of a block of two non-negative floats at once
-__device__ __forceinline__ void block_max2(float& a, float& b, float* red /* [8] in LDS */) {
+// max over the W wavefronts' partial results in red (16 of them: a lane takes one, the exchanges do the rest)
+template <int W>
+__device__ __forceinline__ float max_of(const float* red) {
+    static_assert(W == 4 || W == 16, "wavefronts of a block");
+    if constexpr (W == 4) return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    else return wave_max<16>(red[threadIdx.x & 15]);
+}
+
+// max over the 64 W threads of a block of two non-negative floats at once
+template <int W = 4>
+__device__ __forceinline__ void block_max2(float& a, float& b, float* red /* [2 W] in LDS */) {
     a = wave_max(a);
     b = wave_max(b);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         red[wave] = a;
-        red[4 + wave] = b;
+        red[W + wave] = b;
     }
     __syncthreads();
-    a = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    b = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
+    a = max_of<W>(red);
+    b = max_of<W>(red + W);
 }
 
-// max over the 256 threads of a block of four floats at once
-__device__ __forceinline__ void block_max4(float (&a)[4], float* red /* [16] in LDS */) {
+// max over the 64 W threads of a block of four floats at once
+template <int W = 4>
+__device__ __forceinline__ void block_max4(float (&a)[4], float* red /* [4 W] in LDS */) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) a[i] = wave_max(a[i]);
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) red[4 * i + wave] = a[i];
+        for (int i = 0; i < 4; ++i) red[W * i + wave] = a[i];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        a[i] = fmaxf(fmaxf(red[4 * i], red[4 * i + 1]), fmaxf(red[4 * i + 2], red[4 * i + 3]));
+    for (int i = 0; i < 4; ++i) a[i] = max_of<W>(red + W * i);
 }
 
 // Asymmetric branch of Section 3 Eq. 1: z = min, s = (max - min) / (2^N - 1),
@@ -94,12 +104,14 @@ __device__ __forceinline__ int quant_code_asym(float x, float zero, float scale,
     return (int)q;
 }
 
-// sum over the 256 threads of a block
-__device__ __forceinline__ int block_sum(int v, int* red /* [4] in LDS */) {
+// sum over the 64 W threads of a block
+template <int W = 4>
+__device__ __forceinline__ int block_sum(int v, int* red /* [W] in LDS */) {
     v = wave_sum(v);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
     __syncthreads();
-    return red[0] + red[1] + red[2] + red[3];
+    if constexpr (W == 4) return red[0] + red[1] + red[2] + red[3];
+    else return wave_sum<16>(red[threadIdx.x & 15]);
 }
 
 __device__ __forceinline__ float group_scale(float amax, int qmax) {
@@ -234,15 +246,15 @@ struct RotateArgs {
 
 // ASYM: the asymmetric quantizer; c_hi / c_lo [M] receive z + 2^(N-1) s, the real
 // value that the stored code 0 stands for (what the GEMM's epilogue needs).
-template <int ITERS, bool ROTATE, bool ASYM>
-__global__ __launch_bounds__(kQuantThreads) void quantize_act_vec_kernel(
+template <int ITERS, bool ROTATE, bool ASYM, int RT = kQuantThreads>
+__global__ __launch_bounds__(RT) void quantize_act_vec_kernel(
     const uint16_t* __restrict__ x, int64_t ldx, int K, int r, int8_t* __restrict__ q_hi,
     int64_t ld_hi, uint8_t* __restrict__ q_lo, int64_t ld_lo, float* __restrict__ s_hi,
     float* __restrict__ s_lo, int32_t* __restrict__ lo_sum, const RotateArgs rot,
     float* __restrict__ c_hi, float* __restrict__ c_lo) {
-    constexpr int RT = kQuantThreads;     // threads per row
-    __shared__ float red[16];
-    __shared__ int red_sum[4];
+    constexpr int W = RT / 64;            // RT threads per row
+    __shared__ float red[4 * W];
+    __shared__ int red_sum[W];
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
     const int nunits = K >> 3;
@@ -296,7 +308,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_vec_kernel(
                 ext[g + 1] = fmaxf(ext[g + 1], -mn);
             }
         }
-        block_max4(ext, red);
+        block_max4<W>(ext, red);
         zh = -ext[1];
         zl = -ext[3];
         sh = r > 0 ? asym_scale(zh, ext[0], 255) : 1.0f;
@@ -316,7 +328,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_vec_kernel(
                 else amax_l = fmaxf(amax_l, a);
             }
         }
-        block_max2(amax_h, amax_l, red);
+        block_max2<W>(amax_h, amax_l, red);
         sh = group_scale(amax_h, kQmaxHi);
         sl = group_scale(amax_l, kQmaxLo);
     }
@@ -358,7 +370,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_vec_kernel(
         *reinterpret_cast<uint2*>(qh + b) = make_uint2(0u, 0u);
     for (int64_t b = (int64_t)(K - r) / 2 + 4 * t; b < ld_lo; b += 4 * RT)
         *reinterpret_cast<uint32_t*>(ql + b) = 0x08080808u;
-    odd_sum = block_sum(odd_sum, red_sum);
+    odd_sum = block_sum<W>(odd_sum, red_sum);
     if (t == 0 && K - r > 0) lo_sum[m] = odd_sum;
 }
 
@@ -394,20 +406,20 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_vec_kernel(
 // them, so a rotated value may round to the neighbouring bf16 there.
 //
 // HI: units of 8 high columns per thread; LO: spans per wavefront.
-// Requires r <= 2048 HI, K - r <= 2048 LO, r and K - r multiples of 256.
+// Requires r <= 8 RT HI, K - r <= 8 RT LO, r and K - r multiples of 256.
 // ---------------------------------------------------------------------------
 typedef __bf16 v8bf_q __attribute__((ext_vector_type(8)));
 typedef float v4f_q __attribute__((ext_vector_type(4)));
 
-template <int HI, int LO, bool ASYM>
-__global__ __launch_bounds__(kQuantThreads) void hadamard256_quantize_kernel(
+template <int HI, int LO, bool ASYM, int RT = kQuantThreads>
+__global__ __launch_bounds__(RT) void hadamard256_quantize_kernel(
     const uint16_t* __restrict__ x, int64_t ldx, int K, int r, int8_t* __restrict__ q_hi,
     int64_t ld_hi, uint8_t* __restrict__ q_lo, int64_t ld_lo, float* __restrict__ s_hi,
     float* __restrict__ s_lo, int32_t* __restrict__ lo_sum, const RotateArgs rot,
     float* __restrict__ c_hi, float* __restrict__ c_lo) {
-    constexpr int RT = kQuantThreads;
-    __shared__ float red[16];
-    __shared__ int red_sum[4];
+    constexpr int W = RT / 64;
+    __shared__ float red[4 * W];
+    __shared__ int red_sum[W];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int64_t m = blockIdx.x;
     const int hi_units = r >> 3;
@@ -452,12 +464,12 @@ __global__ __launch_bounds__(kQuantThreads) void hadamard256_quantize_kernel(
     // clamped into it and the loaded value replaced by zero)
 #pragma unroll
     for (int i = 0; i < LO; ++i) {
-        const int col = (wave + 4 * i) * 512 + 32 * rho + 8 * q;
+        const int col = (wave + W * i) * 512 + 32 * rho + 8 * q;
         vl[i] = *reinterpret_cast<const uint4*>(row + r + (col < lo_cols ? col : lo_cols - 8));
     }
 #pragma unroll
     for (int i = 0; i < LO; ++i) {
-        const int s = wave + 4 * i;
+        const int s = wave + W * i;
         const int col = s * 512 + 32 * rho + 8 * q;
         const uint4 raw = col < lo_cols ? vl[i] : make_uint4(0u, 0u, 0u, 0u);
         const v4f_q zero = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -514,8 +526,8 @@ __global__ __launch_bounds__(kQuantThreads) void hadamard256_quantize_kernel(
             if (t + i * RT < hi_units) take(vh[i], 0);
 #pragma unroll
         for (int i = 0; i < LO; ++i)
-            if ((wave + 4 * i) * 512 + out_col < lo_cols) take(vl[i], 2);
-        block_max4(ext, red);
+            if ((wave + W * i) * 512 + out_col < lo_cols) take(vl[i], 2);
+        block_max4<W>(ext, red);
         zh = -ext[1];
         zl = -ext[3];
         sh = r > 0 ? asym_scale(zh, ext[0], 255) : 1.0f;
@@ -530,7 +542,7 @@ __global__ __launch_bounds__(kQuantThreads) void hadamard256_quantize_kernel(
         for (int i = 0; i < HI; ++i) amax_h = fmaxf(amax_h, absmax8(vh[i]));   // zeros past the group
 #pragma unroll
         for (int i = 0; i < LO; ++i) amax_l = fmaxf(amax_l, absmax8(vl[i]));   // zeros past the row
-        block_max2(amax_h, amax_l, red);
+        block_max2<W>(amax_h, amax_l, red);
         sh = group_scale(amax_h, kQmaxHi);
         sl = group_scale(amax_l, kQmaxLo);
     }
@@ -556,7 +568,7 @@ __global__ __launch_bounds__(kQuantThreads) void hadamard256_quantize_kernel(
     }
 #pragma unroll
     for (int i = 0; i < LO; ++i) {
-        const int oc = (wave + 4 * i) * 512 + out_col;
+        const int oc = (wave + W * i) * 512 + out_col;
         if (oc < lo_cols) {   // the last span may hold one block only: its upper 8 rows are idle
             uint32_t c[8];
             if constexpr (ASYM) quant8_asym<true>(vl[i], zl, sl, inv_l, c, odd_f);
@@ -575,7 +587,7 @@ __global__ __launch_bounds__(kQuantThreads) void hadamard256_quantize_kernel(
         *reinterpret_cast<uint2*>(qh + b) = make_uint2(0u, 0u);
     for (int64_t b = (int64_t)lo_cols / 2 + 4 * t; b < ld_lo; b += 4 * RT)
         *reinterpret_cast<uint32_t*>(ql + b) = 0x08080808u;
-    odd_sum = block_sum(odd_sum, red_sum);
+    odd_sum = block_sum<W>(odd_sum, red_sum);
     if (t == 0) lo_sum[m] = odd_sum;
 }
 

@@ -121,6 +121,35 @@ def test_quantize_act_generic_path(oracle, rq, M, K, r):
     check_act_codes(oracle, rq, wl.make_activations(s), r)
 
 
+# both sides of each line between 256 and 1024 threads to a row, and rows that end inside a wavefront
+@pytest.mark.parametrize("M,K,r", [(256, 4104, 520), (257, 4104, 520), (2, 4096, 512), (3, 8192, 1024), (2, 8200, 1032),
+                                   (512, 8200, 1032), (513, 8200, 1032), (1, 16384, 0), (2, 12296, 12296)])
+def test_quantize_act_threads_per_row(oracle, rq, M, K, r):
+    x = wl.random_small_case(M + K, M, K, 16, r, act="student_t3")[0]
+    check_act_codes(oracle, rq, x, r)
+    act = rq.resq_quantize_act_asym(x.cuda(), r)
+    torch.cuda.synchronize()
+    compare_asym_codes(oracle, act, wl.bf16_bits(x), r)
+
+
+@pytest.mark.parametrize("M,K,r", [(256, 4608, 256), (257, 4608, 256), (2, 8448, 256), (512, 8704, 512), (513, 8704, 512),
+                                   (3, 16896, 256), (5, 28672, 3584), (1025, 16896, 512)])
+@pytest.mark.parametrize("asym", [False, True])
+def test_hadamard256_quantize_threads_per_row(oracle, rq, M, K, r, asym):
+    # codes bit-exact on the kernel's own rotated row; the row itself is the transform's test elsewhere
+    x = wl.random_small_case(M + K, M, K, 16, r, act="student_t3")[0]
+    x_rot = torch.zeros((M, K), dtype=torch.bfloat16, device="cuda")
+    fn = rq.resq_hadamard_quantize_act_asym if asym else rq.resq_hadamard_quantize_act
+    act = fn(x.cuda(), r, 256, x_rot=x_rot)
+    torch.cuda.synchronize()
+    x_rot[:, :r] = x[:, :r].cuda()
+    want = rq.resq_online_hadamard(x.cuda(), r, K, 256)
+    torch.cuda.synchronize()
+    # the two take their sums in another order: neighbouring bf16 numbers at most
+    assert (x_rot.float() - want.float()).abs().max() <= 2.0 ** -7 * want.float().abs().max()
+    (compare_asym_codes if asym else compare_act_codes)(oracle, act, wl.bf16_bits(x_rot.cpu()), r)
+
+
 def test_quantize_act_strided_rows_zero_rows_and_ties(oracle, rq):
     # rows taken from a wider buffer (ldx > K), an all-zero token, an all-zero group,
     # and exact ties (values on half-integers of a power-of-two scale)
