@@ -7,17 +7,19 @@
 // number is the exact sum of three bf16 numbers (8 + 8 + 8 significant bits, each
 // the truncated rest of the one before), every product with a bf16 a is exact in
 // fp32, and the accumulator is fp32 as before.  Three products instead of one, at
-// sixteen times the rate: 0.46 ms for the same fold (900 TFLOP/s of bf16 products).
+// sixteen times the rate: 0.44 ms for the same fold (940 TFLOP/s of bf16 products, matrix
+// pipes busy 52 % of the clocks at 1.7 GHz: the power limit).
 // Error against 64 bits with fp32 output (2-norm, before / now): 1.2e-6 / 7.0e-7 at
 // K = 4096, 4.0e-7 / 2.4e-7 at 512, 2.0e-7 / 1.2e-7 at 128: the sum has fewer roundings
 // (one per 16 products of the instruction instead of one per 2).
 //
 // Workgroup: 4 wavefronts, 128 x 128 outputs, 64 x 64 each as 2 x 2 tiles of
-// v_mfma_f32_32x32x16_bf16; the reduction in chunks of 32 through two LDS buffers,
-// the next chunk travelling through registers while this one is multiplied, one
-// barrier per chunk; two workgroups share a compute unit, so that one splits and
-// stores while the other multiplies.  The B operand wants eight consecutive t of
-// one column per lane: a thread reads them as eight rows of u (lanes along j, 256
+// v_mfma_f32_32x32x16_bf16; the reduction in chunks of 32 through two LDS buffers, one
+// barrier per chunk, two workgroups to a compute unit.  A chunk's fragments are read
+// at once; behind each product five vector instructions of the next chunk's split run
+// (with the split after the products instead: 1000 x 1003 x 904 46 / 36 us, 256 x 512 x 512
+// 25 / 21, 4096^3 at the power limit either way).  The B operand wants eight consecutive
+// t of one column per lane: a thread reads them as eight rows of u (lanes along j, 256
 // contiguous bytes a wavefront), splits them and writes three 16-byte units, so
 // the transposition costs nothing.  LDS units of 16 bytes, column-major over the
 // pieces: reads and writes run along consecutive rows or columns.
@@ -72,22 +74,25 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const Pr
     }
     const uint32_t u_col = (uint32_t)((j0 + bj < g.J ? j0 + bj : g.J - 1) - j0);
     const uint16_t* a_base = g.a + i0 * g.lda + ap * 8;
-    uint4 ra[2];
-    float rb[2][8];
+    // a chunk on its way from memory to LDS
+    struct Chunk {
+        uint4 a[2];
+        float u[2][8];
+    };
     // the chunk of steps tc .. tc + 31, all of them there
-    auto fetch = [&](int64_t tc) __attribute__((always_inline)) {
+    auto fetch = [&](Chunk& c, int64_t tc) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            ra[h] = *reinterpret_cast<const uint4*>(a_base + a_row[h] * g.lda + tc);
+            c.a[h] = *reinterpret_cast<const uint4*>(a_base + a_row[h] * g.lda + tc);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const float* row = g.u + (tc + (bp + 2 * h) * 8) * g.ldu + j0;   // wave-uniform
 #pragma unroll
-            for (int e = 0; e < 8; ++e) rb[h][e] = row[e * g.ldu + u_col];
+            for (int e = 0; e < 8; ++e) c.u[h][e] = row[e * g.ldu + u_col];
         }
     };
     // the last chunk of a ragged reduction axis: what lies behind it in a row of a is not ours
-    auto fetch_tail = [&](int64_t tc) __attribute__((always_inline)) {
+    auto fetch_tail = [&](Chunk& c, int64_t tc) __attribute__((always_inline)) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int64_t tt = tc + ap * 8;
@@ -96,25 +101,25 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const Pr
 #pragma unroll
             for (int e = 0; e < 8; ++e)
                 if (tt + e < g.T) w[e >> 1] |= (uint32_t)src[e] << (16 * (e & 1));
-            ra[h] = make_uint4(w[0], w[1], w[2], w[3]);
+            c.a[h] = make_uint4(w[0], w[1], w[2], w[3]);
         }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int64_t tt = tc + (bp + 2 * h) * 8;
             const float* row = g.u + tt * g.ldu + j0;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) rb[h][e] = tt + e < g.T ? row[e * g.ldu + u_col] : 0.0f;
+            for (int e = 0; e < 8; ++e) c.u[h][e] = tt + e < g.T ? row[e * g.ldu + u_col] : 0.0f;
         }
     };
-    auto fetch_any = [&](int64_t tc) __attribute__((always_inline)) {
-        if (tc + kProjChunk <= g.T) fetch(tc);
-        else fetch_tail(tc);
+    auto fetch_any = [&](Chunk& c, int64_t tc) __attribute__((always_inline)) {
+        if (tc + kProjChunk <= g.T) fetch(c, tc);
+        else if (tc < g.T) fetch_tail(c, tc);
     };
-    auto stash = [&](int buf) __attribute__((always_inline)) {
+    auto stash = [&](const Chunk& c, int buf) __attribute__((always_inline)) {
         uint8_t* base = lds + buf * kProjBytes;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-            *reinterpret_cast<uint4*>(base + ap * kProjPieceA + (ar + 64 * h) * 16) = ra[h];
+            *reinterpret_cast<uint4*>(base + ap * kProjPieceA + (ar + 64 * h) * 16) = c.a[h];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             uint32_t part[3][4];
@@ -123,7 +128,7 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const Pr
                 uint32_t x[2], y[2], z[2];
 #pragma unroll
                 for (int k = 0; k < 2; ++k) {
-                    const float v = rb[h][e + k];
+                    const float v = c.u[h][e + k];
                     x[k] = __float_as_uint(v);
                     const float r1 = v - __uint_as_float(x[k] & 0xFFFF0000u);   // exact
                     y[k] = __float_as_uint(r1);
@@ -150,36 +155,76 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const Pr
             for (int v = 0; v < 16; ++v) acc[p][q][v] = 0.0f;
 
     const int ol = lane & 31, oh = lane >> 5;
-    fetch_any(0);
-    stash(0);
-    __syncthreads();
-    int buf = 0;
-    for (int64_t tc = 0; tc < g.T; tc += kProjChunk) {
-        const bool more = tc + kProjChunk < g.T;
-        if (more) fetch_any(tc + kProjChunk);
+    constexpr int kSteps = kProjChunk / 16;
+    struct Frags {
+        v8bf a[kSteps][2], b[kSteps][3][2];
+    };
+    auto read_frags = [&](Frags& f, int buf) __attribute__((always_inline)) {
         const uint8_t* base = lds + buf * kProjBytes;
 #pragma unroll
-        for (int s = 0; s < kProjChunk / 16; ++s) {
+        for (int s = 0; s < kSteps; ++s) {
             const int piece = 2 * s + oh;
-            v8bf fa[2];
 #pragma unroll
             for (int p = 0; p < 2; ++p)
-                fa[p] = *reinterpret_cast<const v8bf*>(base + piece * kProjPieceA + (wi * 64 + p * 32 + ol) * 16);
-            // the smallest parts first
+                f.a[s][p] = *reinterpret_cast<const v8bf*>(base + piece * kProjPieceA + (wi * 64 + p * 32 + ol) * 16);
 #pragma unroll
             for (int part = 2; part >= 0; --part)
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const v8bf fb = *reinterpret_cast<const v8bf*>(base + kProjBytesA + part * kProjSplitB +
-                                                                   piece * kProjPieceB + (wj * 64 + q * 32 + ol) * 16);
+                for (int q = 0; q < 2; ++q)
+                    f.b[s][part][q] = *reinterpret_cast<const v8bf*>(base + kProjBytesA + part * kProjSplitB +
+                                                                     piece * kProjPieceB + (wj * 64 + q * 32 + ol) * 16);
+        }
+    };
+    // the smallest parts first
+    auto multiply = [&](const Frags& f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+            for (int part = 2; part >= 0; --part)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
 #pragma unroll
                     for (int p = 0; p < 2; ++p)
-                        acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[p], fb, acc[p][q], 0, 0, 0);
-                }
+                        acc[p][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[s][p], f.b[s][part][q], acc[p][q], 0, 0, 0);
+    };
+
+    // Chunk i is multiplied out of buffer i % 2 while chunk i + 1, in registers since the step before, is
+    // split and written into the other one, a few instructions behind each product, and chunk
+    // i + 2 is on its way from memory.
+    Chunk c0, c1;
+    fetch_any(c0, 0);
+    stash(c0, 0);
+    fetch_any(c0, kProjChunk);
+    __syncthreads();
+    auto step = [&](Chunk& here, Chunk& next, int64_t tc, int buf) __attribute__((always_inline)) {
+        fetch(next, tc + 2 * kProjChunk);
+        Frags f;
+        read_frags(f, buf);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(f);
+        stash(here, buf ^ 1);
+#pragma unroll
+        for (int k = 0; k < 24; ++k) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // a product
+            __builtin_amdgcn_sched_group_barrier(0x002, 5, 0);   // vector instructions
+            if (k % 3 == 2) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   // an LDS write
         }
-        if (more) stash(buf ^ 1);  // last read in the previous iteration, before its barrier
+        __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
-        buf ^= 1;
+    };
+    int64_t tc = 0;
+    for (; tc + 4 * kProjChunk <= g.T; tc += 2 * kProjChunk) {
+        step(c0, c1, tc, 0);
+        step(c1, c0, tc + kProjChunk, 1);
+    }
+    for (int buf = 0; tc < g.T; tc += kProjChunk, buf ^= 1) {   // up to four chunks are left, the last one perhaps ragged
+        fetch_any(c1, tc + 2 * kProjChunk);
+        Frags f;
+        read_frags(f, buf);
+        multiply(f);
+        if (tc + kProjChunk < g.T) stash(c0, buf ^ 1);
+        __syncthreads();
+        c0 = c1;
     }
 
     // acc[p][q][v]: row 8 (v / 4) + 4 (lane / 32) + v % 4, column lane % 32 of matrix tile (p, q)
