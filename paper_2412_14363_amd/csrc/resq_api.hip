@@ -142,7 +142,8 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
     // the units are full of wavefronts: 512 x 14336 9.04 / 8.04, transformed 10.44 / 9.48 (1024: equal;
     // 512 x 8192: 5.48 / 6.64), 1024 x 28672 transformed 24.5 / 23.0 (2048: 38.4 / 41.9).
     const bool few = M <= (K > 16384 ? 1024 : K > 8192 ? 512 : (rot.log2b ? K - r > 4096 : K > 4096) && !asym ? 256 : 0);
-    const bool vec = aligned(x, 16) && ldx % 8 == 0 && K % 8 == 0 && r % 8 == 0 && K <= 16384;
+    const bool pieces = aligned(x, 16) && ldx % 8 == 0 && K % 8 == 0 && r % 8 == 0;  // rows of whole 16-byte pieces
+    const bool vec = pieces && K <= 16384;
     const bool rotate = rot.log2b > 0;
 #define RESQ_QA_ARGS xp, ldx, (int)K, (int)r, q_hi, ld_hi, q_lo, ld_lo, s_hi, s_lo, lo_sum
     // blocks of 256: the first five butterfly stages on the matrix cores
@@ -207,9 +208,12 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else if (K <= 256) RESQ_LAUNCH_SHORT(32);
         else RESQ_LAUNCH_SHORT(64);
 #undef RESQ_LAUNCH_SHORT
-    } else if (vec && !rotate && few) {
+    } else if (pieces && !rotate && K <= 32768 && (few || K > 16384)) {
+        // (beyond 16384 columns at every M: the element-wise kernel is the other one there; 28672
+        // columns 1 row 28.6 / 4.9 us, 128 rows 29.8 / 6.7, 4096 rows 206 / 65)
         if (K <= 8192) RESQ_LAUNCH_QA_WIDE(1);
-        else RESQ_LAUNCH_QA_WIDE(2);
+        else if (K <= 16384) RESQ_LAUNCH_QA_WIDE(2);
+        else RESQ_LAUNCH_QA_WIDE(4);
     } else if (vec) {
         if (K <= 2048) RESQ_LAUNCH_QA(1);
         else if (K <= 4096) RESQ_LAUNCH_QA(2);
