@@ -219,6 +219,12 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else if (K <= 4096) RESQ_LAUNCH_QA(2);
         else if (K <= 8192) RESQ_LAUNCH_QA(4);
         else RESQ_LAUNCH_QA(8);
+    } else if (M <= (K > 8192 ? 1024 : K > 4096 ? 512 : K > 2048 ? 256 : 0)) {
+        // few long rows without whole 16-byte pieces (256 / 1024 threads, us): 256 rows of 2050 columns
+        // 4.48 / 4.12, 512 of 5002 8.48 / 6.52, 1024 of 9186 21.4 / 17.4, 16 of 28674 29.6 / 10.6; not below or
+        // above (1002 columns equal, 512 of 2050 equal, 4096 of 9186 53.4 / 59.0)
+        if (asym) launch(quantize_act_generic_kernel<true, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, c_hi, c_lo);
+        else launch(quantize_act_generic_kernel<false, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, c_hi, c_lo);
     } else if (asym) {
         launch(quantize_act_generic_kernel<true>, grid, block, 0, st, RESQ_QA_ARGS, c_hi, c_lo);
     } else {

@@ -809,14 +809,15 @@ __global__ __launch_bounds__(kQuantThreads) void dequantize_kv_cache_kernel(
 // Activations, any K, r (K - r even) and alignment: two passes over the row
 // with 2-byte loads.  Correct everywhere, fast nowhere.
 // ---------------------------------------------------------------------------
-template <bool ASYM>
-__global__ __launch_bounds__(kQuantThreads) void quantize_act_generic_kernel(
+template <bool ASYM, int RT = kQuantThreads>
+__global__ __launch_bounds__(RT) void quantize_act_generic_kernel(
     const uint16_t* __restrict__ x, int64_t ldx, int K, int r, int8_t* __restrict__ q_hi,
     int64_t ld_hi, uint8_t* __restrict__ q_lo, int64_t ld_lo, float* __restrict__ s_hi,
     float* __restrict__ s_lo, int32_t* __restrict__ lo_sum, float* __restrict__ c_hi,
     float* __restrict__ c_lo) {
-    __shared__ float red[16];
-    __shared__ int red_sum[4];
+    constexpr int W = RT / 64;            // RT threads per row
+    __shared__ float red[4 * W];
+    __shared__ int red_sum[W];
     const int64_t m = blockIdx.x;
     const int t = threadIdx.x;
     const uint16_t* row = x + m * ldx;
@@ -824,13 +825,13 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_generic_kernel(
     if constexpr (ASYM) {
         const float inf = __builtin_huge_valf();
         float ext[4] = {-inf, -inf, -inf, -inf};  // max_h, -min_h, max_l, -min_l
-        for (int k = t; k < K; k += kQuantThreads) {
+        for (int k = t; k < K; k += RT) {
             const float a = bf16_bits_to_f32(row[k]);
             const int g = k < r ? 0 : 2;
             ext[g] = fmaxf(ext[g], a);
             ext[g + 1] = fmaxf(ext[g + 1], -a);
         }
-        block_max4(ext, red);
+        block_max4<W>(ext, red);
         zh = -ext[1];
         zl = -ext[3];
         sh = r > 0 ? asym_scale(zh, ext[0], 255) : 1.0f;
@@ -841,12 +842,12 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_generic_kernel(
         }
     } else {
         float amax_h = 0.0f, amax_l = 0.0f;
-        for (int k = t; k < K; k += kQuantThreads) {
+        for (int k = t; k < K; k += RT) {
             const float a = bf16_bits_to_f32(row[k] & 0x7FFFu);
             if (k < r) amax_h = fmaxf(amax_h, a);
             else amax_l = fmaxf(amax_l, a);
         }
-        block_max2(amax_h, amax_l, red);
+        block_max2<W>(amax_h, amax_l, red);
         sh = group_scale(amax_h, kQmaxHi);
         sl = group_scale(amax_l, kQmaxLo);
     }
@@ -865,11 +866,11 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_generic_kernel(
     };
     int8_t* qh = q_hi + m * ld_hi;
     uint8_t* ql = q_lo + m * ld_lo;
-    for (int64_t k = t; k < ld_hi; k += kQuantThreads)
+    for (int64_t k = t; k < ld_hi; k += RT)
         qh[k] = k < r ? (int8_t)code_hi(bf16_bits_to_f32(row[k])) : (int8_t)0;
     const int pairs = (K - r) / 2;
     int odd_sum = 0;
-    for (int64_t j = t; j < ld_lo; j += kQuantThreads) {
+    for (int64_t j = t; j < ld_lo; j += RT) {
         uint32_t byte = 0x08u;
         if (j < pairs) {
             const int c0 = code_lo(bf16_bits_to_f32(row[r + 2 * j]));
@@ -879,7 +880,7 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_act_generic_kernel(
         }
         ql[j] = (uint8_t)byte;
     }
-    odd_sum = block_sum(odd_sum, red_sum);
+    odd_sum = block_sum<W>(odd_sum, red_sum);
     if (t == 0 && K - r > 0) lo_sum[m] = odd_sum;
 }
 

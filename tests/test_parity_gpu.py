@@ -125,7 +125,10 @@ def test_quantize_act_generic_path(oracle, rq, M, K, r):
 @pytest.mark.parametrize("M,K,r", [(256, 4104, 520), (257, 4104, 520), (2, 4096, 512), (3, 8192, 1024), (2, 8200, 1032),
                                    (512, 8200, 1032), (513, 8200, 1032), (1, 16384, 0), (2, 12296, 12296),
                                    # beyond 16384 columns, the last that 1024 threads hold and the first that they do not
-                                   (3, 16392, 2056), (1030, 17000, 128), (2, 32768, 4096), (2, 32776, 4096), (2, 20000, 0)])
+                                   (3, 16392, 2056), (1030, 17000, 128), (2, 32768, 4096), (2, 32776, 4096), (2, 20000, 0),
+                                   # ... and rows without whole 16-byte pieces
+                                   (256, 2050, 258), (257, 2050, 258), (3, 2046, 0), (512, 4100, 516), (513, 4100, 516),
+                                   (1024, 8198, 1026), (1025, 8198, 1026), (1, 28674, 3584)])
 def test_quantize_act_threads_per_row(oracle, rq, M, K, r):
     x = wl.random_small_case(M + K, M, K, 16, r, act="student_t3")[0]
     check_act_codes(oracle, rq, x, r)
