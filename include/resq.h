@@ -210,8 +210,9 @@ int resq_unpack_weights(const void* packed, int64_t N, int64_t K, int64_t r, int
  *   A_hi[m, n] = sum_{k <  r} q_hi[m, k] * w_hi[n, k]       (int8 x int8 -> int32)
  *   A_lo[m, n] = sum_{k >= r} q_lo[m, k] * w_lo[n, k]       (int4 x int4 -> int32)
  *   y[m, n]    = bf16( A_hi * s_hi[m] * sw_hi[n] + A_lo * s_lo[m] * sw_lo[n] )
- * Both sums run on the int8 matrix cores (nibbles are widened in registers)
- * inside one kernel; y is written once.  The integer sums are exact: the call
+ * Both sums run on the matrix cores inside one kernel (int8, the nibbles widened in
+ * registers; on layers of more than one round of 128 x 128 tiles the low group as fp8
+ * numbers, which hold the codes and their sums exactly); y is written once.  The integer sums are exact: the call
  * accepts r <= 132104 and K - r <= 2^20, so neither 128 * 127 * r (stored asymmetric
  * codes reach -128) nor the widened low sum 1680 * (K - r) can reach 2^31 (larger
  * groups: RESQ_ERR_SHAPE).
@@ -350,8 +351,9 @@ int resq_sym_eig_static(const float* c, int64_t ldc, int64_t K, int sweeps, floa
                         int64_t ldp, void* stream);
 
 /*
- * 3. Rows expressed in a basis:  out[i][j] = sum_k a[i][k] u[k][j]  (fp32
- *    accumulation on the fp32 matrix cores).  This one product serves every
+ * 3. Rows expressed in a basis:  out[i][j] = sum_k a[i][k] u[k][j]  (exact
+ *    products, fp32 accumulation: fp32 matrix cores for fp32 a; for bf16 a the bf16
+ *    ones, u in three bf16 parts whose sum it is).  This one product serves every
  *    remaining step: U_h = P_h R_h and U_l = P_l R_l (the definition of U in
  *    Section 4.2: a = a column block of p, u = a random orthogonal matrix passed
  *    in by the caller, out = a column block of U), the folding of U into the

@@ -2,7 +2,8 @@
 //
 //   gram:    C[i][j] += sum_t X[t][i] X[t][j]      covariance of the calibration activations
 //   project: Y[i][j]  = sum_t A[i][t] U[t][j]      rows of A (activations, weights, P_h, P_l)
-//                                                  expressed in a basis / rotated inside a group
+//                                                  expressed in a basis / rotated inside a group (fp32 rows;
+//                                                  bf16 rows: resq_project.hip.h)
 //
 // Both are C(i, j) = sum_t A(i, t) B(t, j) with fp32 accumulation on the fp32
 // matrix-core instruction v_mfma_f32_32x32x2_f32 (bf16 inputs are widened exactly,
