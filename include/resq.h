@@ -327,6 +327,8 @@ int resq_gram_accumulate(const void* x, int64_t ldx, int64_t T, int64_t K, float
  *               that found nothing to rotate cost only their empty launches
  *      eigvals  fp32 [K]                             (written)
  *      p        fp32 [K, ldp], ldp >= K              (written)
+ *               eigvals and p may lie on c's memory (c is lost then), not on each other's; orders
+ *               up to 128 run in one launch on separate memory, and through the workspace in place
  *      workspace  device memory, 256-byte aligned, resq_sym_eig_workspace_bytes(K)
  *               bytes (else RESQ_ERR_BUFFER); contents meaningless afterwards
  */

@@ -880,14 +880,26 @@ size_t resq_sym_eig_workspace_bytes(int64_t K) {
            round_up(K * (int64_t)sizeof(int), 256) + round_up(kEigMaxSweeps * (int64_t)sizeof(int), 256);
 }
 
+// whether two row-major fp32 blocks of cols columns share memory: their address ranges meet and they are not
+// separate column blocks of one matrix
+static bool blocks_overlap(const float* a, int64_t rows_a, int64_t lda, const float* b, int64_t rows_b, int64_t ldb,
+                           int64_t cols) {
+    const int64_t d = (int64_t)((reinterpret_cast<uintptr_t>(b) - reinterpret_cast<uintptr_t>(a))) / (int64_t)sizeof(float);
+    if (d >= (rows_a - 1) * lda + cols || -d >= (rows_b - 1) * ldb + cols) return false;
+    if (lda != ldb) return true;
+    const int64_t shift = (d % lda + lda) % lda;  // b's first column, counted from a's, modulo the row
+    return shift < cols || shift + cols > lda;
+}
+
 // the Jacobi iteration on a workspace that holds resq_sym_eig_workspace_bytes(K) bytes
 static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int sweeps, float* eigvals, float* p,
                                 int64_t ldp, void* workspace, void* stream) {
     const int n = (int)K;
     // one launch on LDS while the matrix and a slice of the vectors fit there, up to 128 columns:
     // 1.06 ms at n = 128 against 6.9 ms in two launches a round (0.15 / 1.69 ms at n = 32, 0.39 / 4.9
-    // at 64)
-    if (n <= kEigSmallMax) {
+    // at 64).  Not where an output lies on c: its workgroups all read c at their start and write p and
+    // eigvals at their end, in no order among each other; the workspace takes a copy of c first.
+    if (n <= kEigSmallMax && !blocks_overlap(c, K, ldc, p, K, ldp, K) && !blocks_overlap(c, K, ldc, eigvals, 1, K, K)) {
         const int small_lds = eig_small_lds_bytes(n);
         if (small_lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void*>(eig_small_kernel),

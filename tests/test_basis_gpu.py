@@ -161,6 +161,55 @@ def test_sym_eig_small_orders(rq, K):
     assert np.abs(c64 @ p - p * lam).max() <= 1e-6 * lam_ref[0]
 
 
+# Outputs on the memory of c, at orders on both sides of the single-launch kernel's limit.  Its workgroups do not
+# wait for each other, so such calls go through the workspace, which they leave written.
+@pytest.mark.parametrize("K", [2, 8, 10, 64, 126, 128, 130])
+def test_sym_eig_in_place(rq, K):
+    g = torch.Generator().manual_seed(K)
+    x = torch.randn(2 * K + 3, K, generator=g, dtype=torch.float64) * torch.exp(-3.0 * torch.arange(K) / K)
+    c0 = (x.T @ x).float()
+    c64 = c0.double().numpy()
+    lam_ref = np.linalg.eigvalsh(c64)[::-1]
+    L, st = rq.lib(), torch.cuda.current_stream().cuda_stream
+    nbytes = L.resq_sym_eig_workspace_bytes(K)
+
+    def call(c, lam, p, through_workspace):
+        work = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        rc = L.resq_sym_eig(c.data_ptr(), c.stride(0), K, 12, lam.data_ptr(), p.data_ptr(), p.stride(0), work.data_ptr(), nbytes, st)
+        assert rc == 0, rq.STATUS_NAMES.get(rc, rc)
+        torch.cuda.synchronize()
+        assert bool((work != 0xA5).any()) == through_workspace
+        ld, pd = lam.double().cpu().numpy(), p.double().cpu().numpy()
+        assert np.abs(ld - lam_ref).max() <= 1e-7 * lam_ref[0]
+        assert np.allclose(pd.T @ pd, np.eye(K), atol=1e-6)
+        assert np.abs(c64 @ pd - pd * ld).max() <= 1e-6 * lam_ref[0]
+
+    def buffers(rows, cols):
+        return torch.full((rows, cols), 7.0, device="cuda")
+
+    c, lam = buffers(K, K), torch.empty(K, device="cuda")
+    c.copy_(c0)
+    call(c, lam, c, True)                                          # p on c
+    wide = buffers(K, K + 6)
+    wide[:, :K].copy_(c0)
+    call(wide[:, :K], lam, wide[:, 1:K + 1], True)                 # ... shifted by a column
+    both = buffers(2 * K, K + 2)
+    both[:K, :K].copy_(c0)
+    call(both[:K, :K], lam, both[K - 1:2 * K - 1, :K], True)       # ... p begins in c's last row
+    c.copy_(c0)
+    call(c, c.view(-1)[:K], buffers(K, K), True)                   # eigenvalues on c
+    pair = buffers(K, 2 * K)
+    pair[:, K:].copy_(c0)
+    call(pair[:, K:], lam, pair[:, :K], K > 128)                   # column blocks of one matrix: separate
+    assert torch.equal(pair[:, K:].cpu(), c0)
+    if K <= 512:
+        c.copy_(c0)
+        rq.resq_sym_eig_static(c, lam, c)
+        torch.cuda.synchronize()
+        pd = c.double().cpu().numpy()
+        assert np.abs(c64 @ pd - pd * lam.double().cpu().numpy()).max() <= 1e-6 * lam_ref[0]
+
+
 def test_sym_eig_small_orders_without_rotations(rq):
     # nothing to rotate, singular and indefinite input
     lam, p = rq.resq_sym_eig(torch.zeros(64, 64, device="cuda"))
