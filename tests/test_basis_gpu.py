@@ -103,6 +103,49 @@ def test_project_rows_split(rq, rows, K, J):
     assert np.all(np.abs(buf[:, :J].double().cpu().numpy() - ad @ ud) <= 3 * K * 2.0 ** -24 * (np.abs(ad) @ np.abs(ud)) + 1e-30)
 
 
+# Infinities and NaN in either operand: what a plain sum gives, not the NaN that infinity x 0 among the three
+# parts of u would leave (bf16 numbers have two zero parts).
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+def test_project_rows_split_infinities(rq, out_dtype):
+    rows, K, J = 131, 70, 136
+    g = torch.Generator().manual_seed(5)
+    a = torch.randn(rows, K, generator=g).bfloat16()
+    u = torch.randn(K, J, generator=g)
+    u[:, ::2] = u[:, ::2].bfloat16().float()
+    inf, nan = float("inf"), float("nan")
+    a[0, 3], a[5, 60], a[130, 69], a[7, 2], a[7, 9], a[9, 1], a[11, 5] = inf, -inf, inf, inf, -inf, nan, 0.0
+    u[64, 4], u[5, 7], u[2, 135], u[3, 8] = inf, -inf, inf, 0.0
+    ld = 72
+    ad = torch.zeros(rows, ld, dtype=torch.bfloat16)
+    ad[:, :K] = a
+    got = rq.resq_project_rows(ad.cuda()[:, :K], u.cuda(), out_dtype=out_dtype).cpu().double().numpy()
+    with np.errstate(invalid="ignore"):
+        ref = a.double().numpy() @ u.double().numpy()
+    assert np.isinf(ref).sum() > 500 and np.isnan(ref).sum() > 100
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    fin = np.isfinite(ref)
+    mag = np.abs(np.nan_to_num(a.double().numpy(), posinf=0, neginf=0)) @ np.abs(np.nan_to_num(u.double().numpy(), posinf=0, neginf=0))
+    tol = 3 * K * 2.0 ** -24 * mag + (2.0 ** -8 * np.abs(np.where(fin, ref, 0)) if out_dtype == torch.bfloat16 else 0)
+    assert np.all(np.abs(got[fin] - ref[fin]) <= tol[fin])
+    if out_dtype == torch.bfloat16:   # out on a: one column of tiles, so that rows stay a workgroup's own
+        buf = ad.cuda()
+        rq.resq_project_rows(buf[:, :K], u[:, :64].contiguous().cuda(), out=buf[:, :64])
+        assert np.array_equal(buf[:, :64].cpu().double().numpy(), got[:, :64], equal_nan=True)
+
+
+# Entries of u so small that their third part falls under the smallest bf16 subnormal, 2^-133
+def test_project_rows_split_tiny_basis(rq):
+    rows, K, J = 40, 96, 64
+    g = torch.Generator().manual_seed(6)
+    a = (torch.randn(rows, K, generator=g) * 2.0 ** 60).bfloat16()
+    u = torch.randn(K, J, generator=g) * torch.exp2(torch.randint(-130, -105, (K, J), generator=g).float())
+    got = rq.resq_project_rows(a.cuda(), u.cuda(), out_dtype=torch.float32).cpu().double().numpy()
+    ad, ud = a.double().numpy(), u.double().numpy()
+    tol = 3 * K * 2.0 ** -24 * (np.abs(ad) @ np.abs(ud)) + 2.0 ** -133 * np.abs(ad).sum(1, keepdims=True)
+    assert np.all(np.abs(got - ad @ ud) <= tol)
+
+
 def test_project_rows_on_column_blocks(rq):
     # U_h = P_h R_h written into the first r columns of U: sub-blocks in and out
     K, r = 64, 16
