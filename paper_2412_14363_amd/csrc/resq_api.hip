@@ -487,7 +487,10 @@ static GemmPlan plan_gemm(int64_t M, const WeightLayout& L) {
 // 2 % per high stage.  So not where a single round runs below the power limit (2048 x 4096 -> 4096
 // 31.7 / 32.1 us), where stages are few (2048 x 2048 -> 8192, 14 low: 35.6 / 36.8; 4096 x 1024 -> 8192,
 // 8 low: 46.9 / 48.3) or mostly high (4096 x 4096 -> 8192, r = K/2: 126.4 / 130.2); and not where its
-// sums could leave the whole numbers of fp32.
+// sums could leave the whole numbers of fp32.  In a whole call, a quantizer in front of every GEMM, over
+// 1 to 16 rounds, whole and ragged ones: 2 to 9 % at 8 high stages and 28 low ones or more, and on the
+// line's high side (24 low and 16 high, 36 and 24, 46 and 26) 2 to 6 %, at the least equal (2811 x 7552 -> 4096,
+// 704 tiles: 83.8 / 84.3).
 static bool use_f8(int64_t M, const WeightLayout& L) {
     const int64_t tiles = ((M + kBM - 1) / kBM) * ((L.N + kBN - 1) / kBN);
     return tiles > 512 && L.lo_blocks >= 24 && 2 * L.lo_blocks >= 3 * L.hi_blocks && L.kl_pad <= kF8MaxLoWidth;

@@ -348,6 +348,19 @@ def test_layer_tiled_kernel_fp8_low_group_asym_and_saturated(oracle, rq):
     check_layer(oracle, rq, x, w, r)
 
 
+# grids whose number of tiles leaves 2, 4 and 6 over eight: every XCD has its own run of tiles, the first of them one more
+@pytest.mark.parametrize("M,K,N,r,kernel,tiles", [
+    (385, 512, 2562, 64, 3, 154), (321, 512, 3300, 64, 3, 156), (385, 512, 3300, 64, 3, 182),
+    (1025, 512, 2050, 64, 3, 306), (577, 512, 3300, 64, 3, 260), (700, 512, 3300, 64, 3, 286),
+    (1537, 512, 3300, 64, 2, 338), (1700, 512, 2562, 64, 2, 308), (1793, 512, 2300, 64, 2, 270),
+])
+def test_layer_tile_order(oracle, rq, M, K, N, r, kernel, tiles):
+    assert rq.resq_gemm_mixed_plan(M, N, K, r)[0] == kernel
+    assert -(-M // (64 if kernel == 3 else 128)) * -(-N // 256) * 2 == tiles
+    x, w = wl.random_small_case(M + N, M, K, N, r, act="student_t3")
+    check_layer(oracle, rq, x, w, r, ldy_extra=8 if N % 4 == 0 else 3)
+
+
 @pytest.mark.parametrize("M,K,N,r", [
     (385, 2048, 400, 256), (512, 4096, 272, 512), (1000, 1000, 515, 104), (1024, 3200, 256, 448),
     (700, 256, 256, 0), (640, 256, 64, 256), (1024, 14336, 144, 1792),
