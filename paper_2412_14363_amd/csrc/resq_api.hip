@@ -135,13 +135,22 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     const uint16_t* xp = static_cast<const uint16_t*>(x);
     const dim3 block(kQuantThreads), wide(kQuantWideThreads), grid((unsigned)M);
-    // Few long rows: 1024 threads to a row instead of 256 (256 / 1024 threads, us).  Up to one row per
-    // compute unit from two units of eight columns a thread on: 16 rows of 6400 columns 4.56 / 4.08, of 8192
-    // 4.44 / 4.20, of 14336 6.12 / 4.16, transformed ones of 8192 5.76 / 5.00; not below (4096: equal), nor
-    // with the asymmetric quantizer's four maxima (8192: 4.36 / 4.56).  Longer rows keep the gain until
-    // the units are full of wavefronts: 512 x 14336 9.04 / 8.04, transformed 10.44 / 9.48 (1024: equal;
-    // 512 x 8192: 5.48 / 6.64), 1024 x 28672 transformed 24.5 / 23.0 (2048: 38.4 / 41.9).
-    const bool few = M <= (K > 16384 ? 1024 : K > 8192 ? 512 : (rot.log2b ? K - r > 4096 : K > 4096) && !asym ? 256 : 0);
+    // Few long rows: 1024 threads to a row instead of 256 (256 / 1024 threads, us).  Up to one row per compute
+    // unit from two units of eight columns a thread on: 16 rows of 6400 columns 4.56 / 4.08, of 8192 4.44 / 4.20,
+    // of 14336 6.12 / 4.16, transformed ones of 8192 5.76 / 5.00; not below (4096: equal).  Symmetric rows
+    // beyond 8192 columns keep the gain with two rows to a unit, transformed ones from 10240 low columns on:
+    // 512 x 14336 9.04 / 8.04, transformed 10.44 / 9.48 (1024: equal; 512 x 8192: 5.48 / 6.64, 512 x 8704 transformed
+    // 7.64 / 8.52); beyond 16384 with four, 1024 x 28672 transformed 24.5 / 23.0 (2048: 38.4 / 41.9).  The asymmetric
+    // quantizer, with four maxima to reduce and more registers, starts beyond 8192 columns (8192: 4.36 / 4.56)
+    // and ends at one row to a unit (512 x 8704 6.44 / 7.32, 257 x 8704 transformed 6.84 / 8.20, 1024 x 28672
+    // 26.9 / 31.4).  Where the transform with 256 threads takes its 15 units a thread and 1024 threads hold the
+    // row in three, both gain further: 512 x 16384 at r = 4096 1.23 and, asymmetric, 1.12 times faster, 1024 x 18432
+    // 1.18 and 1.11.
+    const int64_t lo_cols = K - r;
+    const bool h256_15 = (r > 2048 || lo_cols > 7 * 2048) && lo_cols <= 2 * 8192 && K > 8192;
+    const int64_t few_plain = K > 8192 ? (asym ? 256 : 512) : K > 4096 && !asym ? 256 : 0;
+    const int64_t few_h256 = asym ? (h256_15 ? (K > 16384 ? 1024 : 512) : K > 8192 ? 256 : 0)
+                                  : (K > 16384 ? 1024 : h256_15 || lo_cols > 10240 ? 512 : lo_cols > 4096 ? 256 : 0);
     const bool pieces = aligned(x, 16) && ldx % 8 == 0 && K % 8 == 0 && r % 8 == 0;  // rows of whole 16-byte pieces
     const bool vec = pieces && K <= 16384;
     const bool rotate = rot.log2b > 0;
@@ -162,7 +171,7 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else                                                                                        \
             launch(hadamard256_quantize_kernel<1, LO, false, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo); \
     } while (0)
-        if (few) {
+        if (M <= few_h256) {
             if (K - r <= 8192) RESQ_LAUNCH_H256_WIDE(1);
             else if (K - r <= 2 * 8192) RESQ_LAUNCH_H256_WIDE(2);
             else RESQ_LAUNCH_H256_WIDE(4);
@@ -208,7 +217,7 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else if (K <= 256) RESQ_LAUNCH_SHORT(32);
         else RESQ_LAUNCH_SHORT(64);
 #undef RESQ_LAUNCH_SHORT
-    } else if (pieces && !rotate && K <= 32768 && (few || K > 16384)) {
+    } else if (pieces && !rotate && K <= 32768 && (M <= few_plain || K > 16384)) {
         // (beyond 16384 columns at every M: the element-wise kernel is the other one there; 28672
         // columns 1 row 28.6 / 4.9 us, 128 rows 29.8 / 6.7, 4096 rows 206 / 65)
         if (K <= 8192) RESQ_LAUNCH_QA_WIDE(1);

@@ -133,7 +133,7 @@ __device__ __forceinline__ float absmax8(const uint4& v) {
 // bytes per lane, coalesced), kept in registers across the absmax reduction,
 // then quantized and stored.  (One wavefront per token, without LDS or barrier,
 // was measured slower at every size: fewer, fatter waves hide less latency.)
-// Requires K, r, ldx multiples of 8 and x 16-byte aligned; ITERS * 2048 >= K.
+// Requires K, r, ldx multiples of 8 and x 16-byte aligned; 8 RT ITERS >= K.
 //
 // The division x / scale is what the quantizer is defined by, but a correctly
 // rounded fp32 division costs about ten instructions per element, as much time

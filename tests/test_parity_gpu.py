@@ -123,7 +123,7 @@ def test_quantize_act_generic_path(oracle, rq, M, K, r):
 
 # both sides of each line between 256 and 1024 threads to a row, and rows that end inside a wavefront
 @pytest.mark.parametrize("M,K,r", [(256, 4104, 520), (257, 4104, 520), (2, 4096, 512), (3, 8192, 1024), (2, 8200, 1032),
-                                   (512, 8200, 1032), (513, 8200, 1032), (1, 16384, 0), (2, 12296, 12296),
+                                   (512, 8200, 1032), (513, 8200, 1032), (256, 8200, 1032), (257, 16384, 2048), (1, 16384, 0), (2, 12296, 12296),
                                    # beyond 16384 columns, the last that 1024 threads hold and the first that they do not
                                    (3, 16392, 2056), (1030, 17000, 128), (2, 32768, 4096), (2, 32776, 4096), (2, 20000, 0),
                                    # ... and rows without whole 16-byte pieces
@@ -138,7 +138,10 @@ def test_quantize_act_threads_per_row(oracle, rq, M, K, r):
 
 
 @pytest.mark.parametrize("M,K,r", [(256, 4608, 256), (257, 4608, 256), (2, 8448, 256), (512, 8704, 512), (513, 8704, 512),
-                                   (3, 16896, 256), (5, 28672, 3584), (1025, 16896, 512)])
+                                   (3, 16896, 256), (5, 28672, 3584), (1025, 16896, 512),
+                                   # ... and the transform's own lines: 10240 low columns, 2048 high ones, 16384 low ones
+                                   (512, 11776, 1536), (512, 12032, 1536), (257, 10240, 2304), (513, 10240, 2304), (256, 10240, 2048),
+                                   (257, 10240, 2048), (1024, 18432, 2048), (1024, 18688, 2048), (257, 18688, 2048), (256, 18688, 2048)])
 @pytest.mark.parametrize("asym", [False, True])
 def test_hadamard256_quantize_threads_per_row(oracle, rq, M, K, r, asym):
     # codes bit-exact on the kernel's own rotated row; the row itself is the transform's test elsewhere
