@@ -257,6 +257,11 @@ int resq_gemm_mixed(const int8_t* q_hi, const uint8_t* q_lo, const float* s_hi,
  */
 int resq_gemm_mixed_plan(int64_t M, int64_t N, int64_t K, int64_t r, int* kernel, int* token_groups,
                          int* runs);
+/*
+ * Whether kernel 2 of that plan takes the low group as fp8 numbers for the shape (1) or int8 ones (0);
+ * 0 for the other kernels and for sizes that resq_gemm_mixed refuses.  Host only.
+ */
+int resq_gemm_mixed_low_fp8(int64_t M, int64_t N, int64_t K, int64_t r);
 
 /*
  * The layer in ONE call for the generation stage (a handful of tokens, Section 1:

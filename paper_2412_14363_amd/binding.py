@@ -35,6 +35,7 @@ SYMBOLS = {
     "resq_hadamard_quantize_act_asym": (C.c_int, [_p, _i64, _i64, _i64, _i64, _i64, _p, _p, _p, _p, _p, _p, _p, _p, _i64, _p]),
     "resq_gemm_mixed_asym": (C.c_int, [_p, _p, _p, _p, _p, _p, _p, _i64, _p, _i64, _i64, _i64, _p, _i64, _p, _p, _p]),
     "resq_gemm_mixed_plan": (C.c_int, [_i64, _i64, _i64, _i64, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]),
+    "resq_gemm_mixed_low_fp8": (C.c_int, [_i64, _i64, _i64, _i64]),
     "resq_quantize_gemm_mixed": (C.c_int, [_p, _i64, _i64, _p, _i64, _i64, _i64, _p, _i64, _p]),
     "resq_gemm_mixed_swiglu": (C.c_int, [_p, _p, _p, _p, _p, _i64, _p, _i64, _i64, _i64, _p, _i64, _p]),
     "resq_gram_accumulate": (C.c_int, [_p, _i64, _i64, _i64, _p, _i64, _p]),
@@ -240,6 +241,11 @@ def resq_gemm_mixed_plan(M: int, N: int, K: int, r: int):
     k, tg, sk = C.c_int(), C.c_int(), C.c_int()
     _check(lib().resq_gemm_mixed_plan(M, N, K, r, C.byref(k), C.byref(tg), C.byref(sk)), "resq_gemm_mixed_plan")
     return k.value, tg.value, sk.value
+
+
+def resq_gemm_mixed_low_fp8(M: int, N: int, K: int, r: int) -> bool:
+    """Whether the 128 x 128 tiles take the low group of this shape as fp8 numbers; host only."""
+    return bool(lib().resq_gemm_mixed_low_fp8(M, N, K, r))
 
 
 def resq_quantize_gemm_mixed(x: torch.Tensor, packed: torch.Tensor, N: int, r: int,

@@ -737,6 +737,12 @@ int resq_gemm_mixed_plan(int64_t M, int64_t N, int64_t K, int64_t r, int* kernel
     return RESQ_OK;
 }
 
+int resq_gemm_mixed_low_fp8(int64_t M, int64_t N, int64_t K, int64_t r) {
+    int kernel, tg, sk;
+    if (resq_gemm_mixed_plan(M, N, K, r, &kernel, &tg, &sk) != RESQ_OK) return 0;
+    return kernel == 2 && use_f8(M, make_weight_layout(N, K, r)) ? 1 : 0;
+}
+
 int resq_gemm_mixed_swiglu(const int8_t* q_hi, const uint8_t* q_lo, const float* s_hi,
                            const float* s_lo, const int32_t* lo_sum, int64_t M, const void* packed,
                            int64_t N2, int64_t K, int64_t r, void* y, int64_t ldy, void* stream) {

@@ -293,3 +293,21 @@ def test_gemm_mixed_plan():
     assert f(0, 256, 256, 32, ctypes.byref(a), ctypes.byref(b), ctypes.byref(c)) == 2
     assert f(4, 256, 256, 33, ctypes.byref(a), ctypes.byref(b), ctypes.byref(c)) == 2
     assert f(4, 256, 256, 32, None, ctypes.byref(b), ctypes.byref(c)) == 1
+
+
+def test_gemm_mixed_low_fp8():
+    fp8, plan = binding.resq_gemm_mixed_low_fp8, binding.resq_gemm_mixed_plan
+    assert fp8(8192, 29568, 8192, 1024) and fp8(8192, 29568, 8192, 0) and fp8(4096, 28672, 4096, 512)
+    # more than one round of 512 tiles
+    assert plan(2048, 4096, 4096, 512)[0] == 2 and not fp8(2048, 4096, 4096, 512)
+    assert plan(2049, 4096, 4096, 512)[0] == 2 and fp8(2049, 4096, 4096, 512)
+    # 24 low stages of 128 columns (an even number: 3072 columns, the last 256 perhaps padding)
+    assert fp8(4096, 4096, 2818 + 128, 128) and not fp8(4096, 4096, 2816 + 128, 128)
+    # at least three low stages to two high ones of 64 columns (an even number)
+    assert fp8(4096, 4096, 3072 + 1024, 1024) and not fp8(4096, 4096, 3072 + 1026, 1026)
+    # sums that stay whole numbers of fp32: 65536 low columns
+    assert fp8(4096, 4096, 65536, 0) and not fp8(4096, 4096, 65538, 0)
+    # the other kernels, and sizes that are refused
+    assert plan(512, 4096, 14336, 1792)[0] == 3 and not fp8(512, 4096, 14336, 1792)
+    assert plan(64, 28672, 8192, 1024)[0] == 1 and not fp8(64, 28672, 8192, 1024)
+    assert not fp8(0, 4096, 4096, 512) and not fp8(4096, 4096, 4096, 4098) and not fp8(4096, 4096, 4096, 511)

@@ -330,13 +330,21 @@ def test_layer_tiled_kernel_wide_tiles(oracle, rq, M, K, N, r):
 
 # 128 x 128 tiles in more than one round and 24 low stages or more: the low group on the fp8 matrix
 # cores.  Ragged tiles; 2 and 4 high stages (the first buffer) and none; 24, 26 and 28 low stages (what
-# the four-stage turns of the loop leave over); groups that end inside their padding
-TILED_F8_SHAPES = [(1925, 3200, 4500, 128), (1921, 3584, 4400, 256), (1930, 3072, 4300, 0), (4200, 3450, 2050, 122)]
+# the four-stage turns of the loop leave over); groups that fill their padded width, and groups that end inside it:
+# each padding column adds 64 to the sums of offset codes, which the epilogue takes out again (2, 72 and 254 of them)
+TILED_F8_SHAPES = [(1925, 3200, 4500, 128), (1921, 3584, 4400, 256), (1930, 3072, 4300, 0), (4200, 3450, 2050, 122),
+                   (1921, 3202, 4400, 128), (1930, 3712, 4300, 130), (1925, 3000, 4500, 0)]
+F8_STAGES = [(2, 24), (4, 26), (0, 24), (2, 26), (2, 26), (4, 28), (0, 24)]   # high, low
+
+
+def is_f8(rq, M, K, N, r):
+    return rq.resq_gemm_mixed_plan(M, N, K, r) == (2, 0, 0) and rq.resq_gemm_mixed_low_fp8(M, N, K, r)
 
 
 @pytest.mark.parametrize("M,K,N,r", TILED_F8_SHAPES)
 def test_layer_tiled_kernel_fp8_low_group(oracle, rq, M, K, N, r):
-    assert rq.resq_gemm_mixed_plan(M, N, K, r) == (2, 0, 0)
+    assert is_f8(rq, M, K, N, r)
+    assert (-(-r // 128) * 2, -(-(K - r) // 256) * 2) == F8_STAGES[TILED_F8_SHAPES.index((M, K, N, r))]
     x, w = wl.random_small_case(M * 17 + K + 3, M, K, N, r, act="student_t3")
     check_layer(oracle, rq, x, w, r, ldy_extra=8 if N % 4 == 0 else 3)
 
@@ -345,10 +353,44 @@ def test_layer_tiled_kernel_fp8_low_group_asym_and_saturated(oracle, rq):
     M, K, N, r = TILED_F8_SHAPES[0]
     x, w = wl.random_small_case(5, M, K, N, r, act="student_t3")
     check_layer_asym(oracle, rq, (x.float() + 1.5).to(torch.bfloat16), w, r)
-    # every low code at +7 or -7, the same in all columns of a row: the largest sums there are
+    # every low code at +7 or -7, the same in all columns of a row
     x[:, r:] = torch.where(torch.arange(M) % 2 == 0, 1.0, -1.0)[:, None].to(torch.bfloat16)
     w[:, r:] = torch.where(torch.arange(N) % 3 == 0, 0.5, -0.5)[:, None].to(torch.bfloat16)
     check_layer(oracle, rq, x, w, r)
+
+
+@pytest.mark.parametrize("M,K,N,r", TILED_F8_SHAPES[4:])
+def test_layer_tiled_kernel_fp8_low_group_asym_padding(oracle, rq, M, K, N, r):
+    assert is_f8(rq, M, K, N, r)
+    x, w = wl.random_small_case(M + K, M, K, N, r, act="student_t3")
+    check_layer_asym(oracle, rq, (x.float() + 1.5).to(torch.bfloat16), w, r, ldy_extra=3)
+
+
+# The largest sums of offset codes there are, up to 225 x 65536 < 2^24, odd and even ones: codes of 7 and here and
+# there 6, so that a sum that lost its lowest bits in the fp32 accumulator would show.  One more pair of columns goes
+# to the int8 kernel.
+@pytest.mark.parametrize("low,f8", [(65536, True), (65534, True), (32770, True), (65538, False)])
+def test_layer_tiled_kernel_fp8_low_group_largest_sums(rq, low, f8):
+    M, N = 2930, 2900
+    assert rq.resq_gemm_mixed_plan(M, N, low, 0) == (2, 0, 0) and rq.resq_gemm_mixed_low_fp8(M, N, low, 0) == f8
+    g = torch.Generator(device="cuda").manual_seed(low)
+
+    def codes(rows):
+        c = 7 - (torch.rand(rows, low, generator=g, device="cuda") < 0.05).to(torch.bfloat16)
+        c[:, 0] = 7.0   # scale 1
+        return c
+
+    x, w = codes(M), codes(N)
+    dbg = torch.zeros((M, N), dtype=torch.int32, device="cuda")
+    act = rq.resq_quantize_act(x, 0)
+    y = rq.resq_gemm_mixed(act, rq.resq_pack_weights(w, 0), N, dbg_acc_lo=dbg)
+    y2 = rq.resq_gemm_mixed(act, rq.resq_pack_weights(w, 0), N)
+    torch.cuda.synchronize()
+    want = x.double() @ w.double().t().contiguous()     # whole numbers, exact in fp64
+    offset = want + 8 * x.double().sum(1, keepdim=True) + 8 * w.double().sum(1) + 64 * low
+    assert 0.95 * 225 * low < offset.max() <= 225 * low and bool((offset % 2 == 1).any())
+    assert torch.equal(dbg.double(), want)
+    assert torch.equal(y, want.float().to(torch.bfloat16)) and torch.equal(y2, y)   # both scales are 1
 
 
 # grids whose number of tiles leaves 2, 4 and 6 over eight: every XCD has its own run of tiles, the first of them one more
@@ -1011,7 +1053,7 @@ def test_project_heads_no_rows(rq):
     (300, 256, 2050, 32), (130, 520, 4100, 64),                                           # ... and below, on wide layers
     (1153, 256, 1050, 32), (1300, 640, 1150, 128),                                        # ... 257 to 512 such tiles: one ring
     (2100, 256, 1100, 32), (4100, 256, 550, 0), (4100, 256, 550, 256), (1100, 1000, 2100, 104),  # 128 x 128 tiles
-    (1925, 3200, 2250, 128),                                                              # ... with the low group in fp8
+    (1925, 3200, 2250, 128), (1921, 3202, 2200, 128),                                     # ... with the low group in fp8, without and with padding
 ])
 def test_layer_swiglu(oracle, rq, M, K, F, r):
     x, w = wl.random_small_case(M + K + F, M, K, 2 * F, r, act="student_t3")
