@@ -716,8 +716,9 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_kv_cache_kernel(
     const float nmn_l = wave_max<G>(live && !high ? nmn : -inf);
     // A lane's columns are all of one group: it needs one scale, one reciprocal and one pass of the
     // quantizer, with the constants of its own group (run for both groups on all lanes and
-    // selected afterwards, which the votes across the wavefront suggest, it took 6.3 instead of 4.9 us
-    // for 32768 rows of 128 columns, and 30.9 instead of 22.9, 4.0 TB/s, for 262144).
+    // selected afterwards, which the votes across the wavefront suggest, it took 6.7 instead of 5.0 us
+    // for 32768 rows of 128 columns at r = 16, and 30.4 instead of 22.4, 4.0 TB/s, for 262144; by events at the
+    // kernel's start and end, a kernel trace says 0.7 us more).
     const float levels = high ? 255.0f : 15.0f;
     const float zero = live ? -(high ? nmn_h : nmn_l) : 0.0f;
     const float range = live ? (high ? mx_h : mx_l) - zero : 0.0f;
@@ -757,14 +758,19 @@ __global__ __launch_bounds__(kQuantThreads) void quantize_kv_cache_kernel(
         for (int k = 0; k < 4; ++k) by[k] = (u[2 * k + 1] << 4) | (u[2 * k] & 0xFu);
         *reinterpret_cast<uint32_t*>(row + r + (gl - hi_units) * 4) = pack_low_bytes(by[0], by[1], by[2], by[3]);
     }
-    // the first lane of a group writes its constants; an absent group: scale 1, zero-point 0
-    if (gl == 0 || gl == hi_units) {
+    // The first lane of a group writes its constants.  A row of one group: all four in one store by the first
+    // lane, scale 1 and zero-point 0 for the absent group (the present one's two and the absent one's apart:
+    // 262144 rows of 128 columns 24.4 / 21.1 us at r = 0, 24.8 / 22.1 at r = 128).
+    if (hi_units == 0 || hi_units == nunits) {
+        if (gl == 0) {
+            par[0] = high ? scale : 1.0f;
+            par[1] = high ? zero : 0.0f;
+            par[2] = high ? 1.0f : scale;
+            par[3] = high ? 0.0f : zero;
+        }
+    } else if (gl == 0 || gl == hi_units) {
         par[high ? 0 : 2] = scale;
         par[high ? 1 : 3] = zero;
-        if (gl == 0 && (hi_units == 0 || hi_units == nunits)) {
-            par[high ? 2 : 0] = 1.0f;
-            par[high ? 3 : 1] = 0.0f;
-        }
     }
 }
 
