@@ -542,7 +542,6 @@ static DecodeArgs make_decode_args(const int8_t* q_hi, const uint8_t* q_lo, cons
 // kernels quantize d.x themselves instead of reading codes.
 static int launch_decode(const DecodeArgs& d, bool dbg, bool fused, hipStream_t st) {
     const WeightLayout& L = d.L;
-    // the code rows go through LDS only when the kernel makes them itself
     const int sk = decode_runs(L);
     // the code rows go through LDS only when the kernel makes them itself
     int lds_bytes = fused ? ((d.M * d.lds_row + 15) & ~15) : 0;
@@ -849,7 +848,7 @@ int resq_gram_accumulate(const void* x, int64_t ldx, int64_t T, int64_t K, float
     slices = (T + g.t_per_slice - 1) / g.t_per_slice;
     const dim3 grid((unsigned)((K + kBasisTile - 1) / kBasisTile), (unsigned)((K + kBasisTile - 1) / kBasisTile),
                     (unsigned)slices);
-    launch(basis_gemm_kernel<true, true, true, false>, grid, dim3(kBasisThreads), 0,
+    launch(basis_gemm_kernel<true, false>, grid, dim3(kBasisThreads), 0,
            static_cast<hipStream_t>(stream), g);
     return launch_status();
 }
@@ -886,8 +885,8 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
     g.I = rows; g.J = J; g.T = K;
     g.accumulate = 0;
     g.t_per_slice = round_up(K, kBasisChunk);
-    if (out_is_bf16) launch(basis_gemm_kernel<false, false, false, true>, grid, dim3(kBasisThreads), 0, st, g);
-    else launch(basis_gemm_kernel<false, false, false, false>, grid, dim3(kBasisThreads), 0, st, g);
+    if (out_is_bf16) launch(basis_gemm_kernel<false, true>, grid, dim3(kBasisThreads), 0, st, g);
+    else launch(basis_gemm_kernel<false, false>, grid, dim3(kBasisThreads), 0, st, g);
     return launch_status();
 }
 

@@ -34,8 +34,8 @@ constexpr int kBasisChunk = 16;   // reduction steps per LDS buffer
 constexpr int kBasisPitch = kBasisTile + 4;  // floats; rows 16-byte aligned
 
 struct BasisGemmArgs {
-    const void* a;   // A_TRANS: [T][lda] (element (i, t) at a[t * lda + i]); else [I][lda]
-    const void* b;   // [T][ldb]
+    const void* a;   // GRAM: bf16 [T][lda] (element (i, t) at a[t * lda + i]); else fp32 [I][lda]
+    const void* b;   // [T][ldb], the same type
     void* c;         // [I][ldc], fp32 or bf16
     int64_t lda, ldb, ldc;
     int64_t I, J, T;
@@ -64,9 +64,9 @@ __device__ __forceinline__ void load8(const void* base, int64_t elem, bool live,
     }
 }
 
-// Requires lda, ldb multiples of 8 elements and 16-byte (bf16) / 32-byte... aligned bases
-// (checked on the host); I, J, T arbitrary.
-template <bool A_TRANS, bool A_BF16, bool B_BF16, bool OUT_BF16>
+// Requires lda, ldb multiples of 8 elements and 16-byte aligned bases (checked on the host), J and, for GRAM, I
+// multiples of 8; I (rows of fp32 data) and T arbitrary.
+template <bool GRAM, bool OUT_BF16>
 __global__ __launch_bounds__(kBasisThreads) void basis_gemm_kernel(const BasisGemmArgs g) {
     __shared__ __attribute__((aligned(16))) float lds_a[2][kBasisChunk][kBasisPitch];
     __shared__ __attribute__((aligned(16))) float lds_b[2][kBasisChunk][kBasisPitch];
@@ -83,28 +83,27 @@ __global__ __launch_bounds__(kBasisThreads) void basis_gemm_kernel(const BasisGe
     const int ar = t & 127, at = (t >> 7) * 8;     // i-major A: tile row, first step
     float ra[8], rb[8];
     auto fetch = [&](int64_t tc) {
-        if constexpr (A_TRANS) {
+        if constexpr (GRAM) {
             const int64_t tt = tc + lr, i = i0 + lc;
-            load8<A_BF16>(g.a, tt * g.lda + i, tt < t_end && i < g.I, ra);   // I % 8 == 0 in this form
+            load8<true>(g.a, tt * g.lda + i, tt < t_end && i < g.I, ra);   // I % 8 == 0 in this form
         } else {
             const int64_t i = i0 + ar, tt = tc + at;
-            load8<A_BF16>(g.a, i * g.lda + tt, i < g.I && tt + 8 <= t_end, ra);
+            load8<false>(g.a, i * g.lda + tt, i < g.I && tt + 8 <= t_end, ra);
             if (i < g.I && tt < t_end && tt + 8 > t_end) {   // ragged end of the reduction axis
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     ra[k] = 0.0f;
                     if (tt + k < t_end) {
-                        if constexpr (A_BF16) ra[k] = __uint_as_float((uint32_t)static_cast<const uint16_t*>(g.a)[i * g.lda + tt + k] << 16);
-                        else ra[k] = static_cast<const float*>(g.a)[i * g.lda + tt + k];
+                        ra[k] = static_cast<const float*>(g.a)[i * g.lda + tt + k];
                     }
                 }
             }
         }
         const int64_t tt = tc + lr, j = j0 + lc;
-        load8<B_BF16>(g.b, tt * g.ldb + j, tt < t_end && j < g.J, rb);       // J % 8 == 0
+        load8<GRAM>(g.b, tt * g.ldb + j, tt < t_end && j < g.J, rb);       // J % 8 == 0
     };
     auto stash = [&](int buf) {
-        if constexpr (A_TRANS) {
+        if constexpr (GRAM) {
             *reinterpret_cast<float4*>(&lds_a[buf][lr][lc]) = make_float4(ra[0], ra[1], ra[2], ra[3]);
             *reinterpret_cast<float4*>(&lds_a[buf][lr][lc + 4]) = make_float4(ra[4], ra[5], ra[6], ra[7]);
         } else {

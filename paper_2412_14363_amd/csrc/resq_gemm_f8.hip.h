@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
     const int64_t m0 = (int64_t)tile_m * kBM;
     const int64_t n0 = (int64_t)tile_n * kBN;
     if (n0 >= a.L.N) return;  // a tile of padding channels only
-    const int S_hi = a.stages_hi, S_lo = a.stages_lo, S = S_hi + S_lo;  // S_hi and S_lo are even
+    const int S_hi = a.stages_hi, S_lo = a.stages_lo, S = S_hi + S_lo;  // both even, S_lo at least 24 (the host's rule)
     const uint16_t* sw_hi = reinterpret_cast<const uint16_t*>(a.packed + a.L.scale_off);
     const uint16_t* sw_lo = sw_hi + a.L.n_pad;
     const int32_t* wsum_hi = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 8 * a.L.n_pad);
@@ -129,11 +129,11 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
             m = m < a.M ? m : a.M - 1;
             if (wave == 2) {
                 if (S_hi > 0) load_to_lds_4B(a.s_hi + m, lds + kMetaOff + kMetaSHi + h * 256);
-                if (S_lo > 0) load_to_lds_4B(a.s_lo + m, lds + kMetaOff + kMetaSLo + h * 256);
+                load_to_lds_4B(a.s_lo + m, lds + kMetaOff + kMetaSLo + h * 256);
             } else {
-                if (S_lo > 0) load_to_lds_4B(a.lo_sum + m, lds + kMetaOff + kMetaLoSum + h * 256);
+                load_to_lds_4B(a.lo_sum + m, lds + kMetaOff + kMetaLoSum + h * 256);
                 if (asym && S_hi > 0) load_to_lds_4B(a.c_hi + m, lds + kMetaOff + kMetaCHi + h * 256);
-                if (asym && S_lo > 0) load_to_lds_4B(a.c_lo + m, lds + kMetaOff + kMetaCLo + h * 256);
+                if (asym) load_to_lds_4B(a.c_lo + m, lds + kMetaOff + kMetaCLo + h * 256);
             }
         }
     }
@@ -236,9 +236,8 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
 
     const int tl = wm * 64 + (lane & 31);         // + 32 (i ^ wn)
     const int cl = wn * 64 + (lane >> 5) * 4;     // + 32 j + 8 q + v
-    auto fold = [&](auto has_hi, auto has_lo, auto is_asym, auto is_glu) __attribute__((always_inline)) {
-        constexpr bool HI_ON = decltype(has_hi)::value, LO_ON = decltype(has_lo)::value;
-        constexpr bool ASYM = decltype(is_asym)::value, GLU = decltype(is_glu)::value;
+    auto fold = [&](auto has_hi, auto is_asym, auto is_glu) __attribute__((always_inline)) {
+        constexpr bool HI_ON = decltype(has_hi)::value, ASYM = decltype(is_asym)::value, GLU = decltype(is_glu)::value;
         const uint8_t* meta = lds + kMetaOff;
         float st_hi[2], st_lo[2], ct_hi[2], ct_lo[2], ca[2];
         int row[2];
@@ -248,12 +247,10 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
             row[i] = tl + 32 * (i ^ wn);
             if constexpr (HI_ON) st_hi[i] = *reinterpret_cast<const float*>(meta + kMetaSHi + row[i] * 4);
             if constexpr (ASYM && HI_ON) ct_hi[i] = *reinterpret_cast<const float*>(meta + kMetaCHi + row[i] * 4);
-            if constexpr (ASYM && LO_ON) ct_lo[i] = *reinterpret_cast<const float*>(meta + kMetaCLo + row[i] * 4);
-            if constexpr (LO_ON) {
-                st_lo[i] = *reinterpret_cast<const float*>(meta + kMetaSLo + row[i] * 4);
-                ca[i] = (float)(8 * (*reinterpret_cast<const int*>(meta + kMetaLoSum + row[i] * 4) +
-                                     *reinterpret_cast<const int*>(meta + kMetaSe + row[i] * 4)) + 32 * (int)a.L.kl_pad);
-            }
+            if constexpr (ASYM) ct_lo[i] = *reinterpret_cast<const float*>(meta + kMetaCLo + row[i] * 4);
+            st_lo[i] = *reinterpret_cast<const float*>(meta + kMetaSLo + row[i] * 4);
+            ca[i] = (float)(8 * (*reinterpret_cast<const int*>(meta + kMetaLoSum + row[i] * 4) +
+                                 *reinterpret_cast<const int*>(meta + kMetaSe + row[i] * 4)) + 32 * (int)a.L.kl_pad);
         }
         int32_t* dbg_row_hi[2] = {nullptr, nullptr};
         int32_t* dbg_row_lo[2] = {nullptr, nullptr};
@@ -285,7 +282,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
                     for (int v = 0; v < 4; ++v) zw_hi[v] = (float)ws[v] * sn_hi[v];
                 }
             }
-            if constexpr (LO_ON) {
+            {
                 const v4h h = *reinterpret_cast<const v4h*>(meta + kMetaSwLo + c * 2);
                 const v4i ws = *reinterpret_cast<const v4i*>(meta + kMetaEven + c * 4);
 #pragma unroll
@@ -309,14 +306,12 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
                             if (a.dbg_hi && dbg_ok[i] && cc + v < dbg_cols) dbg_row_hi[i][cc + v] = ih;
                         }
                     }
-                    if constexpr (LO_ON) {
-                        // whole numbers below 2^24 throughout: exact
-                        const float fl = __builtin_fmaf(__int_as_float(from_acc(__float_as_int(acc_lo[j][i][4 * q + v]))), kF8Unit, -(ev[v] + ca[i]));
-                        val[v] += fl * (st_lo[i] * sn_lo[v]);
-                        if constexpr (ASYM) val[v] += ct_lo[i] * zw_lo[v];
-                        if constexpr (DBG) {
-                            if (a.dbg_lo && dbg_ok[i] && cc + v < dbg_cols) dbg_row_lo[i][cc + v] = (int)fl;
-                        }
+                    // whole numbers below 2^24 throughout: exact
+                    const float fl = __builtin_fmaf(__int_as_float(from_acc(__float_as_int(acc_lo[j][i][4 * q + v]))), kF8Unit, -(ev[v] + ca[i]));
+                    val[v] += fl * (st_lo[i] * sn_lo[v]);
+                    if constexpr (ASYM) val[v] += ct_lo[i] * zw_lo[v];
+                    if constexpr (DBG) {
+                        if (a.dbg_lo && dbg_ok[i] && cc + v < dbg_cols) dbg_row_lo[i][cc + v] = (int)fl;
                     }
                 }
                 if constexpr (GLU)
@@ -457,49 +452,44 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
             stage_hi(NO{}, p1, p0, sg + 1);
         }
         static_for<8>([&](auto k) __attribute__((always_inline)) { lds_wait<0>(frag_of(k, p0)); });
-        if (S_lo > 0) {
-            // p0 holds the first low stage, as read
-            static_for<4>([&](auto k) __attribute__((always_inline)) { widen_k(k, frag_of(k, p0)); });
-            raw[4] = frag_of(IC<4>{}, p0);
-            raw[5] = frag_of(IC<5>{}, p0);
-            sum = __builtin_amdgcn_sad_u8(bytes, 0u, sum);
+        // p0 holds the first low stage, as read
+        static_for<4>([&](auto k) __attribute__((always_inline)) { widen_k(k, frag_of(k, p0)); });
+        raw[4] = frag_of(IC<4>{}, p0);
+        raw[5] = frag_of(IC<5>{}, p0);
+        sum = __builtin_amdgcn_sad_u8(bytes, 0u, sum);
+        bytes = 0;
+        asm volatile("s_nop 4" ::: "memory");  // wait states between the widening and the first product
+        auto pair = [&](auto steady, auto buf_) __attribute__((always_inline)) {
+            stage_lo(steady, buf_, sg);
+            stage_lo(steady, IC<decltype(buf_)::value + 1>{}, sg + 1);
+            sum = __builtin_amdgcn_sad_u8(bytes, 0u, sum);  // two stages: 16 codes of 0..15 in each byte
             bytes = 0;
-            asm volatile("s_nop 4" ::: "memory");  // wait states between the widening and the first product
-            auto pair = [&](auto steady, auto buf_) __attribute__((always_inline)) {
-                stage_lo(steady, buf_, sg);
-                stage_lo(steady, IC<decltype(buf_)::value + 1>{}, sg + 1);
-                sum = __builtin_amdgcn_sad_u8(bytes, 0u, sum);  // two stages: 16 codes of 0..15 in each byte
-                bytes = 0;
-                sg += 2;
-            };
-            // the buffers are in the instructions, so that a read costs no address: four stages a turn
-            while (sg + 3 + kPrefetch < S) {
-                pair(YES{}, IC<0>{});
-                pair(YES{}, IC<2>{});
-            }
-            buf = 0;
-            while (sg < S) pair(NO{}, IC<0>{});
-            // the last stage widened what lies behind it: its h = 0 does not count
-            bytes = (uint32_t)wa[0][0][0] + (uint32_t)wa[0][0][2] + (uint32_t)wa[0][0][4] + (uint32_t)wa[0][0][6];
-            sum -= __builtin_amdgcn_sad_u8(bytes, 0u, 0u);
-            sum += __shfl_xor(sum, 32);
-            if (lane < 32) *reinterpret_cast<uint32_t*>(lds + kMetaOff + kMetaSe + (wm * 64 + wn * 32 + lane) * 4) = sum;
+            sg += 2;
+        };
+        // the buffers are in the instructions, so that a read costs no address: four stages a turn
+        while (sg + 3 + kPrefetch < S) {
+            pair(YES{}, IC<0>{});
+            pair(YES{}, IC<2>{});
         }
+        buf = 0;
+        while (sg < S) pair(NO{}, IC<0>{});
+        // the last stage widened what lies behind it: its h = 0 does not count
+        bytes = (uint32_t)wa[0][0][0] + (uint32_t)wa[0][0][2] + (uint32_t)wa[0][0][4] + (uint32_t)wa[0][0][6];
+        sum -= __builtin_amdgcn_sad_u8(bytes, 0u, 0u);
+        sum += __shfl_xor(sum, 32);
+        if (lane < 32) *reinterpret_cast<uint32_t*>(lds + kMetaOff + kMetaSe + (wm * 64 + wn * 32 + lane) * 4) = sum;
         wait_loads_and_barrier<0>();
         __syncthreads();  // every wave is done reading the stage buffers, and the sums are there
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions have written their tiles
         if (a.swiglu) {  // symmetric codes only (checked on the host)
-            if (S_hi > 0 && S_lo > 0) fold(YES{}, YES{}, NO{}, YES{});
-            else if (S_hi > 0) fold(YES{}, NO{}, NO{}, YES{});
-            else fold(NO{}, YES{}, NO{}, YES{});
+            if (S_hi > 0) fold(YES{}, NO{}, YES{});
+            else fold(NO{}, NO{}, YES{});
         } else if (asym) {
-            if (S_hi > 0 && S_lo > 0) fold(YES{}, YES{}, YES{}, NO{});
-            else if (S_hi > 0) fold(YES{}, NO{}, YES{}, NO{});
-            else fold(NO{}, YES{}, YES{}, NO{});
+            if (S_hi > 0) fold(YES{}, YES{}, NO{});
+            else fold(NO{}, YES{}, NO{});
         } else {
-            if (S_hi > 0 && S_lo > 0) fold(YES{}, YES{}, NO{}, NO{});
-            else if (S_hi > 0) fold(YES{}, NO{}, NO{}, NO{});
-            else fold(NO{}, YES{}, NO{}, NO{});
+            if (S_hi > 0) fold(YES{}, NO{}, NO{});
+            else fold(NO{}, NO{}, NO{});
         }
     }
     __syncthreads();
