@@ -45,17 +45,19 @@ PEAK_HBM_GBS = 8000.0     # MI355X HBM3E peak, GB/s
 # device copy (x2.000 and x1.000).  This run does not measure it: the figures are copied from
 # the summaries under profiles/ (named in `traffic_source`); absent = not measured.
 MEASURED_TRAFFIC = {
-    "qwen_r1024": (3241.78e6 + 484.44e6, "profiles/qwen_r1024.txt"),
+    "qwen_r1024": (3238.78e6 + 484.44e6, "profiles/qwen_r1024.txt"),
+    "qwen_r0": (2879.53e6 + 484.44e6, "profiles/qwen_r0.txt"),
+    "gate_up_prefill": (291.13e6 + 117.44e6, "profiles/gate_up_prefill.txt"),
+    "down_prefill": (371.16e6 + 33.55e6, "profiles/down_prefill.txt"),
     "oproj_prefill": (38.29e6 + 16.78e6, "profiles/oproj_prefill.txt"),
-    "gate_up_prefill": (284.52e6 + 117.44e6, "profiles/gate_up_prefill.txt"),
-    "down_prefill": (366.70e6 + 33.55e6, "profiles/down_prefill.txt"),
-    "oproj_m512": (19.28e6 + 4.19e6, "profiles/oproj_m512.txt"),
-    "down_m512": (66.47e6 + 4.19e6, "profiles/down_m512.txt"),
+    "oproj_m512": (19.31e6 + 4.19e6, "profiles/oproj_m512.txt"),
+    "down_m512": (66.50e6 + 4.19e6, "profiles/down_m512.txt"),
     "decode_m1": (133.04e6 + 0.06e6, "profiles/decode_m1.txt"),
-    "decode_m16": (133.12e6 + 0.92e6, "profiles/decode_m16.txt"),
-    "decode_m64": (135.09e6 + 3.67e6, "profiles/decode_m64.txt"),
+    "decode_m4": (133.15e6 + 0.23e6, "profiles/decode_m4.txt"),
+    "decode_m16": (133.13e6 + 0.92e6, "profiles/decode_m16.txt"),
+    "decode_m64": (135.10e6 + 3.67e6, "profiles/decode_m64.txt"),
+    "kv_quant": (8.45e6 + 2.88e6, "profiles/kv_quant.txt"),
     "uc_proj": (21.35e6 + 20.97e6, "profiles/uc_proj.txt"),
-    "kv_quant": (8.47e6 + 2.88e6, "profiles/kv_quant.txt"),
 }
 
 
@@ -404,6 +406,7 @@ def calib_lib():
     lib = ctypes.CDLL(str(so))
     vp, ci = ctypes.c_void_p, ctypes.c_int
     lib.calib_mfma_int8.argtypes = [vp, vp, ci, ci, vp, vp, vp, vp]
+    lib.calib_mfma_f8.argtypes = [vp, vp, ci, ci, vp, vp, vp, vp]
     lib.calib_hbm_read.argtypes = [vp, ctypes.c_size_t, ci, vp, vp, vp, vp]
     return lib
 
@@ -415,6 +418,9 @@ def calibration(mfma_ms: float = 1.5, quick: bool = True) -> dict:
       the low nibble, the other 16 * code) and like the high group's (random INT8).  The matrix
       pipes are power-limited, so the rate depends on the bytes; `mix_r_eighth` is the rate of a
       kernel that spends 7/8 of its products on the first kind and 1/8 on the second.
+    * v_mfma_f32_32x32x64_f8f6f4 alone on the low group's offset codes (bytes 1..15 on both sides), which
+      is how the layers of more than one round of 128 x 128 tiles take their low group;
+      `mix_r_eighth_fp8` is that rate for 7/8 of the products and the int8 one on random bytes for 1/8.
     * a plain streaming read of as many bytes as the decode GEMM's packed weights, regions
       rotated through 1 GiB so that the last-level cache cannot serve them."""
     import ctypes
@@ -451,16 +457,20 @@ def calibration(mfma_ms: float = 1.5, quick: bool = True) -> dict:
         return sum(best) / len(best)
 
     out = {}
-    ops_per_iter = 2.0 * 16 * 16 * 64 * 32 * 8 * 256
-    iters = max(1, int(mfma_ms * 1e-3 * 4.0e15 / ops_per_iter))
+    kinds["low_group_fp8"] = (c + 8, w + 8)
+    ops_per_iter = 2.0 * 16 * 16 * 64 * 32 * 8 * 256     # half of the fp8 kernel's 2 * 32 * 32 * 64 * 16 * 8 * 256
     for name, (ha, hb) in kinds.items():
+        f8 = name == "low_group_fp8"
+        fn, ops = (L.calib_mfma_f8, 2.0 * ops_per_iter) if f8 else (L.calib_mfma_int8, ops_per_iter)
+        iters = max(1, int(mfma_ms * 1e-3 * (5.0e15 if f8 else 4.0e15) / ops))
         da = torch.from_numpy(ha.astype(np.uint8)).cuda()
         db = torch.from_numpy(hb.astype(np.uint8)).cuda()
-        ms = timed(lambda i, a, b: L.calib_mfma_int8(da.data_ptr(), db.data_ptr(), iters, 256, sink.data_ptr(), a, b, st),
+        ms = timed(lambda i, a, b: fn(da.data_ptr(), db.data_ptr(), iters, 256, sink.data_ptr(), a, b, st),
                    3 if quick else 6)
-        out[name] = {"kernel_ms": ms, "tops": ops_per_iter * iters / (ms * 1e-3) / 1e12}
-    lo, hi = out["low_group_like"]["tops"], out["high_group_like"]["tops"]
+        out[name] = {"kernel_ms": ms, "tops": ops * iters / (ms * 1e-3) / 1e12}
+    lo, hi, lo_f8 = (out[k]["tops"] for k in ("low_group_like", "high_group_like", "low_group_fp8"))
     out["mix_r_eighth"] = {"tops": 1.0 / (0.875 / lo + 0.125 / hi)}
+    out["mix_r_eighth_fp8"] = {"tops": 1.0 / (0.875 / lo_f8 + 0.125 / hi)}
     region = 132_600_000 // 256 * 256
     buf = torch.ones(1 << 30, dtype=torch.uint8, device="cuda")
     span = buf.numel() - region
@@ -499,7 +509,8 @@ def calib_bench(args) -> None:
         "metric": "sustained int8 MFMA rate, matrix instructions only (TOPS)", "value": best, "unit": "TOPS",
         "n_gpus": 1, "steps": 6, "warmup": 1, "ms_per_step": cal["low_group_like"]["kernel_ms"],
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int8", "data": "synthetic",
-        "config": {"workload": "calib: v_mfma_i32_16x16x64_i8 alone (256 workgroups x 8 wavefronts) and a plain read of 132.6 MB",
+        "config": {"workload": "calib: v_mfma_i32_16x16x64_i8 and v_mfma_f32_32x32x64_f8f6f4 alone (256 workgroups x 8 "
+                               "wavefronts) and a plain read of 132.6 MB",
                    "tag": "calib"},
         "calibration": cal,
         "roofline": {"bound": "mfma", "achieved": best, "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
@@ -751,6 +762,8 @@ def layer_bench(args, tag: str, steps: int, warmup: int, with_cpu_baseline: bool
         roof = {"bound": "mfma", "achieved": achieved, "peak": PEAK_INT8_TOPS, "unit": "TOP/s",
                 "frac": achieved / PEAK_INT8_TOPS, **traffic_fields(tag)}
     roof["kernel"] = "resq quantize_gemm_mixed" if one_call else "resq gemm_mixed"
+    if not one_call and rq.resq_gemm_mixed_low_fp8(s.M, s.N, s.K, s.r):
+        roof["kernel"] += " (low group in fp8)"
     roof["kernel_ms"] = gemm_ms        # the mean: what `achieved` is priced with
     roof["kernel_ms_median"] = gemm_all[len(gemm_all) // 2]
     roof["kernel_ms_min"] = gemm_all[0]
@@ -858,10 +871,12 @@ def headline(args) -> None:
     out["decode"] = dec
     cal = calibration()
     out["calibration"] = cal
-    out["roofline"]["measured_peak"] = cal["mix_r_eighth"]["tops"]
-    out["roofline"]["frac_of_measured"] = out["roofline"]["achieved"] / cal["mix_r_eighth"]["tops"]
-    out["roofline"]["measured_peak_source"] = ("calibration.mix_r_eighth: the matrix instruction alone on operand "
-                                               "bytes like this workload's, same process")
+    from paper_2412_14363_amd import binding as rq
+    mix = "mix_r_eighth_fp8" if rq.resq_gemm_mixed_low_fp8(s.M, s.N, s.K, s.r) else "mix_r_eighth"
+    out["roofline"]["measured_peak"] = cal[mix]["tops"]
+    out["roofline"]["frac_of_measured"] = out["roofline"]["achieved"] / cal[mix]["tops"]
+    out["roofline"]["measured_peak_source"] = (f"calibration.{mix}: the matrix instructions of this workload's kernel alone, "
+                                               "on operand bytes like its own, same process")
     # the quantizer of the headline step against HBM and against the measured copy rate
     qbytes = s.M * (2 * s.K + s.r + (s.K - s.r) // 2 + 12)
     qgbs = qbytes / (out["quantize_ms"] * 1e-3) / 1e9

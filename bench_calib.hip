@@ -1,6 +1,6 @@
 // Calibration kernels for bench.py (not part of the library, nothing of the method):
-// what this chip sustains on the int8 matrix instruction alone and on a plain streaming
-// read, so that the benchmark can quote its kernels against the measured ceilings next to
+// what this chip sustains on the matrix instructions alone (int8, and fp8 for the low group of
+// large layers) and on a plain streaming read, so that the benchmark can quote its kernels against the measured ceilings next to
 // the nominal peaks.  The matrix pipes are power-limited: the rate depends on the operand
 // bytes, which the caller supplies.
 #include <hip/hip_runtime.h>
@@ -42,6 +42,49 @@ __global__ __launch_bounds__(kThreads) void calib_mfma_kernel(int iters, const v
     if (s == 0x7fffffff) sink[0] = s;  // keeps the loop alive; practically never true
 }
 
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// the same for the fp8 instruction of the large layers' low group: 2 x 2 tiles of 32 x 32 and two fragments of 32 bytes
+// a lane on each side, as there; 16 x v_mfma_f32_32x32x64_f8f6f4 per iteration and wavefront
+__global__ __launch_bounds__(kThreads) void calib_mfma_f8_kernel(int iters, const v4i* __restrict__ a_bytes,
+                                                                const v4i* __restrict__ b_bytes, int* __restrict__ sink) {
+    const int t = threadIdx.x;
+    v16f acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
+    v8i a[4], b[4];
+    auto fragment = [&](const v4i* p, int i) {
+        const v4i x = p[(t + kThreads * 2 * i) & 4095], y = p[(t + kThreads * (2 * i + 1)) & 4095];
+        return (v8i){x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+    };
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        a[i] = fragment(a_bytes, i);
+        b[i] = fragment(b_bytes, i);
+    }
+    // the wait states between the writes of the operands and the first product
+    asm volatile("s_nop 15" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
+    asm volatile("s_nop 15" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(b[0]), "+v"(b[1]), "+v"(b[2]), "+v"(b[3]));
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)   // fragments 2 (e / 2) + (0, 1) of a, 2 (e % 2) + (0, 1) of b
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                asm volatile("v_mfma_f32_32x32x64_f8f6f4 %0, %1, %2, %0"
+                             : "+a"(acc[i]) : "v"(b[2 * (e & 1) + (i >> 1)]), "v"(a[2 * (e >> 1) + (i & 1)]));
+    }
+    asm volatile("s_nop 15\n\ts_nop 15" : "+a"(acc[0]), "+a"(acc[1]), "+a"(acc[2]), "+a"(acc[3]));
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s += acc[i][v];
+    if (s == 0.123456789f) sink[0] = 1;  // keeps the loop alive
+}
+
 // plain streaming read of n16 16-byte words, four loads in flight per lane
 __global__ __launch_bounds__(256) void calib_read_kernel(const uint4* __restrict__ p, size_t n16,
                                                          uint32_t* __restrict__ sink) {
@@ -67,6 +110,17 @@ int calib_mfma_int8(const void* a_bytes, const void* b_bytes, int iters, int wor
                     void* start_event, void* stop_event, void* stream) {
     if (!a_bytes || !b_bytes || !sink || iters < 1 || workgroups < 1) return 1;
     hipExtLaunchKernelGGL(calib_mfma_kernel, dim3((unsigned)workgroups), dim3(kThreads), 0,
+                          static_cast<hipStream_t>(stream), static_cast<hipEvent_t>(start_event),
+                          static_cast<hipEvent_t>(stop_event), 0, iters, static_cast<const v4i*>(a_bytes),
+                          static_cast<const v4i*>(b_bytes), sink);
+    return hipGetLastError() == hipSuccess ? 0 : 5;
+}
+
+// the fp8 instruction; arguments as calib_mfma_int8.  Operations per launch: 2 * 32 * 32 * 64 * 16 * 8 * iters * workgroups.
+int calib_mfma_f8(const void* a_bytes, const void* b_bytes, int iters, int workgroups, int* sink,
+                  void* start_event, void* stop_event, void* stream) {
+    if (!a_bytes || !b_bytes || !sink || iters < 1 || workgroups < 1) return 1;
+    hipExtLaunchKernelGGL(calib_mfma_f8_kernel, dim3((unsigned)workgroups), dim3(kThreads), 0,
                           static_cast<hipStream_t>(stream), static_cast<hipEvent_t>(start_event),
                           static_cast<hipEvent_t>(stop_event), 0, iters, static_cast<const v4i*>(a_bytes),
                           static_cast<const v4i*>(b_bytes), sink);
