@@ -329,7 +329,8 @@ int resq_gram_accumulate(const void* x, int64_t ldx, int64_t T, int64_t K, float
  *               sweeps bring every off-diagonal element of a K = 4096 covariance
  *               below 2^-40 of its diagonal neighbours.  The count is fixed so
  *               that the call never has to wait for the device; sweeps after one
- *               that found nothing to rotate cost only their empty launches
+ *               that found nothing to rotate are skipped (orders up to 128) or cost
+ *               only their empty launches
  *      eigvals  fp32 [K]                             (written)
  *      p        fp32 [K, ldp], ldp >= K              (written)
  *               eigvals and p may lie on c's memory (c is lost then), not on each other's; orders
@@ -349,10 +350,11 @@ int resq_sym_eig(const float* c, int64_t ldc, int64_t K, int sweeps, float* eigv
  * call on, held until the process ends).  The call allocates and frees nothing.
  *   K   even, 2 .. 512 (head-size and small hidden-size bases); larger: RESQ_ERR_BUFFER,
  *       nothing is launched
- * Results are those of resq_sym_eig bit for bit.  All calls on one GPU share the one array:
- * calls that overlap on a GPU (different streams or host threads) race, and its contents
- * after a call are meaningless (every call initializes what it reads).  RESQ_ERR_HIP if the
- * array's address cannot be obtained on the current device.
+ * Results are those of resq_sym_eig bit for bit.  Calls on one GPU that work on the array
+ * (orders above 128, and any order with an output on c's memory) share the one array: those
+ * that overlap (different streams or host threads) race, and its contents after a call are
+ * meaningless (every call initializes what it reads).  Other calls do not touch it.
+ * RESQ_ERR_HIP if the array's address cannot be obtained on the current device.
  */
 int resq_sym_eig_static(const float* c, int64_t ldc, int64_t K, int sweeps, float* eigvals, float* p,
                         int64_t ldp, void* stream);

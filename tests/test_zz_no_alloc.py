@@ -1,8 +1,8 @@
 """The entry point that allocates nothing (resq_sym_eig_static: the Jacobi eigensolver on the
 library's built-in scratch area) against the entry point it is a variant of (resq_sym_eig with
 a caller-provided workspace), through the C ABI: same kernels, same arguments, so eigenvalues
-and eigenvectors must agree bit for bit, on two calls in a row of which the second is smaller
-(it reuses the scratch area that the first left dirty)."""
+and eigenvectors must agree bit for bit, on calls in a row of which each is smaller than the one before.
+Orders above 128, and any order in place, work on the scratch area, which the call before left dirty."""
 import numpy as np
 import pytest
 import torch
@@ -24,7 +24,8 @@ def test_sym_eig_static_matches_sym_eig_on_two_calls_in_a_row():
     from paper_2412_14363_amd import binding as rq
     L = rq.lib()
     st = torch.cuda.current_stream().cuda_stream
-    for K, r, sweeps in ((256, 32, 10), (64, 8, 9)):          # the second call is the smaller one
+    # 512, 256, 192 and 130 share the scratch area; 128 and 64 run without it, between and after them
+    for K, r, sweeps in ((512, 64, 10), (128, 16, 10), (256, 32, 10), (192, 24, 9), (130, 16, 9), (64, 8, 9)):
         c = planted(K, r, K + 1).cuda()
         lam = torch.full((K,), -1.0, dtype=torch.float32, device="cuda")
         p = torch.full((K, K + 8), -1.0, dtype=torch.float32, device="cuda")   # ldp > K: padding stays
@@ -58,3 +59,44 @@ def test_sym_eig_static_python_binding_and_size_limit():
     big = torch.eye(514, dtype=torch.float32, device="cuda")
     with pytest.raises(rq.ResqError, match="RESQ_ERR_BUFFER"):
         rq.resq_sym_eig_static(big, torch.empty(514, device="cuda"), torch.empty((514, 514), device="cuda"))
+
+
+def test_sym_eig_static_in_place_on_dirty_scratch():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU; there is no CPU fallback")
+    from paper_2412_14363_amd import binding as rq
+    big = planted(256, 32, 1).cuda()
+    rq.resq_sym_eig_static(big, torch.empty(256, device="cuda"), torch.empty((256, 256), device="cuda"), sweeps=10)
+    for K in (64, 128):
+        c = planted(K, 8, K).cuda()
+        p, lam = c.clone(), torch.empty(K, device="cuda")
+        rq.resq_sym_eig_static(p, lam, p, sweeps=10)       # through the scratch area
+        p2, lam2 = c.clone(), torch.empty(K, device="cuda")
+        nbytes = rq.lib().resq_sym_eig_workspace_bytes(K)
+        work = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+        assert rq.lib().resq_sym_eig(p2.data_ptr(), K, K, 10, lam2.data_ptr(), p2.data_ptr(), K, work.data_ptr(), nbytes,
+                                     torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        assert torch.equal(lam, lam2) and torch.equal(p, p2)
+
+
+def test_sym_eig_static_under_graph_capture():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU; there is no CPU fallback")
+    from paper_2412_14363_amd import binding as rq
+    K = 128
+    c, lam, p = planted(K, 16, 3).cuda(), torch.empty(K, device="cuda"), torch.empty((K, K), device="cuda")
+    rq.resq_sym_eig_static(c, lam, p, sweeps=10)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        rq.resq_sym_eig_static(c, lam, p, sweeps=10)
+    for seed in (5, 6, 7):
+        c.copy_(planted(K, 16, seed))
+        lam.fill_(-1.0)
+        p.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        lam_ref, p_ref = rq.resq_sym_eig(c, sweeps=10)
+        torch.cuda.synchronize()
+        assert torch.equal(lam, lam_ref) and torch.equal(p, p_ref), seed
