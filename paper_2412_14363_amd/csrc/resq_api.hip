@@ -865,8 +865,8 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)((J + kBasisTile - 1) / kBasisTile), (unsigned)((rows + kBasisTile - 1) / kBasisTile), 1);
     // bf16 rows: three exact bf16 products instead of one fp32 product, at every size (same
-    // tiles and grid as the fp32 kernel: 4096 x 4096 x 4096 0.44 ms against 1.19, 256 x 512 x 512 21 us
-    // against 56, 128 x 128 x 128 11 us against 22); fp32 rows would need at least six, and stay on the
+    // tiles and grid as the fp32 kernel: 4096 x 4096 x 4096 0.40 ms against 1.19, 256 x 512 x 512 17 us
+    // against 56, 128 x 128 x 128 8.4 us against 22); fp32 rows would need at least six, and stay on the
     // fp32 instruction
     if (a_is_bf16) {
         ProjectArgs pa;
@@ -913,8 +913,8 @@ static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int swee
                                 int64_t ldp, void* workspace, void* stream) {
     const int n = (int)K;
     // one launch on LDS while the matrix and a slice of the vectors fit there, up to 128 columns:
-    // 1.06 ms at n = 128 against 6.9 ms in two launches a round (0.15 / 1.69 ms at n = 32, 0.39 / 4.9
-    // at 64).  Not where an output lies on c: its workgroups all read c at their start and write p and
+    // 1.06 to 1.70 ms at n = 128 against 6.9 to 10.5 in two launches a round, by the sweeps that the matrix
+    // needs (0.15 / 1.69 ms at n = 32, 0.39 / 4.9 at 64).  Not where an output lies on c: its workgroups all read c at their start and write p and
     // eigvals at their end, in no order among each other; the workspace takes a copy of c first.
     if (n <= kEigSmallMax && !blocks_overlap(c, K, ldc, p, K, ldp, K) && !blocks_overlap(c, K, ldc, eigvals, 1, K, K)) {
         const int small_lds = eig_small_lds_bytes(n);

@@ -114,9 +114,9 @@ __global__ void eig_rotations_kernel(EigPlan e, int sweep, int round) {
 // only the blocks that the next angles need, and the others all the rest behind one
 // barrier a round instead of two, measured the same: 1.04 ms at n = 128.)
 //
-// Measured on the covariance of Gaussian rows, 12 sweeps allowed, two launches a round /
-// this kernel: n = 128 6.9 / 1.06 ms (3000 clocks a round), n = 64 4.9 / 0.39, n = 32
-// 1.69 / 0.15.
+// Measured, 12 sweeps allowed, two launches a round / this kernel: n = 128 9.9 to 10.5 / 1.70 ms on a
+// covariance with a spectrum that decays by e^-6, 6.9 / 1.06 on that of Gaussian rows, which
+// converges in fewer sweeps (3000 clocks a round); Gaussian n = 64 4.9 / 0.39, n = 32 1.69 / 0.15.
 constexpr int kEigSmallMax = 128;
 constexpr int kEigSmallThreads = 1024;
 constexpr int kEigSmallCols = 8;  // columns of Vt per workgroup

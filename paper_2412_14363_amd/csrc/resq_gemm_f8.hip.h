@@ -3,8 +3,8 @@
 // those of resq_gemm.hip.h; what differs:
 //
 // The low group.  Under the chip's power limit the int8 instruction alone, on nibble
-// operands, sustains 3.8 to 4.8 POPS and the fp8 one 4.9 (its full rate, 2.4 GHz): a 4-bit
-// operand lights up a quarter of an fp8 multiplier's bits.  And 4-bit codes are exact in it:
+// operands, sustains 3.7 to 3.9 POPS over milliseconds and the fp8 one 4.3 to 4.6 (4.1 to 4.8 and 4.9, its
+// full rate, on shorter runs): a 4-bit operand lights up a quarter of an fp8 multiplier's bits.  And 4-bit codes are exact in it:
 // the e4m3 numbers below 2^-5 are the multiples of 2^-9, so the byte 0..15 IS the number
 // u * 2^-9, u = code + 8 the offset code.  An even activation column and an odd weight column
 // are stored offset already (one AND); the others, in two's complement in the upper nibble,
@@ -27,11 +27,11 @@
 // l % 32, piece 2 h + l / 32: 16 lanes meet 16 bank groups (the 16x16x64 reads did not: half
 // of their LDS cycles were conflicts).
 //
-// Measured (kernel alone, back to back, int8 kernel / this one): 8192 x 8192 -> 29568 at
-// r = 0 1389 / 1322 us, r = K/8 1557 / 1505; 4096 x 14336 -> 4096 182 / 175; 1100 x 14336 ->
-// 8192 125.5 / 117.5.  Matrix pipes busy 82 % of the clocks (71 %), which fall from 1.82 to
-// 1.68 GHz: the power limit again.  What the rest goes to, timing-only builds at r = 0:
-// global->LDS loads 21 %, widening 9 %, LDS reads 8 %.
+// Measured (int8 kernel / this one, the two in turn): 8192 x 8192 -> 29568 at r = 0 1461 / 1399 us, r = K/8 1558 /
+// 1507; 4096 x 14336 -> 4096 182 / 175; 1100 x 14336 -> 8192 125.5 / 117.5.  At r = 0 the matrix pipes are busy
+// 79 % of 2.39 M clocks (71 % of 2.66 M), and the clock falls from 1.82 to 1.71 GHz: the power limit again; LDS
+// bank conflicts 5.7 M (129 M).  What the rest goes to, timing-only builds at r = 0: global->LDS loads 21 %,
+// widening 9 %, LDS reads 8 %.
 #pragma once
 #include "resq_gemm.hip.h"
 

@@ -7,8 +7,8 @@
 // number is the exact sum of three bf16 numbers (8 + 8 + 8 significant bits, each
 // the truncated rest of the one before), every product with a bf16 a is exact in
 // fp32, and the accumulator is fp32 as before.  Three products instead of one, at
-// sixteen times the rate: 0.44 ms for the same fold (940 TFLOP/s of bf16 products, matrix
-// pipes busy 52 % of the clocks at 1.7 GHz: the power limit).
+// sixteen times the rate: 0.40 ms for the same fold (1030 TFLOP/s of bf16 products, matrix
+// pipes busy 52 % of the clocks at 1.7 GHz: the power limit; 0.41 to 0.46 behind other work).
 // Error against 64 bits with fp32 output (2-norm, before / now): 1.2e-6 / 7.0e-7 at
 // K = 4096, 4.0e-7 / 2.4e-7 at 512, 2.0e-7 / 1.2e-7 at 128: the sum has fewer roundings
 // (one per 16 products of the instruction instead of one per 2).
