@@ -361,8 +361,8 @@ int resq_sym_eig_static(const float* c, int64_t ldc, int64_t K, int sweeps, floa
 
 /*
  * 3. Rows expressed in a basis:  out[i][j] = sum_k a[i][k] u[k][j]  (exact
- *    products, fp32 accumulation: fp32 matrix cores for fp32 a; for bf16 a the bf16
- *    ones, u in three bf16 parts whose sum it is, up to what lies under 2^-133).
+ *    products, fp32 accumulation: fp32 matrix cores for fp32 a and for K <= 16; else for bf16
+ *    a the bf16 ones, u in three bf16 parts whose sum it is, up to what lies under 2^-133).
  *    Infinities and NaN go through as in a plain fp32 sum.  This one product serves every
  *    remaining step: U_h = P_h R_h and U_l = P_l R_l (the definition of U in
  *    Section 4.2: a = a column block of p, u = a random orthogonal matrix passed

@@ -848,7 +848,7 @@ int resq_gram_accumulate(const void* x, int64_t ldx, int64_t T, int64_t K, float
     slices = (T + g.t_per_slice - 1) / g.t_per_slice;
     const dim3 grid((unsigned)((K + kBasisTile - 1) / kBasisTile), (unsigned)((K + kBasisTile - 1) / kBasisTile),
                     (unsigned)slices);
-    launch(basis_gemm_kernel<true, false>, grid, dim3(kBasisThreads), 0,
+    launch(basis_gemm_kernel<true, true, false>, grid, dim3(kBasisThreads), 0,
            static_cast<hipStream_t>(stream), g);
     return launch_status();
 }
@@ -864,11 +864,13 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
         return RESQ_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)((J + kBasisTile - 1) / kBasisTile), (unsigned)((rows + kBasisTile - 1) / kBasisTile), 1);
-    // bf16 rows: three exact bf16 products instead of one fp32 product, at every size (same
+    // bf16 rows: three exact bf16 products instead of one fp32 product (same
     // tiles and grid as the fp32 kernel: 4096 x 4096 x 4096 0.40 ms against 1.19, 256 x 512 x 512 17 us
     // against 56, 128 x 128 x 128 8.4 us against 22); fp32 rows would need at least six, and stay on the
-    // fp32 instruction
-    if (a_is_bf16) {
+    // fp32 instruction.  So do bf16 rows of one chunk of that kernel: half a chunk of the other, whose
+    // ragged end costs more than its products save (16 steps, 128 x 128 outputs 5.5 / 7.1 us, 4096 x 4096 15.6 / 18.6; 17
+    // steps 7.0 / 7.2, 20.4 / 18.7)
+    if (a_is_bf16 && K > kBasisChunk) {
         ProjectArgs pa;
         pa.a = static_cast<const uint16_t*>(a);
         pa.u = u;
@@ -885,8 +887,10 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
     g.I = rows; g.J = J; g.T = K;
     g.accumulate = 0;
     g.t_per_slice = round_up(K, kBasisChunk);
-    if (out_is_bf16) launch(basis_gemm_kernel<false, true>, grid, dim3(kBasisThreads), 0, st, g);
-    else launch(basis_gemm_kernel<false, false>, grid, dim3(kBasisThreads), 0, st, g);
+    if (a_is_bf16 && out_is_bf16) launch(basis_gemm_kernel<false, true, true>, grid, dim3(kBasisThreads), 0, st, g);
+    else if (a_is_bf16) launch(basis_gemm_kernel<false, true, false>, grid, dim3(kBasisThreads), 0, st, g);
+    else if (out_is_bf16) launch(basis_gemm_kernel<false, false, true>, grid, dim3(kBasisThreads), 0, st, g);
+    else launch(basis_gemm_kernel<false, false, false>, grid, dim3(kBasisThreads), 0, st, g);
     return launch_status();
 }
 

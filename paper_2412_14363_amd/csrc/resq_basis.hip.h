@@ -2,8 +2,8 @@
 //
 //   gram:    C[i][j] += sum_t X[t][i] X[t][j]      covariance of the calibration activations
 //   project: Y[i][j]  = sum_t A[i][t] U[t][j]      rows of A (activations, weights, P_h, P_l)
-//                                                  expressed in a basis / rotated inside a group (fp32 rows;
-//                                                  bf16 rows: resq_project.hip.h)
+//                                                  expressed in a basis / rotated inside a group (fp32 rows,
+//                                                  and bf16 rows of at most 16 steps; others: resq_project.hip.h)
 //
 // Both are C(i, j) = sum_t A(i, t) B(t, j) with fp32 accumulation on the fp32
 // matrix-core instruction v_mfma_f32_32x32x2_f32 (bf16 inputs are widened exactly,
@@ -34,8 +34,8 @@ constexpr int kBasisChunk = 16;   // reduction steps per LDS buffer
 constexpr int kBasisPitch = kBasisTile + 4;  // floats; rows 16-byte aligned
 
 struct BasisGemmArgs {
-    const void* a;   // GRAM: bf16 [T][lda] (element (i, t) at a[t * lda + i]); else fp32 [I][lda]
-    const void* b;   // [T][ldb], the same type
+    const void* a;   // GRAM: bf16 [T][lda] (element (i, t) at a[t * lda + i]); else bf16 (A_BF16) or fp32 [I][lda]
+    const void* b;   // [T][ldb], GRAM: bf16, else fp32
     void* c;         // [I][ldc], fp32 or bf16
     int64_t lda, ldb, ldc;
     int64_t I, J, T;
@@ -65,8 +65,8 @@ __device__ __forceinline__ void load8(const void* base, int64_t elem, bool live,
 }
 
 // Requires lda, ldb multiples of 8 elements and 16-byte aligned bases (checked on the host), J and, for GRAM, I
-// multiples of 8; I (rows of fp32 data) and T arbitrary.
-template <bool GRAM, bool OUT_BF16>
+// multiples of 8; I (rows) and T arbitrary.
+template <bool GRAM, bool A_BF16, bool OUT_BF16>
 __global__ __launch_bounds__(kBasisThreads) void basis_gemm_kernel(const BasisGemmArgs g) {
     __shared__ __attribute__((aligned(16))) float lds_a[2][kBasisChunk][kBasisPitch];
     __shared__ __attribute__((aligned(16))) float lds_b[2][kBasisChunk][kBasisPitch];
@@ -88,13 +88,14 @@ __global__ __launch_bounds__(kBasisThreads) void basis_gemm_kernel(const BasisGe
             load8<true>(g.a, tt * g.lda + i, tt < t_end && i < g.I, ra);   // I % 8 == 0 in this form
         } else {
             const int64_t i = i0 + ar, tt = tc + at;
-            load8<false>(g.a, i * g.lda + tt, i < g.I && tt + 8 <= t_end, ra);
+            load8<A_BF16>(g.a, i * g.lda + tt, i < g.I && tt + 8 <= t_end, ra);
             if (i < g.I && tt < t_end && tt + 8 > t_end) {   // ragged end of the reduction axis
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
                     ra[k] = 0.0f;
                     if (tt + k < t_end) {
-                        ra[k] = static_cast<const float*>(g.a)[i * g.lda + tt + k];
+                        if constexpr (A_BF16) ra[k] = __uint_as_float((uint32_t)static_cast<const uint16_t*>(g.a)[i * g.lda + tt + k] << 16);
+                        else ra[k] = static_cast<const float*>(g.a)[i * g.lda + tt + k];
                     }
                 }
             }

@@ -1,5 +1,5 @@
 // Rows of bf16 data expressed in an fp32 basis (Section 4.2 and 4.3: X U, W U):
-//   out[i][j] = sum_t a[i][t] u[t][j],   a bf16, u fp32, out bf16 or fp32.
+//   out[i][j] = sum_t a[i][t] u[t][j],   a bf16, u fp32, out bf16 or fp32, more than 16 steps t (fewer: the fp32 kernel).
 //
 // The fp32 matrix instruction (157 TFLOP/s) bounds this product at 0.87 ms for a
 // 4096^3 fold; it took 1.19 ms there (115 TFLOP/s).  The bf16 matrix cores are

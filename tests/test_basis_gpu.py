@@ -83,8 +83,8 @@ def test_project_rows(rq, rows, K, J, a_dtype, out_dtype):
 
 
 # bf16 rows go through the bf16 matrix cores with u in three exact parts: edges of the 128 x 128
-# tiles and of the 32 steps of a chunk
-@pytest.mark.parametrize("rows,K,J", [(1, 1, 8), (128, 32, 128), (129, 33, 136), (127, 31, 120), (40, 64, 1000), (300, 515, 16)])
+# tiles and of the 32 steps of a chunk; rows of at most 16 steps through the fp32 ones
+@pytest.mark.parametrize("rows,K,J", [(1, 1, 8), (129, 16, 136), (130, 15, 8), (40, 17, 264), (128, 32, 128), (129, 33, 136), (127, 31, 120), (40, 64, 1000), (300, 515, 16)])
 def test_project_rows_split(rq, rows, K, J):
     g = torch.Generator().manual_seed(rows + K + J)
     ld = (K + 7) // 8 * 8 + 8
@@ -106,16 +106,17 @@ def test_project_rows_split(rq, rows, K, J):
 # Infinities and NaN in either operand: what a plain sum gives, not the NaN that infinity x 0 among the three
 # parts of u would leave (bf16 numbers have two zero parts).
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
-def test_project_rows_split_infinities(rq, out_dtype):
-    rows, K, J = 131, 70, 136
+@pytest.mark.parametrize("K", [70, 16])
+def test_project_rows_split_infinities(rq, out_dtype, K):
+    rows, J = 131, 136
     g = torch.Generator().manual_seed(5)
     a = torch.randn(rows, K, generator=g).bfloat16()
     u = torch.randn(K, J, generator=g)
     u[:, ::2] = u[:, ::2].bfloat16().float()
     inf, nan = float("inf"), float("nan")
-    a[0, 3], a[5, 60], a[130, 69], a[7, 2], a[7, 9], a[9, 1], a[11, 5] = inf, -inf, inf, inf, -inf, nan, 0.0
-    u[64, 4], u[5, 7], u[2, 135], u[3, 8] = inf, -inf, inf, 0.0
-    ld = 72
+    a[0, 3], a[5, K - 10], a[130, K - 1], a[7, 2], a[7, 9], a[9, 1], a[11, 5] = inf, -inf, inf, inf, -inf, nan, 0.0
+    u[K - 6, 4], u[5, 7], u[2, 135], u[3, 8] = inf, -inf, inf, 0.0
+    ld = (K + 7) // 8 * 8
     ad = torch.zeros(rows, ld, dtype=torch.bfloat16)
     ad[:, :K] = a
     got = rq.resq_project_rows(ad.cuda()[:, :K], u.cuda(), out_dtype=out_dtype).cpu().double().numpy()
@@ -128,7 +129,7 @@ def test_project_rows_split_infinities(rq, out_dtype):
     mag = np.abs(np.nan_to_num(a.double().numpy(), posinf=0, neginf=0)) @ np.abs(np.nan_to_num(u.double().numpy(), posinf=0, neginf=0))
     tol = 3 * K * 2.0 ** -24 * mag + (2.0 ** -8 * np.abs(np.where(fin, ref, 0)) if out_dtype == torch.bfloat16 else 0)
     assert np.all(np.abs(got[fin] - ref[fin]) <= tol[fin])
-    if out_dtype == torch.bfloat16:   # out on a: one column of tiles, so that rows stay a workgroup's own
+    if out_dtype == torch.bfloat16 and K >= 64:   # out on a: one column of tiles, so that rows stay a workgroup's own
         buf = ad.cuda()
         rq.resq_project_rows(buf[:, :K], u[:, :64].contiguous().cuda(), out=buf[:, :64])
         assert np.array_equal(buf[:, :64].cpu().double().numpy(), got[:, :64], equal_nan=True)
