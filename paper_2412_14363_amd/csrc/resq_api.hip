@@ -671,6 +671,8 @@ static int gemm_mixed_impl(const int8_t* q_hi, const uint8_t* q_lo, const float*
     const bool narrow = plan.kernel == 3;  // 64-token tiles
     a.tiles_m = narrow ? (int)((M + kBM64 - 1) / kBM64) : (int)((M + kBM - 1) / kBM);
     a.tiles_n = (int)(a.L.n_pad / kBN);
+    a.bands = (int64_t)a.tiles_m * a.tiles_n % 8 != 0;   // see tile_of_block
+    if (a.bands) a.tiles_n = (int)((N + kBN - 1) / kBN);
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > 0x7FFFFFFF) return RESQ_ERR_SHAPE;
 

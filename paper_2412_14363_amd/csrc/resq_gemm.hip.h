@@ -127,6 +127,7 @@ struct GemmArgs {
     int32_t* dbg_lo;
     int stages_hi, stages_lo;
     int tiles_m, tiles_n;
+    int bands;   // 1: the order in bands of tile_of_block, tiles_n without padding tiles
     int swiglu;  // 1: channels 2c and 2c+1 are the gate and the up row of feature c; y[m, c] = silu(gate) * up
 };
 
@@ -244,25 +245,33 @@ __device__ __forceinline__ void buffer_load_to_lds_16B(__amdgpu_buffer_rsrc_t rs
 // allows it, the 64 tiles an XCD works on together form an 8 x 8 patch (1024
 // tokens x 1024 channels), so that each activation stage and each weight stage
 // is fetched into that L2 once per 8 tiles; the 8 XCDs take neighbouring patches.
-// Any other grid: each XCD takes a run of consecutive tiles of its own (the first total % 8 of
-// them one more), down the token axis first.  (In id order where total % 8 != 0, neighbouring
-// tiles were spread over all eight L2s, and the fp8 low group, which leans most on operand
-// traffic, fell behind the int8 one there: 3323 x 7552 -> 3328 at r = 1664 with the quantizer in
-// front of it 82.0 us in int8, 80.2 to 86.9 in fp8 in that order, 76.8 in fp8 in this one.  int8 tiles 2100 x
-// 2048 -> 6400 36.7 / 33.9, 64-token tiles 777 x 5000 -> 3328 26.3 / 23.1, 700 x 8192 -> 3328 38.7 / 31.3; equal
-// where a grid has many rounds or stages few: 5000 x 1024 -> 5376 42.8 / 42.9.)
+// Other grids of a multiple of eight tiles: each XCD takes a run of consecutive tiles of its own, down
+// the token axis first.  The rest (a.bands): such runs too, the first total % 8 of them one longer, through bands of eight
+// token tiles, channel by channel inside a band, so that what an XCD works on together is close to a patch
+// there as well; and of the layer's own tiles only, since padding tiles (N is padded to two) would fall to the last XCDs
+// and leave the others more to do.  Measured with the quantizer in front (id order, which spreads neighbours over
+// all eight L2s / one run of the token axis after the other, padding tiles among them / bands): fp8 3451 x 7552 -> 3328 at r = 1664
+// 81.6 / 77.2 / 73.9 us (int8 82.0), int8 7550 x 1088 -> 1065 34.9 / 36.4 / 32.9, 9000 x 2048 -> 5376 106.7 / 105.3 /
+// 93.9, 64-token tiles 700 x 8192 -> 3328 38.5 / 31.5 / 31.7, 3000 x 4096 -> 600 16.4 / 26.0 / 15.6; equal where stages are
+// few: 5000 x 1024 -> 5376 43.6 / 43.9 / 43.8.  (Bands of 4 and of 16: within 3 % of these, mostly slower.)
+constexpr int kBand = 8;
 __device__ __forceinline__ void tile_of_block(const GemmArgs& a, int& tm, int& tn) {
     const int total = a.tiles_m * a.tiles_n;
-    const int id = blockIdx.x;
-    if (total % 512 == 0 && a.tiles_m % 8 == 0 && a.tiles_n % 8 == 0) {
-        const int xcd = id & 7, k = id >> 3;
+    const int id = blockIdx.x, xcd = id & 7, k = id >> 3;
+    if (a.bands) {
+        const int rest = total & 7;
+        const int lin = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + k;
+        const int band = lin / (kBand * a.tiles_n), in_band = lin - band * kBand * a.tiles_n;
+        const int left = a.tiles_m - kBand * band, height = left < kBand ? left : kBand;
+        tn = in_band / height;
+        tm = kBand * band + (in_band - tn * height);
+    } else if (total % 512 == 0 && a.tiles_m % 8 == 0 && a.tiles_n % 8 == 0) {
         const int patch = (k >> 6) * 8 + xcd, within = k & 63;
         const int patches_m = a.tiles_m >> 3;
         tm = (patch % patches_m) * 8 + (within & 7);
         tn = (patch / patches_m) * 8 + (within >> 3);
     } else {
-        const int xcd = id & 7, rest = total & 7;
-        const int lin = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + (id >> 3);
+        const int lin = xcd * (total >> 3) + k;
         tn = lin / a.tiles_m;
         tm = lin % a.tiles_m;
     }
@@ -341,7 +350,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
     const int64_t m0 = (int64_t)tile_m * kBM;
     const int64_t n0 = (int64_t)tile_n * kBN;
     // the grid covers the padded channel count (a multiple of 256, which keeps the patches of
-    // tile_of_block whole): a tile that holds padding channels only has nothing to do
+    // tile_of_block whole) but in bands: a tile that holds padding channels only has nothing to do
     if (n0 >= a.L.N) return;
     const int S_hi = a.stages_hi, S_lo = a.stages_lo, S = S_hi + S_lo;  // S_hi and S_lo are even
     const uint16_t* sw_hi = reinterpret_cast<const uint16_t*>(a.packed + a.L.scale_off);

@@ -393,11 +393,13 @@ def test_layer_tiled_kernel_fp8_low_group_largest_sums(rq, low, f8):
     assert torch.equal(y, want.float().to(torch.bfloat16)) and torch.equal(y2, y)   # both scales are 1
 
 
-# grids whose number of tiles leaves 2, 4 and 6 over eight: every XCD has its own run of tiles, the first of them one more
+# Grids whose number of tiles, padding tiles included, leaves 2, 4 and 6 over eight: bands of eight token tiles, of the layer's
+# own tiles.  Whole bands and a last one of 1 to 7, one channel tile and many, padding tiles left out and none there
 @pytest.mark.parametrize("M,K,N,r,kernel,tiles", [
     (385, 512, 2562, 64, 3, 154), (321, 512, 3300, 64, 3, 156), (385, 512, 3300, 64, 3, 182),
     (1025, 512, 2050, 64, 3, 306), (577, 512, 3300, 64, 3, 260), (700, 512, 3300, 64, 3, 286),
     (1537, 512, 3300, 64, 2, 338), (1700, 512, 2562, 64, 2, 308), (1793, 512, 2300, 64, 2, 270),
+    (1025, 512, 256, 64, 3, 34), (1100, 512, 100, 64, 3, 36), (1153, 512, 300, 64, 3, 76), (1537, 512, 2562, 0, 2, 286), (7550, 256, 1065, 32, 2, 590),
 ])
 def test_layer_tile_order(oracle, rq, M, K, N, r, kernel, tiles):
     assert rq.resq_gemm_mixed_plan(M, N, K, r)[0] == kernel
