@@ -497,9 +497,9 @@ static GemmPlan plan_gemm(int64_t M, const WeightLayout& L) {
 // 31.7 / 32.1 us), where stages are few (2048 x 2048 -> 8192, 14 low: 35.6 / 36.8; 4096 x 1024 -> 8192,
 // 8 low: 46.9 / 48.3) or mostly high (4096 x 4096 -> 8192, r = K/2: 126.4 / 130.2); and not where its
 // sums could leave the whole numbers of fp32.  In a whole call, a quantizer in front of every GEMM, over
-// 1 to 16 rounds, whole and ragged ones: 2 to 9 % at 8 high stages and 28 low ones or more, and on the
-// line's high side (24 low and 16 high, 36 and 24, 46 and 26) 2 to 6 %, at the least equal (2811 x 7552 -> 4096,
-// 704 tiles: 83.8 / 84.3).
+// 1 to 50 rounds, whole and ragged ones: 2 to 17 % at 8 high stages and 28 low ones or more, and on the
+// line's high side (24 low and 16 high, 36 and 24, 46 and 26) 2 to 11 %; least on heavy-tailed data with asymmetric
+// codes, whose offset codes lie about 7 and 8 (2.5 to 10 %).
 static bool use_f8(int64_t M, const WeightLayout& L) {
     const int64_t tiles = ((M + kBM - 1) / kBM) * ((L.N + kBN - 1) / kBN);
     return tiles > 512 && L.lo_blocks >= 24 && 2 * L.lo_blocks >= 3 * L.hi_blocks && L.kl_pad <= kF8MaxLoWidth;
@@ -671,8 +671,14 @@ static int gemm_mixed_impl(const int8_t* q_hi, const uint8_t* q_lo, const float*
     const bool narrow = plan.kernel == 3;  // 64-token tiles
     a.tiles_m = narrow ? (int)((M + kBM64 - 1) / kBM64) : (int)((M + kBM - 1) / kBM);
     a.tiles_n = (int)(a.L.n_pad / kBN);
-    a.bands = (int64_t)a.tiles_m * a.tiles_n % 8 != 0;   // see tile_of_block
-    if (a.bands) a.tiles_n = (int)((N + kBN - 1) / kBN);
+    const bool f8 = !narrow && use_f8(M, L);
+    // the order of the tiles (see tile_of_block)
+    a.bands = 0;
+    if ((int64_t)a.tiles_m * a.tiles_n % 8 != 0 || (f8 && !whole_patches(a.tiles_m, a.tiles_n))) {
+        const int n = (a.tiles_m + kBand - 1) / kBand;
+        a.bands = (a.tiles_m + n - 1) / n;
+        a.tiles_n = (int)((N + kBN - 1) / kBN);
+    }
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > 0x7FFFFFFF) return RESQ_ERR_SHAPE;
 
@@ -685,7 +691,7 @@ static int gemm_mixed_impl(const int8_t* q_hi, const uint8_t* q_lo, const float*
             if (dbg) launch(gemm_mixed_m64_kernel<true, 1>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
             else launch(gemm_mixed_m64_kernel<false, 1>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
         }
-    } else if (use_f8(M, L)) {
+    } else if (f8) {
         if (dbg) launch(gemm_mixed_f8_kernel<true>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
         else launch(gemm_mixed_f8_kernel<false>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, a);
     } else {

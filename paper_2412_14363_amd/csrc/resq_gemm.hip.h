@@ -127,7 +127,7 @@ struct GemmArgs {
     int32_t* dbg_lo;
     int stages_hi, stages_lo;
     int tiles_m, tiles_n;
-    int bands;   // 1: the order in bands of tile_of_block, tiles_n without padding tiles
+    int bands;   // > 0: token tiles to a band in the order of tile_of_block, tiles_n without padding tiles
     int swiglu;  // 1: channels 2c and 2c+1 are the gate and the up row of feature c; y[m, c] = silu(gate) * up
 };
 
@@ -246,26 +246,32 @@ __device__ __forceinline__ void buffer_load_to_lds_16B(__amdgpu_buffer_rsrc_t rs
 // tokens x 1024 channels), so that each activation stage and each weight stage
 // is fetched into that L2 once per 8 tiles; the 8 XCDs take neighbouring patches.
 // Other grids of a multiple of eight tiles: each XCD takes a run of consecutive tiles of its own, down
-// the token axis first.  The rest (a.bands): such runs too, the first total % 8 of them one longer, through bands of eight
-// token tiles, channel by channel inside a band, so that what an XCD works on together is close to a patch
-// there as well; and of the layer's own tiles only, since padding tiles (N is padded to two) would fall to the last XCDs
-// and leave the others more to do.  Measured with the quantizer in front (id order, which spreads neighbours over
-// all eight L2s / one run of the token axis after the other, padding tiles among them / bands): fp8 3451 x 7552 -> 3328 at r = 1664
-// 81.6 / 77.2 / 73.9 us (int8 82.0), int8 7550 x 1088 -> 1065 34.9 / 36.4 / 32.9, 9000 x 2048 -> 5376 106.7 / 105.3 /
-// 93.9, 64-token tiles 700 x 8192 -> 3328 38.5 / 31.5 / 31.7, 3000 x 4096 -> 600 16.4 / 26.0 / 15.6; equal where stages are
-// few: 5000 x 1024 -> 5376 43.6 / 43.9 / 43.8.  (Bands of 4 and of 16: within 3 % of these, mostly slower.)
+// the token axis first.  The rest, and all that are no patches with the low group in fp8 (a.bands > 0): such runs too, the
+// first total % 8 of them one longer, through bands of at most eight token tiles, as equal as they get, channel by channel
+// inside a band, so that what an XCD works on together is close to a patch there as well; and of the layer's own
+// tiles only, since padding tiles (N is padded to two) would fall to the last XCDs and leave the others more to do.
+// Measured with the quantizer in front (id order, which spreads neighbours over all eight L2s / one run down the token
+// axis after the other, padding tiles among them / bands): fp8 3451 x 7552 -> 3328 at r = 1664 81.6 / 77.2 / 73.9 us
+// (int8 82.0), int8 7550 x 1088 -> 1065 34.9 / 36.4 / 32.6, 9000 x 2048 -> 5376 106.7 / 105.3 / 92.4, 64-token tiles
+// 700 x 8192 -> 3328 38.5 / 31.5 / 31.7, 3000 x 4096 -> 600 16.4 / 26.0 / 15.6; equal where stages are few: 5000 x 1024 -> 5376
+// 42.6 / 42.9 / 42.7; 1240 x 1028 -> 3287, 260 tiles stored in 2-byte pieces, 20.4 / - / 20.8.  Multiples of eight, runs / bands:
+// fp8 7766 x 3928 -> 1893 73.2 / 67.6, 12000 x 4096 -> 4096 169.6 / 153.6 (int8 75.0, 174.4), but 64-token tiles 640 x 8192 ->
+// 4096 30.7 / 31.6.  (Bands of 4 and of 16 throughout: within 3 %, mostly slower.)
 constexpr int kBand = 8;
+__host__ __device__ inline bool whole_patches(int tiles_m, int tiles_n) {
+    return tiles_m % 8 == 0 && tiles_n % 8 == 0 && (int64_t)tiles_m * tiles_n % 512 == 0;
+}
 __device__ __forceinline__ void tile_of_block(const GemmArgs& a, int& tm, int& tn) {
     const int total = a.tiles_m * a.tiles_n;
     const int id = blockIdx.x, xcd = id & 7, k = id >> 3;
     if (a.bands) {
         const int rest = total & 7;
         const int lin = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + k;
-        const int band = lin / (kBand * a.tiles_n), in_band = lin - band * kBand * a.tiles_n;
-        const int left = a.tiles_m - kBand * band, height = left < kBand ? left : kBand;
+        const int band = lin / (a.bands * a.tiles_n), in_band = lin - band * a.bands * a.tiles_n;
+        const int left = a.tiles_m - a.bands * band, height = left < a.bands ? left : a.bands;
         tn = in_band / height;
-        tm = kBand * band + (in_band - tn * height);
-    } else if (total % 512 == 0 && a.tiles_m % 8 == 0 && a.tiles_n % 8 == 0) {
+        tm = a.bands * band + (in_band - tn * height);
+    } else if (whole_patches(a.tiles_m, a.tiles_n)) {
         const int patch = (k >> 6) * 8 + xcd, within = k & 63;
         const int patches_m = a.tiles_m >> 3;
         tm = (patch % patches_m) * 8 + (within & 7);
