@@ -491,15 +491,15 @@ static GemmPlan plan_gemm(int64_t M, const WeightLayout& L) {
 }
 
 // Whether the 128 x 128 tiles take the low group through the fp8 matrix cores (resq_gemm_f8.hip.h).
-// That saves power and issue slots per low stage (5 to 6 % on an all-low layer, 2.5 to 6 % at r = K/8
-// with 28 low stages and more, on more than one round of 512 tiles); it costs 0.3 us per round and 1 to
+// That saves power and issue slots per low stage (GEMMs back to back: 5 to 6 % on an all-low layer, 2.5 to 6 %
+// at r = K/8 with 28 low stages and more, on more than one round of 512 tiles); it costs 0.3 us per round and 1 to
 // 2 % per high stage.  So not where a single round runs below the power limit (2048 x 4096 -> 4096
 // 31.7 / 32.1 us), where stages are few (2048 x 2048 -> 8192, 14 low: 35.6 / 36.8; 4096 x 1024 -> 8192,
 // 8 low: 46.9 / 48.3) or mostly high (4096 x 4096 -> 8192, r = K/2: 126.4 / 130.2); and not where its
-// sums could leave the whole numbers of fp32.  In a whole call, a quantizer in front of every GEMM, over
-// 1 to 50 rounds, whole and ragged ones: 2 to 17 % at 8 high stages and 28 low ones or more, and on the
-// line's high side (24 low and 16 high, 36 and 24, 46 and 26) 2 to 11 %; least on heavy-tailed data with asymmetric
-// codes, whose offset codes lie about 7 and 8 (2.5 to 10 %).
+// sums could leave the whole numbers of fp32.  In whole calls, quantizer and GEMM,
+// against the int8 kernel in the tile order it had: 0 to 2 % in grids that are whole patches (8192 x 4096 -> 4096,
+// r = 512, asymmetric codes of Student-t data 141.9 / 141.8 us, symmetric ones of normal data 140.4 / 138.5), 1 to
+// 9 % in others, part of it by the tile order (2811 x 7552 -> 4096, r = 1664: 95.8 / 89.4).
 static bool use_f8(int64_t M, const WeightLayout& L) {
     const int64_t tiles = ((M + kBM - 1) / kBM) * ((L.N + kBN - 1) / kBN);
     return tiles > 512 && L.lo_blocks >= 24 && 2 * L.lo_blocks >= 3 * L.hi_blocks && L.kl_pad <= kF8MaxLoWidth;

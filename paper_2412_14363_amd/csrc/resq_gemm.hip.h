@@ -252,9 +252,9 @@ __device__ __forceinline__ void buffer_load_to_lds_16B(__amdgpu_buffer_rsrc_t rs
 // tiles only, since padding tiles (N is padded to two) would fall to the last XCDs and leave the others more to do.
 // Measured with the quantizer in front (id order, which spreads neighbours over all eight L2s / one run down the token
 // axis after the other, padding tiles among them / bands): fp8 3451 x 7552 -> 3328 at r = 1664 81.6 / 77.2 / 73.9 us
-// (int8 82.0), int8 7550 x 1088 -> 1065 34.9 / 36.4 / 32.6, 9000 x 2048 -> 5376 106.7 / 105.3 / 92.4, 64-token tiles
+// (int8 82.0), int8 7550 x 1088 -> 1065 34.9 / 36.4 / 32.6, 9000 x 2048 -> 5376 109.1 / - / 97.5, 64-token tiles
 // 700 x 8192 -> 3328 38.5 / 31.5 / 31.7, 3000 x 4096 -> 600 16.4 / 26.0 / 15.6; equal where stages are few: 5000 x 1024 -> 5376
-// 42.6 / 42.9 / 42.7; 1240 x 1028 -> 3287, 260 tiles stored in 2-byte pieces, 20.4 / - / 20.8.  Multiples of eight, runs / bands:
+// 42.6 / 42.9 / 42.7; 1240 x 1028 -> 3287, 260 tiles stored in 2-byte pieces, 20.4 / - / 21.8.  Multiples of eight, runs / bands:
 // fp8 7766 x 3928 -> 1893 73.2 / 67.6, 12000 x 4096 -> 4096 169.6 / 153.6 (int8 75.0, 174.4), but 64-token tiles 640 x 8192 ->
 // 4096 30.7 / 31.6.  (Bands of 4 and of 16 throughout: within 3 %, mostly slower.)
 constexpr int kBand = 8;
