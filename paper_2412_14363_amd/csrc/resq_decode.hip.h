@@ -133,17 +133,13 @@ __device__ __forceinline__ void stream_epilogue(const DecodeArgs& a, int tok, in
         const int64_t ch = n >> 1, ch_end = a.L.N >> 1;
         uint16_t* d2 = a.y + (int64_t)tok * a.ldy + ch;
         const uint32_t pair = pack_bf16(silu_f32(out[0]) * out[1], silu_f32(out[2]) * out[3]);
-        if (ch + 1 < ch_end && ((reinterpret_cast<uintptr_t>(a.y) & 3) == 0) && (a.ldy % 2 == 0)) {
-            *reinterpret_cast<uint32_t*>(d2) = pair;
-        } else {
-            if (ch < ch_end) d2[0] = (uint16_t)pair;
-            if (ch + 1 < ch_end) d2[1] = (uint16_t)(pair >> 16);
-        }
+        if (ch + 1 < ch_end) *reinterpret_cast<Piece4*>(d2) = Piece4{pair};
+        else if (ch < ch_end) d2[0] = (uint16_t)pair;
         return;
     }
     uint16_t* dst = a.y + (int64_t)tok * a.ldy + n;
-    if (n + 3 < a.L.N && ((reinterpret_cast<uintptr_t>(a.y) & 7) == 0) && (a.ldy % 4 == 0)) {
-        *reinterpret_cast<uint2*>(dst) = make_uint2(pack_bf16(out[0], out[1]), pack_bf16(out[2], out[3]));
+    if (n + 3 < a.L.N) {  // at any 2-byte aligned address, see store_piece
+        *reinterpret_cast<Piece8*>(dst) = Piece8{pack_bf16(out[0], out[1]), pack_bf16(out[2], out[3])};
     } else {
 #pragma unroll
         for (int v = 0; v < 4; ++v)

@@ -254,7 +254,7 @@ __device__ __forceinline__ void buffer_load_to_lds_16B(__amdgpu_buffer_rsrc_t rs
 // axis after the other, padding tiles among them / bands): fp8 3451 x 7552 -> 3328 at r = 1664 81.6 / 77.2 / 73.9 us
 // (int8 82.0), int8 7550 x 1088 -> 1065 34.9 / 36.4 / 32.6, 9000 x 2048 -> 5376 109.1 / - / 97.5, 64-token tiles
 // 700 x 8192 -> 3328 38.5 / 31.5 / 31.7, 3000 x 4096 -> 600 16.4 / 26.0 / 15.6; equal where stages are few: 5000 x 1024 -> 5376
-// 42.6 / 42.9 / 42.7; 1240 x 1028 -> 3287, 260 tiles stored in 2-byte pieces, 20.4 / - / 21.8.  Multiples of eight, runs / bands:
+// 42.6 / 42.9 / 42.7.  Multiples of eight, runs / bands:
 // fp8 7766 x 3928 -> 1893 73.2 / 67.6, 12000 x 4096 -> 4096 169.6 / 153.6 (int8 75.0, 174.4), but 64-token tiles 640 x 8192 ->
 // 4096 30.7 / 31.6.  (Bands of 4 and of 16 throughout: within 3 %, mostly slower.)
 constexpr int kBand = 8;
@@ -295,12 +295,31 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// Eight bf16 outputs at any 2-byte aligned address, of which `left` (any sign) lie in the row: rows whose
+// length or leading dimension is no multiple of eight start anywhere.  The hardware stores 16 bytes at any
+// address (unaligned access is on for every HSA queue, and the packed type makes the compiler rely on it, not on
+// an alignment that is not there), so only the piece that holds the end of a row goes element by element.
+// Stored in 2-byte pieces, 16 bytes apart from lane to lane, such outputs cost up to a third of the
+// whole call (quantizer and GEMM, us, before / now): 2025 x 1088 -> 10790 64.7 / 40.2, 3000 x 2048 -> 3001 49.2 / 37.8,
+// 1240 x 1028 -> 3287 25.4 / 18.6, 777 x 5000 -> 3001 asymmetric 31.3 / 28.4; rows of whole pieces are as fast as they were.
+struct __attribute__((packed, aligned(2))) Piece16 { uint32_t x, y, z, w; };
+struct __attribute__((packed, aligned(2))) Piece8 { uint32_t x, y; };
+struct __attribute__((packed, aligned(2))) Piece4 { uint32_t x; };
+__device__ __forceinline__ void store_piece(uint16_t* dst, const uint4& v, int64_t left) {
+    if (left >= 8) {
+        *reinterpret_cast<Piece16*>(dst) = Piece16{v.x, v.y, v.z, v.w};
+    } else if (left > 0) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (e < left) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+    }
+}
+
 // Write y once: the 128 x 128 bf16 tile sits in LDS; wave w stores rows 32 w .. 32 w + 31, four
 // whole 256-byte row segments per store instruction.
 __device__ __forceinline__ void store_tile(const GemmArgs& a, const uint8_t* lds, int wave, int lane, int64_t m0,
                                            int64_t n0) {
-    const bool fast = ((reinterpret_cast<uintptr_t>(a.y) & 15) == 0) && (a.ldy % 8 == 0) &&
-                      (n0 + kBN <= a.L.N);
     if (a.swiglu) {
         // 64 outputs per row: eight 128-byte row segments per store instruction
         const int64_t n_out = a.L.N / 2;
@@ -311,14 +330,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const uint8_t* lds
             const int64_t n = n0 / 2 + (lane & 7) * 8;
             const uint4 v = *reinterpret_cast<const uint4*>(lds + row * kOutRowBytes + (lane & 7) * 16);
             if (m >= a.M) continue;
-            if (fast) {
-                *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
-            } else {
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (n + e < n_out) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-            }
+            store_piece(a.y + m * a.ldy + n, v, n_out - n);
         }
         return;
     }
@@ -329,14 +341,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& a, const uint8_t* lds
         const int64_t n = n0 + (lane & 15) * 8;
         const uint4 v = *reinterpret_cast<const uint4*>(lds + row * kOutRowBytes + (lane & 15) * 16);
         if (m >= a.M) continue;
-        if (fast) {
-            *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (n + e < a.L.N) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-        }
+        store_piece(a.y + m * a.ldy + n, v, a.L.N - n);
     }
 }
 

@@ -526,8 +526,6 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
     // ---- write y once: each wavefront of the workgroup stores 16 / KS rows of the staged tile ----
     constexpr int kRowsPerWave = 16 / KS;
     __syncthreads();
-    const bool fast = ((reinterpret_cast<uintptr_t>(a.y) & 15) == 0) && (a.ldy % 8 == 0) &&
-                      (n0 + kBN <= a.L.N);
     if (a.swiglu) {
         const int64_t n_out = a.L.N / 2;
 #pragma unroll
@@ -537,14 +535,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
             const int64_t n = n0 / 2 + (lane & 7) * 8;
             const uint4 v = *reinterpret_cast<const uint4*>(staged + row * kOutRowBytes + (lane & 7) * 16);
             if (m >= a.M) continue;
-            if (fast) {
-                *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
-            } else {
-                const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (n + e < n_out) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-            }
+            store_piece(a.y + m * a.ldy + n, v, n_out - n);
         }
         return;
     }
@@ -555,14 +546,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
         const int64_t n = n0 + (lane & 15) * 8;
         const uint4 v = *reinterpret_cast<const uint4*>(staged + row * kOutRowBytes + (lane & 15) * 16);
         if (m >= a.M) continue;
-        if (fast) {
-            *reinterpret_cast<uint4*>(a.y + m * a.ldy + n) = v;
-        } else {
-            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                if (n + e < a.L.N) a.y[m * a.ldy + n + e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
-        }
+        store_piece(a.y + m * a.ldy + n, v, a.L.N - n);
     }
 }
 

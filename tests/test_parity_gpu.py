@@ -408,6 +408,28 @@ def test_layer_tile_order(oracle, rq, M, K, N, r, kernel, tiles):
     check_layer(oracle, rq, x, w, r, ldy_extra=8 if N % 4 == 0 else 3)
 
 
+@pytest.mark.parametrize("M,K,N,r,kernel", [
+    (3, 512, 21, 64, 0), (16, 512, 130, 64, 0), (40, 512, 150, 64, 1), (1025, 512, 2049, 64, 3), (700, 512, 3300, 64, 3),
+    (1100, 512, 8190, 64, 2), (300, 512, 4094, 0, 3), (8200, 3072, 998, 0, 2)])
+def test_layer_output_rows_at_any_address(rq, M, K, N, r, kernel):
+    """Outputs whose rows start at any 2-byte aligned address, rows of any length: the values of a call on rows of
+    whole 16-byte pieces (which other tests hold against the oracle), and not a byte beside them."""
+    assert rq.resq_gemm_mixed_plan(M, N, K, r)[0] == kernel
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    x = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    packed = rq.resq_pack_weights((torch.randn(N, K, generator=g, device="cuda") * 0.02).bfloat16(), r)
+    act = rq.resq_quantize_act(x, r)
+    calls = [(rq.resq_gemm_mixed, N)] + ([(rq.resq_gemm_mixed_swiglu, N // 2)] if N % 2 == 0 else [])
+    for call, width in calls:
+        want = call(act, packed, N, y=torch.zeros((M, (width + 15) // 8 * 8), dtype=torch.bfloat16, device="cuda")[:, :width])
+        for offset, ld in ((1, width), (0, width + 1), (5, width + 3), (2, width + 4)):
+            buf = torch.full((offset + M * ld + 16,), 77.0, dtype=torch.bfloat16, device="cuda")
+            expect = buf.clone()
+            torch.as_strided(expect, (M, width), (ld, 1), offset).copy_(want)
+            call(act, packed, N, y=torch.as_strided(buf, (M, width), (ld, 1), offset))
+            assert torch.equal(buf, expect), (call.__name__, offset, ld)
+
+
 @pytest.mark.parametrize("M,K,N,r", [
     (385, 2048, 400, 256), (512, 4096, 272, 512), (1000, 1000, 515, 104), (1024, 3200, 256, 448),
     (700, 256, 256, 0), (640, 256, 64, 256), (1024, 14336, 144, 1792),
