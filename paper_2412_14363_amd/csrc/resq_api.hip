@@ -201,6 +201,25 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else                                                                                        \
             launch(quantize_act_vec_kernel<ITERS, false, false, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo); \
     } while (0)
+#define RESQ_LAUNCH_RAGGED(ITERS, RT)                                                               \
+    do {                                                                                            \
+        if (asym)                                                                                   \
+            launch(quantize_act_vec_kernel<ITERS, false, true, RT, true>, grid, dim3(RT), 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo);  \
+        else                                                                                        \
+            launch(quantize_act_vec_kernel<ITERS, false, false, RT, true>, grid, dim3(RT), 0, st, RESQ_QA_ARGS, rot, c_hi, c_lo); \
+    } while (0)
+    // Rows without whole 16-byte pieces: units of eight columns from each group's first column on (element-wise kernel /
+    // 256 threads / 1024 threads, us, launches in a row, 3.4 of them the launch): 4096 rows of 2050 columns 15.7 / 10.6 / 23.5,
+    // of 8190 47.7 / 20.0 / 29.3, 1024 of 4098 9.2 / 5.5 / 7.6, of 16378 25.9 / 14.7 / 14.4, 16 of 28674 10.9 / - / 6.7.
+    // 1024 threads up to one row per compute unit beyond 3072 columns (256 x 4098 4.26 / 4.45 / 3.71, 256 x 14338 7.8 / 7.9 / 5.5)
+    // and up to two beyond 8192 (512 x 10242 10.0 / 7.4 / 6.6, 520 rows 13.7 / 7.6 / 8.0; asymmetric beyond 12288:
+    // 512 x 14338 14.0 / 10.4 / 9.2, of 8706 9.8 / 7.0 / 7.2).  Element-wise where a row per compute unit gives each
+    // thread a few columns: 16 x 514 3.62 / 3.62 / 3.70, 256 x 2050 3.68 / 4.10 / 3.86 (x 1538 3.97 / 3.62, x 3586 4.00 / 4.20 / 3.88).
+    const int64_t units = (r + 7) / 8 + (lo_cols + 7) / 8;
+    const int64_t few_ragged = K > 8192 && (!asym || K > 12288) ? 512 : K > 3072 ? 256 : 0;
+    const bool few_columns = M <= 256 && (K <= 1024 || (K > 2048 && K <= 3072));
+    const bool ragged = !pieces && !rotate && !few_columns && (r == 0 || r >= 8) && (lo_cols == 0 || lo_cols >= 8) &&
+                        units <= 4096;
     if (vec && K <= 512 && !rotate) {
         // short rows (an attention head of a K/V cache entry): 16, 32 or 64 lanes per row
 #define RESQ_LAUNCH_SHORT(G)                                                                       \
@@ -228,10 +247,18 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
         else if (K <= 4096) RESQ_LAUNCH_QA(2);
         else if (K <= 8192) RESQ_LAUNCH_QA(4);
         else RESQ_LAUNCH_QA(8);
+    } else if (ragged) {
+        if (M <= few_ragged || units > 2048) {
+            if (units <= 1024) RESQ_LAUNCH_RAGGED(1, kQuantWideThreads);
+            else if (units <= 2048) RESQ_LAUNCH_RAGGED(2, kQuantWideThreads);
+            else RESQ_LAUNCH_RAGGED(4, kQuantWideThreads);
+        } else if (units <= 256) RESQ_LAUNCH_RAGGED(1, kQuantThreads);
+        else if (units <= 512) RESQ_LAUNCH_RAGGED(2, kQuantThreads);
+        else if (units <= 1024) RESQ_LAUNCH_RAGGED(4, kQuantThreads);
+        else RESQ_LAUNCH_RAGGED(8, kQuantThreads);
     } else if (M <= (K > 8192 ? 1024 : K > 4096 ? 512 : K > 2048 ? 256 : 0)) {
-        // few long rows without whole 16-byte pieces (256 / 1024 threads, us): 256 rows of 2050 columns
-        // 4.48 / 4.12, 512 of 5002 8.48 / 6.52, 1024 of 9186 21.4 / 17.4, 16 of 28674 29.6 / 10.6; not below or
-        // above (1002 columns equal, 512 of 2050 equal, 4096 of 9186 53.4 / 59.0)
+        // few rows for the element-wise kernel (256 / 1024 threads, us): 256 of 2050 columns 4.48 / 4.12, 16 of 28674
+        // 29.6 / 10.6; not below or above (1002 columns equal, 512 of 2050 equal, 4096 of 9186 53.4 / 59.0)
         if (asym) launch(quantize_act_generic_kernel<true, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, c_hi, c_lo);
         else launch(quantize_act_generic_kernel<false, kQuantWideThreads>, grid, wide, 0, st, RESQ_QA_ARGS, c_hi, c_lo);
     } else if (asym) {
@@ -241,6 +268,7 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
     }
 #undef RESQ_LAUNCH_QA
 #undef RESQ_LAUNCH_QA_WIDE
+#undef RESQ_LAUNCH_RAGGED
 #undef RESQ_QA_ARGS
     return launch_status();
 }

@@ -244,9 +244,48 @@ struct RotateArgs {
     int64_t ld_rot;
 };
 
+// Sixteen bytes at any 2-byte aligned address (every HSA queue runs with unaligned access on, and the packed type
+// makes the compiler rely on that, not on an alignment that is not there).
+struct __attribute__((packed, aligned(2))) Unaligned16 { uint32_t x, y, z, w; };
+__device__ __forceinline__ uint4 load16_any(const uint16_t* p) {
+    const Unaligned16 v = *reinterpret_cast<const Unaligned16*>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+// the eight 16-bit elements of v turned round so that element n comes first, 0 < n < 8
+__device__ __forceinline__ uint4 rotate_elements(const uint4& v, int n) {
+    uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
+    if (n & 4) {
+        const uint64_t s = lo;
+        lo = hi;
+        hi = s;
+    }
+    const int b = 16 * (n & 3);
+    if (b) {
+        const uint64_t l = lo >> b | hi << (64 - b);
+        hi = hi >> b | lo << (64 - b);
+        lo = l;
+    }
+    return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+}
+// The stored values of elements cnt .. 7 of a unit become those of padding codes, and leave the sum of odd ones.
+template <bool LOW>
+__device__ __forceinline__ void pad_codes(uint32_t (&u)[8], int cnt, float& odd_sum) {
+#pragma unroll
+    for (int j = 1; j < 8; ++j) {
+        if (j < cnt) continue;
+        if (LOW && (j & 1)) odd_sum -= (float)((int)(u[j] << 28) >> 28);
+        u[j] = LOW && !(j & 1) ? 8u : 0u;
+    }
+}
+
 // ASYM: the asymmetric quantizer; c_hi / c_lo [M] receive z + 2^(N-1) s, the real
 // value that the stored code 0 stands for (what the GEMM's epilogue needs).
-template <int ITERS, bool ROTATE, bool ASYM, int RT = kQuantThreads>
+// RAGGED: any K, r (K - r even; a group has no column or at least eight) and 2-byte alignment: each group is
+// cut into units of eight columns from its own first one, and a group's last unit, if it is short, is read as the
+// group's last eight columns (the maxima do not mind columns that are seen twice) and turned round.
+// Such rows took the element-wise kernel, two passes with 2-byte loads: 4096 x 9186 at r = 1150, whole layer with N = 256,
+// 85.4 us, 45.3 here (the figures of the kernel alone stand at the dispatch).
+template <int ITERS, bool ROTATE, bool ASYM, int RT = kQuantThreads, bool RAGGED = false>
 __global__ __launch_bounds__(RT) void quantize_act_vec_kernel(
     const uint16_t* __restrict__ x, int64_t ldx, int K, int r, int8_t* __restrict__ q_hi,
     int64_t ld_hi, uint8_t* __restrict__ q_lo, int64_t ld_lo, float* __restrict__ s_hi,
@@ -257,15 +296,23 @@ __global__ __launch_bounds__(RT) void quantize_act_vec_kernel(
     __shared__ int red_sum[W];
     const int t = threadIdx.x;
     const int64_t m = blockIdx.x;
-    const int nunits = K >> 3;
-    const int hi_units = r >> 3;
+    static_assert(!(RAGGED && ROTATE), "the transform needs whole blocks");
+    const int hi_units = RAGGED ? (r + 7) >> 3 : r >> 3;
+    const int nunits = RAGGED ? hi_units + ((K - r + 7) >> 3) : K >> 3;
     const uint4* row = reinterpret_cast<const uint4*>(x + m * ldx);
+    // columns that unit u is short of (RAGGED)
+    auto missing = [&](int u) { return u < hi_units ? max(8 * u + 8 - r, 0) : max(8 * (u - hi_units) + 8 - (K - r), 0); };
 
     uint4 v[ITERS];
 #pragma unroll
     for (int i = 0; i < ITERS; ++i) {
         const int u = t + i * RT;
-        v[i] = u < nunits ? row[u] : make_uint4(0u, 0u, 0u, 0u);
+        if constexpr (RAGGED) {
+            const int col = (u < hi_units ? 8 * u : r + 8 * (u - hi_units)) - missing(u);
+            v[i] = u < nunits ? load16_any(x + m * ldx + col) : make_uint4(0u, 0u, 0u, 0u);
+        } else {
+            v[i] = u < nunits ? row[u] : make_uint4(0u, 0u, 0u, 0u);
+        }
     }
     if constexpr (ROTATE) {
         // The same butterflies, in the same order, as the stand-alone transform
@@ -323,7 +370,16 @@ __global__ __launch_bounds__(RT) void quantize_act_vec_kernel(
         for (int i = 0; i < ITERS; ++i) {
             const int u = t + i * RT;
             if (u < nunits) {
-                const float a = absmax8(v[i]);
+                float a;
+                if constexpr (RAGGED) {
+                    // a NaN is passed over, as the element-wise kernel does
+                    float f[8];
+                    unpack8_bf16(v[i], f);
+                    a = fmaxf(fmaxf(fmaxf(fabsf(f[0]), fabsf(f[1])), fmaxf(fabsf(f[2]), fabsf(f[3]))),
+                              fmaxf(fmaxf(fabsf(f[4]), fabsf(f[5])), fmaxf(fabsf(f[6]), fabsf(f[7]))));
+                } else {
+                    a = absmax8(v[i]);
+                }
                 if (u < hi_units) amax_h = fmaxf(amax_h, a);
                 else amax_l = fmaxf(amax_l, a);
             }
@@ -346,14 +402,18 @@ __global__ __launch_bounds__(RT) void quantize_act_vec_kernel(
         const int u = t + i * RT;
         if (u < nunits) {
             uint32_t c[8];
+            const int miss = RAGGED ? missing(u) : 0;
+            if (RAGGED && miss > 0) v[i] = rotate_elements(v[i], miss);
             if (u < hi_units) {
                 if constexpr (ASYM) quant8_asym<false>(v[i], zh, sh, inv_h, c, odd_f);
                 else quant8<false>(v[i], sh, inv_h, c, odd_f);
+                if (RAGGED && miss > 0) pad_codes<false>(c, 8 - miss, odd_f);
                 *reinterpret_cast<uint2*>(qh + (int64_t)u * 8) =
                     make_uint2(pack_low_bytes(c[0], c[1], c[2], c[3]), pack_low_bytes(c[4], c[5], c[6], c[7]));
             } else {
                 if constexpr (ASYM) quant8_asym<true>(v[i], zl, sl, inv_l, c, odd_f);
                 else quant8<true>(v[i], sl, inv_l, c, odd_f);
+                if (RAGGED && miss > 0) pad_codes<true>(c, 8 - miss, odd_f);
                 // byte k = (even code + 8) | (odd code << 4); the even value is 1..15 in
                 // its low byte already, and only the low byte of by[k] is kept
                 uint32_t by[4];
@@ -366,9 +426,9 @@ __global__ __launch_bounds__(RT) void quantize_act_vec_kernel(
     }
     int odd_sum = (int)odd_f;
     // zero codes in the padding of both rows
-    for (int64_t b = (int64_t)r + 8 * t; b < ld_hi; b += 8 * RT)
+    for (int64_t b = 8 * (int64_t)(hi_units + t); b < ld_hi; b += 8 * RT)
         *reinterpret_cast<uint2*>(qh + b) = make_uint2(0u, 0u);
-    for (int64_t b = (int64_t)(K - r) / 2 + 4 * t; b < ld_lo; b += 4 * RT)
+    for (int64_t b = 4 * (int64_t)(nunits - hi_units + t); b < ld_lo; b += 4 * RT)
         *reinterpret_cast<uint32_t*>(ql + b) = 0x08080808u;
     odd_sum = block_sum<W>(odd_sum, red_sum);
     if (t == 0 && K - r > 0) lo_sum[m] = odd_sum;
@@ -812,8 +872,8 @@ __global__ __launch_bounds__(kQuantThreads) void dequantize_kv_cache_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Activations, any K, r (K - r even) and alignment: two passes over the row
-// with 2-byte loads.  Correct everywhere, fast nowhere.
+// Activations, any K, r (K - r even) and alignment: two passes over the row with 2-byte loads.  For groups of one to
+// seven columns, rows beyond 32768 columns, and the few short rows that the dispatch names.
 // ---------------------------------------------------------------------------
 template <bool ASYM, int RT = kQuantThreads>
 __global__ __launch_bounds__(RT) void quantize_act_generic_kernel(

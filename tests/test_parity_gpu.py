@@ -121,6 +121,48 @@ def test_quantize_act_generic_path(oracle, rq, M, K, r):
     check_act_codes(oracle, rq, wl.make_activations(s), r)
 
 
+# Rows without whole 16-byte pieces: short last units of both groups, groups of exactly one unit and of one unit and a
+# bit, units at the edges of what a thread holds (256, 512, 1024, 2048 and 4096 of them), 256 and 1024 threads
+@pytest.mark.parametrize("M,K,r", [
+    (3, 2042, 250), (257, 35, 17), (257, 16, 8), (257, 18, 8), (300, 25, 9), (260, 57, 57), (3, 1100, 0), (3, 1101, 1101), (3, 2048, 12),
+    (3, 2051, 11), (257, 1024, 12), (256, 1022, 12), (256, 2050, 258), (257, 2050, 258), (256, 3072, 12), (256, 3074, 12),
+    (300, 4090, 8), (300, 4098, 1022), (513, 8190, 14), (513, 8193, 1023), (2, 8190, 14), (2, 8193, 1023), (2, 16382, 4),
+    (600, 16382, 2046), (600, 16386, 2046), (512, 12290, 1538), (513, 12290, 1538), (2, 16386, 2046), (3, 32766, 4094), (3, 32770, 4094)])
+@pytest.mark.parametrize("asym", [False, True])
+def test_quantize_act_rows_at_any_address(oracle, rq, M, K, r, asym):
+    s = wl.LayerShape("qr", M=M, K=K, N=1, r=r, act="student_t3", seed=K + r)
+    x = wl.make_activations(s)
+    for offset, ld in ((0, K), (1, K + 1), (3, K + 5), (6, (K + 7) // 8 * 8)):
+        buf = torch.full((offset + M * ld + 8,), float("inf"), dtype=torch.bfloat16, device="cuda")  # beside the rows
+        rows = torch.as_strided(buf, (M, K), (ld, 1), offset)
+        rows.copy_(x)
+        act = (rq.resq_quantize_act_asym if asym else rq.resq_quantize_act)(rows, r)
+        torch.cuda.synchronize()
+        (compare_asym_codes if asym else compare_act_codes)(oracle, act, wl.bf16_bits(x), r)
+
+
+def test_quantize_act_rows_at_any_address_not_finite(rq):
+    """Infinities and NaN in rows without whole pieces: what the element-wise definition gives (a NaN does not count
+    for the maximum; quotients that are NaN clip to the lowest code)."""
+    K, r = 2050, 258
+    x = torch.randn(260, K, generator=torch.Generator().manual_seed(5)).bfloat16()
+    x[0, 3], x[0, 400], x[1, K - 1], x[2, 0], x[2, K - 2], x[3, r] = (float(v) for v in ("nan", "nan", "inf", "-inf", "nan", "-inf"))
+    act = rq.resq_quantize_act(x.cuda(), r)
+    v = x.float()
+    for g, (lo, hi, qmax) in enumerate(((0, r, 127), (r, K, 7))):
+        amax = torch.nan_to_num(v[:, lo:hi].abs(), nan=0.0, posinf=float("inf")).amax(1, keepdim=True)
+        scale = amax / qmax
+        want = torch.nan_to_num(torch.round(v[:, lo:hi] / scale), nan=-qmax).clamp(-qmax, qmax).int()
+        assert torch.equal((act.s_hi if g == 0 else act.s_lo).cpu(), scale[:, 0])
+        if g == 0:
+            assert torch.equal(act.q_hi.cpu()[:, :r].int(), want)
+        else:
+            byte = act.q_lo.cpu()[:, :(K - r) // 2].int()
+            got = torch.stack([(byte & 15) - 8, ((byte >> 4) ^ 8) - 8], 2).reshape(len(x), K - r)
+            assert torch.equal(got, want)
+            assert torch.equal(act.lo_sum.cpu().long(), want[:, 1::2].sum(1))
+
+
 # both sides of each line between 256 and 1024 threads to a row, and rows that end inside a wavefront
 @pytest.mark.parametrize("M,K,r", [(256, 4104, 520), (257, 4104, 520), (2, 4096, 512), (3, 8192, 1024), (2, 8200, 1032),
                                    (512, 8200, 1032), (513, 8200, 1032), (256, 8200, 1032), (257, 16384, 2048), (1, 16384, 0), (2, 12296, 12296),
