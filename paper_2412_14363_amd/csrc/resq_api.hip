@@ -702,10 +702,11 @@ static int gemm_mixed_impl(const int8_t* q_hi, const uint8_t* q_lo, const float*
     const bool f8 = !narrow && use_f8(M, L);
     // the order of the tiles (see tile_of_block)
     a.bands = 0;
-    if ((int64_t)a.tiles_m * a.tiles_n % 8 != 0 || (f8 && !whole_patches(a.tiles_m, a.tiles_n))) {
+    const int own_n = (int)((N + kBN - 1) / kBN);
+    if ((int64_t)a.tiles_m * a.tiles_n % 8 != 0 || ((f8 || own_n != a.tiles_n) && !whole_patches(a.tiles_m, a.tiles_n))) {
         const int n = (a.tiles_m + kBand - 1) / kBand;
         a.bands = (a.tiles_m + n - 1) / n;
-        a.tiles_n = (int)((N + kBN - 1) / kBN);
+        a.tiles_n = own_n;
     }
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > 0x7FFFFFFF) return RESQ_ERR_SHAPE;

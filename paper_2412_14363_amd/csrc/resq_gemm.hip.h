@@ -246,7 +246,8 @@ __device__ __forceinline__ void buffer_load_to_lds_16B(__amdgpu_buffer_rsrc_t rs
 // tokens x 1024 channels), so that each activation stage and each weight stage
 // is fetched into that L2 once per 8 tiles; the 8 XCDs take neighbouring patches.
 // Other grids of a multiple of eight tiles: each XCD takes a run of consecutive tiles of its own, down
-// the token axis first.  The rest, and all that are no patches with the low group in fp8 (a.bands > 0): such runs too, the
+// the token axis first.  The rest, and of those that are no patches also the ones with a column of padding tiles and all with
+// the low group in fp8 (a.bands > 0): such runs too, the
 // first total % 8 of them one longer, through bands of at most eight token tiles, as equal as they get, channel by channel
 // inside a band, so that what an XCD works on together is close to a patch there as well; and of the layer's own
 // tiles only, since padding tiles (N is padded to two) would fall to the last XCDs and leave the others more to do.
@@ -256,7 +257,8 @@ __device__ __forceinline__ void buffer_load_to_lds_16B(__amdgpu_buffer_rsrc_t rs
 // 700 x 8192 -> 3328 38.5 / 31.5 / 31.7, 3000 x 4096 -> 600 16.4 / 26.0 / 15.6; equal where stages are few: 5000 x 1024 -> 5376
 // 42.6 / 42.9 / 42.7.  Multiples of eight, runs / bands:
 // fp8 7766 x 3928 -> 1893 73.2 / 67.6, 12000 x 4096 -> 4096 169.6 / 153.6 (int8 75.0, 174.4), but 64-token tiles 640 x 8192 ->
-// 4096 30.7 / 31.6.  (Bands of 4 and of 16 throughout: within 3 %, mostly slower.)
+// 4096 30.7 / 31.6.  A column of padding tiles in a multiple of eight, runs with it / bands without, whole calls: 2500 x 2048 ->
+// 3200, 520 tiles of which 500 are its own, 35.4 / 27.9, 8192 x 1024 -> 640 29.0 / 27.6; 14 of 18 such shapes equal.  (Bands of 4 and of 16 throughout: within 3 %, mostly slower.)
 constexpr int kBand = 8;
 __host__ __device__ inline bool whole_patches(int tiles_m, int tiles_n) {
     return tiles_m % 8 == 0 && tiles_n % 8 == 0 && (int64_t)tiles_m * tiles_n % 512 == 0;

@@ -442,6 +442,8 @@ def test_layer_tiled_kernel_fp8_low_group_largest_sums(rq, low, f8):
     (1025, 512, 2050, 64, 3, 306), (577, 512, 3300, 64, 3, 260), (700, 512, 3300, 64, 3, 286),
     (1537, 512, 3300, 64, 2, 338), (1700, 512, 2562, 64, 2, 308), (1793, 512, 2300, 64, 2, 270),
     (1025, 512, 256, 64, 3, 34), (1100, 512, 100, 64, 3, 36), (1153, 512, 300, 64, 3, 76), (1537, 512, 2562, 0, 2, 286), (7550, 256, 1065, 32, 2, 590),
+    # a column of padding tiles in a multiple of eight: left out as well
+    (512, 512, 3200, 64, 3, 208), (1537, 512, 3967, 64, 2, 416), (2500, 512, 3200, 64, 2, 520), (5100, 256, 129, 32, 3, 160),
 ])
 def test_layer_tile_order(oracle, rq, M, K, N, r, kernel, tiles):
     assert rq.resq_gemm_mixed_plan(M, N, K, r)[0] == kernel
