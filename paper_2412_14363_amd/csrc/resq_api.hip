@@ -562,13 +562,14 @@ static DecodeArgs make_decode_args(const int8_t* q_hi, const uint8_t* q_lo, cons
     d.lds_row = (int)lds_row;
     d.x = nullptr;
     d.ldx = 0;
-    d.fuse_rows = 1;
+    d.log2_rows = 0;
     return d;
 }
 
-// The weight-streaming kernels for at most 16 tokens whose code rows fit LDS.  fused: the
-// kernels quantize d.x themselves instead of reading codes.
-static int launch_decode(const DecodeArgs& d, bool dbg, bool fused, hipStream_t st) {
+// The weight-streaming kernels for at most 16 tokens whose code rows fit LDS.  act: where the codes come from
+// (kActDirect: they are read; else the kernels quantize d.x themselves).
+static int launch_decode(const DecodeArgs& d, bool dbg, int act, hipStream_t st) {
+    const bool fused = act != kActDirect;
     const WeightLayout& L = d.L;
     const int sk = decode_runs(L);
     // the code rows go through LDS only when the kernel makes them itself
@@ -590,7 +591,9 @@ static int launch_decode(const DecodeArgs& d, bool dbg, bool fused, hipStream_t 
         const dim3 grid((unsigned)(sets < 256 ? sets : 256));
 #define RESQ_LAUNCH_SPLITK(SK)                                                                     \
     do {                                                                                           \
-        if (fused) RESQ_LAUNCH_DECODE((gemm_decode_splitk_kernel<false, SK, kActQuantize>), grid);  \
+        if (act == 4) RESQ_LAUNCH_DECODE((gemm_decode_splitk_kernel<false, SK, 4>), grid); \
+        else if (act == 8) RESQ_LAUNCH_DECODE((gemm_decode_splitk_kernel<false, SK, 8>), grid); \
+        else if (fused) RESQ_LAUNCH_DECODE((gemm_decode_splitk_kernel<false, SK, kFusedUnits>), grid);  \
         else if (dbg) RESQ_LAUNCH_DECODE((gemm_decode_splitk_kernel<true, SK, kActDirect>), grid);  \
         else RESQ_LAUNCH_DECODE((gemm_decode_splitk_kernel<false, SK, kActDirect>), grid);          \
     } while (0)
@@ -603,7 +606,9 @@ static int launch_decode(const DecodeArgs& d, bool dbg, bool fused, hipStream_t 
     lds_bytes += extra;
     // one workgroup per compute unit (256 of them), fewer when there is less work
     const dim3 grid((unsigned)(d.groups < 256 ? d.groups : 256));
-    if (fused) RESQ_LAUNCH_DECODE((gemm_decode_kernel<false, kActQuantize>), grid);
+    if (act == 4) RESQ_LAUNCH_DECODE((gemm_decode_kernel<false, 4>), grid);
+    else if (act == 8) RESQ_LAUNCH_DECODE((gemm_decode_kernel<false, 8>), grid);
+    else if (fused) RESQ_LAUNCH_DECODE((gemm_decode_kernel<false, kFusedUnits>), grid);
     else if (dbg) RESQ_LAUNCH_DECODE((gemm_decode_kernel<true, kActDirect>), grid);
     else RESQ_LAUNCH_DECODE((gemm_decode_kernel<false, kActDirect>), grid);
 #undef RESQ_LAUNCH_DECODE
@@ -640,7 +645,7 @@ static int gemm_mixed_impl(const int8_t* q_hi, const uint8_t* q_lo, const float*
         const int64_t lds_row = L.kh_pad + L.kl_pad / 2 + kDecodeRowPad;
         const DecodeArgs d = make_decode_args(q_hi, q_lo, s_hi, s_lo, c_hi, c_lo, lo_sum, M, packed, L, y, ldy,
                                               dbg_acc_hi, dbg_acc_lo, swiglu, lds_row);
-        return launch_decode(d, dbg, false, st);
+        return launch_decode(d, dbg, kActDirect, st);
     }
     if (plan.kernel == 1) {
         const int tg = plan.tg, sk = plan.sk;
@@ -755,10 +760,14 @@ int resq_quantize_gemm_mixed(const void* x, int64_t ldx, int64_t M, const void* 
     // rows quantized at a time, each by 512 / R threads holding at most kFusedUnits 16-byte units
     const int64_t nunits = K / 8;
     if (nunits > (int64_t)kFusedUnits * kDecodeThreads) return RESQ_ERR_SHAPE;
-    int R = 1;
-    while (R < 8 && R < M && nunits * (2 * R) <= (int64_t)kFusedUnits * kDecodeThreads) R *= 2;
-    d.fuse_rows = R;
-    return launch_decode(d, false, true, static_cast<hipStream_t>(stream));
+    int log2_rows = 0;
+    while (log2_rows < 3 && (1 << log2_rows) < M && (nunits << (log2_rows + 1)) <= (int64_t)kFusedUnits * kDecodeThreads) ++log2_rows;
+    d.log2_rows = log2_rows;
+    // all rows in one batch and at most 4 or 8 units a thread: kernels of their own (figures at fill_act_quantize)
+    const bool one = M <= (1 << log2_rows);
+    const int64_t held = nunits << log2_rows;
+    return launch_decode(d, false, one && held <= 4 * kDecodeThreads ? 4 : one && held <= 8 * kDecodeThreads ? 8 : kFusedUnits,
+                         static_cast<hipStream_t>(stream));
 }
 
 int resq_gemm_mixed_plan(int64_t M, int64_t N, int64_t K, int64_t r, int* kernel, int* token_groups,

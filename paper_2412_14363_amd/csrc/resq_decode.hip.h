@@ -52,10 +52,10 @@ struct DecodeArgs {
     // q_hi .. lo_sum above are not read then
     const uint16_t* x;
     int64_t ldx;
-    int fuse_rows;    // rows quantized at a time: 1, 2, 4 or 8
+    int log2_rows;    // rows quantized at a time: 1, 2, 4 or 8
 };
 
-constexpr int kFusedScratchFloats = 3 * 16 + 8 * 3;  // LDS beside the token rows, see fill_act_quantize
+constexpr int kFusedScratchFloats = 3 * 16 + 2 * 2 * 8;  // LDS beside the token rows, see fill_act_quantize
 
 // Epilogue of the weight-streaming kernels for one lane: token `tok`, channels
 // n .. n + 3, the two integer sums of each.  Dequantizes (Eq. 4), adds the
@@ -73,12 +73,36 @@ struct EpilogueConsts {
     int ev[4];
     int wsh[4], wsl[4];  // asymmetric activation codes only
 };
+// the channels' part as it lies in memory (asked for early, taken apart where it is needed)
+struct ChannelConsts {
+    uint2 sw_hi, sw_lo;
+    int4 even;
+};
+__device__ __forceinline__ ChannelConsts load_channel_consts(const DecodeArgs& a, int64_t n) {
+    const uint8_t* at = a.packed + a.L.scale_off;
+    ChannelConsts h;
+    h.sw_hi = *reinterpret_cast<const uint2*>(at + 2 * n);
+    h.sw_lo = *reinterpret_cast<const uint2*>(at + 2 * (a.L.n_pad + n));
+    h.even = *reinterpret_cast<const int4*>(at + 4 * (a.L.n_pad + n));
+    return h;
+}
+__device__ __forceinline__ void take_channel_consts(EpilogueConsts& c, const ChannelConsts& h) {
+    c.snh[0] = fp16_bits_to_f32(h.sw_hi.x & 0xFFFFu);
+    c.snh[1] = fp16_bits_to_f32(h.sw_hi.x >> 16);
+    c.snh[2] = fp16_bits_to_f32(h.sw_hi.y & 0xFFFFu);
+    c.snh[3] = fp16_bits_to_f32(h.sw_hi.y >> 16);
+    c.snl[0] = fp16_bits_to_f32(h.sw_lo.x & 0xFFFFu);
+    c.snl[1] = fp16_bits_to_f32(h.sw_lo.x >> 16);
+    c.snl[2] = fp16_bits_to_f32(h.sw_lo.y & 0xFFFFu);
+    c.snl[3] = fp16_bits_to_f32(h.sw_lo.y >> 16);
+    c.ev[0] = h.even.x;
+    c.ev[1] = h.even.y;
+    c.ev[2] = h.even.z;
+    c.ev[3] = h.even.w;
+}
 __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
-    const uint16_t* sw_hi = reinterpret_cast<const uint16_t*>(a.packed + a.L.scale_off);
-    const uint16_t* sw_lo = sw_hi + a.L.n_pad;
-    const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
-    const int32_t* wsum_hi = even_sum + a.L.n_pad;
-    const int32_t* wsum_lo = even_sum + 2 * a.L.n_pad;
+    const int32_t* wsum_hi = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 8 * a.L.n_pad);
+    const int32_t* wsum_lo = wsum_hi + a.L.n_pad;
     const bool has_hi = a.L.r > 0, has_lo = a.L.K - a.L.r > 0;
     const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
     EpilogueConsts c;
@@ -87,27 +111,18 @@ __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs&
     c.ca = has_lo ? a.lo_sum[tok] : 0;
     c.cth = (asym && has_hi) ? a.c_hi[tok] : 0.f;
     c.ctl = (asym && has_lo) ? a.c_lo[tok] : 0.f;
-    const uint2 sch = *reinterpret_cast<const uint2*>(sw_hi + n);
-    const uint2 scl = *reinterpret_cast<const uint2*>(sw_lo + n);
-    const int4 es = *reinterpret_cast<const int4*>(even_sum + n);
-    c.snh[0] = fp16_bits_to_f32(sch.x & 0xFFFFu);
-    c.snh[1] = fp16_bits_to_f32(sch.x >> 16);
-    c.snh[2] = fp16_bits_to_f32(sch.y & 0xFFFFu);
-    c.snh[3] = fp16_bits_to_f32(sch.y >> 16);
-    c.snl[0] = fp16_bits_to_f32(scl.x & 0xFFFFu);
-    c.snl[1] = fp16_bits_to_f32(scl.x >> 16);
-    c.snl[2] = fp16_bits_to_f32(scl.y & 0xFFFFu);
-    c.snl[3] = fp16_bits_to_f32(scl.y >> 16);
-    c.ev[0] = es.x;
-    c.ev[1] = es.y;
-    c.ev[2] = es.z;
-    c.ev[3] = es.w;
+    take_channel_consts(c, load_channel_consts(a, n));
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         c.wsh[v] = asym ? wsum_hi[n + v] : 0;
         c.wsl[v] = asym ? wsum_lo[n + v] : 0;
     }
     return c;
+}
+
+// barrier of the workgroup for what lies in LDS: loads from memory stay in flight
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 template <bool DBG>
@@ -157,56 +172,81 @@ __device__ __forceinline__ void stream_epilogue(const DecodeArgs& a, int tok, in
 // every workgroup can afford to redo it, which saves a kernel launch in front of the
 // weight stream.  The arithmetic is the quantizer kernel's (absmax8, group_scale,
 // quant8), so the codes, scales and sums are the ones resq_quantize_act would have
-// written.  R = a.fuse_rows (1, 2, 4 or 8) rows are in flight at a time, each with a team
-// of 512 / R threads that holds the whole row in registers (at most kFusedUnits 16-byte
+// written.  R = 2^a.log2_rows (1, 2, 4 or 8) rows are in flight at a time, each with a team
+// of 512 / R threads that holds the whole row in registers (at most U 16-byte
 // loads per thread, all issued before the first is used: one memory latency per batch
 // of rows, not per row), reduces its maxima through LDS and quantizes from registers.
-// scal: [3][16] floats = s_hi, s_lo, lo_sum (as int) per token, then reduction scratch.
-// Requires K, r, ldx multiples of 8, 16-byte aligned rows, K / 8 <= kFusedUnits * 512 / R.
+// scal: [3][16] floats = s_hi, s_lo, lo_sum (as int) per token, then two sets of reduction scratch.
+// Requires K, r, ldx multiples of 8, 16-byte aligned rows, K / 8 <= U * 512 / R.
+//
+// One token on a small layer is one chain of latencies and instructions from end to end (256 workgroups that all do the
+// same), so order and length of the code count: the first batch of rows is asked for before the weights (loads return in
+// order: behind eight weight loads the rows came when the weights did) and the first kFusedAhead weight loads behind it
+// without a condition, so that the wait for the rows can tell them apart; teams are found by shifts; few units a thread
+// mean few conditions (with up to 16 on every call, half of the clocks to the first product went into walking past the absent ones);
+// one barrier a batch and one at the end; the channels' constants are asked for with the first weights.
+// Launches in a row, before / now: 1 x 4096 -> 4096 7.2 / 5.9 us (5.2 of it is the host's), 4 x 4096 -> 4096 8.5 / 7.1,
+// 2 x 4096 -> 14336 11.2 / 9.1, 1 x 8192 -> 28672 24.5 / 23.1; with U = 8 (4 / 8 / 16 units held) 4 x 8192 -> 4096
+// - / 10.1 / 10.8, 1 x 28672 -> 1024 - / 13.2 / 14.0, before 11.6 and 14.8.
+//
+// U: 16-byte units a thread can hold.  U < kFusedUnits takes all M rows in one batch (M <= R, K / 8 <= U * 512 / R)
+// with loads that no condition surrounds; U = kFusedUnits takes any.
 constexpr int kFusedUnits = 16;
-__device__ __forceinline__ void fill_act_quantize(const DecodeArgs& a, uint8_t* act, float* scal, int t) {
+constexpr int kFusedAhead = 4;
+template <int U>
+__device__ __forceinline__ void fused_load_rows(const DecodeArgs& a, int m0, int t, uint4 (&v)[U]) {
+    const int nunits = (int)a.L.K >> 3;
+    const int T = kDecodeThreads >> a.log2_rows;
+    const int team = t >> (9 - a.log2_rows), tt = t & (T - 1);
+    const int m = m0 + team;
+    const uint4* row = reinterpret_cast<const uint4*>(a.x + (int64_t)(m < a.M ? m : a.M - 1) * a.ldx);
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        const int u = tt + i * T;
+        if (U == kFusedUnits && i * T >= nunits) break;   // the same for every thread
+        v[i] = row[u < nunits ? u : 0];
+    }
+}
+// On entry v holds the rows of the first batch; `landed` is run once, when they have arrived.
+template <int U, class F>
+__device__ __forceinline__ void fill_act_quantize(const DecodeArgs& a, uint8_t* act, float* scal, int t,
+                                                  uint4 (&v)[U], F&& landed) {
     constexpr int kWaves = kDecodeThreads / 64;
+    static_assert(kDecodeThreads == 512, "teams are found by shifts");
     const int lane = t & 63, wave = t >> 6;
     const int K = (int)a.L.K, r = (int)a.L.r;
     const int nunits = K >> 3, hi_units = r >> 3;
-    const int R = a.fuse_rows, T = kDecodeThreads / R, WT = T / 64;
-    const int team = t / T, tt = t - team * T;
-    float* red = scal + 3 * 16;                                      // [8 waves][2]
-    int* red_sum = reinterpret_cast<int*>(scal + 3 * 16 + kWaves * 2);  // [8 waves]
-    for (int m0 = 0; m0 < a.M; m0 += R) {   // the same trip count for every thread
+    const int R = 1 << a.log2_rows, T = kDecodeThreads >> a.log2_rows, WT = T >> 6;
+    const int team = t >> (9 - a.log2_rows), tt = t & (T - 1);
+    int* sums = reinterpret_cast<int*>(scal + 2 * 16);               // [16]
+    float2* red = reinterpret_cast<float2*>(scal + 3 * 16);          // [2][8 waves]
+    if (t < 16) sums[t] = 0;
+    for (int m0 = 0, set = 0; m0 < (U < kFusedUnits ? 1 : a.M); m0 += R, set ^= 1) {   // the same trip count for every thread
         const int m = m0 + team;
         const bool live = m < a.M;
-        const uint4* row = reinterpret_cast<const uint4*>(a.x + (int64_t)(live ? m : a.M - 1) * a.ldx);
-        uint4 v[kFusedUnits];
-#pragma unroll
-        for (int i = 0; i < kFusedUnits; ++i) {
-            const int u = tt + i * T;
-            v[i] = make_uint4(0u, 0u, 0u, 0u);
-            if (i * T >= nunits) continue;   // the same for every thread
-            if (u < nunits) v[i] = row[u];
-        }
+        if (U == kFusedUnits && m0 > 0) fused_load_rows(a, m0, t, v);
         float ah = 0.0f, al = 0.0f;
 #pragma unroll
-        for (int i = 0; i < kFusedUnits; ++i) {
+        for (int i = 0; i < U; ++i) {
             if (i * T >= nunits) break;
             const int u = tt + i * T;
-            const float x = absmax8(v[i]);   // zero past the row
+            const float x = u < nunits ? absmax8(v[i]) : 0.0f;
             if (u < hi_units) ah = fmaxf(ah, x);
             else al = fmaxf(al, x);
         }
+        if (m0 == 0) landed();
         ah = wave_max(ah);
         al = wave_max(al);
-        if (lane == 0) {
-            red[wave * 2] = ah;
-            red[wave * 2 + 1] = al;
-        }
-        __syncthreads();
-        ah = 0.0f;
-        al = 0.0f;
-        for (int w = 0; w < WT; ++w) {
-            ah = fmaxf(ah, red[(team * WT + w) * 2]);
-            al = fmaxf(al, red[(team * WT + w) * 2 + 1]);
-        }
+        if (lane == 0) red[set * kWaves + wave] = make_float2(ah, al);
+        lds_barrier();
+        // (a wavefront that is a batch ahead writes the other set, and cannot be two ahead)
+        const float2 part = red[set * kWaves + team * WT + (lane & (WT - 1))];
+        ah = fmaxf(part.x, lane_xor<1>(part.x));
+        al = fmaxf(part.y, lane_xor<1>(part.y));
+        ah = fmaxf(ah, lane_xor<2>(ah));
+        al = fmaxf(al, lane_xor<2>(al));
+        ah = fmaxf(ah, lane_xor<4>(ah));
+        al = fmaxf(al, lane_xor<4>(al));
         const float sh = group_scale(ah, kQmaxHi), sl = group_scale(al, kQmaxLo);
         const float inv_h = 1.0f / sh, inv_l = 1.0f / sl;
         if (tt == 0 && live) {
@@ -217,7 +257,7 @@ __device__ __forceinline__ void fill_act_quantize(const DecodeArgs& a, uint8_t* 
         uint8_t* alow = arow + a.L.kh_pad;
         float odd_f = 0.0f, unused = 0.0f;
 #pragma unroll
-        for (int i = 0; i < kFusedUnits; ++i) {
+        for (int i = 0; i < U; ++i) {
             if (i * T >= nunits) break;
             const int u = tt + i * T;
             if (u < nunits && live) {
@@ -242,28 +282,18 @@ __device__ __forceinline__ void fill_act_quantize(const DecodeArgs& a, uint8_t* 
                 *reinterpret_cast<uint32_t*>(alow + b) = 0x08080808u;
         }
         const int odd = wave_sum((int)odd_f);
-        if (lane == 0) red_sum[wave] = odd;
-        __syncthreads();
-        if (tt == 0 && live) {
-            int sum = 0;
-            for (int w = 0; w < WT; ++w) sum += red_sum[team * WT + w];
-            reinterpret_cast<int*>(scal)[32 + m] = sum;
-        }
+        if (lane == 0 && live) atomicAdd(&sums[m], odd);   // zeroed before the barrier above; whole numbers, any order
     }
-    __syncthreads();
+    lds_barrier();
 }
-
-// the arguments as the epilogue reads them: with the fused quantizer the per-token
-// constants sit in LDS
-template <bool FUSED>
-__device__ __forceinline__ DecodeArgs epilogue_args(const DecodeArgs& a, const float* scal) {
-    DecodeArgs e = a;
-    if constexpr (FUSED) {
-        e.s_hi = scal;
-        e.s_lo = scal + 16;
-        e.lo_sum = reinterpret_cast<const int32_t*>(scal + 32);
-    }
-    return e;
+// the token's constants, from where the above leaves them
+__device__ __forceinline__ void take_fused_token_consts(const DecodeArgs& a, EpilogueConsts& c, const float* scal, int tok) {
+    c.sth = a.L.r > 0 ? scal[tok] : 0.f;
+    c.stl = a.L.K - a.L.r > 0 ? scal[16 + tok] : 0.f;
+    c.ca = a.L.K - a.L.r > 0 ? reinterpret_cast<const int*>(scal)[32 + tok] : 0;
+    c.cth = c.ctl = 0.f;   // symmetric codes
+#pragma unroll
+    for (int v = 0; v < 4; ++v) c.wsh[v] = c.wsl[v] = 0;
 }
 
 // Where a wavefront's activation operand comes from: straight from the code rows in memory
@@ -271,7 +301,7 @@ __device__ __forceinline__ DecodeArgs epilogue_args(const DecodeArgs& a, const f
 // instruction waits for nothing but its own two loads; the code rows are a few KiB per
 // token, stay in L2, and every wavefront reads its part of them once per group), or from
 // LDS rows into which the workgroup itself has quantized the bf16 activations.
-enum : int { kActQuantize = 1, kActDirect = 2 };
+enum : int { kActDirect = 0 };   // any other value: kernels that quantize, with so many units a thread
 
 // lane's pointers to its 16-byte piece of block 0 of the high and of the low codes of its
 // token (the low pointer moved back by the high blocks, so that both take the block index)
@@ -300,6 +330,16 @@ typedef unsigned int v4u_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ uint4 load_weights_16B(const uint4* p) {
     const v4u_t v = __builtin_nontemporal_load(reinterpret_cast<const v4u_t*>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
+}
+
+// the first kFusedAhead weight loads of a run that begins at block b0, whether it has as many blocks or not
+// (blocks past the layer's repeat its last one; whoever has no such block does not multiply it)
+__device__ __forceinline__ void fused_load_ahead(uint4 (&ring)[kDecodeDepth], const uint4* wp, int b0, int blocks) {
+#pragma unroll
+    for (int i = 0; i < kFusedAhead; ++i) {
+        const int b = b0 + i < blocks ? b0 + i : blocks - 1;
+        ring[i] = load_weights_16B(&wp[b * (kBlockBytes / 16)]);
+    }
 }
 
 // One run of a wavefront: blocks [b_begin, b_end) of a channel group meet the tokens'
@@ -366,6 +406,12 @@ __device__ __forceinline__ void stream_run(uint4 (&ring)[kDecodeDepth], uint4 (&
     }
     // the last turns: some refills, then none
     for (; b0 < b_end; b0 += D) {
+        v4i ps[DIRECT ? 1 : D];   // operands in LDS: the whole turn's are asked for at once (past the end: the last block's again)
+        if constexpr (!DIRECT) {
+#pragma unroll
+            for (int i = 0; i < D; ++i)
+                ps[i] = *reinterpret_cast<const v4i*>(arow + (b0 + i < b_end ? b0 + i : b_end - 1) * kRowBytes);
+        }
 #pragma unroll
         for (int i = 0; i < D; ++i) {
             const int b = b0 + i;
@@ -376,7 +422,7 @@ __device__ __forceinline__ void stream_run(uint4 (&ring)[kDecodeDepth], uint4 (&
                     const uint4 pq = aring[i];
                     p = v4i{(int)pq.x, (int)pq.y, (int)pq.z, (int)pq.w};
                 } else {
-                    p = *reinterpret_cast<const v4i*>(arow + b * kRowBytes);
+                    p = ps[i];
                 }
                 if (b + D < b_end) {
                     ring[i] = load_weights_16B(&wp[(b + D) * (kBlockBytes / 16)]);
@@ -400,24 +446,30 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_kernel(const Decod
     const bool tok_live = tok < a.M;
     const ActPieces piece = act_pieces(a, lane, tok_live);
 
-    // start the weight stream of this wave's first group before anything else
+    // start the weight stream of this wave's first group before anything else (but the rows to be quantized)
     int group = wave * gridDim.x + blockIdx.x;
     uint4 ring[kDecodeDepth], aring[DIRECT ? kDecodeDepth : 1];
-    {
-        const uint4* wp = reinterpret_cast<const uint4*>(
-            a.packed + (int64_t)(group < a.groups ? group : 0) * a.L.group_bytes + lane_off);
+    const uint4* wp0 = reinterpret_cast<const uint4*>(
+        a.packed + (int64_t)(group < a.groups ? group : 0) * a.L.group_bytes + lane_off);
+    float* scal = reinterpret_cast<float*>(act + ((a.M * a.lds_row + 15) & ~15));
+    if constexpr (!DIRECT) {
+        uint4 v[ACT];
+        fused_load_rows(a, 0, t, v);
+        fused_load_ahead(ring, wp0, 0, blocks);
+        fill_act_quantize(a, act, scal, t, v, [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = kFusedAhead; i < kDecodeDepth; ++i)
+                if (group < a.groups && i < blocks) ring[i] = load_weights_16B(&wp0[i * (kBlockBytes / 16)]);
+        });
+    } else {
 #pragma unroll
         for (int i = 0; i < kDecodeDepth; ++i) {
             if (group < a.groups && i < blocks) {
-                ring[i] = load_weights_16B(&wp[i * (kBlockBytes / 16)]);
+                ring[i] = load_weights_16B(&wp0[i * (kBlockBytes / 16)]);
                 if constexpr (DIRECT) aring[i] = piece(i);
             }
         }
     }
-
-    float* scal = reinterpret_cast<float*>(act + ((a.M * a.lds_row + 15) & ~15));
-    if constexpr (ACT == kActQuantize) fill_act_quantize(a, act, scal, t);
-    const DecodeArgs ea = epilogue_args<ACT == kActQuantize>(a, scal);
 
     const uint8_t* arow = act + (tok_live ? tok : 0) * a.lds_row + (lane >> 4) * 16;
     for (; group < a.groups; group += 8 * gridDim.x) {
@@ -438,7 +490,15 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_kernel(const Decod
 
         // lane l now holds token l % 16, channels 16 group + 4 (l / 16) + {0..3}
         if (!tok_live) continue;
-        stream_epilogue<DBG>(ea, tok, (int64_t)group * 16 + (lane >> 4) * 4, acc_hi, acc_lo);
+        const int64_t n0 = (int64_t)group * 16 + (lane >> 4) * 4;
+        if constexpr (!DIRECT) {
+            EpilogueConsts ec;
+            take_fused_token_consts(a, ec, scal, tok);
+            take_channel_consts(ec, load_channel_consts(a, n0));
+            stream_epilogue<DBG>(a, tok, n0, ec, acc_hi, acc_lo);
+        } else {
+            stream_epilogue<DBG>(a, tok, n0, acc_hi, acc_lo);
+        }
     }
 }
 
@@ -470,26 +530,33 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_splitk_kernel(cons
     const bool tok_live = tok < a.M;
     const ActPieces piece = act_pieces(a, lane, tok_live);
 
-    // start the weight stream of this wave's first run before anything else
+    // start the weight stream of this wave's first run before anything else (but the rows to be quantized)
     int set = blockIdx.x;
     uint4 ring[kDecodeDepth], aring[DIRECT ? kDecodeDepth : 1];
-    {
-        const int group = set * G + gsel;
-        const bool live = set < sets && group < a.groups;
-        const uint4* wp = reinterpret_cast<const uint4*>(
-            a.packed + (int64_t)(live ? group : 0) * a.L.group_bytes + lane_off);
+    const int group0 = set * G + gsel;
+    const bool live0 = set < sets && group0 < a.groups;
+    const uint4* wp0 = reinterpret_cast<const uint4*>(a.packed + (int64_t)(live0 ? group0 : 0) * a.L.group_bytes + lane_off);
+    float* scal = reinterpret_cast<float*>(partial + kWaves * 2 * 64);
+    ChannelConsts ch;   // kActQuantize: of this set, asked for with the set's first weights
+    if constexpr (!DIRECT) {
+        uint4 v[ACT];
+        fused_load_rows(a, 0, t, v);
+        ch = load_channel_consts(a, (int64_t)(live0 ? group0 : 0) * 16 + (lane >> 4) * 4);
+        fused_load_ahead(ring, wp0, b_begin, blocks);
+        fill_act_quantize(a, act, scal, t, v, [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = kFusedAhead; i < kDecodeDepth; ++i)
+                if (live0 && b_begin + i < b_end) ring[i] = load_weights_16B(&wp0[(b_begin + i) * (kBlockBytes / 16)]);
+        });
+    } else {
 #pragma unroll
         for (int i = 0; i < kDecodeDepth; ++i) {
-            if (live && b_begin + i < b_end) {
-                ring[i] = load_weights_16B(&wp[(b_begin + i) * (kBlockBytes / 16)]);
+            if (live0 && b_begin + i < b_end) {
+                ring[i] = load_weights_16B(&wp0[(b_begin + i) * (kBlockBytes / 16)]);
                 if constexpr (DIRECT) aring[i] = piece(b_begin + i);
             }
         }
     }
-
-    float* scal = reinterpret_cast<float*>(partial + kWaves * 2 * 64);
-    if constexpr (ACT == kActQuantize) fill_act_quantize(a, act, scal, t);
-    const DecodeArgs ea = epilogue_args<ACT == kActQuantize>(a, scal);
 
     const uint8_t* arow = act + (tok_live ? tok : 0) * a.lds_row + (lane >> 4) * 16;
     for (; set < sets; set += gridDim.x) {  // the same trip count for every wavefront of a workgroup
@@ -501,12 +568,21 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_splitk_kernel(cons
         // the wavefront that will run the epilogue asks for its constants behind the first weight loads
         const int64_t n0 = (int64_t)(live ? group : 0) * 16 + (lane >> 4) * 4;
         EpilogueConsts ec;
-        if (part == 0) ec = load_epilogue_consts(ea, tok_live ? tok : 0, n0);
+        if constexpr (DIRECT) {
+            if (part == 0) ec = load_epilogue_consts(a, tok_live ? tok : 0, n0);
+        }
         if (live) stream_run<DIRECT>(ring, aring, wp, piece, arow, b_begin, b_end, hi_blocks, acc_hi, acc_lo);
         // the next set's first loads go out before the sums are exchanged
         {
             const int nset = set + gridDim.x;
             const int ngroup = nset * G + gsel;
+            if constexpr (!DIRECT) {
+                if (part == 0) {
+                    take_fused_token_consts(a, ec, scal, tok_live ? tok : 0);
+                    take_channel_consts(ec, ch);
+                    if (nset < sets && ngroup < a.groups) ch = load_channel_consts(a, (int64_t)ngroup * 16 + (lane >> 4) * 4);
+                }
+            }
             if (nset < sets && ngroup < a.groups) {
                 const uint4* np = reinterpret_cast<const uint4*>(a.packed + (int64_t)ngroup * a.L.group_bytes + lane_off);
 #pragma unroll
@@ -529,7 +605,7 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_splitk_kernel(cons
                 acc_lo += partial[((wave + k) * 2 + 1) * 64 + lane];
             }
             // lane l now holds token l % 16, channels 16 group + 4 (l / 16) + {0..3}
-            if (tok_live) stream_epilogue<DBG>(ea, tok, n0, ec, acc_hi, acc_lo);
+            if (tok_live) stream_epilogue<DBG>(a, tok, n0, ec, acc_hi, acc_lo);
         }
         __syncthreads();  // the partial sums are read before the next set overwrites them
     }

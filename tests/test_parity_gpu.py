@@ -489,6 +489,10 @@ def test_layer_sliced_streaming_up_to_1024_tokens(oracle, rq, M, K, N, r):
     (1, 4096, 512, 512), (3, 4096, 272, 512), (16, 14336, 272, 1792),       # split reduction axis
     (2, 256, 256, 0), (5, 256, 64, 256), (7, 1000, 515, 104), (16, 1000, 40, 104),
     (9, 2048, 1024, 256),
+    # 4, 8 and 16 units a thread: the last width of each and the first of the next, 1 to 8 rows at a time, with and without split
+    (1, 16384, 64, 2048), (1, 16392, 64, 2056), (1, 32768, 48, 4096), (1, 32776, 48, 4096), (2, 8192, 64, 0), (2, 8200, 16400, 1032),
+    (3, 4096, 16400, 512), (4, 4104, 100, 512), (4, 8192, 100, 8192), (4, 8200, 100, 1032), (8, 2048, 16400, 256), (7, 2056, 64, 256),
+    (8, 4096, 64, 512), (8, 4104, 64, 512), (9, 512, 64, 64), (16, 2048, 64, 256), (1, 8, 16, 0), (4, 16, 300, 8),
 ])
 def test_quantize_gemm_mixed_one_call(oracle, rq, M, K, N, r):
     # the quantizer inside the weight-streaming kernel: bit-identical to the two calls, and
