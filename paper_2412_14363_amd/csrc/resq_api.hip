@@ -963,7 +963,7 @@ static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int swee
                                 int64_t ldp, void* workspace, void* stream) {
     const int n = (int)K;
     // one launch on LDS while the matrix and a slice of the vectors fit there, up to 128 columns:
-    // 1.06 to 1.70 ms at n = 128 against 6.9 to 10.5 in two launches a round, by the sweeps that the matrix
+    // 1.1 to 1.35 ms at n = 128 against 6.9 to 10.5 in two launches a round, by the sweeps that the matrix
     // needs (0.15 / 1.69 ms at n = 32, 0.39 / 4.9 at 64).  Not where an output lies on c: its workgroups all read c at their start and write p and
     // eigvals at their end, in no order among each other; the workspace takes a copy of c first.
     if (n <= kEigSmallMax && !blocks_overlap(c, K, ldc, p, K, ldp, K) && !blocks_overlap(c, K, ldc, eigvals, 1, K, K)) {

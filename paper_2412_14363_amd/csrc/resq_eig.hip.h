@@ -22,6 +22,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace resq {
 
 constexpr int kEigThreads = 256;
@@ -108,15 +110,19 @@ __global__ void eig_rotations_kernel(EigPlan e, int sweep, int round) {
 // The vectors do not fit beside the matrix, but column j of Vt is rotated
 // independently of every other column: each of the ceil(n / 8) workgroups repeats
 // the iteration on the matrix (same arithmetic, same decisions) and carries 8
-// columns of Vt, so that the workgroups never talk to each other.  The vectors'
-// rotation of round r runs on wavefronts 1..15 while wavefront 0 computes the
-// angles of round r + 1, a chain of fp64 roots and quotients.  (Wavefront 0 rotating
-// only the blocks that the next angles need, and the others all the rest behind one
-// barrier a round instead of two, measured the same: 1.04 ms at n = 128.)
+// columns of Vt, so that the workgroups never talk to each other.
 //
-// Measured, 12 sweeps allowed, two launches a round / this kernel: n = 128 9.9 to 10.5 / 1.70 ms on a
-// covariance with a spectrum that decays by e^-6, 6.9 / 1.06 on that of Gaussian rows, which
-// converges in fewer sweeps (3000 clocks a round); Gaussian n = 64 4.9 / 0.39, n = 32 1.69 / 0.15.
+// One barrier a round.  Wavefront 0 is a round ahead: it turns the blocks that the diagonal blocks of the NEXT round
+// come from, and computes that round's angles, a chain of fp64 roots and quotients, while the others turn the matrix
+// by this round's and, eight of them, the vectors.  (With the angles of a round between two barriers, 900 of 2870
+// clocks were theirs alone.)  What bounds a round of n = 128 now is LDS, 8 elements and 4 numbers of rotations a block, about
+// 1800 of 2150 clocks.  Measured and not taken: the rotations handed from lane to lane instead of read again (29 % slower:
+// vector instructions), n known to the compiler (14 % slower at 128: it joins reads of two planes into one
+// instruction, on the same banks), a thread's blocks loaded together (4 % slower).
+//
+// Measured, 12 sweeps allowed, two launches a round / two barriers a round / this kernel: n = 128 9.9 to 10.5 / 1.79 / 1.35 ms on a
+// covariance with a spectrum that decays by e^-6, - / 1.50 / 1.14 on that of Gaussian rows, which
+// converges in fewer sweeps; n = 100 - / 1.11 / 0.84, n = 64 4.9 / 0.58 / 0.40, n = 34 - / 0.22 / 0.16, n = 32 1.69 / 0.19 / 0.15.
 constexpr int kEigSmallMax = 128;
 constexpr int kEigSmallThreads = 1024;
 constexpr int kEigSmallCols = 8;  // columns of Vt per workgroup
@@ -124,7 +130,8 @@ constexpr int kEigSmallCols = 8;  // columns of Vt per workgroup
 // blocks (k, l), k < l: lanes of `units` rows of n / 2 (see below)
 __host__ __device__ inline int eig_small_units(int half) { return (half + 1) >> 1; }
 // doubles of one of the two buffers: the four planes, the diagonal blocks (three numbers each)
-__host__ __device__ inline int eig_small_buf(int half) { return 4 * eig_small_units(half) * half + 3 * half + (half & 1); }  // even: what lies behind is 16-byte aligned
+// and a place that nothing reads; even, so that what lies behind is 16-byte aligned
+__host__ __device__ inline int eig_small_buf(int half) { return 4 * eig_small_units(half) * half + 3 * half + (half & 1) + 2; }
 // bytes of LDS: both buffers, both buffers of the Vt slice [n][8], cosines and sines of two rounds, two flags
 __host__ __device__ inline int eig_small_lds_bytes(int n) {
     return (2 * eig_small_buf(n / 2) + 2 * n * kEigSmallCols + 2 * n) * (int)sizeof(double) + 2 * (int)sizeof(int);
@@ -136,7 +143,7 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
     extern __shared__ __attribute__((aligned(16))) double lds[];
     const int half = n >> 1, units = eig_small_units(half), plane = units * half, bufsz = eig_small_buf(half);
     const int diag = 4 * plane;                        // a00[half], a11[half], a01[half] of the pairs
-    double* vt = lds + 2 * bufsz;                      // [2][n][8]: columns j0 .. j0 + 7 of Vt, rows by slot 2 k + x
+    double* vt = lds + 2 * bufsz;                      // [2][n][8]: columns j0 .. j0 + 7 of Vt, rows by slot: half x + k
     double2* cs = reinterpret_cast<double2*>(vt + 2 * n * kEigSmallCols);  // [2][half]
     int* flag = reinterpret_cast<int*>(cs + n);        // [2]: does the round rotate anything
     const int t = threadIdx.x, lane = t & 63;
@@ -178,131 +185,170 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
     }
     for (int idx = t; idx < n * kEigSmallCols; idx += kEigSmallThreads) {
         const int s0 = idx / kEigSmallCols;
-        vt[idx] = index_of(s0 >> 1, s0 & 1) == j0 + idx % kEigSmallCols ? 1.0 : 0.0;
+        vt[idx] = index_of(s0 % half, s0 / half) == j0 + idx % kEigSmallCols ? 1.0 : 0.0;
     }
 
-    // this thread's blocks (two rows of units at most), their places and where their four elements go
-    bool on[2];
-    int bk[2], bl[2], rd[2], wr[2][4];
+    // wavefronts 1 .. 15: this thread's blocks (two rows of units, a third one on the first two), their places and
+    // where their four elements go (what goes to a diagonal block is wavefront 0's to write)
+    constexpr int kWaves = kEigSmallThreads / 64;
+    const int unused = bufsz - 1;
+    bool on[3], row_on[3];   // row_on: for the whole wavefront
+    int bk[3], bl[3], rd[3], wr[3][4];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int u = wave + h * (kEigSmallThreads / 64);
+    for (int h = 0; h < 3; ++h) {
+        const int u = h < 2 ? wave - 1 + h * (kWaves - 1) : 2 * (kWaves - 1) + wave - 1;
         const bool upper = lane > u;
         // not the diagonal, and not the lower lanes of the middle row of an odd number of pairs
-        on[h] = u < units && lane < half && lane != u && (upper || 2 * u != half - 1);
+        on[h] = wave > 0 && (h < 2 || wave <= 2) && u < units && lane < half && lane != u && (upper || 2 * u != half - 1);
         bk[h] = on[h] ? (upper ? u : half - 1 - u) : 0;
         bl[h] = on[h] ? (upper ? lane : half - 1 - lane) : 0;
-        rd[h] = on[h] ? u * half + lane : 0;
+        row_on[h] = wave > 0 && (h < 2 || wave <= 2) && u < units;
+        rd[h] = row_on[h] && lane < half ? u * half + lane : 0;   // lanes without a block compute for nobody
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             int k = bk[h], x = e >> 1, l = bl[h], y = e & 1;
             move(k, x);
             move(l, y);
-            wr[h][e] = on[h] ? at(k, x, l, y) : 0;
+            wr[h][e] = on[h] && k != l ? at(k, x, l, y) : unused;
         }
     }
-    // wavefront 0: the diagonal block of pair `lane`
-    int wd[3];
-    {
-        int k0 = lane < half ? lane : 0, x0 = 0, k1 = k0, x1 = 1;
+    // Wavefront 0, lane k, in the same registers: the slots that the elements in slots (k, 0) and (k, 1) come from, bk[0], rd[0]
+    // and bl[0], rd[1], the block that they share, wr[0], and where the off-diagonal element of lane k's own diagonal block goes, wr[1][0].
+    const bool lk_on = lane < half;
+    if (wave == 0) {
+        auto from = [&](int& k, int& x) {
+            if (half == 1 || (k == 0 && x == 0)) return;
+            if (x == 0) {
+                if (k < half - 1) ++k;
+                else x = 1;
+            } else {
+                if (k == 0) { k = 1; x = 0; }
+                else --k;
+            }
+        };
+        const int own = lk_on ? lane : 0;
+        int k0 = own, x0 = 0, k1 = own, x1 = 1;
+        from(k0, x0);
+        from(k1, x1);
+        bk[0] = k0;
+        rd[0] = x0;
+        bl[0] = k1;
+        rd[1] = x1;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) wr[0][e] = at(k0, e >> 1, k1, e & 1);
+        k0 = k1 = own;
+        x0 = 0;
+        x1 = 1;
         move(k0, x0);
         move(k1, x1);
-        wd[0] = at(k0, x0, k0, x0);
-        wd[1] = at(k1, x1, k1, x1);
-        wd[2] = at(k0, x0, k1, x1);
+        wr[1][0] = lk_on && half > 1 ? at(k0, x0, k1, x1) : unused;
     }
-    // the others: two rows of one column of Vt
-    const int vk = (t - 64) / kEigSmallCols, vc = t & (kEigSmallCols - 1);
-    const bool v_on = t >= 64 && vk < half;
+    // wavefronts 8 .. 15: two rows of one column of Vt
+    const int vk = (t - kEigSmallThreads / 2) / kEigSmallCols, vc = t & (kEigSmallCols - 1);
+    const bool v_on = wave >= kWaves / 2 && vk < half;
     int vw[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
         int k = v_on ? vk : 0, y = x;
         move(k, y);
-        vw[x] = (2 * k + y) * kEigSmallCols + vc;
+        vw[x] = (half * y + k) * kEigSmallCols + vc;
     }
     __syncthreads();
 
-    // Vt <- J^T Vt for the round whose rotations are rot, from buffer b of the slice into the other
-    auto rotate_vectors = [&](const double2* rot, int b) __attribute__((always_inline)) {
-        if (!v_on) return;
-        const double* src = vt + b * n * kEigSmallCols + 2 * vk * kEigSmallCols + vc;
-        double* dst = vt + (b ^ 1) * n * kEigSmallCols;
-        const double2 r = rot[vk];
-        const double x = src[0], y = src[kEigSmallCols];
-        dst[vw[0]] = r.x * x - r.y * y;
-        dst[vw[1]] = r.y * x + r.x * y;
-    };
-
-    int buf = 0, rounds = 0;  // the vectors are one round behind the matrix
-    for (int sweep = 0; sweep < sweeps; ++sweep) {
-        int rotated = 0;
-        for (int round = 0; round < n - 1; ++round) {
-            const double* cur = lds + buf * bufsz;
-            double* nxt = lds + (buf ^ 1) * bufsz;
-            double2* rot = cs + buf * half;
-            double a00 = 0.0, a11 = 0.0, a01 = 0.0;
-            double2 r = make_double2(1.0, 0.0);
-            if (wave == 0) {
-                bool turn = false;
-                if (lane < half) {
-                    a00 = cur[diag + lane];
-                    a11 = cur[diag + half + lane];
-                    a01 = cur[diag + 2 * half + lane];
-                    // As eig_rotations_kernel has it, |a01| > 2^-40 sqrt(|a00 a11|) and tan of the smaller angle =
-                    // sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with fewer
-                    // roots and quotients in a row.  (The hardware's approximate ones are not enough: the
-                    // signs of some vectors then come out otherwise.)
-                    turn = a01 * a01 > kEigSkip * kEigSkip * fabs(a00 * a11);
-                    if (turn) {
-                        const double d = a11 - a00, b = 2.0 * a01;
-                        double tn = fabs(b) / (fabs(d) + sqrt(d * d + b * b));
-                        if (d != 0.0 && (d < 0.0) != (b < 0.0)) tn = -tn;
-                        r.x = rsqrt(1.0 + tn * tn);
-                        r.y = tn * r.x;
-                    }
-                    rot[lane] = r;
-                }
-                const bool any = __ballot(turn) != 0;
-                if (lane == 0) flag[buf] = any ? 1 : 0;
-            } else if (rounds > 0) {
-                rotate_vectors(cs + (buf ^ 1) * half, buf ^ 1);
-            }
-            __syncthreads();
-            rotated |= flag[buf];
-            double2 x0[2], x1[2], ra[2], rb[2];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (!on[h]) continue;
-                ra[h] = rot[bk[h]];
-                rb[h] = rot[bl[h]];
-                x0[h] = make_double2(cur[rd[h]], cur[plane + rd[h]]);
-                x1[h] = make_double2(cur[2 * plane + rd[h]], cur[3 * plane + rd[h]]);
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (!on[h]) continue;
-                const double y00 = ra[h].x * x0[h].x - ra[h].y * x1[h].x, y10 = ra[h].y * x0[h].x + ra[h].x * x1[h].x;
-                const double y01 = ra[h].x * x0[h].y - ra[h].y * x1[h].y, y11 = ra[h].y * x0[h].y + ra[h].x * x1[h].y;
-                nxt[wr[h][0]] = rb[h].x * y00 - rb[h].y * y01;
-                nxt[wr[h][1]] = rb[h].y * y00 + rb[h].x * y01;
-                nxt[wr[h][2]] = rb[h].x * y10 - rb[h].y * y11;
-                nxt[wr[h][3]] = rb[h].y * y10 + rb[h].x * y11;
-            }
-            if (wave == 0 && lane < half) {
-                const double r00 = r.x * a00 - r.y * a01, r01 = r.x * a01 - r.y * a11;
-                const double r10 = r.y * a00 + r.x * a01, r11 = r.y * a01 + r.x * a11;
-                nxt[wd[0]] = r.x * r00 - r.y * r01;
-                nxt[wd[1]] = r.y * r10 + r.x * r11;
-                nxt[wd[2]] = r.y * r00 + r.x * r01;
-            }
-            __syncthreads();
-            buf ^= 1;
-            ++rounds;
+    // the rotation of the pair whose diagonal block is (a00, a01; a01, a11), for the round that reads buffer b
+    auto angle = [&](double a00, double a11, double a01, int b) __attribute__((always_inline)) {
+        // As eig_rotations_kernel has it, |a01| > 2^-40 sqrt(|a00 a11|) and tan of the smaller angle =
+        // sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with fewer
+        // roots and quotients in a row.  (The hardware's approximate ones are not enough: the
+        // signs of some vectors then come out otherwise.)
+        const bool turn = lk_on && a01 * a01 > kEigSkip * kEigSkip * fabs(a00 * a11);
+        double2 r = make_double2(1.0, 0.0);
+        if (turn) {
+            const double d = a11 - a00, q = 2.0 * a01;
+            double tn = fabs(q) / (fabs(d) + sqrt(d * d + q * q));
+            if (d != 0.0 && (d < 0.0) != (q < 0.0)) tn = -tn;
+            r.x = rsqrt(1.0 + tn * tn);
+            r.y = tn * r.x;
         }
-        if (!rotated) break;  // as every later sweep would find: the same for all threads
+        if (lk_on) cs[b * half + lane] = r;
+        const bool any = __ballot(turn) != 0;
+        if (lane == 0) flag[b] = any ? 1 : 0;
+    };
+    if (wave == 0) angle(lds[diag + lk_on * lane], lds[diag + half + lk_on * lane], lds[diag + 2 * half + lk_on * lane], 0);
+    __syncthreads();
+    // One round, from buffer B, known to the compiler (every access cost an index sum before), into the other.
+    auto one_round = [&](auto buf_) __attribute__((always_inline)) {
+        constexpr int B = decltype(buf_)::value;
+        const double* cur = lds + B * bufsz;
+        double* nxt = lds + (B ^ 1) * bufsz;
+        const double2* rot = cs + B * half;
+        if (wave == 0) {
+            // the diagonal blocks of the next round, and its angles
+            const int lk0 = bk[0], lk1 = bl[0];
+            const bool lx0 = rd[0] != 0, lx1 = rd[1] != 0;
+            const double2 r0 = rot[lk0], r1 = rot[lk1];
+            const double p00 = cur[diag + lk0], p11 = cur[diag + half + lk0], p01 = cur[diag + 2 * half + lk0];
+            const double q00 = cur[diag + lk1], q11 = cur[diag + half + lk1], q01 = cur[diag + 2 * half + lk1];
+            const double e00 = cur[wr[0][0]], e01 = cur[wr[0][1]], e10 = cur[wr[0][2]], e11 = cur[wr[0][3]];
+            // row x of the rotation: new = f old_0 + g old_1
+            const double f0 = lx0 ? r0.y : r0.x, g0 = lx0 ? r0.x : -r0.y;
+            const double f1 = lx1 ? r1.y : r1.x, g1 = lx1 ? r1.x : -r1.y;
+            const double a00 = f0 * (f0 * p00 + g0 * p01) + g0 * (f0 * p01 + g0 * p11);
+            const double a11 = f1 * (f1 * q00 + g1 * q01) + g1 * (f1 * q01 + g1 * q11);
+            double a01;
+            if (half == 1) a01 = f1 * (f0 * p00 + g0 * p01) + g1 * (f0 * p01 + g0 * p11);
+            else a01 = f1 * (f0 * e00 + g0 * e10) + g1 * (f0 * e01 + g0 * e11);
+            if (lk_on) {
+                nxt[diag + lane] = a00;
+                nxt[diag + half + lane] = a11;
+                nxt[diag + 2 * half + lane] = a01;
+            }
+            angle(a00, a11, a01, B ^ 1);
+            const int own = lk_on ? lane : 0;
+            const double2 r = rot[own];
+            const double o00 = cur[diag + own], o11 = cur[diag + half + own], o01 = cur[diag + 2 * half + own];
+            nxt[wr[1][0]] = r.y * (r.x * o00 - r.y * o01) + r.x * (r.x * o01 - r.y * o11);
+        } else {
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {
+                if (!row_on[h]) continue;
+                const double* at = cur + rd[h];
+                const double2 ra = rot[bk[h]], rb = rot[bl[h]];
+                const double2 x0 = make_double2(at[0], at[plane]), x1 = make_double2(at[2 * plane], at[3 * plane]);
+                const double y00 = ra.x * x0.x - ra.y * x1.x, y10 = ra.y * x0.x + ra.x * x1.x;
+                const double y01 = ra.x * x0.y - ra.y * x1.y, y11 = ra.y * x0.y + ra.x * x1.y;
+                nxt[wr[h][0]] = rb.x * y00 - rb.y * y01;
+                nxt[wr[h][1]] = rb.y * y00 + rb.x * y01;
+                nxt[wr[h][2]] = rb.x * y10 - rb.y * y11;
+                nxt[wr[h][3]] = rb.y * y10 + rb.x * y11;
+            }
+            if (v_on) {   // Vt <- J^T Vt
+                const double* src = vt + B * n * kEigSmallCols + vk * kEigSmallCols + vc;
+                double* dst = vt + (B ^ 1) * n * kEigSmallCols;
+                const double2 r = rot[vk];
+                const double x = src[0], y = src[half * kEigSmallCols];
+                dst[vw[0]] = r.x * x - r.y * y;
+                dst[vw[1]] = r.y * x + r.x * y;
+            }
+        }
+    };
+    int buf = 0, rotated = 0, round = 0;
+    for (int sweep = 0;;) {
+        // true when the iteration is over
+        auto step = [&](auto buf_) __attribute__((always_inline)) {
+            constexpr int B = decltype(buf_)::value;
+            rotated |= __builtin_amdgcn_readfirstlane(flag[B]);
+            one_round(buf_);
+            __syncthreads();
+            buf = B ^ 1;
+            if (++round < n - 1) return false;
+            const bool over = !rotated || ++sweep == sweeps;  // a sweep that turned nothing: as every later one would
+            round = rotated = 0;
+            return over;
+        };
+        if (step(std::integral_constant<int, 0>{})) break;
+        if (step(std::integral_constant<int, 1>{})) break;
     }
-    rotate_vectors(cs + (buf ^ 1) * half, buf ^ 1);
     // positions in decreasing order (ties by index), as eig_finish_kernel has them; rank by slot
     const double* a = lds + buf * bufsz + diag;
     vt += buf * n * kEigSmallCols;
@@ -321,7 +367,7 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
     __syncthreads();
     for (int idx = t; idx < n * kEigSmallCols; idx += kEigSmallThreads) {
         const int col = idx / n, s = idx % n;
-        if (j0 + col < n) p[(int64_t)(j0 + col) * ldp + rank[s]] = (float)vt[s * kEigSmallCols + col];
+        if (j0 + col < n) p[(int64_t)(j0 + col) * ldp + rank[s]] = (float)vt[((s & 1) * half + (s >> 1)) * kEigSmallCols + col];
     }
 }
 
