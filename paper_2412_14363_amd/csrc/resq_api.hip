@@ -36,6 +36,11 @@ inline int shape_ok(int64_t rows, int64_t K, int64_t r) {
     return 1;
 }
 
+inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + nb && y < x + na;
+}
+
 inline int launch_status() { return hipGetLastError() == hipSuccess ? RESQ_OK : RESQ_ERR_HIP; }
 
 // One-shot timing request of resq_time_next_kernel(): the next main kernel this
@@ -910,8 +915,8 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
         return RESQ_ERR_ALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)((J + kBasisTile - 1) / kBasisTile), (unsigned)((rows + kBasisTile - 1) / kBasisTile), 1);
-    // bf16 rows: three exact bf16 products instead of one fp32 product (same
-    // tiles and grid as the fp32 kernel: 4096 x 4096 x 4096 0.40 ms against 1.19, 256 x 512 x 512 17 us
+    // bf16 rows: three exact bf16 products instead of one fp32 product (in the
+    // tiles and grid of the fp32 kernel 4096 x 4096 x 4096 0.40 ms against 1.19, 256 x 512 x 512 17 us
     // against 56, 128 x 128 x 128 8.4 us against 22); fp32 rows would need at least six, and stay on the
     // fp32 instruction.  So do bf16 rows of one chunk of that kernel: half a chunk of the other, whose
     // ragged end costs more than its products save (16 steps, 128 x 128 outputs 5.5 / 7.1 us, 4096 x 4096 15.6 / 18.6; 17
@@ -923,7 +928,17 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
         pa.out = out;
         pa.lda = lda; pa.ldu = ldu; pa.ldo = ldo;
         pa.I = rows; pa.J = J; pa.T = K;
-        if (out_is_bf16) launch(project_split_kernel<true>, grid, dim3(kProjThreads), 0, st, pa);
+        // 256 x 128 tiles where they fill the chip, two to a compute unit (128 x 128 / 256 x 128 tiles, us): 4096 x 4096 x 4096, 512 of
+        // them, 390 / 326, 8192 x 4096 x 4096 779 / 631, 5000 x 4096 x 4096, 640, 489 / 469, 8192 x 40 x 8192 73 / 58; half as many are
+        // slower: 4000 x 2000 x 2000 110 / 118, 2048 x 2048 x 2048 61 / 104.  Its reduction ends on whole pieces, its row offsets have 32 bits,
+        // and its second look at sums that are not finite wants a and u as they were.
+        const dim3 wide_grid(grid.x, (unsigned)((rows + kProjWideRows - 1) / kProjWideRows), 1);
+        const bool wide = (int64_t)wide_grid.x * wide_grid.y >= 512 && K % 8 == 0 && lda <= (1 << 22) &&
+                          !overlap(a, (size_t)rows * lda * 2, out, (size_t)rows * ldo * (out_is_bf16 ? 2 : 4)) &&
+                          !overlap(u, (size_t)K * ldu * 4, out, (size_t)rows * ldo * (out_is_bf16 ? 2 : 4));
+        if (wide && out_is_bf16) launch(project_split_wide_kernel<true>, wide_grid, dim3(kProjThreads), 0, st, pa);
+        else if (wide) launch(project_split_wide_kernel<false>, wide_grid, dim3(kProjThreads), 0, st, pa);
+        else if (out_is_bf16) launch(project_split_kernel<true>, grid, dim3(kProjThreads), 0, st, pa);
         else launch(project_split_kernel<false>, grid, dim3(kProjThreads), 0, st, pa);
         return launch_status();
     }

@@ -38,6 +38,7 @@
 namespace resq {
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kProjThreads = 256;
 constexpr int kProjTile = 128;
@@ -56,6 +57,30 @@ struct ProjectArgs {
     int64_t lda, ldu, ldo;
     int64_t I, J, T;
 };
+
+// eight consecutive t of one column of u, split into their three parts, one unit of LDS each
+__device__ __forceinline__ void stash_split(uint8_t* unit, const float (&u)[8]) {
+    uint32_t part[3][4];
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        uint32_t x[2], y[2], z[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float v = u[e + k];
+            x[k] = __float_as_uint(v);
+            const float r1 = v - __uint_as_float(x[k] & 0xFFFF0000u);   // exact
+            y[k] = __float_as_uint(r1);
+            z[k] = __float_as_uint(r1 - __uint_as_float(y[k] & 0xFFFF0000u));  // exact, at most 8 bits left
+        }
+        // upper halves of two numbers into one register
+        part[0][e >> 1] = __builtin_amdgcn_perm(x[1], x[0], 0x07060302);
+        part[1][e >> 1] = __builtin_amdgcn_perm(y[1], y[0], 0x07060302);
+        part[2][e >> 1] = __builtin_amdgcn_perm(z[1], z[0], 0x07060302);
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+        *reinterpret_cast<uint4*>(unit + s * kProjSplitB) = make_uint4(part[s][0], part[s][1], part[s][2], part[s][3]);
+}
 
 template <bool OUT_BF16>
 __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const ProjectArgs g) {
@@ -127,27 +152,7 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const Pr
             *reinterpret_cast<uint4*>(base + ap * kProjPieceA + (ar + 64 * h) * 16) = c.a[h];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            uint32_t part[3][4];
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                uint32_t x[2], y[2], z[2];
-#pragma unroll
-                for (int k = 0; k < 2; ++k) {
-                    const float v = c.u[h][e + k];
-                    x[k] = __float_as_uint(v);
-                    const float r1 = v - __uint_as_float(x[k] & 0xFFFF0000u);   // exact
-                    y[k] = __float_as_uint(r1);
-                    z[k] = __float_as_uint(r1 - __uint_as_float(y[k] & 0xFFFF0000u));  // exact, at most 8 bits left
-                }
-                // upper halves of two numbers into one register
-                part[0][e >> 1] = __builtin_amdgcn_perm(x[1], x[0], 0x07060302);
-                part[1][e >> 1] = __builtin_amdgcn_perm(y[1], y[0], 0x07060302);
-                part[2][e >> 1] = __builtin_amdgcn_perm(z[1], z[0], 0x07060302);
-            }
-#pragma unroll
-            for (int s = 0; s < 3; ++s)
-                *reinterpret_cast<uint4*>(base + kProjBytesA + s * kProjSplitB + (bp + 2 * h) * kProjPieceB + bj * 16) =
-                    make_uint4(part[s][0], part[s][1], part[s][2], part[s][3]);
+            stash_split(base + kProjBytesA + (bp + 2 * h) * kProjPieceB + bj * 16, c.u[h]);
         }
     };
 
@@ -284,6 +289,245 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const Pr
             }
         }
         __syncthreads();   // out may lie on a (one column of tiles): all is read before anything is written
+    }
+}
+
+// ---- 256 x 128 outputs ----------------------------------------------------------------------------
+//
+// The same product where there are enough such tiles to fill the chip.  In the kernel above LDS is as busy as
+// the matrix pipes: a wavefront reads 16 KiB (one operand, three parts of the other) for 64 x 64 outputs of a chunk, and
+// every 128 rows split u again.  Here a wavefront owns 128 x 64 outputs (128 accumulation registers), which takes 20 KiB
+// for twice the products, and u is split once for 256 rows.  The instruction is v_mfma_f32_16x16x32_bf16, which alone
+// sustains 1980 TFLOP/s under the power limit where the 32x32x16 one sustains 1755 (random operands, milliseconds).  One
+// chunk is in registers on its way: it is split behind the products of the smallest parts and written, and the chunk after it is
+// asked for behind those of the middle ones.  4096 x 4096 x 4096 390 -> 326 us (1265 TFLOP/s of bf16 products), error against 64
+// bits with fp32 output 7.02e-7 -> 7.01e-7, at K = 256 1.65e-7 -> 1.60e-7 (one rounding per 32 products instead of 16).
+constexpr int kProjWideRows = 256;
+constexpr int kProjWidePieceA = kProjWideRows * 16;
+constexpr int kProjWideBytesA = kProjPieces * kProjWidePieceA;
+constexpr int kProjWideBytes = kProjWideBytesA + 3 * kProjSplitB;
+static_assert(2 * 2 * kProjWideBytes <= 160 * 1024, "LDS of two resident workgroups");
+
+// acc += b a on the bf16 matrix cores, in place in accumulation registers
+__device__ __forceinline__ void mfma_16x16x32_bf16(v4f& acc, const v8bf& b, const v8bf& a) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
+}
+
+template <bool OUT_BF16>
+__global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(const ProjectArgs g) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kProjWideBytes];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wi = wave >> 1, wj = wave & 1;
+    const int64_t i0 = (int64_t)blockIdx.y * kProjWideRows, j0 = (int64_t)blockIdx.x * kProjTile;
+
+    // a: thread (rows t / 4 + 64 h, piece t % 4); u as above
+    const int ar = t >> 2, ap = t & 3;
+    const int bj = t & 127, bp = wave >> 1;
+    uint32_t a_off[4];   // bytes from the tile's first row (the launch sees to it that they fit)
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const int64_t i = i0 + ar + 64 * h;
+        a_off[h] = (uint32_t)(((i < g.I ? i : g.I - 1) - i0) * g.lda + ap * 8) * 2;
+    }
+    const uint32_t u_col = (uint32_t)((j0 + bj < g.J ? j0 + bj : g.J - 1) - j0);
+    const uint8_t* a_base = reinterpret_cast<const uint8_t*>(g.a + i0 * g.lda);
+    uint4 ca[4];     // the chunk on its way from memory to LDS
+    float cu[2][8];
+    auto fetch = [&](int64_t tc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) ca[h] = *reinterpret_cast<const uint4*>(a_base + a_off[h] + 2 * tc);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const float* row = g.u + (tc + (bp + 2 * h) * 8) * g.ldu + j0;   // wave-uniform
+#pragma unroll
+            for (int e = 0; e < 8; ++e) cu[h][e] = row[e * g.ldu + u_col];
+        }
+    };
+    // The last chunk of a reduction axis that ends inside it (on a whole piece): zeros for a, the last row of u again.
+    auto fetch_any = [&](int64_t tc) __attribute__((always_inline)) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            ca[h] = make_uint4(0u, 0u, 0u, 0u);
+            if (tc + ap * 8 < g.T) ca[h] = *reinterpret_cast<const uint4*>(a_base + a_off[h] + 2 * tc);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int64_t tt = tc + (bp + 2 * h) * 8 + e;
+                cu[h][e] = g.u[(tt < g.T ? tt : g.T - 1) * g.ldu + j0 + u_col];
+            }
+    };
+    auto stash = [&](int buf) __attribute__((always_inline)) {
+        uint8_t* base = lds + buf * kProjWideBytes;
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            *reinterpret_cast<uint4*>(base + ap * kProjWidePieceA + ((ar ^ (4 * ap)) + 64 * h) * 16) = ca[h];   // rows of four pieces side by side
+#pragma unroll
+        for (int h = 0; h < 2; ++h) stash_split(base + kProjWideBytesA + (bp + 2 * h) * kProjPieceB + bj * 16, cu[h]);
+    };
+
+    // acc[q][p]: columns 16 q .., rows 16 p .. of the wavefront's 128 x 64
+    v4f acc[4][8];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int p = 0; p < 8; ++p) acc[q][p] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    const int ol = lane & 15, oh = lane >> 4;   // row (column) of a fragment, piece along the reduction
+    static_assert(kProjChunk == 32, "an instruction takes a whole chunk");
+    v8bf fa[8], fb[2][4];
+    auto read_a = [&](int buf) __attribute__((always_inline)) {
+        const uint8_t* base = lds + buf * kProjWideBytes + oh * kProjWidePieceA + (wi * 128 + (ol ^ (4 * oh))) * 16;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) fa[p] = *reinterpret_cast<const v8bf*>(base + p * 256);
+    };
+    auto read_b = [&](int part, int set, int buf) __attribute__((always_inline)) {
+        const uint8_t* base = lds + buf * kProjWideBytes + kProjWideBytesA + part * kProjSplitB + oh * kProjPieceB + (wj * 64 + ol) * 16;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) fb[set][q] = *reinterpret_cast<const v8bf*>(base + q * 256);
+    };
+    // Product K of a part: tile (q, p) = (K / 8, K % 8), u as first operand, so that a lane ends with four consecutive
+    // columns of a row.  As in resq_gemm.hip.h the instruction is assembly with its tile in place in accumulation
+    // registers: given the builtin, the compiler renames the tiles and spills (8192 x 4096 x 4096 1244 us, this 631).
+    auto product = [&](auto k, int set) __attribute__((always_inline)) {
+        constexpr int K = decltype(k)::value;
+        mfma_16x16x32_bf16(acc[K >> 3][K & 7], fb[set][K >> 3], fa[K & 7]);
+    };
+    auto multiply = [&](int set) __attribute__((always_inline)) {
+        static_for<32>([&](auto k) __attribute__((always_inline)) { product(k, set); });
+    };
+    // columns e, e + 1 of unit h of the chunk in registers into their three parts
+    uint32_t part[3][4];
+    auto split2 = [&](auto h_, auto e_) __attribute__((always_inline)) {
+        constexpr int H = decltype(h_)::value, E = decltype(e_)::value;
+        uint32_t x[2], y[2], z[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const float v = cu[H][E + k];
+            x[k] = __float_as_uint(v);
+            const float r1 = v - __uint_as_float(x[k] & 0xFFFF0000u);   // exact
+            y[k] = __float_as_uint(r1);
+            z[k] = __float_as_uint(r1 - __uint_as_float(y[k] & 0xFFFF0000u));  // exact, at most 8 bits left
+        }
+        part[0][E >> 1] = __builtin_amdgcn_perm(x[1], x[0], 0x07060302);
+        part[1][E >> 1] = __builtin_amdgcn_perm(y[1], y[0], 0x07060302);
+        part[2][E >> 1] = __builtin_amdgcn_perm(z[1], z[0], 0x07060302);
+    };
+
+    // Chunk i is multiplied out of buffer i % 2, the smallest parts of u first, while chunk i + 1 is split and written
+    // into the other one and chunk i + 2 sets out.
+    fetch_any(0);
+    stash(0);
+    fetch_any(kProjChunk);
+    __syncthreads();
+    auto step = [&](int64_t tc, int buf) __attribute__((always_inline)) {
+        read_a(buf);
+        read_b(2, 0, buf);
+        __builtin_amdgcn_sched_barrier(0);
+        uint8_t* const to = lds + (buf ^ 1) * kProjWideBytes;
+        static_for<32>([&](auto k_) __attribute__((always_inline)) {
+            constexpr int K = decltype(k_)::value;
+            product(k_, 0);
+            if constexpr (K < 24 && K % 3 == 1) split2(IC<K / 12>{}, IC<2 * (K / 3 % 4)>{});   // behind every third
+            if constexpr (K == 11 || K == 23) {
+                constexpr int H = K / 12;
+#pragma unroll
+                for (int s = 0; s < 3; ++s)
+                    *reinterpret_cast<uint4*>(to + kProjWideBytesA + s * kProjSplitB + (bp + 2 * H) * kProjPieceB + bj * 16) =
+                        make_uint4(part[s][0], part[s][1], part[s][2], part[s][3]);
+            }
+            if constexpr (K % 6 == 3 && K < 24) {
+                constexpr int H = K / 6;
+                *reinterpret_cast<uint4*>(to + ap * kProjWidePieceA + ((ar ^ (4 * ap)) + 64 * H) * 16) = ca[H];
+            }
+            if constexpr (K == 25) read_b(1, 1, buf);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        static_for<32>([&](auto k_) __attribute__((always_inline)) {
+            constexpr int K = decltype(k_)::value;
+            product(k_, 1);
+            if constexpr (K == 1) read_b(0, 0, buf);
+            if constexpr (K == 3) fetch(tc + 2 * kProjChunk);
+            if constexpr (K == 1 || K == 3) __builtin_amdgcn_sched_barrier(0);
+        });
+        multiply(0);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+    };
+    int64_t tc = 0;
+    for (; tc + 4 * kProjChunk <= g.T; tc += 2 * kProjChunk) {
+        step(tc, 0);
+        step(tc + kProjChunk, 1);
+    }
+    for (int buf = 0; tc < g.T; tc += kProjChunk, buf ^= 1) {   // up to four chunks are left, the last one perhaps ragged
+        read_a(buf);
+        read_b(2, 0, buf);
+        read_b(1, 1, buf);
+        multiply(0);
+        read_b(0, 0, buf);
+        multiply(1);
+        multiply(0);
+        if (tc + kProjChunk < g.T) {
+            stash(buf ^ 1);
+            fetch_any(tc + 2 * kProjChunk);
+            __syncthreads();
+        }
+    }
+
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions have written their tiles
+    // any sum that is not finite (0 x it is NaN) sends the whole workgroup to the second way out
+    float probe[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // eight short chains instead of a long one
+#pragma unroll
+    for (int e = 0; e < 128; ++e) probe[e & 7] = fmaf(acc[e >> 5][(e >> 2) & 7][e & 3], 0.0f, probe[e & 7]);
+    const float sum = ((probe[0] + probe[1]) + (probe[2] + probe[3])) + ((probe[4] + probe[5]) + (probe[6] + probe[7]));
+    int* redo = reinterpret_cast<int*>(lds);   // a sum of this workgroup is not finite
+    __syncthreads();
+    if (t == 0) *redo = 0;
+    __syncthreads();
+    if (sum != sum) *redo = 1;
+    __syncthreads();
+    const bool again = __builtin_amdgcn_readfirstlane(*redo) != 0;
+
+    // acc[q][p][v]: column 4 (lane / 16) + v, row lane % 16 of matrix tile (q, p)
+    auto place = [&](int q, int p, int64_t& i, int64_t& j) __attribute__((always_inline)) {
+        i = i0 + wi * 128 + p * 16 + ol;
+        j = j0 + wj * 64 + q * 16 + 4 * oh;
+    };
+    // J is a multiple of eight, so four columns are there or none; rows start at any address, see store_piece
+    auto store4 = [&](int64_t i, int64_t j, const v4f& c) __attribute__((always_inline)) {
+        if constexpr (OUT_BF16) {
+            uint16_t* dst = static_cast<uint16_t*>(g.out) + i * g.ldo + j;
+            *reinterpret_cast<Piece8*>(dst) = Piece8{pack_bf16(c[0], c[1]), pack_bf16(c[2], c[3])};
+        } else {
+            float* dst = static_cast<float*>(g.out) + i * g.ldo + j;
+            *reinterpret_cast<Piece16*>(dst) = Piece16{__float_as_uint(c[0]), __float_as_uint(c[1]), __float_as_uint(c[2]), __float_as_uint(c[3])};
+        }
+    };
+#pragma unroll
+    for (int p = 0; p < 8; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            int64_t i, j;
+            place(q, p, i, j);
+            if (i < g.I && j < g.J) store4(i, j, acc[q][p]);
+        }
+    if (__builtin_expect(!again, 1)) return;
+    // out does not lie on a or u (the launch sees to it): a lane reads its own outputs again and takes the NaN sums anew
+#pragma unroll 1
+    for (int e = 0; e < 128; ++e) {
+        int64_t i, j;
+        place(e >> 5, (e >> 2) & 7, i, j);
+        j += e & 3;
+        if (i >= g.I || j >= g.J) continue;
+        float s = OUT_BF16 ? __uint_as_float((uint32_t)static_cast<const uint16_t*>(g.out)[i * g.ldo + j] << 16)
+                           : static_cast<const float*>(g.out)[i * g.ldo + j];
+        if (s == s) continue;
+        const uint16_t* row = g.a + i * g.lda;
+        s = 0.0f;
+        for (int64_t k = 0; k < g.T && s == s; ++k) s = fmaf(__uint_as_float((uint32_t)row[k] << 16), g.u[k * g.ldu + j], s);
+        if constexpr (OUT_BF16) static_cast<uint16_t*>(g.out)[i * g.ldo + j] = (uint16_t)pack_bf16(s, 0.0f);
+        else static_cast<float*>(g.out)[i * g.ldo + j] = s;
     }
 }
 

@@ -103,6 +103,51 @@ def test_project_rows_split(rq, rows, K, J):
     assert np.all(np.abs(buf[:, :J].double().cpu().numpy() - ad @ ud) <= 3 * K * 2.0 ** -24 * (np.abs(ad) @ np.abs(ud)) + 1e-30)
 
 
+# From 512 tiles of 256 x 128 on: ragged rows and columns, a reduction axis of less than a chunk, of whole chunks, with one to
+# three pieces of a last one, through the loop and without it; beside them what the smaller tiles keep (one tile less, a ragged
+# piece, out on a)
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,K,J", [(16380, 24, 1032), (16129, 32, 1032), (16385, 40, 1000), (130817, 56, 128), (130816, 56, 128),
+                                      (16300, 64, 1032), (16300, 160, 1032), (16300, 168, 1032), (16300, 232, 1032), (16300, 161, 1032)])
+def test_project_rows_wide_tiles(rq, rows, K, J, out_dtype):
+    g = torch.Generator(device="cuda").manual_seed(rows + K + J)
+    ld = (K + 7) // 8 * 8 + 8
+    a = torch.full((rows, ld), float("nan"), dtype=torch.bfloat16, device="cuda")   # what lies behind a row is not read
+    a[:, :K] = torch.randn(rows, K, generator=g, device="cuda").bfloat16()
+    u = torch.randn(K, J, generator=g, device="cuda") * torch.exp2(torch.randint(-40, 10, (K, J), generator=g, device="cuda").float())
+    u[::3] = u[::3].bfloat16().float()
+    buf = torch.full((rows, J + 3), 7.0, device="cuda", dtype=out_dtype)
+    rq.resq_project_rows(a[:, :K], u, out=buf[:, :J])
+    ad, ud = a[:, :K].double(), u.double()
+    ref, mag = ad @ ud, ad.abs() @ ud.abs()
+    assert torch.all(buf[:, J:] == 7.0)
+    # products are exact; 3 K additions in fp32, one rounding of the output
+    tol = 3 * K * 2.0 ** -24 * mag + (2.0 ** -8 * ref.abs() if out_dtype == torch.bfloat16 else 0) + 1e-30
+    assert torch.all((buf[:, :J].double() - ref).abs() <= tol)
+
+
+def test_project_rows_wide_tiles_infinities_and_in_place(rq):
+    rows, K, J, inf, nan = 131072, 72, 128, float("inf"), float("nan")
+    g = torch.Generator(device="cuda").manual_seed(9)
+    a = torch.randn(rows, 128, generator=g, device="cuda").bfloat16()
+    u = torch.randn(K, J, generator=g, device="cuda")
+    u[:, ::2] = u[:, ::2].bfloat16().float()   # two of the three parts are zero
+    a[0, 3], a[300, K - 1], a[5000, 2], a[5000, 9], a[131071, 1] = inf, -inf, inf, -inf, nan
+    u[K - 6, 4], u[K - 1, 7] = inf, nan
+    ref = a[:, :K].double() @ u.double()
+    for out_dtype in (torch.float32, torch.bfloat16):
+        got = rq.resq_project_rows(a[:, :K], u, out_dtype=out_dtype)
+        assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
+        assert torch.equal(got[ref.isinf()].double(), ref[ref.isinf()])
+        fin = ref.isfinite()
+        assert torch.allclose(got[fin].double(), ref[fin], rtol=2.0 ** -8, atol=1e-4)
+    want = rq.resq_project_rows(a[:, :K], u, out_dtype=torch.bfloat16)
+    buf = a.clone()
+    rq.resq_project_rows(buf[:, :K], u, out=buf)   # the smaller tiles, another order of the sum
+    assert torch.equal(buf.isnan(), want.isnan())
+    assert torch.allclose(buf[want.isfinite()].double(), want[want.isfinite()].double(), rtol=2.0 ** -7, atol=1e-4)
+
+
 # Infinities and NaN in either operand: what a plain sum gives, not the NaN that infinity x 0 among the three
 # parts of u would leave (bf16 numbers have two zero parts).
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
