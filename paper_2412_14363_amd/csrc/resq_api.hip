@@ -398,7 +398,8 @@ int resq_pack_weights(const void* w, int64_t ldw, int64_t N, int64_t K, int64_t 
     if (!aligned(w, 2) || !aligned(packed, 256)) return RESQ_ERR_ALIGN;
     const WeightLayout L = make_weight_layout(N, K, r);
     if (packed_bytes < (size_t)L.total_bytes) return RESQ_ERR_BUFFER;
-    hipLaunchKernelGGL(pack_weights_kernel, dim3((unsigned)L.n_pad), dim3(kQuantThreads), 0,
+    const bool pieces = aligned(w, 16) && ldw % 8 == 0 && K % 8 == 0 && r % 8 == 0;  // rows of whole 16-byte pieces
+    hipLaunchKernelGGL(pieces ? pack_weights_vec_kernel : pack_weights_kernel, dim3((unsigned)L.n_pad), dim3(kQuantThreads), 0,
                        static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(w), ldw, L,
                        static_cast<uint8_t*>(packed));
     return launch_status();

@@ -966,6 +966,124 @@ __device__ __forceinline__ float fp16_normal_to_f32(uint32_t h) {
     return __uint_as_float((((h >> 10) & 0x1Fu) + 112u) << 23 | (h & 0x3FFu) << 13);
 }
 
+// Eight weights of one group (quant8 for weights: the scale was rounded up to fp16, so quotients stay inside the range
+// unless it was cut off at 65504; they are clipped all the same).  On return the low byte of u[j] holds the code in two's
+// complement (plus 8 for odd j when LOW, the weights' offset-binary storage), and the sums have gained the codes of the even
+// and of the odd columns.
+template <bool LOW>
+__device__ __forceinline__ void quant8_weights(const uint4& v, float scale, float inv, uint32_t (&u)[8], float& even,
+                                               float& odd) {
+    constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23
+    constexpr int qmax = LOW ? kQmaxLo : kQmaxHi;
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    float xs[8], rr[8];
+    bool near_tie[8], any_tie = false;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        xs[j] = __uint_as_float((j & 1) ? (w[j >> 1] & 0xFFFF0000u) : (w[j >> 1] << 16));
+        const float off = LOW && (j & 1) ? 8.0f : 0.0f;
+        const float t = xs[j] * inv;
+        const float uf = __builtin_amdgcn_fmed3f(t, -(float)qmax, (float)qmax) + (kMagic + off);
+        rr[j] = uf - (kMagic + off);            // rint of the clipped quotient, exact
+        near_tie[j] = !(fabsf(t - rr[j]) <= 0.5f - (LOW ? 8.0f : 128.0f) * 9.5367431640625e-07f);
+        any_tie |= near_tie[j];
+        u[j] = __float_as_uint(uf);
+    }
+    if (__builtin_amdgcn_ballot_w64(any_tie) != 0) {  // wave-uniform, then per element slot, as in quant8
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (__builtin_amdgcn_ballot_w64(near_tie[j]) != 0) {
+                const int c = quant_code(xs[j], scale, qmax);
+                u[j] = (uint32_t)(c + (LOW && (j & 1) ? 8 : 0));
+                rr[j] = (float)c;
+            }
+        }
+    }
+    even += (rr[0] + rr[2]) + (rr[4] + rr[6]);
+    odd += (rr[1] + rr[3]) + (rr[5] + rr[7]);
+}
+
+// Rows of whole 16-byte pieces (w 16-byte aligned, ldw, K and r multiples of 8): a thread takes units of eight columns, as
+// the per-token kernels do, and their fast quantizer.  The other kernel's units of 32 low codes left more than half of the
+// threads of a 4096-wide row idle, with a true division for every code: us, before / now
+// 4096 x 4096 25.6 / 13.7, 28672 x 8192 210 / 124, 1000 x 1000 7.2 / 4.3.
+__global__ __launch_bounds__(kQuantThreads) void pack_weights_vec_kernel(
+    const uint16_t* __restrict__ w, int64_t ldw, WeightLayout L, uint8_t* __restrict__ packed) {
+    __shared__ float red[8];
+    __shared__ int red_sum[3 * 4];
+    const int64_t n = blockIdx.x;  // 0 .. n_pad - 1
+    const int t = threadIdx.x;
+    const int hi_units = (int)(L.r >> 3), units = (int)(L.K >> 3);
+    uint16_t* sw_hi = reinterpret_cast<uint16_t*>(packed + L.scale_off);
+    uint16_t* sw_lo = sw_hi + L.n_pad;
+    const bool live = n < L.N;
+    const uint4* row = reinterpret_cast<const uint4*>(w + (live ? n : 0) * ldw);
+    float amax_h = 0.0f, amax_l = 0.0f;
+    constexpr int kHeld = 2;   // units a thread keeps in registers between the passes; wider rows are read again
+    uint4 held[kHeld];
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i) {
+        const int u = t + i * kQuantThreads;
+        held[i] = live && u < units ? row[u] : make_uint4(0u, 0u, 0u, 0u);
+        const float a = absmax8(held[i]);
+        if (u < hi_units) amax_h = fmaxf(amax_h, a);
+        else amax_l = fmaxf(amax_l, a);
+    }
+    if (live)
+        for (int u = t + kHeld * kQuantThreads; u < units; u += kQuantThreads) {
+            const float a = absmax8(row[u]);
+            if (u < hi_units) amax_h = fmaxf(amax_h, a);
+            else amax_l = fmaxf(amax_l, a);
+        }
+    block_max2(amax_h, amax_l, red);
+    const uint16_t hh = fp16_round_up(group_scale(amax_h, kQmaxHi));
+    const uint16_t hl = fp16_round_up(group_scale(amax_l, kQmaxLo));
+    const float sh = fp16_normal_to_f32(hh), sl = fp16_normal_to_f32(hl);
+    const float inv_h = 1.0f / sh, inv_l = 1.0f / sl;
+    if (t == 0) {
+        sw_hi[n] = (live && L.r > 0) ? hh : (uint16_t)0x3C00u;      // 1.0
+        sw_lo[n] = (live && L.K - L.r > 0) ? hl : (uint16_t)0x3C00u;
+    }
+    // rows of padding channels are all zeros, whose codes are those of the padding
+    uint8_t* const hi = packed + hi_byte_offset(L, n, 0);
+    uint8_t* const lo = packed + lo_byte_offset(L, n, 0);
+    auto in_row = [](int b) { return (b >> 6) * kBlockBytes + (b & 63); };   // byte b of a row, from its first one
+    float hi_even = 0.0f, hi_odd = 0.0f, lo_even = 0.0f, lo_odd = 0.0f;
+    auto pack_unit = [&](int u, const uint4& v) __attribute__((always_inline)) {
+        uint32_t c[8];
+        if (u < hi_units) {
+            quant8_weights<false>(v, sh, inv_h, c, hi_even, hi_odd);
+            *reinterpret_cast<uint2*>(hi + in_row(u * 8)) =
+                make_uint2(pack_low_bytes(c[0], c[1], c[2], c[3]), pack_low_bytes(c[4], c[5], c[6], c[7]));
+        } else {
+            quant8_weights<true>(v, sl, inv_l, c, lo_even, lo_odd);
+            uint32_t by[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) by[k] = (c[2 * k] << 4) | c[2 * k + 1];   // (even code) << 4 | (odd code + 8)
+            *reinterpret_cast<uint32_t*>(lo + in_row((u - hi_units) * 4)) = pack_low_bytes(by[0], by[1], by[2], by[3]);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < kHeld; ++i)
+        if (t + i * kQuantThreads < units) pack_unit(t + i * kQuantThreads, held[i]);
+    for (int u = t + kHeld * kQuantThreads; u < units; u += kQuantThreads)
+        pack_unit(u, live ? row[u] : make_uint4(0u, 0u, 0u, 0u));
+    for (int b = (int)L.r + 8 * t; b < (int)L.kh_pad; b += 8 * kQuantThreads)
+        *reinterpret_cast<uint2*>(hi + in_row(b)) = make_uint2(0u, 0u);
+    for (int b = (int)(L.K - L.r) / 2 + 4 * t; b < (int)(L.kl_pad / 2); b += 4 * kQuantThreads)
+        *reinterpret_cast<uint32_t*>(lo + in_row(b)) = 0x08080808u;
+    const int s[3] = {wave_sum((int)lo_even), wave_sum((int)(hi_even + hi_odd)), wave_sum((int)(lo_even + lo_odd))};
+    if ((t & 63) == 0)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) red_sum[4 * k + (t >> 6)] = s[k];
+    __syncthreads();
+    if (t < 3) {
+        int32_t* sums = reinterpret_cast<int32_t*>(packed + L.scale_off + 4 * L.n_pad);
+        sums[t * L.n_pad + n] = red_sum[4 * t] + red_sum[4 * t + 1] + red_sum[4 * t + 2] + red_sum[4 * t + 3];
+    }
+}
+
+// Any K, r and alignment.
 __global__ __launch_bounds__(kQuantThreads) void pack_weights_kernel(
     const uint16_t* __restrict__ w, int64_t ldw, WeightLayout L, uint8_t* __restrict__ packed) {
     __shared__ float red[8];
@@ -978,14 +1096,10 @@ __global__ __launch_bounds__(kQuantThreads) void pack_weights_kernel(
     const bool live = n < L.N;
     const uint16_t* row = w + (live ? n : 0) * ldw;
 
-    // rows that can be read 16 bytes at a time (every vector then lies inside one group)
-    const bool vec = (reinterpret_cast<uintptr_t>(w) & 15) == 0 && ldw % 8 == 0 && K % 8 == 0 && r % 8 == 0;
-    const uint4* row4 = reinterpret_cast<const uint4*>(row);
     // eight consecutive weights from column k on (zero where the row or the group has ended)
     auto load8 = [&](int k, int end, uint16_t (&e)[8]) __attribute__((always_inline)) {
-        if (vec) {
-            uint4 v = make_uint4(0u, 0u, 0u, 0u);
-            if (k < end) v = row4[k >> 3];
+        if (k + 8 <= end) {
+            const uint4 v = load16_any(row + k);
             const uint32_t ww[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
             for (int j = 0; j < 8; ++j) e[j] = (uint16_t)(ww[j >> 1] >> (16 * (j & 1)));
@@ -996,18 +1110,10 @@ __global__ __launch_bounds__(kQuantThreads) void pack_weights_kernel(
     };
     float amax_h = 0.0f, amax_l = 0.0f;
     if (live) {
-        if (vec) {
-            for (int u = t; u < (K >> 3); u += kQuantThreads) {
-                const float a = absmax8(row4[u]);
-                if (u < (r >> 3)) amax_h = fmaxf(amax_h, a);
-                else amax_l = fmaxf(amax_l, a);
-            }
-        } else {
-            for (int k = t; k < K; k += kQuantThreads) {
-                const float a = bf16_bits_to_f32(row[k] & 0x7FFFu);
-                if (k < r) amax_h = fmaxf(amax_h, a);
-                else amax_l = fmaxf(amax_l, a);
-            }
+        for (int k = t; k < K; k += kQuantThreads) {
+            const float a = bf16_bits_to_f32(row[k] & 0x7FFFu);
+            if (k < r) amax_h = fmaxf(amax_h, a);
+            else amax_l = fmaxf(amax_l, a);
         }
     }
     block_max2(amax_h, amax_l, red);

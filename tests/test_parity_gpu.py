@@ -255,6 +255,28 @@ def test_pack_weights_roundtrip(oracle, rq, N, K, r):
     check_weights(oracle, rq, w, r)
 
 
+# Both packing kernels (rows of whole 16-byte pieces and any others): units at the edges of what a thread holds, weights at and
+# beside ties, rows whose scale is cut off at either end of fp16 (codes are clipped there), zero rows, infinities
+@pytest.mark.parametrize("N,K,r", [(40, 4096, 512), (17, 4104, 520), (16, 8192, 0), (20, 256, 256), (33, 8, 8), (18, 4098, 514), (20, 2050, 0), (17, 66, 66)])
+def test_pack_weights_values_at_the_edges(oracle, rq, N, K, r):
+    g = torch.Generator().manual_seed(N + K)
+    w = torch.randn(N, K, generator=g) * 0.02
+    w[0] = torch.randint(-14, 15, (K,), generator=g).float() * 0.5     # halves: ties of the low group at scale 1
+    w[0, K - 1] = 7.0
+    w[1] *= 1e-9
+    w[2] *= 1e9
+    w[3] = 0.0
+    w[4, 0], w[4, K - 1] = float("inf"), float("-inf")
+    w[5] = torch.randint(-254, 255, (K,), generator=g).float() * 0.5
+    w[5, 0] = 127.0
+    w = w.bfloat16()
+    check_weights(oracle, rq, w, r)
+    wide = torch.zeros(N, K + 8, dtype=torch.bfloat16, device="cuda")   # strided rows, from an odd address
+    for off in (0, 3):
+        wide[:, off:off + K] = w.cuda()
+        assert torch.equal(rq.resq_pack_weights(wide[:, off:off + K], r), rq.resq_pack_weights(w.cuda(), r))
+
+
 # ---- the layer -------------------------------------------------------------
 
 def test_layer_tiny_config(oracle, rq):
