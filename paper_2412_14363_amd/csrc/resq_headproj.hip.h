@@ -47,8 +47,9 @@ struct HeadProjArgs {
     int vec_store;  // y and ldy allow D / 16-byte stores
 };
 
+// second launch bound: three workgroups to a compute unit, the launch's grid
 template <int D>
-__global__ __launch_bounds__(kHeadProjThreads) void head_project_kernel(const HeadProjArgs a) {
+__global__ __launch_bounds__(kHeadProjThreads, 3) void head_project_kernel(const HeadProjArgs a) {
     static_assert(D == 64 || D == 128, "d_head");
     constexpr int KS = D / 64;     // steps of the reduction axis
     constexpr int NT = D / 16;     // 16-channel tiles = consecutive channels per lane
@@ -82,6 +83,26 @@ __global__ __launch_bounds__(kHeadProjThreads) void head_project_kernel(const He
         amax = fmaxf(amax, lane_xor<32>(amax));
         st = group_scale(amax, kQmaxHi);
         const float inv = 1.0f / st;
+        // wave-uniform: the quotients (see resq_quantize.hip.h), or, where a row's scale is at an end of the range, quant8
+        if (__builtin_amdgcn_ballot_w64(!quotient_range(st)) == 0) {
+            constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: rounds to an integer in the low bits
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {   // four columns at a time: registers
+                    const uint4& u4 = rowv[2 * s + (k >> 1)];
+                    const uint32_t w[2] = {k & 1 ? u4.z : u4.x, k & 1 ? u4.w : u4.y};
+                    uint32_t code[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float x = __uint_as_float((j & 1) ? (w[j >> 1] & 0xFFFF0000u) : (w[j >> 1] << 16));
+                        code[j] = __float_as_uint(quotient(x, st, inv) + kMagic);
+                    }
+                    qa[s][k] = (int)pack_low_bytes(code[0], code[1], code[2], code[3]);
+                }
+            }
+            return;
+        }
         float unused = 0.0f;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {

@@ -229,6 +229,22 @@ __device__ __forceinline__ void quant8_asym(const uint4& v, float zero, float sc
     if (LOW) odd_sum += (rr[1] + rr[3]) + (rr[5] + rr[7]);
 }
 
+// The correctly rounded quotient x / scale, as the division gives it, from inv = RN(1 / scale) in five operations (Markstein,
+// "Computation of elementary functions on the IBM RISC System/6000 processor", 1990): q1 is within 2^-47 of the quotient before
+// its rounding, so within one unit of the last place after it, and such a quotient refined once more with its exact remainder
+// is RN(x / scale).  Needs a scale inside quotient_range (then no remainder of a quotient of a quarter or more underflows, and
+// smaller ones round to 0 whatever their last bits) and finite x.  In rows of a head 70 % of the wavefronts hold a near-tie
+// in any eight columns, so that no near-tie has to be looked for is worth more than the four operations: head projection of
+// 81920 rows of 128 12.5 -> 11.0 us, of 40 rows 4.9 -> 3.8.  (The K/V quantizer measured equal, 5.05 / 5.0 us for 32768 rows: left.)
+__device__ __forceinline__ float quotient(float x, float scale, float inv) {
+    const float q0 = x * inv;
+    const float q1 = fmaf(fmaf(-q0, scale, x), inv, q0);
+    return fmaf(fmaf(-q1, scale, x), inv, q1);
+}
+constexpr float kQuotientMin = 8.077935669463161e-28f;   // 2^-90
+constexpr float kQuotientMax = 1.2676506002282294e+30f;  // 2^100
+__device__ __forceinline__ bool quotient_range(float scale) { return scale >= kQuotientMin && scale <= kQuotientMax; }
+
 // low bytes of four registers -> one dword
 __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
     return __builtin_amdgcn_perm(b, a, 0x0c0c0400u) | __builtin_amdgcn_perm(d, c, 0x04000c0cu);

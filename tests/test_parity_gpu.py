@@ -1131,6 +1131,32 @@ def test_project_heads_fused(oracle, rq, rows, d, ldx_extra, ldy_extra):
     assert torch.equal(y, two)
 
 
+# Rows whose codes come from refined quotients, and beside them in one wavefront rows whose scale is at or past either end of
+# what these take: the codes, and with them the outputs, of the row quantizer and the layer
+@pytest.mark.parametrize("d", [64, 128])
+def test_project_heads_scales_and_ties(rq, d):
+    g = torch.Generator().manual_seed(d)
+    rows = 6000
+    x = torch.randint(-254, 255, (rows, d), generator=g).float() * 0.5     # every quotient of a scale of 1 a half or whole number
+    x[:, 0] = 127.0
+    x[2000:4000] = torch.randn(2000, d, generator=g)
+    x *= torch.exp2(torch.randint(-20, 20, (rows, 1), generator=g).float())
+    for k, e in enumerate((-133, -126, -97, -96, -91, -90, -89, -84, -83, 92, 93, 94, 99, 100, 101, 119)):
+        x[4000 + k * 16] = torch.randn(d, generator=g).clamp(-1, 1) * 2.0 ** e
+        x[4300 + k * 16:4316 + k * 16] = torch.randn(16, d, generator=g).clamp(-1, 1) * 2.0 ** e
+    x[5000] = 0.0
+    x = x.bfloat16().cuda()
+    packed = rq.resq_pack_weights((torch.randn(d, d, generator=g) / d ** 0.5).bfloat16().cuda(), d)
+    two = rq.resq_gemm_mixed(rq.resq_quantize_act(x, d), packed, d)
+    assert torch.equal(rq.resq_project_heads(x, packed), two)
+    x[100, 3], x[117, 5] = float("inf"), float("nan")
+    two = rq.resq_gemm_mixed(rq.resq_quantize_act(x, d), packed, d)
+    got = rq.resq_project_heads(x, packed)
+    fine = torch.ones(rows, dtype=torch.bool)
+    fine[100] = fine[117] = False
+    assert torch.equal(got[fine], two[fine])
+
+
 def test_project_heads_no_rows(rq):
     packed = rq.resq_pack_weights(torch.eye(128, dtype=torch.bfloat16, device="cuda"), 128)
     y = rq.resq_project_heads(torch.empty((0, 128), dtype=torch.bfloat16, device="cuda"), packed)
