@@ -344,19 +344,26 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
             for (int e = 0; e < 8; ++e) cu[h][e] = row[e * g.ldu + u_col];
         }
     };
-    // The last chunk of a reduction axis that ends inside it (on a whole piece): zeros for a, the last row of u again.
+    // The first two and the last four chunks; the last one may end inside (on a whole piece): zeros for a, the last row of u
+    // again.  All from the thread's number anew: kept for here, the addresses would be spilled around the loop.
     auto fetch_any = [&](int64_t tc) __attribute__((always_inline)) {
+        int n = t;
+        asm volatile("" : "+v"(n));
+        const int64_t at = tc + (n & 3) * 8;
 #pragma unroll
         for (int h = 0; h < 4; ++h) {
+            const int64_t i = i0 + (n >> 2) + 64 * h;
             ca[h] = make_uint4(0u, 0u, 0u, 0u);
-            if (tc + ap * 8 < g.T) ca[h] = *reinterpret_cast<const uint4*>(a_base + a_off[h] + 2 * tc);
+            if (at < g.T) ca[h] = *reinterpret_cast<const uint4*>(g.a + (i < g.I ? i : g.I - 1) * g.lda + at);
         }
+        const int64_t j = j0 + (n & 127);
+        const float* col = g.u + (j < g.J ? j : g.J - 1);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const int64_t tt = tc + (bp + 2 * h) * 8 + e;
-                cu[h][e] = g.u[(tt < g.T ? tt : g.T - 1) * g.ldu + j0 + u_col];
+                const int64_t row = tc + (bp + 2 * h) * 8 + e;
+                cu[h][e] = col[(row < g.T ? row : g.T - 1) * g.ldu];
             }
     };
     auto stash = [&](int buf) __attribute__((always_inline)) {
@@ -490,9 +497,11 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
     const bool again = __builtin_amdgcn_readfirstlane(*redo) != 0;
 
     // acc[q][p][v]: column 4 (lane / 16) + v, row lane % 16 of matrix tile (q, p)
+    int n = t;   // as in fetch_any
+    asm volatile("" : "+v"(n));
     auto place = [&](int q, int p, int64_t& i, int64_t& j) __attribute__((always_inline)) {
-        i = i0 + wi * 128 + p * 16 + ol;
-        j = j0 + wj * 64 + q * 16 + 4 * oh;
+        i = i0 + wi * 128 + p * 16 + (n & 15);
+        j = j0 + wj * 64 + q * 16 + 4 * ((n & 63) >> 4);
     };
     // J is a multiple of eight, so four columns are there or none; rows start at any address, see store_piece
     auto store4 = [&](int64_t i, int64_t j, const v4f& c) __attribute__((always_inline)) {
