@@ -930,11 +930,11 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
         pa.lda = lda; pa.ldu = ldu; pa.ldo = ldo;
         pa.I = rows; pa.J = J; pa.T = K;
         // 256 x 128 tiles where they fill the chip, two to a compute unit (128 x 128 / 256 x 128 tiles, us): 4096 x 4096 x 4096, 512 of
-        // them, 390 / 326, 8192 x 4096 x 4096 779 / 631, 5000 x 4096 x 4096, 640, 489 / 469, 8192 x 40 x 8192 73 / 58; half as many are
-        // slower: 4000 x 2000 x 2000 110 / 118, 2048 x 2048 x 2048 61 / 104.  Its reduction ends on whole pieces, its row offsets have 32 bits,
+        // them, 390 / 313, 8192 x 4096 x 4096 765 / 612, 5000 x 4096 x 4096, 640, 490 / 457, 8192 x 40 x 8192 74 / 60; half as many are
+        // slower: 4000 x 2000 x 2000 110 / 118, 2048 x 2048 x 2048 61 / 104.  Its reduction ends on whole pieces, its row offsets have 31 bits,
         // and its second look at sums that are not finite wants a and u as they were.
         const dim3 wide_grid(grid.x, (unsigned)((rows + kProjWideRows - 1) / kProjWideRows), 1);
-        const bool wide = (int64_t)wide_grid.x * wide_grid.y >= 512 && K % 8 == 0 && lda <= (1 << 22) &&
+        const bool wide = (int64_t)wide_grid.x * wide_grid.y >= 512 && K % 8 == 0 && lda <= (1 << 21) && ldu <= (1 << 21) &&
                           !overlap(a, (size_t)rows * lda * 2, out, (size_t)rows * ldo * (out_is_bf16 ? 2 : 4)) &&
                           !overlap(u, (size_t)K * ldu * 4, out, (size_t)rows * ldo * (out_is_bf16 ? 2 : 4));
         if (wide && out_is_bf16) launch(project_split_wide_kernel<true>, wide_grid, dim3(kProjThreads), 0, st, pa);

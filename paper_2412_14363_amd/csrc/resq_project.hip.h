@@ -300,7 +300,7 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_kernel(const Pr
 // for twice the products, and u is split once for 256 rows.  The instruction is v_mfma_f32_16x16x32_bf16, which alone
 // sustains 1980 TFLOP/s under the power limit where the 32x32x16 one sustains 1755 (random operands, milliseconds).  One
 // chunk is in registers on its way: it is split behind the products of the smallest parts and written, and the chunk after it is
-// asked for behind those of the middle ones.  4096 x 4096 x 4096 390 -> 326 us (1265 TFLOP/s of bf16 products), error against 64
+// asked for behind those of the middle ones.  4096 x 4096 x 4096 390 -> 313 us (1317 TFLOP/s of bf16 products), error against 64
 // bits with fp32 output 7.02e-7 -> 7.01e-7, at K = 256 1.65e-7 -> 1.60e-7 (one rounding per 32 products instead of 16).
 constexpr int kProjWideRows = 256;
 constexpr int kProjWidePieceA = kProjWideRows * 16;
@@ -316,7 +316,7 @@ __device__ __forceinline__ void mfma_16x16x32_bf16(v4f& acc, const v8bf& b, cons
 template <bool OUT_BF16>
 __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(const ProjectArgs g) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * kProjWideBytes];
-    const int t = threadIdx.x, lane = t & 63;
+    const int t = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wi = wave >> 1, wj = wave & 1;
     const int64_t i0 = (int64_t)blockIdx.y * kProjWideRows, j0 = (int64_t)blockIdx.x * kProjTile;
@@ -330,18 +330,25 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
         const int64_t i = i0 + ar + 64 * h;
         a_off[h] = (uint32_t)(((i < g.I ? i : g.I - 1) - i0) * g.lda + ap * 8) * 2;
     }
-    const uint32_t u_col = (uint32_t)((j0 + bj < g.J ? j0 + bj : g.J - 1) - j0);
+    const uint32_t u_off = (uint32_t)((j0 + bj < g.J ? j0 + bj : g.J - 1) - j0) * 4;
     const uint8_t* a_base = reinterpret_cast<const uint8_t*>(g.a + i0 * g.lda);
     uint4 ca[4];     // the chunk on its way from memory to LDS
     float cu[2][8];
+    // Buffer loads: a base in scalar registers, a per-lane offset that never changes and a scalar one (given pointers, the
+    // compiler adds up 64-bit addresses per load and lane, and spills some: 4096 x 4096 x 4096 325 us, so 313).
     auto fetch = [&](int64_t tc) __attribute__((always_inline)) {
+        const __amdgpu_buffer_rsrc_t ra = make_rsrc(a_base + 2 * tc);
 #pragma unroll
-        for (int h = 0; h < 4; ++h) ca[h] = *reinterpret_cast<const uint4*>(a_base + a_off[h] + 2 * tc);
+        for (int h = 0; h < 4; ++h) {
+            const auto v = __builtin_amdgcn_raw_buffer_load_b128(ra, (int)a_off[h], 0, 0);
+            ca[h] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const float* row = g.u + (tc + (bp + 2 * h) * 8) * g.ldu + j0;   // wave-uniform
+            const __amdgpu_buffer_rsrc_t ru = make_rsrc(g.u + (tc + (bp + 2 * h) * 8) * g.ldu + j0);   // wave-uniform
 #pragma unroll
-            for (int e = 0; e < 8; ++e) cu[h][e] = row[e * g.ldu + u_col];
+            for (int e = 0; e < 8; ++e)
+                cu[h][e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ru, (int)u_off, e * (int)g.ldu * 4, 0));
         }
     };
     // The first two and the last four chunks; the last one may end inside (on a whole piece): zeros for a, the last row of u
@@ -366,13 +373,15 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
                 cu[h][e] = col[(row < g.T ? row : g.T - 1) * g.ldu];
             }
     };
-    auto stash = [&](int buf) __attribute__((always_inline)) {
+    // (n: the thread's number, here and below)
+    auto stash = [&](int buf, int n) __attribute__((always_inline)) {
         uint8_t* base = lds + buf * kProjWideBytes;
+        const int row = n >> 2, piece = n & 3;
 #pragma unroll
         for (int h = 0; h < 4; ++h)
-            *reinterpret_cast<uint4*>(base + ap * kProjWidePieceA + ((ar ^ (4 * ap)) + 64 * h) * 16) = ca[h];   // rows of four pieces side by side
+            *reinterpret_cast<uint4*>(base + piece * kProjWidePieceA + ((row ^ (4 * piece)) + 64 * h) * 16) = ca[h];   // rows of four pieces side by side
 #pragma unroll
-        for (int h = 0; h < 2; ++h) stash_split(base + kProjWideBytesA + (bp + 2 * h) * kProjPieceB + bj * 16, cu[h]);
+        for (int h = 0; h < 2; ++h) stash_split(base + kProjWideBytesA + (bp + 2 * h) * kProjPieceB + (n & 127) * 16, cu[h]);
     };
 
     // acc[q][p]: columns 16 q .., rows 16 p .. of the wavefront's 128 x 64
@@ -381,22 +390,24 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int p = 0; p < 8; ++p) acc[q][p] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-    const int ol = lane & 15, oh = lane >> 4;   // row (column) of a fragment, piece along the reduction
+    // row (column) of a fragment: lane % 16, piece along the reduction: lane / 16
     static_assert(kProjChunk == 32, "an instruction takes a whole chunk");
     v8bf fa[8], fb[2][4];
-    auto read_a = [&](int buf) __attribute__((always_inline)) {
+    auto read_a = [&](int buf, int n) __attribute__((always_inline)) {
+        const int ol = n & 15, oh = (n & 63) >> 4;
         const uint8_t* base = lds + buf * kProjWideBytes + oh * kProjWidePieceA + (wi * 128 + (ol ^ (4 * oh))) * 16;
 #pragma unroll
         for (int p = 0; p < 8; ++p) fa[p] = *reinterpret_cast<const v8bf*>(base + p * 256);
     };
-    auto read_b = [&](int part, int set, int buf) __attribute__((always_inline)) {
+    auto read_b = [&](int part, int set, int buf, int n) __attribute__((always_inline)) {
+        const int ol = n & 15, oh = (n & 63) >> 4;
         const uint8_t* base = lds + buf * kProjWideBytes + kProjWideBytesA + part * kProjSplitB + oh * kProjPieceB + (wj * 64 + ol) * 16;
 #pragma unroll
         for (int q = 0; q < 4; ++q) fb[set][q] = *reinterpret_cast<const v8bf*>(base + q * 256);
     };
     // Product K of a part: tile (q, p) = (K / 8, K % 8), u as first operand, so that a lane ends with four consecutive
     // columns of a row.  As in resq_gemm.hip.h the instruction is assembly with its tile in place in accumulation
-    // registers: given the builtin, the compiler renames the tiles and spills (8192 x 4096 x 4096 1244 us, this 631).
+    // registers: given the builtin, the compiler renames the tiles and spills (8192 x 4096 x 4096 1244 us, this 612).
     auto product = [&](auto k, int set) __attribute__((always_inline)) {
         constexpr int K = decltype(k)::value;
         mfma_16x16x32_bf16(acc[K >> 3][K & 7], fb[set][K >> 3], fa[K & 7]);
@@ -425,12 +436,12 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
     // Chunk i is multiplied out of buffer i % 2, the smallest parts of u first, while chunk i + 1 is split and written
     // into the other one and chunk i + 2 sets out.
     fetch_any(0);
-    stash(0);
+    stash(0, t);
     fetch_any(kProjChunk);
     __syncthreads();
     auto step = [&](int64_t tc, int buf) __attribute__((always_inline)) {
-        read_a(buf);
-        read_b(2, 0, buf);
+        read_a(buf, t);
+        read_b(2, 0, buf, t);
         __builtin_amdgcn_sched_barrier(0);
         uint8_t* const to = lds + (buf ^ 1) * kProjWideBytes;
         static_for<32>([&](auto k_) __attribute__((always_inline)) {
@@ -448,13 +459,13 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
                 constexpr int H = K / 6;
                 *reinterpret_cast<uint4*>(to + ap * kProjWidePieceA + ((ar ^ (4 * ap)) + 64 * H) * 16) = ca[H];
             }
-            if constexpr (K == 25) read_b(1, 1, buf);
+            if constexpr (K == 25) read_b(1, 1, buf, t);
             __builtin_amdgcn_sched_barrier(0);
         });
         static_for<32>([&](auto k_) __attribute__((always_inline)) {
             constexpr int K = decltype(k_)::value;
             product(k_, 1);
-            if constexpr (K == 1) read_b(0, 0, buf);
+            if constexpr (K == 1) read_b(0, 0, buf, t);
             if constexpr (K == 3) fetch(tc + 2 * kProjChunk);
             if constexpr (K == 1 || K == 3) __builtin_amdgcn_sched_barrier(0);
         });
@@ -468,15 +479,17 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
         step(tc + kProjChunk, 1);
     }
     for (int buf = 0; tc < g.T; tc += kProjChunk, buf ^= 1) {   // up to four chunks are left, the last one perhaps ragged
-        read_a(buf);
-        read_b(2, 0, buf);
-        read_b(1, 1, buf);
+        int n = t;   // as in fetch_any
+        asm volatile("" : "+v"(n));
+        read_a(buf, n);
+        read_b(2, 0, buf, n);
+        read_b(1, 1, buf, n);
         multiply(0);
-        read_b(0, 0, buf);
+        read_b(0, 0, buf, n);
         multiply(1);
         multiply(0);
         if (tc + kProjChunk < g.T) {
-            stash(buf ^ 1);
+            stash(buf ^ 1, n);
             fetch_any(tc + 2 * kProjChunk);
             __syncthreads();
         }
