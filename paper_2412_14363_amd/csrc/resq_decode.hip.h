@@ -101,8 +101,11 @@ __device__ __forceinline__ void take_channel_consts(EpilogueConsts& c, const Cha
     c.ev[3] = h.even.w;
 }
 __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
-    const int32_t* wsum_hi = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 8 * a.L.n_pad);
-    const int32_t* wsum_lo = wsum_hi + a.L.n_pad;
+    const uint16_t* sw_hi = reinterpret_cast<const uint16_t*>(a.packed + a.L.scale_off);
+    const uint16_t* sw_lo = sw_hi + a.L.n_pad;
+    const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
+    const int32_t* wsum_hi = even_sum + a.L.n_pad;
+    const int32_t* wsum_lo = even_sum + 2 * a.L.n_pad;
     const bool has_hi = a.L.r > 0, has_lo = a.L.K - a.L.r > 0;
     const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
     EpilogueConsts c;
@@ -111,7 +114,21 @@ __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs&
     c.ca = has_lo ? a.lo_sum[tok] : 0;
     c.cth = (asym && has_hi) ? a.c_hi[tok] : 0.f;
     c.ctl = (asym && has_lo) ? a.c_lo[tok] : 0.f;
-    take_channel_consts(c, load_channel_consts(a, n));
+    const uint2 sch = *reinterpret_cast<const uint2*>(sw_hi + n);
+    const uint2 scl = *reinterpret_cast<const uint2*>(sw_lo + n);
+    const int4 es = *reinterpret_cast<const int4*>(even_sum + n);
+    c.snh[0] = fp16_bits_to_f32(sch.x & 0xFFFFu);
+    c.snh[1] = fp16_bits_to_f32(sch.x >> 16);
+    c.snh[2] = fp16_bits_to_f32(sch.y & 0xFFFFu);
+    c.snh[3] = fp16_bits_to_f32(sch.y >> 16);
+    c.snl[0] = fp16_bits_to_f32(scl.x & 0xFFFFu);
+    c.snl[1] = fp16_bits_to_f32(scl.x >> 16);
+    c.snl[2] = fp16_bits_to_f32(scl.y & 0xFFFFu);
+    c.snl[3] = fp16_bits_to_f32(scl.y >> 16);
+    c.ev[0] = es.x;
+    c.ev[1] = es.y;
+    c.ev[2] = es.z;
+    c.ev[3] = es.w;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         c.wsh[v] = asym ? wsum_hi[n + v] : 0;
