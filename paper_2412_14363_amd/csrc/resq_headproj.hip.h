@@ -76,15 +76,20 @@ __global__ __launch_bounds__(kHeadProjThreads, 3) void head_project_kernel(const
 
     // quantize the 16 x D values a wavefront holds: row scale and the operand of each step
     auto quantize_tile = [&](const uint4 (&rowv)[UNITS], v4i (&qa)[KS], float& st) {
-        float amax = 0.0f;
+        float amax = 0.0f, all = 0.0f;   // a unit that holds a NaN stays out of the maximum, but not out of the sum
 #pragma unroll
-        for (int u = 0; u < UNITS; ++u) amax = fmaxf(amax, absmax8(rowv[u]));
+        for (int u = 0; u < UNITS; ++u) {
+            const float m = absmax8(rowv[u]);
+            amax = fmaxf(amax, m);
+            all += m;
+        }
         amax = fmaxf(amax, lane_xor<16>(amax));
         amax = fmaxf(amax, lane_xor<32>(amax));
         st = group_scale(amax, kQmaxHi);
         const float inv = 1.0f / st;
-        // wave-uniform: the quotients (see resq_quantize.hip.h), or, where a row's scale is at an end of the range, quant8
-        if (__builtin_amdgcn_ballot_w64(!quotient_range(st)) == 0) {
+        // wave-uniform: the quotients (see resq_quantize.hip.h), or quant8, where a row's scale is at an end of the range
+        // or a value is not finite (quant8 gives a NaN the lowest code, as the row quantizer does)
+        if (__builtin_amdgcn_ballot_w64(!quotient_range(st) || all != all) == 0) {
             constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: rounds to an integer in the low bits
 #pragma unroll
             for (int s = 0; s < KS; ++s) {

@@ -1157,6 +1157,25 @@ def test_project_heads_scales_and_ties(rq, d):
     assert torch.equal(got[fine], two[fine])
 
 
+# Rows with a NaN at each place of a lane's piece, and the neighbours in the wavefront of these and of rows with an infinity
+# (whose own outputs, codes of finite values times an infinite scale, are nobody's): what the row quantizer and the layer give
+@pytest.mark.parametrize("d", [64, 128])
+def test_project_heads_not_finite(rq, d):
+    g = torch.Generator().manual_seed(d + 1)
+    x = torch.randn(40 * d, d, generator=g).clamp(-3, 3)
+    for k in range(d):
+        x[40 * k, (k + 8) % d] = 3.5   # the maximum is in another unit than the NaN, which takes its own unit out of it
+        x[40 * k, k] = float("nan")
+        x[40 * k + 21, k] = (-1.0) ** k * float("inf")
+    x[7, :d // 2], x[23] = float("nan"), float("inf")
+    x = x.bfloat16().cuda()
+    packed = rq.resq_pack_weights((torch.randn(d, d, generator=g) / d ** 0.5).bfloat16().cuda(), d)
+    two = rq.resq_gemm_mixed(rq.resq_quantize_act(x, d), packed, d)
+    got = rq.resq_project_heads(x, packed)
+    scaled = ~x.isinf().any(1)
+    assert torch.equal(got[scaled], two[scaled]) and two[scaled].isfinite().all()
+
+
 def test_project_heads_no_rows(rq):
     packed = rq.resq_pack_weights(torch.eye(128, dtype=torch.bfloat16, device="cuda"), 128)
     y = rq.resq_project_heads(torch.empty((0, 128), dtype=torch.bfloat16, device="cuda"), packed)
