@@ -220,6 +220,19 @@ __device__ __forceinline__ void mfma_16x16x64(v4i& acc, const v4i& b, const v4i&
     asm volatile("v_mfma_i32_16x16x64_i8 %0, %1, %2, %0" : "+a"(acc) : "v"(b), "v"(a));
 }
 
+// Long enough for the last of them to have written its tile.  The wait names no register and the compiler sees no matrix
+// instruction, so it moves plain reads of a tile in front of the wait: tiles are tied down behind it (an empty assembly
+// statement with the tile as in/out operand) or read with from_acc.
+__device__ __forceinline__ void wait_for_products() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
+// one accumulation register, read where this is written (left to itself the compiler copies whole
+// tiles ahead and spills, also where they are tied down behind the wait all at once)
+__device__ __forceinline__ int from_acc(int e) {
+    int x;
+    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(e));
+    return x;
+}
+
 // Keeps the instructions that compute x where they are written, between the assembly
 // statements around them: the matrix instruction above is opaque to the compiler, which
 // therefore neither knows that an operand written by the vector ALU needs two wait states
@@ -576,7 +589,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
                 for (int v = 0; v < 4; ++v) {
                     val[v] = 0.f;
                     if constexpr (HI_ON) {
-                        const int ih = acc_hi[j][i][v];
+                        const int ih = from_acc(acc_hi[j][i][v]);
                         val[v] = (float)ih * (st_hi[i] * sn_hi[v]);
                         if constexpr (ASYM) val[v] += ct_hi[i] * zw_hi[v];
                         if constexpr (DBG) {
@@ -584,7 +597,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
                         }
                     }
                     if constexpr (LO_ON) {
-                        int il = acc_lo[j][i][v] - (ev[v] * 128 + ca[i]);
+                        int il = from_acc(acc_lo[j][i][v]) - (ev[v] * 128 + ca[i]);
                         if constexpr (DBG) il >>= 4;
                         val[v] += (float)il * (st_lo[i] * sn_lo[v]);
                         if constexpr (ASYM) val[v] += ct_lo[i] * zw_lo[v];
@@ -780,7 +793,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
         lds_wait<0>(p0.a);
         lds_wait<0>(p0.b);
         wait_loads_and_barrier<0>();  // every wave is done reading the stage buffers
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions have written their tiles
+        wait_for_products();
         if (a.swiglu) {  // symmetric codes only (checked on the host)
             if (S_hi > 0 && S_lo > 0) fold(YES{}, YES{}, NO{}, YES{});
             else if (S_hi > 0) fold(YES{}, NO{}, NO{}, YES{});

@@ -79,14 +79,6 @@ __device__ __forceinline__ void widen_f8(v8i& w, const v4i& r, int lo_mask, int 
     pin(w);
 }
 
-// one accumulation register, read where this is written (left to itself the compiler copies whole
-// 16-register tiles ahead and spills)
-__device__ __forceinline__ int from_acc(int e) {
-    int x;
-    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(e));
-    return x;
-}
-
 // a stage's fragments as read: [32-row half][32-byte half of the 64-byte rows]
 struct RawF8 {
     v4i a[2][2];
@@ -480,7 +472,9 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
         if (lane < 32) *reinterpret_cast<uint32_t*>(lds + kMetaOff + kMetaSe + (wm * 64 + wn * 32 + lane) * 4) = sum;
         wait_loads_and_barrier<0>();
         __syncthreads();  // every wave is done reading the stage buffers, and the sums are there
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions have written their tiles
+        wait_for_products();
+        park_hi();
+        park_lo();
         if (a.swiglu) {  // symmetric codes only (checked on the host)
             if (S_hi > 0) fold(YES{}, NO{}, YES{});
             else fold(NO{}, NO{}, YES{});

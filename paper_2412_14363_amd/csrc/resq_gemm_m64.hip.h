@@ -470,7 +470,9 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
             }
         }
         wait_loads_and_barrier<0>();  // every wave is done reading the stage buffers
-        asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions have written their tiles
+        wait_for_products();
+        park(acc_hi);
+        park(acc_lo);
         if constexpr (KS == 2) {
             // The first half folds weight fragments 0, 1 and the second 2, 3: wavefront (half, w)
             // hands the other two of its own (both integer sets, 8 tiles of 1 KiB) to wavefront

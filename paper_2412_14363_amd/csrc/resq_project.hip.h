@@ -495,7 +495,11 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
         }
     }
 
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // the last matrix instructions have written their tiles
+    wait_for_products();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int p = 0; p < 8; ++p) asm volatile("" : "+a"(acc[q][p]));   // read behind the wait, not in front of it
     // any sum that is not finite (0 x it is NaN) sends the whole workgroup to the second way out
     float probe[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};   // eight short chains instead of a long one
 #pragma unroll
