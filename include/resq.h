@@ -380,6 +380,18 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
                       int64_t ldo, void* stream);
 
 /*
+ * Which kernel resq_project_rows runs for these arguments (addresses are compared, nothing is read):
+ * host only, no device call.  For callers that want to know, and for tests.
+ *   kernel  0: fp32 matrix cores
+ *           1: bf16 matrix cores, 128 x 128 tiles
+ *           2: bf16 matrix cores, 256 x 128 tiles, another order of the sum     (written)
+ * Errors as resq_project_rows; RESQ_ERR_NULL for a null kernel.
+ */
+int resq_project_rows_plan(const void* a, int a_is_bf16, int64_t lda, int64_t rows, int64_t K,
+                           const float* u, int64_t ldu, int64_t J, const void* out, int out_is_bf16,
+                           int64_t ldo, int* kernel);
+
+/*
  * The online projection of queries and keys onto the basis of the K/V cache
  * (Section 4.3: after the position embedding each head is multiplied by the
  * d_head x d_head matrix U_C, with 8-bit weights and 8-bit activations), as one

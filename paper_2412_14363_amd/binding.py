@@ -43,6 +43,7 @@ SYMBOLS = {
     "resq_sym_eig": (C.c_int, [_p, _i64, _i64, C.c_int, _p, _p, _i64, _p, _sz, _p]),
     "resq_sym_eig_static": (C.c_int, [_p, _i64, _i64, C.c_int, _p, _p, _i64, _p]),
     "resq_project_rows": (C.c_int, [_p, C.c_int, _i64, _i64, _i64, _p, _i64, _i64, _p, C.c_int, _i64, _p]),
+    "resq_project_rows_plan": (C.c_int, [_p, C.c_int, _i64, _i64, _i64, _p, _i64, _i64, _p, C.c_int, _i64, C.POINTER(C.c_int)]),
     "resq_project_heads": (C.c_int, [_p, _i64, _i64, _i64, _p, _p, _i64, _p]),
     "resq_kv_cache_row_bytes": (_sz, [_i64, _i64]),
     "resq_quantize_kv_cache": (C.c_int, [_p, _i64, _i64, _i64, _i64, _p, _i64, _p]),
@@ -448,6 +449,16 @@ def resq_project_rows(a: torch.Tensor, u: torch.Tensor, out: Optional[torch.Tens
                                  _stream(stream))
     _check(st, "resq_project_rows")
     return out
+
+
+def resq_project_rows_plan(a: torch.Tensor, u: torch.Tensor, out: torch.Tensor) -> int:
+    """The kernel that resq_project_rows uses for these operands (0, 1 or 2, see include/resq.h); host only."""
+    kernel = C.c_int()
+    _check(lib().resq_project_rows_plan(a.data_ptr(), int(a.dtype == torch.bfloat16), a.stride(0), a.shape[0], a.shape[1],
+                                        u.data_ptr(), u.stride(0), u.shape[1], out.data_ptr(),
+                                        int(out.dtype == torch.bfloat16), out.stride(0), C.byref(kernel)),
+           "resq_project_rows_plan")
+    return kernel.value
 
 
 def resq_project_heads(x: torch.Tensor, packed: torch.Tensor, y: Optional[torch.Tensor] = None,

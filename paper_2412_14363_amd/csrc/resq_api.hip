@@ -36,9 +36,15 @@ inline int shape_ok(int64_t rows, int64_t K, int64_t r) {
     return 1;
 }
 
-inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
-    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-    return x < y + nb && y < x + na;
+// whether two row-major blocks share memory (pitch and width of a row in bytes): their address ranges meet and they are not
+// separate column blocks of one matrix
+inline bool blocks_overlap(const void* a, int64_t rows_a, int64_t pitch_a, int64_t width_a, const void* b, int64_t rows_b,
+                           int64_t pitch_b, int64_t width_b) {
+    const int64_t d = (int64_t)(reinterpret_cast<uintptr_t>(b) - reinterpret_cast<uintptr_t>(a));
+    if (d >= (rows_a - 1) * pitch_a + width_a || -d >= (rows_b - 1) * pitch_b + width_b) return false;
+    if (pitch_a != pitch_b) return true;
+    const int64_t shift = (d % pitch_a + pitch_a) % pitch_a;  // b's first column, counted from a's, modulo the row
+    return shift < width_a || shift + width_b > pitch_a;
 }
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? RESQ_OK : RESQ_ERR_HIP; }
@@ -905,8 +911,9 @@ int resq_gram_accumulate(const void* x, int64_t ldx, int64_t T, int64_t K, float
     return launch_status();
 }
 
-int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, int64_t K, const float* u,
-                      int64_t ldu, int64_t J, void* out, int out_is_bf16, int64_t ldo, void* stream) {
+// what resq_project_rows refuses
+static int project_rows_status(const void* a, int64_t lda, int64_t rows, int64_t K, const float* u, int64_t ldu, int64_t J,
+                               const void* out, int out_is_bf16, int64_t ldo) {
     if (rows < 0 || rows > 0x7FFFFFFF || K < 1 || K > kMaxK || J < 1 || J > kMaxK || lda < K || ldu < J || ldo < J)
         return RESQ_ERR_SHAPE;
     if (rows == 0) return RESQ_OK;
@@ -914,29 +921,58 @@ int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, i
     if (!aligned(a, 16) || !aligned(u, 16) || !aligned(out, out_is_bf16 ? 2 : 4) || lda % 8 != 0 ||
         ldu % 8 != 0 || J % 8 != 0)
         return RESQ_ERR_ALIGN;
+    return RESQ_OK;
+}
+
+// Its kernel: 0, products on the fp32 instruction; 1, on the bf16 one in 128 x 128 tiles; 2, in 256 x 128 tiles.
+// bf16 rows: three exact bf16 products instead of one fp32 product (in the
+// tiles and grid of the fp32 kernel 4096 x 4096 x 4096 0.40 ms against 1.19, 256 x 512 x 512 17 us
+// against 56, 128 x 128 x 128 8.4 us against 22); fp32 rows would need at least six, and stay on the
+// fp32 instruction.  So do bf16 rows of one chunk of that kernel: half a chunk of the other, whose
+// ragged end costs more than its products save (16 steps, 128 x 128 outputs 5.5 / 7.1 us, 4096 x 4096 15.6 / 18.6; 17
+// steps 7.0 / 7.2, 20.4 / 18.7).
+// 256 x 128 tiles where they fill the chip, two to a compute unit (128 x 128 / 256 x 128 tiles, us): 4096 x 4096 x 4096, 512 of
+// them, 390 / 313, 8192 x 4096 x 4096 765 / 612, 5000 x 4096 x 4096, 640, 490 / 457, 8192 x 40 x 8192 74 / 60; half as many are
+// slower: 4000 x 2000 x 2000 110 / 118, 2048 x 2048 x 2048 61 / 104.  Its reduction ends on whole pieces, its row offsets have 31 bits,
+// and its second look at sums that are not finite wants a and u as they were.  (The two kernels add in another order, so the
+// choice hangs on the operands themselves, not on what an allocator has put beside them.)
+static int project_rows_kernel(const void* a, int a_is_bf16, int64_t lda, int64_t rows, int64_t K, const float* u, int64_t ldu,
+                               int64_t J, const void* out, int out_is_bf16, int64_t ldo) {
+    if (!a_is_bf16 || K <= kBasisChunk) return 0;
+    const int64_t tiles = ((J + kProjTile - 1) / kProjTile) * ((rows + kProjWideRows - 1) / kProjWideRows);
+    if (tiles < 512 || K % 8 != 0 || lda > (1 << 21) || ldu > (1 << 21)) return 1;
+    const int64_t out_pitch = ldo * (out_is_bf16 ? 2 : 4), out_width = J * (out_is_bf16 ? 2 : 4);
+    if (blocks_overlap(a, rows, 2 * lda, 2 * K, out, rows, out_pitch, out_width) ||
+        blocks_overlap(u, K, 4 * ldu, 4 * J, out, rows, out_pitch, out_width))
+        return 1;
+    return 2;
+}
+
+int resq_project_rows_plan(const void* a, int a_is_bf16, int64_t lda, int64_t rows, int64_t K, const float* u, int64_t ldu,
+                           int64_t J, const void* out, int out_is_bf16, int64_t ldo, int* kernel) {
+    const int st = project_rows_status(a, lda, rows, K, u, ldu, J, out, out_is_bf16, ldo);
+    if (st != RESQ_OK) return st;
+    if (!kernel) return RESQ_ERR_NULL;
+    *kernel = rows == 0 ? 0 : project_rows_kernel(a, a_is_bf16, lda, rows, K, u, ldu, J, out, out_is_bf16, ldo);
+    return RESQ_OK;
+}
+
+int resq_project_rows(const void* a, int a_is_bf16, int64_t lda, int64_t rows, int64_t K, const float* u,
+                      int64_t ldu, int64_t J, void* out, int out_is_bf16, int64_t ldo, void* stream) {
+    const int status = project_rows_status(a, lda, rows, K, u, ldu, J, out, out_is_bf16, ldo);
+    if (status != RESQ_OK || rows == 0) return status;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 grid((unsigned)((J + kBasisTile - 1) / kBasisTile), (unsigned)((rows + kBasisTile - 1) / kBasisTile), 1);
-    // bf16 rows: three exact bf16 products instead of one fp32 product (in the
-    // tiles and grid of the fp32 kernel 4096 x 4096 x 4096 0.40 ms against 1.19, 256 x 512 x 512 17 us
-    // against 56, 128 x 128 x 128 8.4 us against 22); fp32 rows would need at least six, and stay on the
-    // fp32 instruction.  So do bf16 rows of one chunk of that kernel: half a chunk of the other, whose
-    // ragged end costs more than its products save (16 steps, 128 x 128 outputs 5.5 / 7.1 us, 4096 x 4096 15.6 / 18.6; 17
-    // steps 7.0 / 7.2, 20.4 / 18.7)
-    if (a_is_bf16 && K > kBasisChunk) {
+    const int kernel = project_rows_kernel(a, a_is_bf16, lda, rows, K, u, ldu, J, out, out_is_bf16, ldo);
+    if (kernel > 0) {
         ProjectArgs pa;
         pa.a = static_cast<const uint16_t*>(a);
         pa.u = u;
         pa.out = out;
         pa.lda = lda; pa.ldu = ldu; pa.ldo = ldo;
         pa.I = rows; pa.J = J; pa.T = K;
-        // 256 x 128 tiles where they fill the chip, two to a compute unit (128 x 128 / 256 x 128 tiles, us): 4096 x 4096 x 4096, 512 of
-        // them, 390 / 313, 8192 x 4096 x 4096 765 / 612, 5000 x 4096 x 4096, 640, 490 / 457, 8192 x 40 x 8192 74 / 60; half as many are
-        // slower: 4000 x 2000 x 2000 110 / 118, 2048 x 2048 x 2048 61 / 104.  Its reduction ends on whole pieces, its row offsets have 31 bits,
-        // and its second look at sums that are not finite wants a and u as they were.
         const dim3 wide_grid(grid.x, (unsigned)((rows + kProjWideRows - 1) / kProjWideRows), 1);
-        const bool wide = (int64_t)wide_grid.x * wide_grid.y >= 512 && K % 8 == 0 && lda <= (1 << 21) && ldu <= (1 << 21) &&
-                          !overlap(a, (size_t)rows * lda * 2, out, (size_t)rows * ldo * (out_is_bf16 ? 2 : 4)) &&
-                          !overlap(u, (size_t)K * ldu * 4, out, (size_t)rows * ldo * (out_is_bf16 ? 2 : 4));
+        const bool wide = kernel == 2;
         if (wide && out_is_bf16) launch(project_split_wide_kernel<true>, wide_grid, dim3(kProjThreads), 0, st, pa);
         else if (wide) launch(project_split_wide_kernel<false>, wide_grid, dim3(kProjThreads), 0, st, pa);
         else if (out_is_bf16) launch(project_split_kernel<true>, grid, dim3(kProjThreads), 0, st, pa);
@@ -963,17 +999,6 @@ size_t resq_sym_eig_workspace_bytes(int64_t K) {
            round_up(K * (int64_t)sizeof(int), 256) + round_up(kEigMaxSweeps * (int64_t)sizeof(int), 256);
 }
 
-// whether two row-major fp32 blocks of cols columns share memory: their address ranges meet and they are not
-// separate column blocks of one matrix
-static bool blocks_overlap(const float* a, int64_t rows_a, int64_t lda, const float* b, int64_t rows_b, int64_t ldb,
-                           int64_t cols) {
-    const int64_t d = (int64_t)((reinterpret_cast<uintptr_t>(b) - reinterpret_cast<uintptr_t>(a))) / (int64_t)sizeof(float);
-    if (d >= (rows_a - 1) * lda + cols || -d >= (rows_b - 1) * ldb + cols) return false;
-    if (lda != ldb) return true;
-    const int64_t shift = (d % lda + lda) % lda;  // b's first column, counted from a's, modulo the row
-    return shift < cols || shift + cols > lda;
-}
-
 // the Jacobi iteration on a workspace that holds resq_sym_eig_workspace_bytes(K) bytes
 static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int sweeps, float* eigvals, float* p,
                                 int64_t ldp, void* workspace, void* stream) {
@@ -982,7 +1007,8 @@ static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int swee
     // 1.1 to 1.35 ms at n = 128 against 6.9 to 10.5 in two launches a round, by the sweeps that the matrix
     // needs (0.15 / 1.69 ms at n = 32, 0.39 / 4.9 at 64).  Not where an output lies on c: its workgroups all read c at their start and write p and
     // eigvals at their end, in no order among each other; the workspace takes a copy of c first.
-    if (n <= kEigSmallMax && !blocks_overlap(c, K, ldc, p, K, ldp, K) && !blocks_overlap(c, K, ldc, eigvals, 1, K, K)) {
+    if (n <= kEigSmallMax && !blocks_overlap(c, K, 4 * ldc, 4 * K, p, K, 4 * ldp, 4 * K) &&
+        !blocks_overlap(c, K, 4 * ldc, 4 * K, eigvals, 1, 4 * K, 4 * K)) {
         const int small_lds = eig_small_lds_bytes(n);
         if (small_lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void*>(eig_small_kernel),

@@ -148,6 +148,28 @@ def test_project_rows_wide_tiles_infinities_and_in_place(rq):
     assert torch.allclose(buf[want.isfinite()].double(), want[want.isfinite()].double(), rtol=2.0 ** -7, atol=1e-4)
 
 
+# Operands that are column blocks, out in the columns beside a's: the bits of contiguous copies, from the same kernel
+@pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("rows,K,J", [(131072, 72, 128), (131000, 136, 120), (66000, 264, 256)])
+def test_project_rows_wide_tiles_on_column_blocks(rq, rows, K, J, out_dtype):
+    g = torch.Generator(device="cuda").manual_seed(rows + K)
+    per = 2 if out_dtype == torch.float32 else 1   # bf16 columns that an output takes
+    buf = torch.randn(rows, K + 16 + J * per + 8, generator=g, device="cuda").bfloat16()
+    u_buf = torch.randn(K, J + 24, generator=g, device="cuda")
+    a, u = buf[:, 8:8 + K], u_buf[:, 16:16 + J]
+    out = buf.view(out_dtype)[:, (K + 16) // per:(K + 16) // per + J]
+    assert rq.resq_project_rows_plan(a, u, out) == 2
+    a_copy, u_copy = a.contiguous(), u.contiguous()
+    want = torch.empty((rows, J), dtype=out_dtype, device="cuda")
+    assert rq.resq_project_rows_plan(a_copy, u_copy, want) == 2
+    rq.resq_project_rows(a_copy, u_copy, out=want)
+    before = buf.clone()
+    rq.resq_project_rows(a, u, out=out)
+    assert torch.equal(out, want)
+    out.copy_(before.view(out_dtype)[:, (K + 16) // per:(K + 16) // per + J])
+    assert torch.equal(buf.view(torch.int16), before.view(torch.int16))   # nothing beside out
+
+
 # Infinities and NaN in either operand: what a plain sum gives, not the NaN that infinity x 0 among the three
 # parts of u would leave (bf16 numbers have two zero parts).
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])

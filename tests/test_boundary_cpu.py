@@ -186,6 +186,46 @@ def test_basis_entry_points_reject_bad_arguments():
     assert r(P, 1, 64, 0, 64, P, 64, 64, P, 1, 64, None) == 0
 
 
+def project_plan(rows, K, J, lda=None, ldu=None, ldo=None, bf16=1, out_bf16=1, a=P, u=1 << 44, out=1 << 45):
+    kernel = C.c_int(-1)
+    st = binding.lib().resq_project_rows_plan(a, bf16, lda or (K + 7) // 8 * 8, rows, K, u, ldu or J, J, out, out_bf16, ldo or J,
+                                              C.byref(kernel))
+    return kernel.value if st == 0 else -st
+
+
+def test_project_rows_plan():
+    assert project_plan(4096, 4096, 4096) == 2 and project_plan(4096, 4096, 4096, out_bf16=0) == 2
+    assert project_plan(4096, 4096, 4096, bf16=0) == 0 and project_plan(4096, 16, 4096) == 0 and project_plan(40, 17, 8) == 1
+    assert project_plan(3840, 4096, 4096) == 1                                   # 480 tiles of 256 x 128
+    assert project_plan(4096, 4090, 4096) == 1                                   # no whole pieces
+    assert project_plan(4096, 4096, 4096, lda=(1 << 21) + 8) == 1 and project_plan(4096, 4096, 4096, ldu=(1 << 21) + 8) == 1
+    assert project_plan(0, 64, 64) == 0 and project_plan(8, 64, 60) == -3 and project_plan(8, 64, 64, ldu=56) == -2
+    assert project_plan(8, 64, 64, out=None) == -1
+    assert binding.lib().resq_project_rows_plan(P, 1, 64, 8, 64, P, 64, 64, P, 1, 64, None) == 1
+
+
+def test_project_rows_kernel_hangs_on_the_operands_alone():
+    """Where out lies beside a or u, in the same buffer or behind their last element, the 256 x 128 tiles run as they do
+    anywhere else; where it lies on them, the others."""
+    rows, K, J = 131072, 72, 128
+    for esize in (2, 4):
+        plan = lambda out, ldo=J, **kw: project_plan(rows, K, J, out=out, ldo=ldo, out_bf16=int(esize == 2), **kw)
+        # column blocks of one buffer whose rows have 1024 bytes: out behind a, out in front of it
+        block = dict(ldo=1024 // esize, lda=512)
+        assert plan(P + 2 * K, **block) == 2 and plan(P + 2 * K - esize, **block) == 1
+        assert plan(P, a=P + J * esize, **block) == 2 and plan(P, a=P + J * esize - 16, **block) == 1
+        # behind the last element of a column block, before the end of its last row; and in front of the first
+        end = P + ((rows - 1) * 512 + K) * 2
+        assert plan(end, lda=512) == 2 and plan(end - esize, lda=512) == 1
+        size = rows * J * esize
+        assert plan(1 << 40, a=(1 << 40) + size) == 2 and plan(1 << 40, a=(1 << 40) + size - 16) == 1
+        # the same for u, a block of 128 of 192 columns
+        u = 1 << 44
+        end = u + ((K - 1) * 192 + J) * 4
+        assert plan(end, ldu=192) == 2 and plan(end - esize, ldu=192) == 1
+        assert plan(u - size, ldu=192) == 2 and plan(u - size + esize, ldu=192) == 1
+
+
 def test_binding_fails_loudly_without_device_tensors():
     import torch
     x = torch.zeros(4, 256, dtype=torch.bfloat16)
