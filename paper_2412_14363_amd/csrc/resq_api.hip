@@ -931,16 +931,29 @@ static int project_rows_status(const void* a, int64_t lda, int64_t rows, int64_t
 // fp32 instruction.  So do bf16 rows of one chunk of that kernel: half a chunk of the other, whose
 // ragged end costs more than its products save (16 steps, 128 x 128 outputs 5.5 / 7.1 us, 4096 x 4096 15.6 / 18.6; 17
 // steps 7.0 / 7.2, 20.4 / 18.7).
-// 256 x 128 tiles where they fill the chip, two to a compute unit (128 x 128 / 256 x 128 tiles, us): 4096 x 4096 x 4096, 512 of
-// them, 390 / 313, 8192 x 4096 x 4096 765 / 612, 5000 x 4096 x 4096, 640, 490 / 457, 8192 x 40 x 8192 74 / 60; half as many are
-// slower: 4000 x 2000 x 2000 110 / 118, 2048 x 2048 x 2048 61 / 104.  Its reduction ends on whole pieces, its row offsets have 31 bits,
-// and its second look at sums that are not finite wants a and u as they were.  (The two kernels add in another order, so the
+// 256 x 128 tiles where they fill the chip, two to a compute unit (half as many are slower: 4000 x 2000 x 2000 110 / 118,
+// 2048 x 2048 x 2048 61 / 104; here and below us, 128 x 128 / 256 x 128 tiles), and where they take less time by this count: both
+// kernels go in rounds of a tile to each of the 256 compute units, and a round takes, in tenths of a microsecond, 28 and 7 a chunk,
+// 53 and 12 a chunk; the smaller tiles 14 more where the last chunk is ragged and 3 where the last column tile is, and a last round that
+// a compute unit runs alone, not two at once, 36 more with the larger ones.  So what decides is how full the rounds
+// are, tiles that hang over the last row among them, and the reduction's length: 4096 x 4096 x 4096 376 / 309, 8192 x 40 x 8192
+// 72 / 59, 3968 x 1024 x 8192 194 / 169, but 4352 x 512 x 4096, 4 full rounds and 64 tiles against 2 and 32, 66 / 73, 3968 x 64 x 5376 24 / 27,
+// 600 x 1024 x 43776 183 / 203, 100 x 1024 x 65536 59 / 89.  Over 985 such shapes the count is 0.2 % behind the better kernel
+// of each in the mean, 4 % or more in 2 % of them; the larger tiles wherever 512 of them are 2.5 %, the smaller ones 9 %.
+// The larger ones' reduction ends on whole pieces, their row offsets have 31 bits,
+// and their second look at sums that are not finite wants a and u as they were.  (The two kernels add in another order, so the
 // choice hangs on the operands themselves, not on what an allocator has put beside them.)
 static int project_rows_kernel(const void* a, int a_is_bf16, int64_t lda, int64_t rows, int64_t K, const float* u, int64_t ldu,
                                int64_t J, const void* out, int out_is_bf16, int64_t ldo) {
     if (!a_is_bf16 || K <= kBasisChunk) return 0;
-    const int64_t tiles = ((J + kProjTile - 1) / kProjTile) * ((rows + kProjWideRows - 1) / kProjWideRows);
+    const int64_t cols = (J + kProjTile - 1) / kProjTile;
+    const int64_t tiles = cols * ((rows + kProjWideRows - 1) / kProjWideRows);
     if (tiles < 512 || K % 8 != 0 || lda > (1 << 21) || ldu > (1 << 21)) return 1;
+    const int64_t chunks = (K + kProjChunk - 1) / kProjChunk;
+    const int64_t wide = (tiles + 255) / 256, narrow = (cols * ((rows + kProjTile - 1) / kProjTile) + 255) / 256;
+    if (narrow * (28 + 7 * chunks + (K % kProjChunk ? 14 : 0) + (J % kProjTile ? 3 : 0)) <=
+        wide * (53 + 12 * chunks) + (wide & 1 ? 36 : 0))
+        return 1;
     const int64_t out_pitch = ldo * (out_is_bf16 ? 2 : 4), out_width = J * (out_is_bf16 ? 2 : 4);
     if (blocks_overlap(a, rows, 2 * lda, 2 * K, out, rows, out_pitch, out_width) ||
         blocks_overlap(u, K, 4 * ldu, 4 * J, out, rows, out_pitch, out_width))

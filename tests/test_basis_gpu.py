@@ -103,13 +103,15 @@ def test_project_rows_split(rq, rows, K, J):
     assert np.all(np.abs(buf[:, :J].double().cpu().numpy() - ad @ ud) <= 3 * K * 2.0 ** -24 * (np.abs(ad) @ np.abs(ud)) + 1e-30)
 
 
-# From 512 tiles of 256 x 128 on: ragged rows and columns, a reduction axis of less than a chunk, of whole chunks, with one to
-# three pieces of a last one, through the loop and without it; beside them what the smaller tiles keep (one tile less, a ragged
-# piece, out on a)
+# 256 x 128 tiles (kernel 2): ragged rows and columns, a reduction axis of less than a chunk, of whole chunks, with one to
+# three pieces of a last one, through the loop and without it; beside them what the smaller tiles (1) keep: one tile less, a
+# ragged piece, rounds that would be emptier
 @pytest.mark.parametrize("out_dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("rows,K,J", [(16380, 24, 1032), (16129, 32, 1032), (16385, 40, 1000), (130817, 56, 128), (130816, 56, 128),
-                                      (16300, 64, 1032), (16300, 160, 1032), (16300, 168, 1032), (16300, 232, 1032), (16300, 161, 1032)])
-def test_project_rows_wide_tiles(rq, rows, K, J, out_dtype):
+@pytest.mark.parametrize("rows,K,J,kernel", [
+    (16380, 24, 1032, 2), (16129, 32, 1032, 1), (16129, 32, 1024, 2), (16385, 40, 1000, 2), (130817, 56, 128, 2), (130816, 56, 128, 1),
+    (16300, 64, 1032, 1), (16300, 64, 1016, 2), (16300, 96, 1016, 2), (16300, 128, 1024, 2), (16300, 160, 1032, 1), (16300, 160, 1024, 2),
+    (16300, 168, 1032, 2), (16300, 232, 1032, 2), (16300, 161, 1032, 1)])
+def test_project_rows_wide_tiles(rq, rows, K, J, kernel, out_dtype):
     g = torch.Generator(device="cuda").manual_seed(rows + K + J)
     ld = (K + 7) // 8 * 8 + 8
     a = torch.full((rows, ld), float("nan"), dtype=torch.bfloat16, device="cuda")   # what lies behind a row is not read
@@ -117,6 +119,7 @@ def test_project_rows_wide_tiles(rq, rows, K, J, out_dtype):
     u = torch.randn(K, J, generator=g, device="cuda") * torch.exp2(torch.randint(-40, 10, (K, J), generator=g, device="cuda").float())
     u[::3] = u[::3].bfloat16().float()
     buf = torch.full((rows, J + 3), 7.0, device="cuda", dtype=out_dtype)
+    assert rq.resq_project_rows_plan(a[:, :K], u, buf[:, :J]) == kernel
     rq.resq_project_rows(a[:, :K], u, out=buf[:, :J])
     ad, ud = a[:, :K].double(), u.double()
     ref, mag = ad @ ud, ad.abs() @ ud.abs()
@@ -136,13 +139,16 @@ def test_project_rows_wide_tiles_infinities_and_in_place(rq):
     u[K - 6, 4], u[K - 1, 7] = inf, nan
     ref = a[:, :K].double() @ u.double()
     for out_dtype in (torch.float32, torch.bfloat16):
-        got = rq.resq_project_rows(a[:, :K], u, out_dtype=out_dtype)
+        got = torch.empty((rows, J), dtype=out_dtype, device="cuda")
+        assert rq.resq_project_rows_plan(a[:, :K], u, got) == 2
+        rq.resq_project_rows(a[:, :K], u, out=got)
         assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isinf(), ref.isinf())
         assert torch.equal(got[ref.isinf()].double(), ref[ref.isinf()])
         fin = ref.isfinite()
         assert torch.allclose(got[fin].double(), ref[fin], rtol=2.0 ** -8, atol=1e-4)
     want = rq.resq_project_rows(a[:, :K], u, out_dtype=torch.bfloat16)
     buf = a.clone()
+    assert rq.resq_project_rows_plan(buf[:, :K], u, buf) == 1
     rq.resq_project_rows(buf[:, :K], u, out=buf)   # the smaller tiles, another order of the sum
     assert torch.equal(buf.isnan(), want.isnan())
     assert torch.allclose(buf[want.isfinite()].double(), want[want.isfinite()].double(), rtol=2.0 ** -7, atol=1e-4)

@@ -204,6 +204,17 @@ def test_project_rows_plan():
     assert binding.lib().resq_project_rows_plan(P, 1, 64, 8, 64, P, 64, 64, P, 1, 64, None) == 1
 
 
+@pytest.mark.parametrize("rows,K,J,kernel", [
+    # tiles that hang over the last row: one of two 128-row tiles, or one of four
+    (100, 1024, 65536, 1), (128, 4096, 131072, 1), (129, 1024, 65536, 2), (384, 1024, 32768, 1), (385, 1024, 32768, 2),
+    # rounds of 256 tiles: 2 of the larger against 4, 3 against 5, 3 against 6, 4 against 7
+    (4096, 512, 4096, 2), (4224, 512, 4096, 1), (5120, 2048, 4096, 1), (5248, 2048, 4096, 2), (7000, 256, 4096, 1), (7000, 4096, 4096, 2),
+    # short reductions: whole chunks and ragged ones, whole column tiles and ragged ones
+    (6144, 64, 4096, 1), (6144, 72, 4096, 2), (8192, 40, 8192, 2), (16384, 32, 1024, 2), (16384, 96, 1000, 2), (131072, 128, 128, 2)])
+def test_project_rows_plan_counts_rounds(rows, K, J, kernel):
+    assert project_plan(rows, K, J) == kernel and project_plan(rows, K, J, out_bf16=0) == kernel
+
+
 def test_project_rows_kernel_hangs_on_the_operands_alone():
     """Where out lies beside a or u, in the same buffer or behind their last element, the 256 x 128 tiles run as they do
     anywhere else; where it lies on them, the others."""
