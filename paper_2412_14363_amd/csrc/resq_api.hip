@@ -224,11 +224,16 @@ static int quantize_act_impl(const void* x, int64_t ldx, int64_t M, int64_t K, i
     // of 8190 47.7 / 20.0 / 29.3, 1024 of 4098 9.2 / 5.5 / 7.6, of 16378 25.9 / 14.7 / 14.4, 16 of 28674 10.9 / - / 6.7.
     // 1024 threads up to one row per compute unit beyond 3072 columns (256 x 4098 4.26 / 4.45 / 3.71, 256 x 14338 7.8 / 7.9 / 5.5)
     // and up to two beyond 8192 (512 x 10242 10.0 / 7.4 / 6.6, 520 rows 13.7 / 7.6 / 8.0; asymmetric beyond 12288:
-    // 512 x 14338 14.0 / 10.4 / 9.2, of 8706 9.8 / 7.0 / 7.2).  Element-wise where a row per compute unit gives each
-    // thread a few columns: 16 x 514 3.62 / 3.62 / 3.70, 256 x 2050 3.68 / 4.10 / 3.86 (x 1538 3.97 / 3.62, x 3586 4.00 / 4.20 / 3.88).
+    // 512 x 14338 14.0 / 10.4 / 9.2, of 8706 9.8 / 7.0 / 7.2).  Element-wise where units leave most of the threads of a row without one:
+    // up to 80 of 256 (kernel alone, element-wise / 256 threads: 4096 x 130 5.8 / 6.95, x 258 6.3 / 7.1, x 514 7.05 / 7.3, x 578 7.25 / 7.4,
+    // x 642 7.8 / 7.6; asymmetric x 578 8.4 / 8.7, x 642 9.2 / 9.2; more rows, where its 2-byte loads bind, 16384 x 402 19.6 / 20.2, x 450 20.9 / 20.7,
+    // 65536 x 258 74.5 / 74.3, x 330 79.2 / 73.6); and with a row per compute unit at most, where one pass is as long as another, up to
+    // 128 of them, or with 257 to 384, most threads without a second one: 16 x 514 3.62 / 3.62 / 3.70, 256 x 2050 3.68 / 4.10 / 3.86
+    // (x 1538 3.97 / 3.62, x 3586 4.00 / 4.20 / 3.88).
     const int64_t units = (r + 7) / 8 + (lo_cols + 7) / 8;
     const int64_t few_ragged = K > 8192 && (!asym || K > 12288) ? 512 : K > 3072 ? 256 : 0;
-    const bool few_columns = M <= 256 && (K <= 1024 || (K > 2048 && K <= 3072));
+    const int64_t few_units = M <= 256 ? 128 : M <= 12288 ? 80 : M <= 32768 ? 56 : 40;
+    const bool few_columns = units <= few_units || (M <= 256 && units > 256 && units <= 384);
     const bool ragged = !pieces && !rotate && !few_columns && (r == 0 || r >= 8) && (lo_cols == 0 || lo_cols >= 8) &&
                         units <= 4096;
     if (vec && K <= 512 && !rotate) {

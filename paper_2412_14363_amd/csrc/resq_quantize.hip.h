@@ -889,7 +889,7 @@ __global__ __launch_bounds__(kQuantThreads) void dequantize_kv_cache_kernel(
 
 // ---------------------------------------------------------------------------
 // Activations, any K, r (K - r even) and alignment: two passes over the row with 2-byte loads.  For groups of one to
-// seven columns, rows beyond 32768 columns, and the few short rows that the dispatch names.
+// seven columns, rows beyond 32768 columns, and the short rows that the dispatch names.
 // ---------------------------------------------------------------------------
 template <bool ASYM, int RT = kQuantThreads>
 __global__ __launch_bounds__(RT) void quantize_act_generic_kernel(

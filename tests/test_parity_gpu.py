@@ -124,6 +124,8 @@ def test_quantize_act_generic_path(oracle, rq, M, K, r):
 # Rows without whole 16-byte pieces: short last units of both groups, groups of exactly one unit and of one unit and a
 # bit, units at the edges of what a thread holds (256, 512, 1024, 2048 and 4096 of them), 256 and 1024 threads
 @pytest.mark.parametrize("M,K,r", [
+    # units that begin and end in a group of 8 columns and a bit, in rows that take this kernel
+    (257, 700, 8), (257, 657, 9), (257, 1001, 993), (257, 1003, 993), (257, 651, 651), (257, 650, 0), (12289, 458, 10), (32769, 330, 18),
     (3, 2042, 250), (257, 35, 17), (257, 16, 8), (257, 18, 8), (300, 25, 9), (260, 57, 57), (3, 1100, 0), (3, 1101, 1101), (3, 2048, 12),
     (3, 2051, 11), (257, 1024, 12), (256, 1022, 12), (256, 2050, 258), (257, 2050, 258), (256, 3072, 12), (256, 3074, 12),
     (300, 4090, 8), (300, 4098, 1022), (513, 8190, 14), (513, 8193, 1023), (2, 8190, 14), (2, 8193, 1023), (2, 16382, 4),
