@@ -1027,6 +1027,10 @@ static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int swee
     // eigvals at their end, in no order among each other; the workspace takes a copy of c first.
     if (n <= kEigSmallMax && !blocks_overlap(c, K, 4 * ldc, 4 * K, p, K, 4 * ldp, 4 * K) &&
         !blocks_overlap(c, K, 4 * ldc, 4 * K, eigvals, 1, 4 * K, 4 * K)) {
+        if (n == 2) {
+            launch(eig_pair_kernel, dim3(1), dim3(64), 0, static_cast<hipStream_t>(stream), c, ldc, sweeps, eigvals, p, ldp);
+            return launch_status();
+        }
         const int small_lds = eig_small_lds_bytes(n);
         if (small_lds > 64 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void*>(eig_small_kernel),

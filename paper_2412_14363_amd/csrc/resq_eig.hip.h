@@ -127,6 +127,52 @@ constexpr int kEigSmallMax = 128;
 constexpr int kEigSmallThreads = 1024;
 constexpr int kEigSmallCols = 8;  // columns of Vt per workgroup
 
+// As eig_rotations_kernel has it, |a01| > 2^-40 sqrt(|a00 a11|) and tan of the smaller angle =
+// sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with fewer
+// roots and quotients in a row.  (The hardware's approximate ones are not enough: the
+// signs of some vectors then come out otherwise.)
+__device__ __forceinline__ bool eig_turns(double a00, double a11, double a01) {
+    return a01 * a01 > kEigSkip * kEigSkip * fabs(a00 * a11);
+}
+__device__ __forceinline__ double2 eig_rotation(double a00, double a11, double a01) {
+    const double d = a11 - a00, q = 2.0 * a01;
+    double tn = fabs(q) / (fabs(d) + sqrt(d * d + q * q));
+    if (d != 0.0 && (d < 0.0) != (q < 0.0)) tn = -tn;
+    const double c = rsqrt(1.0 + tn * tn);
+    return make_double2(c, tn * c);
+}
+
+// Order 2: one block, the iteration below in one thread's registers.  (eig_small_kernel, whose length is mostly that of its code
+// there, takes 4.65 us, this 4.05; with two barriers a round it took 4.0.)  Index 1 in slot 0, index 0 in slot 1, as there.
+__global__ __launch_bounds__(64) void eig_pair_kernel(const float* __restrict__ c, int64_t ldc, int sweeps,
+                                                      float* __restrict__ eigvals, float* __restrict__ p, int64_t ldp) {
+    if (threadIdx.x > 0) return;
+    double a00 = c[ldc + 1], a11 = c[0], a01 = 0.5 * ((double)c[1] + (double)c[ldc]);
+    double v0[2] = {0.0, 1.0}, v1[2] = {1.0, 0.0};   // rows of Vt
+    for (int sweep = 0; sweep < sweeps && eig_turns(a00, a11, a01); ++sweep) {
+        const double2 r = eig_rotation(a00, a11, a01);
+        const double x0 = r.x * a00 - r.y * a01, x1 = r.x * a01 - r.y * a11;
+        const double y0 = r.y * a00 + r.x * a01, y1 = r.y * a01 + r.x * a11;
+        a00 = r.x * x0 - r.y * x1;
+        a01 = r.y * x0 + r.x * x1;
+        a11 = r.y * y0 + r.x * y1;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const double x = v0[j], y = v1[j];
+            v0[j] = r.x * x - r.y * y;
+            v1[j] = r.y * x + r.x * y;
+        }
+    }
+    const int at0 = a11 >= a00 ? 1 : 0, at1 = 1 - at0;   // decreasing, ties by index
+    eigvals[at0] = (float)a00;
+    eigvals[at1] = (float)a11;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        p[j * ldp + at0] = (float)v0[j];
+        p[j * ldp + at1] = (float)v1[j];
+    }
+}
+
 // blocks (k, l), k < l: lanes of `units` rows of n / 2 (see below)
 __host__ __device__ inline int eig_small_units(int half) { return (half + 1) >> 1; }
 // doubles of one of the two buffers: the four planes, the diagonal blocks (three numbers each)
@@ -257,19 +303,9 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
 
     // the rotation of the pair whose diagonal block is (a00, a01; a01, a11), for the round that reads buffer b
     auto angle = [&](double a00, double a11, double a01, int b) __attribute__((always_inline)) {
-        // As eig_rotations_kernel has it, |a01| > 2^-40 sqrt(|a00 a11|) and tan of the smaller angle =
-        // sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with fewer
-        // roots and quotients in a row.  (The hardware's approximate ones are not enough: the
-        // signs of some vectors then come out otherwise.)
-        const bool turn = lk_on && a01 * a01 > kEigSkip * kEigSkip * fabs(a00 * a11);
         double2 r = make_double2(1.0, 0.0);
-        if (turn) {
-            const double d = a11 - a00, q = 2.0 * a01;
-            double tn = fabs(q) / (fabs(d) + sqrt(d * d + q * q));
-            if (d != 0.0 && (d < 0.0) != (q < 0.0)) tn = -tn;
-            r.x = rsqrt(1.0 + tn * tn);
-            r.y = tn * r.x;
-        }
+        const bool turn = lk_on && eig_turns(a00, a11, a01);
+        if (turn) r = eig_rotation(a00, a11, a01);
         if (lk_on) cs[b * half + lane] = r;
         const bool any = __ballot(turn) != 0;
         if (lane == 0) flag[b] = any ? 1 : 0;

@@ -256,6 +256,24 @@ def test_sym_eig_against_oracle(rq, K, r):
     assert np.allclose(p[:, :r] @ p[:, :r].T, p_ref[:, :r] @ p_ref[:, :r].T, atol=1e-4)
 
 
+# order 2, a kernel of its own: nothing to turn, equal values, either order, either sign, an element far below the others
+@pytest.mark.parametrize("c", [[[3., 0.], [0., 1.]], [[1., 0.], [0., 3.]], [[2., 0.], [0., 2.]], [[2., 1.], [1., 2.]], [[2., -1.], [-1., 2.]],
+                               [[0., 0.], [0., 0.]], [[0., 5.], [5., 0.]], [[-4., 1.], [1., -7.]], [[1e-20, 1e-21], [1e-21, 3e-20]],
+                               [[1e30, 1e18], [1e18, 1.]], [[1., 1e-8], [1e-8, 1.]], [[1., 1e-5], [2e-5, 1e-9]]])
+@pytest.mark.parametrize("sweeps", [1, 12])
+def test_sym_eig_order_two(rq, c, sweeps):
+    buf = torch.full((2, 5), 7.0, device="cuda")
+    buf[:, :2] = torch.tensor(c)
+    lam, p = (t.double().cpu().numpy() for t in rq.resq_sym_eig(buf[:, :2], sweeps=sweeps))
+    m = buf[:, :2].double().cpu().numpy()
+    m = 0.5 * (m + m.T)
+    scale = np.abs(m).max()
+    # fp32 outputs of an fp64 iteration, which one rotation ends
+    assert lam[0] >= lam[1] and np.all(np.abs(lam - np.linalg.eigvalsh(m)[::-1]) <= 2.0 ** -23 * scale)
+    assert np.allclose(p.T @ p, np.eye(2), atol=2.0 ** -22)
+    assert np.all(np.abs(m @ p - p * lam) <= 2.0 ** -21 * scale)
+
+
 # orders that take the single-launch kernel (at most 128): the smallest, odd and even numbers of
 # pairs, one more column than a slice of the vectors holds, and the first order beyond it
 @pytest.mark.parametrize("K", [2, 4, 6, 18, 30, 32, 62, 98, 122, 126, 128, 130])
