@@ -551,7 +551,16 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
         if (s == s) continue;
         const uint16_t* row = g.a + i * g.lda;
         s = 0.0f;
-        for (int64_t k = 0; k < g.T && s == s; ++k) s = fmaf(__uint_as_float((uint32_t)row[k] << 16), g.u[k * g.ldu + j], s);
+        for (int64_t k = 0; k < g.T && s == s; k += 8) {   // whole pieces; a NaN stays one
+            const uint4 piece = *reinterpret_cast<const uint4*>(row + k);
+            const uint32_t w[4] = {piece.x, piece.y, piece.z, piece.w};
+            float c[8];
+#pragma unroll
+            for (int n = 0; n < 8; ++n) c[n] = g.u[(k + n) * g.ldu + j];
+#pragma unroll
+            for (int n = 0; n < 8; ++n)
+                s = fmaf(__uint_as_float(n & 1 ? w[n >> 1] & 0xFFFF0000u : w[n >> 1] << 16), c[n], s);
+        }
         if constexpr (OUT_BF16) static_cast<uint16_t*>(g.out)[i * g.ldo + j] = (uint16_t)pack_bf16(s, 0.0f);
         else static_cast<float*>(g.out)[i * g.ldo + j] = s;
     }
