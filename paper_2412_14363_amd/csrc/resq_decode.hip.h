@@ -52,7 +52,7 @@ struct DecodeArgs {
     // q_hi .. lo_sum above are not read then
     const uint16_t* x;
     int64_t ldx;
-    int log2_rows;    // rows quantized at a time: 1, 2, 4 or 8
+    int log2_rows;    // rows quantized at a time: 2^0 .. 2^3
 };
 
 constexpr int kFusedScratchFloats = 3 * 16 + 2 * 2 * 8;  // LDS beside the token rows, see fill_act_quantize
@@ -79,11 +79,13 @@ struct ChannelConsts {
     int4 even;
 };
 __device__ __forceinline__ ChannelConsts load_channel_consts(const DecodeArgs& a, int64_t n) {
-    const uint8_t* at = a.packed + a.L.scale_off;
+    const uint16_t* sw_hi = reinterpret_cast<const uint16_t*>(a.packed + a.L.scale_off);
+    const uint16_t* sw_lo = sw_hi + a.L.n_pad;
+    const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
     ChannelConsts h;
-    h.sw_hi = *reinterpret_cast<const uint2*>(at + 2 * n);
-    h.sw_lo = *reinterpret_cast<const uint2*>(at + 2 * (a.L.n_pad + n));
-    h.even = *reinterpret_cast<const int4*>(at + 4 * (a.L.n_pad + n));
+    h.sw_hi = *reinterpret_cast<const uint2*>(sw_hi + n);
+    h.sw_lo = *reinterpret_cast<const uint2*>(sw_lo + n);
+    h.even = *reinterpret_cast<const int4*>(even_sum + n);
     return h;
 }
 __device__ __forceinline__ void take_channel_consts(EpilogueConsts& c, const ChannelConsts& h) {
@@ -101,8 +103,6 @@ __device__ __forceinline__ void take_channel_consts(EpilogueConsts& c, const Cha
     c.ev[3] = h.even.w;
 }
 __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
-    const uint16_t* sw_hi = reinterpret_cast<const uint16_t*>(a.packed + a.L.scale_off);
-    const uint16_t* sw_lo = sw_hi + a.L.n_pad;
     const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
     const int32_t* wsum_hi = even_sum + a.L.n_pad;
     const int32_t* wsum_lo = even_sum + 2 * a.L.n_pad;
@@ -114,21 +114,7 @@ __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs&
     c.ca = has_lo ? a.lo_sum[tok] : 0;
     c.cth = (asym && has_hi) ? a.c_hi[tok] : 0.f;
     c.ctl = (asym && has_lo) ? a.c_lo[tok] : 0.f;
-    const uint2 sch = *reinterpret_cast<const uint2*>(sw_hi + n);
-    const uint2 scl = *reinterpret_cast<const uint2*>(sw_lo + n);
-    const int4 es = *reinterpret_cast<const int4*>(even_sum + n);
-    c.snh[0] = fp16_bits_to_f32(sch.x & 0xFFFFu);
-    c.snh[1] = fp16_bits_to_f32(sch.x >> 16);
-    c.snh[2] = fp16_bits_to_f32(sch.y & 0xFFFFu);
-    c.snh[3] = fp16_bits_to_f32(sch.y >> 16);
-    c.snl[0] = fp16_bits_to_f32(scl.x & 0xFFFFu);
-    c.snl[1] = fp16_bits_to_f32(scl.x >> 16);
-    c.snl[2] = fp16_bits_to_f32(scl.y & 0xFFFFu);
-    c.snl[3] = fp16_bits_to_f32(scl.y >> 16);
-    c.ev[0] = es.x;
-    c.ev[1] = es.y;
-    c.ev[2] = es.z;
-    c.ev[3] = es.w;
+    take_channel_consts(c, load_channel_consts(a, n));
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         c.wsh[v] = asym ? wsum_hi[n + v] : 0;
@@ -453,7 +439,7 @@ __device__ __forceinline__ void stream_run(uint4 (&ring)[kDecodeDepth], uint4 (&
 
 template <bool DBG, int ACT>
 __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_kernel(const DecodeArgs a) {
-    extern __shared__ __attribute__((aligned(16))) uint8_t act[];  // kActQuantize: [M][lds_row]
+    extern __shared__ __attribute__((aligned(16))) uint8_t act[];  // kernels that quantize: [M][lds_row]
     constexpr bool DIRECT = ACT == kActDirect;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int hi_blocks = (int)a.L.hi_blocks, blocks = (int)(a.L.hi_blocks + a.L.lo_blocks);
@@ -533,7 +519,7 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_splitk_kernel(cons
     static_assert(SK == 2 || SK == 4 || SK == 8, "runs per group");
     constexpr int kWaves = kDecodeThreads / 64;
     constexpr int G = kWaves / SK;  // groups per set
-    extern __shared__ __attribute__((aligned(16))) uint8_t act[];  // kActQuantize: [M][lds_row]; then the partial sums
+    extern __shared__ __attribute__((aligned(16))) uint8_t act[];  // kernels that quantize: [M][lds_row]; then the partial sums
     constexpr bool DIRECT = ACT == kActDirect;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -554,7 +540,7 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_decode_splitk_kernel(cons
     const bool live0 = set < sets && group0 < a.groups;
     const uint4* wp0 = reinterpret_cast<const uint4*>(a.packed + (int64_t)(live0 ? group0 : 0) * a.L.group_bytes + lane_off);
     float* scal = reinterpret_cast<float*>(partial + kWaves * 2 * 64);
-    ChannelConsts ch;   // kActQuantize: of this set, asked for with the set's first weights
+    ChannelConsts ch;   // kernels that quantize: of this set, asked for with the set's first weights
     if constexpr (!DIRECT) {
         uint4 v[ACT];
         fused_load_rows(a, 0, t, v);
