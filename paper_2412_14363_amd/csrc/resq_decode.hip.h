@@ -156,7 +156,7 @@ __device__ __forceinline__ void stream_epilogue(const DecodeArgs& a, int tok, in
         return;
     }
     uint16_t* dst = a.y + (int64_t)tok * a.ldy + n;
-    if (n + 3 < a.L.N) {  // at any 2-byte aligned address, see store_piece
+    if (n + 3 < a.L.N) {  // at any 2-byte aligned address, see Piece16
         *reinterpret_cast<Piece8*>(dst) = Piece8{pack_bf16(out[0], out[1]), pack_bf16(out[2], out[3])};
     } else {
 #pragma unroll

@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
     // positions in decreasing order (ties by index), as eig_finish_kernel has them; rank by slot
     const double* a = lds + buf * bufsz + diag;
     vt += buf * n * kEigSmallCols;
-    int* rank = reinterpret_cast<int*>(cs + buf * half);   // not the rotations that are still read
+    int* rank = reinterpret_cast<int*>(cs + buf * half);   // no rotation is read any more
     if (t < n) {
         const double li = a[(t & 1) * half + (t >> 1)];
         const int i = index_of(t >> 1, t & 1);

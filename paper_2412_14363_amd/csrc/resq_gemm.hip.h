@@ -311,15 +311,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // Eight bf16 outputs at any 2-byte aligned address, of which `left` (any sign) lie in the row: rows whose
-// length or leading dimension is no multiple of eight start anywhere.  The hardware stores 16 bytes at any
-// address (unaligned access is on for every HSA queue, and the packed type makes the compiler rely on it, not on
-// an alignment that is not there), so only the piece that holds the end of a row goes element by element.
+// length or leading dimension is no multiple of eight start anywhere (see Piece16), so only the piece that holds
+// the end of a row goes element by element.
 // Stored in 2-byte pieces, 16 bytes apart from lane to lane, such outputs cost up to a third of the
 // whole call (quantizer and GEMM, us, before / now): 2025 x 1088 -> 10790 64.7 / 40.2, 3000 x 2048 -> 3001 49.2 / 37.8,
 // 1240 x 1028 -> 3287 25.4 / 18.6, 777 x 5000 -> 3001 asymmetric 31.3 / 28.4; rows of whole pieces are as fast as they were.
-struct __attribute__((packed, aligned(2))) Piece16 { uint32_t x, y, z, w; };
-struct __attribute__((packed, aligned(2))) Piece8 { uint32_t x, y; };
-struct __attribute__((packed, aligned(2))) Piece4 { uint32_t x; };
 __device__ __forceinline__ void store_piece(uint16_t* dst, const uint4& v, int64_t left) {
     if (left >= 8) {
         *reinterpret_cast<Piece16*>(dst) = Piece16{v.x, v.y, v.z, v.w};

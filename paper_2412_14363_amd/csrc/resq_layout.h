@@ -32,6 +32,13 @@
 
 namespace resq {
 
+// Pieces of a row at any 2-byte aligned address.  The hardware loads and stores them there in one instruction (unaligned
+// access is on for every HSA queue), and the packed types make the compiler rely on that, not on an alignment that is
+// not there.
+struct __attribute__((packed, aligned(2))) Piece16 { uint32_t x, y, z, w; };
+struct __attribute__((packed, aligned(2))) Piece8 { uint32_t x, y; };
+struct __attribute__((packed, aligned(2))) Piece4 { uint32_t x; };
+
 constexpr int kQmaxHi = 127;  // 2^(8-1) - 1  (Section 3, Eq. 1, N = 8)
 constexpr int kQmaxLo = 7;    // 2^(4-1) - 1  (Section 3, Eq. 1, N = 4)
 

@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kProjThreads, 2) void project_split_wide_kernel(con
         i = i0 + wi * 128 + p * 16 + (n & 15);
         j = j0 + wj * 64 + q * 16 + 4 * ((n & 63) >> 4);
     };
-    // J is a multiple of eight, so four columns are there or none; rows start at any address, see store_piece
+    // J is a multiple of eight, so four columns are there or none; rows start at any address, see Piece16
     auto store4 = [&](int64_t i, int64_t j, const v4f& c) __attribute__((always_inline)) {
         if constexpr (OUT_BF16) {
             uint16_t* dst = static_cast<uint16_t*>(g.out) + i * g.ldo + j;

@@ -260,11 +260,9 @@ struct RotateArgs {
     int64_t ld_rot;
 };
 
-// Sixteen bytes at any 2-byte aligned address (every HSA queue runs with unaligned access on, and the packed type
-// makes the compiler rely on that, not on an alignment that is not there).
-struct __attribute__((packed, aligned(2))) Unaligned16 { uint32_t x, y, z, w; };
+// sixteen bytes at any 2-byte aligned address
 __device__ __forceinline__ uint4 load16_any(const uint16_t* p) {
-    const Unaligned16 v = *reinterpret_cast<const Unaligned16*>(p);
+    const Piece16 v = *reinterpret_cast<const Piece16*>(p);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 // the eight 16-bit elements of v turned round so that element n comes first, 0 < n < 8
