@@ -473,8 +473,6 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_f8_kernel(const Ge
         wait_loads_and_barrier<0>();
         __syncthreads();  // every wave is done reading the stage buffers, and the sums are there
         wait_for_products();
-        park_hi();
-        park_lo();
         if (a.swiglu) {  // symmetric codes only (checked on the host)
             if (S_hi > 0) fold(YES{}, NO{}, YES{});
             else fold(NO{}, NO{}, YES{});
