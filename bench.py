@@ -49,7 +49,7 @@ MEASURED_TRAFFIC = {
     "qwen_r0": (2879.53e6 + 484.44e6, "profiles/qwen_r0.txt"),
     "gate_up_prefill": (291.13e6 + 117.44e6, "profiles/gate_up_prefill.txt"),
     "down_prefill": (371.16e6 + 33.55e6, "profiles/down_prefill.txt"),
-    "oproj_prefill": (38.29e6 + 16.78e6, "profiles/oproj_prefill.txt"),
+    "oproj_prefill": (38.24e6 + 16.78e6, "profiles/oproj_prefill.txt"),
     "oproj_m512": (19.31e6 + 4.19e6, "profiles/oproj_m512.txt"),
     "down_m512": (66.50e6 + 4.19e6, "profiles/down_m512.txt"),
     "decode_m1": (133.04e6 + 0.06e6, "profiles/decode_m1.txt"),
@@ -57,7 +57,7 @@ MEASURED_TRAFFIC = {
     "decode_m16": (133.13e6 + 0.92e6, "profiles/decode_m16.txt"),
     "decode_m64": (135.10e6 + 3.67e6, "profiles/decode_m64.txt"),
     "kv_quant": (8.45e6 + 2.88e6, "profiles/kv_quant.txt"),
-    "uc_proj": (21.35e6 + 20.97e6, "profiles/uc_proj.txt"),
+    "uc_proj": (21.26e6 + 20.97e6, "profiles/uc_proj.txt"),
 }
 
 
