@@ -940,7 +940,9 @@ static int project_rows_status(const void* a, int64_t lda, int64_t rows, int64_t
 // 2048 x 2048 x 2048 61 / 104; here and below us, 128 x 128 / 256 x 128 tiles), and where they take less time by this count: both
 // kernels go in rounds of a tile to each of the 256 compute units, and a round takes, in tenths of a microsecond, 28 and 7 a chunk,
 // 53 and 12 a chunk; the smaller tiles 14 more where the last chunk is ragged and 3 where the last column tile is, and a last round that
-// a compute unit runs alone, not two at once, 36 more with the larger ones.  So what decides is how full the rounds
+// a compute unit runs alone, not two at once, 36 more with the larger ones; and all of them a tenth more with the smaller ones where u
+// is larger than the 256 MB last-level cache, out of which twice as many rows of tiles read it (1152 x 4096 x 16384, 256 MB, 490 / 507, but
+// x 28672 934 / 860, 1664 x 4096 x 28672 1393 / 1190).  So what decides is how full the rounds
 // are, tiles that hang over the last row among them, and the reduction's length: 4096 x 4096 x 4096 376 / 309, 8192 x 40 x 8192
 // 72 / 59, 3968 x 1024 x 8192 194 / 169, but 4352 x 512 x 4096, 4 full rounds and 64 tiles against 2 and 32, 66 / 73, 3968 x 64 x 5376 24 / 27,
 // 600 x 1024 x 43776 183 / 203, 100 x 1024 x 65536 59 / 89.  Over 985 such shapes the count is 0.2 % behind the better kernel
@@ -956,9 +958,9 @@ static int project_rows_kernel(const void* a, int a_is_bf16, int64_t lda, int64_
     if (tiles < 512 || K % 8 != 0 || lda > (1 << 21) || ldu > (1 << 21)) return 1;
     const int64_t chunks = (K + kProjChunk - 1) / kProjChunk;
     const int64_t wide = (tiles + 255) / 256, narrow = (cols * ((rows + kProjTile - 1) / kProjTile) + 255) / 256;
-    if (narrow * (28 + 7 * chunks + (K % kProjChunk ? 14 : 0) + (J % kProjTile ? 3 : 0)) <=
-        wide * (53 + 12 * chunks) + (wide & 1 ? 36 : 0))
-        return 1;
+    const int64_t narrow_round = 28 + 7 * chunks + (K % kProjChunk ? 14 : 0) + (J % kProjTile ? 3 : 0);
+    const int64_t slower = 4 * K * J > (int64_t)256 << 20 ? 11 : 10;   // tenths
+    if (slower * narrow * narrow_round <= 10 * (wide * (53 + 12 * chunks) + (wide & 1 ? 36 : 0))) return 1;
     const int64_t out_pitch = ldo * (out_is_bf16 ? 2 : 4), out_width = J * (out_is_bf16 ? 2 : 4);
     if (blocks_overlap(a, rows, 2 * lda, 2 * K, out, rows, out_pitch, out_width) ||
         blocks_overlap(u, K, 4 * ldu, 4 * J, out, rows, out_pitch, out_width))

@@ -209,6 +209,8 @@ def test_project_rows_plan():
     (100, 1024, 65536, 1), (128, 4096, 131072, 1), (129, 1024, 65536, 2), (384, 1024, 32768, 1), (385, 1024, 32768, 2),
     # rounds of 256 tiles: 2 of the larger against 4, 3 against 5, 3 against 6, 4 against 7
     (4096, 512, 4096, 2), (4224, 512, 4096, 1), (5120, 2048, 4096, 1), (5248, 2048, 4096, 2), (7000, 256, 4096, 1), (7000, 4096, 4096, 2),
+    # u inside and outside of the last-level cache
+    (1152, 4096, 16384, 1), (1152, 4096, 28672, 2), (1664, 4096, 28672, 2), (1152, 14336, 14336, 1),
     # short reductions: whole chunks and ragged ones, whole column tiles and ragged ones
     (6144, 64, 4096, 1), (6144, 72, 4096, 2), (8192, 40, 8192, 2), (16384, 32, 1024, 2), (16384, 96, 1000, 2), (131072, 128, 128, 2)])
 def test_project_rows_plan_counts_rounds(rows, K, J, kernel):
