@@ -108,38 +108,44 @@ __global__ void eig_rotations_kernel(EigPlan e, int sweep, int round) {
 // the 2 x 2 block of two pairs lie in four planes: no bank is met twice.
 //
 // The vectors do not fit beside the matrix, but column j of Vt is rotated
-// independently of every other column: each of the ceil(n / 8) workgroups repeats
-// the iteration on the matrix (same arithmetic, same decisions) and carries 8
-// columns of Vt, so that the workgroups never talk to each other.
+// independently of every other column: each of the n / 2 workgroups repeats
+// the iteration on the matrix (same arithmetic, same decisions) and carries two
+// columns of Vt, so that the workgroups never talk to each other.  (Eight columns are a tenth of the traffic of a workgroup's LDS,
+// which bounds a round of the large orders: n = 128 1267 us with eight, 1234 with four, 1208 with two.)
 //
 // One barrier a round.  Wavefront 0 is a round ahead: it turns the blocks that the diagonal blocks of the NEXT round
 // come from, and computes that round's angles, a chain of fp64 roots and quotients, while the others turn the matrix
-// by this round's and, eight of them, the vectors.  (With the angles of a round between two barriers, 900 of 2870
+// by this round's and, two of them, the vectors.  (With the angles of a round between two barriers, 900 of 2870
 // clocks were theirs alone.)  What bounds a round of n = 128 now is LDS, 8 elements and 4 numbers of rotations a block, about
-// 1800 of 2150 clocks.  Measured and not taken: the rotations handed from lane to lane instead of read again (29 % slower:
+// 1650 of 2050 clocks; of n = 64 and less the chain of wavefront 0.  Measured and not taken: two neighbouring rows of blocks to a wavefront, half of their elements handed
+// on from lane to lane (6 % a round, and what wavefront 0 needs of them is written to LDS after all), the rotations handed from lane to lane instead of read again (29 % slower:
 // vector instructions), n known to the compiler (14 % slower at 128: it joins reads of two planes into one
 // instruction, on the same banks), a thread's blocks loaded together (4 % slower).
 //
-// Measured, 12 sweeps allowed, two launches a round / two barriers a round / this kernel: n = 128 9.9 to 10.5 / 1.79 / 1.35 ms on a
-// covariance with a spectrum that decays by e^-6, - / 1.50 / 1.14 on that of Gaussian rows, which
-// converges in fewer sweeps; n = 100 - / 1.11 / 0.84, n = 64 4.9 / 0.58 / 0.40, n = 34 - / 0.22 / 0.16, n = 32 1.69 / 0.19 / 0.15.
+// Measured, 12 sweeps allowed, two launches a round / two barriers a round / this kernel: n = 128 9.9 to 10.5 / 1.79 / 1.21 to 1.28 ms on a
+// covariance with a spectrum that decays by e^-6, - / 1.50 / 1.10 on that of Gaussian rows, which
+// converges in fewer sweeps; n = 100 - / 1.11 / 0.90, n = 64 4.9 / 0.58 / 0.35, n = 34 - / 0.22 / 0.15, n = 32 1.69 / 0.19 / 0.14.
 constexpr int kEigSmallMax = 128;
 constexpr int kEigSmallThreads = 1024;
-constexpr int kEigSmallCols = 8;  // columns of Vt per workgroup
+constexpr int kEigSmallCols = 2;  // columns of Vt per workgroup
 
 // As eig_rotations_kernel has it, |a01| > 2^-40 sqrt(|a00 a11|) and tan of the smaller angle =
-// sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with fewer
-// roots and quotients in a row.  (The hardware's approximate ones are not enough: the
-// signs of some vectors then come out otherwise.)
+// sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with two roots and no quotient in
+// the chain, which is the longest of a round: with h the root of (a11 - a00)^2 + (2 a01)^2, the square of the cosine is (1 + |a11 - a00| / h) / 2
+// and the sine |a01| / (h cos).  A root, a quotient and a root, us (the columns of Vt two in both): n = 128 1208 / 1206, 100 922 / 904,
+// 64 371 / 351, 32 157 / 142, 8 30.9 / 28.4.  (The hardware's approximate roots are not enough: the
+// signs of some vectors then come out otherwise.)  Squares below 1e-280 are no turn: roots of what has lost digits there
+// would not give an orthogonal one.
 __device__ __forceinline__ bool eig_turns(double a00, double a11, double a01) {
-    return a01 * a01 > kEigSkip * kEigSkip * fabs(a00 * a11);
+    return a01 * a01 > fmax(kEigSkip * kEigSkip * fabs(a00 * a11), 1e-280);
 }
 __device__ __forceinline__ double2 eig_rotation(double a00, double a11, double a01) {
     const double d = a11 - a00, q = 2.0 * a01;
-    double tn = fabs(q) / (fabs(d) + sqrt(d * d + q * q));
-    if (d != 0.0 && (d < 0.0) != (q < 0.0)) tn = -tn;
-    const double c = rsqrt(1.0 + tn * tn);
-    return make_double2(c, tn * c);
+    const double rh = rsqrt(fma(d, d, q * q));              // 1 / hypotenuse
+    const double x = fma(0.5 * fabs(d), rh, 0.5);           // the square of the cosine
+    const double rc = rsqrt(x);
+    const double s = 0.5 * fabs(q) * rh * rc;
+    return make_double2(x * rc, d != 0.0 && (d < 0.0) != (q < 0.0) ? -s : s);
 }
 
 // Order 2: one block, the iteration below in one thread's registers.  (eig_small_kernel, whose length is mostly that of its code
@@ -242,13 +248,13 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
     int bk[3], bl[3], rd[3], wr[3][4];
 #pragma unroll
     for (int h = 0; h < 3; ++h) {
-        const int u = h < 2 ? wave - 1 + h * (kWaves - 1) : 2 * (kWaves - 1) + wave - 1;
+        const int u = wave - 1 + h * (kWaves - 1);
         const bool upper = lane > u;
         // not the diagonal, and not the lower lanes of the middle row of an odd number of pairs
-        on[h] = wave > 0 && (h < 2 || wave <= 2) && u < units && lane < half && lane != u && (upper || 2 * u != half - 1);
+        row_on[h] = wave > 0 && u < units;
+        on[h] = row_on[h] && lane < half && lane != u && (upper || 2 * u != half - 1);
         bk[h] = on[h] ? (upper ? u : half - 1 - u) : 0;
         bl[h] = on[h] ? (upper ? lane : half - 1 - lane) : 0;
-        row_on[h] = wave > 0 && (h < 2 || wave <= 2) && u < units;
         rd[h] = row_on[h] && lane < half ? u * half + lane : 0;   // lanes without a block compute for nobody
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

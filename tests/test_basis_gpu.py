@@ -296,6 +296,21 @@ def test_sym_eig_small_orders(rq, K):
     assert np.abs(c64 @ p - p * lam).max() <= 1e-6 * lam_ref[0]
 
 
+# zero eigenvalues (fewer rows than columns), and entries at both ends of fp32: squares and products far out of its range
+@pytest.mark.parametrize("K", [4, 34, 128])
+@pytest.mark.parametrize("scale", [2.0 ** -110, 1.0, 2.0 ** 110])
+def test_sym_eig_small_orders_rank_and_scale(rq, K, scale):
+    g = torch.Generator().manual_seed(K)
+    x = torch.randn(K // 2 + 1, K, generator=g, dtype=torch.float64)
+    c = (x.T @ x * scale).float()
+    lam, p = (t.double().cpu().numpy() for t in rq.resq_sym_eig(c.cuda()))
+    c64 = c.double().numpy()
+    lam_ref = np.linalg.eigvalsh(c64 / scale)[::-1] * scale
+    assert np.abs(lam - lam_ref).max() <= 1e-7 * lam_ref[0]      # the bounds of the test above
+    assert np.allclose(p.T @ p, np.eye(K), atol=1e-6)
+    assert np.abs(c64 @ p - p * lam).max() <= 1e-6 * lam_ref[0]
+
+
 # Outputs on the memory of c, at orders on both sides of the single-launch kernel's limit.  Its workgroups do not
 # wait for each other, so such calls go through the workspace, which they leave written.
 @pytest.mark.parametrize("K", [2, 8, 10, 64, 126, 128, 130])
