@@ -102,24 +102,29 @@ __device__ __forceinline__ void take_channel_consts(EpilogueConsts& c, const Cha
     c.ev[2] = h.even.z;
     c.ev[3] = h.even.w;
 }
-__device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
-    const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
-    const int32_t* wsum_hi = even_sum + a.L.n_pad;
-    const int32_t* wsum_lo = even_sum + 2 * a.L.n_pad;
+__device__ __forceinline__ void load_token_consts(EpilogueConsts& c, const DecodeArgs& a, int tok) {
     const bool has_hi = a.L.r > 0, has_lo = a.L.K - a.L.r > 0;
-    const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
-    EpilogueConsts c;
     c.sth = has_hi ? a.s_hi[tok] : 0.f;
     c.stl = has_lo ? a.s_lo[tok] : 0.f;
     c.ca = has_lo ? a.lo_sum[tok] : 0;
-    c.cth = (asym && has_hi) ? a.c_hi[tok] : 0.f;
-    c.ctl = (asym && has_lo) ? a.c_lo[tok] : 0.f;
+    c.cth = a.c_hi ? a.c_hi[tok] : 0.f;   // (null where there is no such group, see gemm_mixed_impl)
+    c.ctl = a.c_lo ? a.c_lo[tok] : 0.f;
+}
+__device__ __forceinline__ void load_channel_consts(EpilogueConsts& c, const DecodeArgs& a, int64_t n) {
+    const int32_t* wsum_hi = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 8 * a.L.n_pad);
+    const int32_t* wsum_lo = wsum_hi + a.L.n_pad;
+    const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
     take_channel_consts(c, load_channel_consts(a, n));
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         c.wsh[v] = asym ? wsum_hi[n + v] : 0;
         c.wsl[v] = asym ? wsum_lo[n + v] : 0;
     }
+}
+__device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
+    EpilogueConsts c;
+    load_token_consts(c, a, tok);
+    load_channel_consts(c, a, n);
     return c;
 }
 
@@ -637,25 +642,8 @@ constexpr int kStreamMaxM = 64;
 // NT: the weights are read with the non-temporal hint (one token slice on a layer too large
 // for the caches: nobody reads them again)
 template <bool DBG, int TG, int SK, bool NT = false>
-__global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const DecodeArgs a_in) {
+__global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const DecodeArgs a) {
     static_assert(TG * 16 <= kStreamMaxM && SK * TG <= 8, "LDS holds two chunks of every run");
-    // blockIdx.y selects a slice of TG * 16 tokens (more tokens than that: every slice
-    // streams the weights for itself, out of the last-level cache after the first)
-    DecodeArgs a = a_in;
-    {
-        const int tok0 = (int)blockIdx.y * (TG * 16);
-        a.M = a_in.M - tok0 < TG * 16 ? a_in.M - tok0 : TG * 16;
-        if (a.q_hi) a.q_hi += (int64_t)tok0 * a.ld_hi;
-        if (a.q_lo) a.q_lo += (int64_t)tok0 * a.ld_lo;
-        if (a.s_hi) a.s_hi += tok0;
-        if (a.s_lo) a.s_lo += tok0;
-        if (a.lo_sum) a.lo_sum += tok0;
-        if (a.c_hi) a.c_hi += tok0;
-        if (a.c_lo) a.c_lo += tok0;
-        a.y += (int64_t)tok0 * a.ldy;
-        if (a.dbg_hi) a.dbg_hi += (int64_t)tok0 * a.L.N;
-        if (a.dbg_lo) a.dbg_lo += (int64_t)tok0 * a.L.N;
-    }
     extern __shared__ __attribute__((aligned(1024))) uint8_t act[];  // [2][SK][kChunkBlocks][TG] blocks
     constexpr int kWaves = kDecodeThreads / 64;
     constexpr int G = kWaves / SK;  // groups per set
@@ -672,6 +660,32 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const Decod
     const int b_begin = run_begin(part), b_end = run_begin(part + 1);
     const int chunks = ((blocks + SK - 1) / SK + kChunkBlocks - 1) / kChunkBlocks;
     const int lane_off = (lane & 15) * kRowBytes + (lane >> 4) * 16;
+    auto load_w = [](const uint4* ptr) __attribute__((always_inline)) {
+        if constexpr (NT) return load_weights_16B(ptr);
+        else return *ptr;
+    };
+    const int sets = (a.groups + G - 1) / G;
+    auto weights_of = [&](int group) __attribute__((always_inline)) {
+        return reinterpret_cast<const uint4*>(a.packed + (int64_t)(group < a.groups ? group : 0) * a.L.group_bytes + lane_off);
+    };
+    // The first weights of a set: those of the first set before anything else (the addresses of everything else are 350
+    // instructions, 3500 clocks, and the compiler puts them in front of the first load when it may).
+    uint4 ring[kDecodeDepth];
+    auto ask = [&](int set) __attribute__((always_inline)) {
+        const int group = set * G + gsel;
+        const uint4* wp = weights_of(group);
+#pragma unroll
+        for (int i = 0; i < kDecodeDepth; ++i)
+            if (set < sets && group < a.groups && b_begin + i < b_end) ring[i] = load_w(&wp[(b_begin + i) * (kBlockBytes / 16)]);
+    };
+    ask(blockIdx.x);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+
+    // blockIdx.y selects a slice of TG * 16 tokens (more tokens than that: every slice
+    // streams the weights for itself, out of the last-level cache after the first)
+    const int tok0 = (int)blockIdx.y * (TG * 16);
+    const int M = a.M - tok0 < TG * 16 ? a.M - tok0 : TG * 16;
     // operand read: lane l supplies token l % 16, piece l / 16 of a block
     const int rr = lane & 15, rk = lane >> 4;
     const int read_off = part * kRunBytes + (4 * rr + (rk ^ (rr >> 2))) * 16;
@@ -686,7 +700,8 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const Decod
     // (Buffer loads, not global ones: a global load to LDS counts for the compiler as an access
     // through a flat address, after which it waits for every load in flight before any
     // use of a loaded register.)
-    const __amdgpu_buffer_rsrc_t rs_hi = make_rsrc(a.q_hi), rs_lo = make_rsrc(a.q_lo);
+    const __amdgpu_buffer_rsrc_t rs_hi = make_rsrc(a.q_hi + (int64_t)tok0 * a.ld_hi),
+                                 rs_lo = make_rsrc(a.q_lo + (int64_t)tok0 * a.ld_lo);
     auto fetch_one = [&](int q, int c, int buf, bool all) __attribute__((always_inline)) {
         const int f = q * kWaves + wave;
         const int g = f % TG, i = (f / TG) % kChunkBlocks, p = f / (TG * kChunkBlocks);
@@ -694,7 +709,7 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const Decod
         if (!all && b >= run_begin(p + 1)) return;
         b = b < blocks ? b : blocks - 1;  // a block past the end of its run: valid memory, never read from LDS
         int m = g * 16 + f_r;
-        m = m < a.M ? m : a.M - 1;  // rows past M repeat the last token (never stored)
+        m = m < M ? m : M - 1;  // rows past M repeat the last token (never stored)
         const bool hi = b < hi_blocks;
         const uint32_t voff = hi ? (uint32_t)(m * (int)a.ld_hi + b * kRowBytes + f_kc * 16)
                                  : (uint32_t)(m * (int)a.ld_lo + (b - hi_blocks) * kRowBytes + f_kc * 16);
@@ -713,22 +728,28 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const Decod
     };
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)act;
 
-    auto load_w = [](const uint4* ptr) __attribute__((always_inline)) {
-        if constexpr (NT) return load_weights_16B(ptr);
-        else return *ptr;
-    };
-    const int sets = (a.groups + G - 1) / G;
+    fetch_chunk(0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    // the epilogue's constants too are asked for long before they are needed: as four trips to memory, one after the
+    // other behind the last product, they took 5400 of 60000 clocks of 64 x 8192 -> 28672
+    EpilogueConsts ec[TG];
+    if (part == 0) {
+#pragma unroll
+        for (int g = 0; g < TG; ++g) {
+            const int tok = g * 16 + (lane & 15);
+            load_token_consts(ec[g], a, tok0 + (tok < M ? tok : M - 1));
+        }
+    }
     for (int set = blockIdx.x; set < sets; set += gridDim.x) {
         const int group = set * G + gsel;
         const bool live = group < a.groups;
-        const uint4* wp = reinterpret_cast<const uint4*>(
-            a.packed + (int64_t)(live ? group : 0) * a.L.group_bytes + lane_off);
-        uint4 ring[kDecodeDepth];
-#pragma unroll
-        for (int i = 0; i < kDecodeDepth; ++i)
-            if (live && b_begin + i < b_end) ring[i] = load_w(&wp[(b_begin + i) * (kBlockBytes / 16)]);
-        __syncthreads();  // every wavefront is done with the LDS buffers of the previous set
-        fetch_chunk(0, 0);
+        const uint4* wp = weights_of(group);
+        const int64_t n0 = (int64_t)(live ? group : 0) * 16 + (lane >> 4) * 4;
+        if (part == 0) load_channel_consts(ec[0], a, n0);
+        if (set != (int)blockIdx.x) {
+            __syncthreads();  // every wavefront is done with the LDS buffers of the previous set
+            fetch_chunk(0, 0);
+        }
         wait_loads_and_barrier<0>();
 
         v4i acc_hi[TG], acc_lo[TG];
@@ -904,12 +925,18 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const Decod
                 }
             }
         }
+        ask(set + gridDim.x);
         if (!live || part != 0) continue;  // the barriers of the next set are reached all the same
 #pragma unroll
         for (int g = 0; g < TG; ++g) {
             const int tok = g * 16 + (lane & 15);
-            if (tok < a.M)
-                stream_epilogue<DBG>(a, tok, (int64_t)group * 16 + (lane >> 4) * 4, acc_hi[g], acc_lo[g]);
+            EpilogueConsts c = ec[0];   // the channels' part
+            c.sth = ec[g].sth;
+            c.stl = ec[g].stl;
+            c.cth = ec[g].cth;
+            c.ctl = ec[g].ctl;
+            c.ca = ec[g].ca;
+            if (tok < M) stream_epilogue<DBG>(a, tok0 + tok, n0, c, acc_hi[g], acc_lo[g]);
             __builtin_amdgcn_sched_barrier(0);  // one token group at a time: keeps the registers few
         }
     }
