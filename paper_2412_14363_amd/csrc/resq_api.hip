@@ -732,6 +732,7 @@ static int gemm_mixed_impl(const int8_t* q_hi, const uint8_t* q_lo, const float*
     }
     const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
     if (tiles > 0x7FFFFFFF) return RESQ_ERR_SHAPE;
+    set_tile_order(a);
 
     // static LDS (68.5 or 76.5 KiB): two workgroups per compute unit
     if (narrow) {

@@ -109,6 +109,22 @@ constexpr int kMetaBytes = 4608;
 // two workgroups fit the 160 KiB of a compute unit
 static_assert(2 * (kMetaOff + kMetaBytes) <= 160 * 1024, "LDS of two resident workgroups");
 
+// n / d for 0 <= n < 2^31 by one multiplication and a shift (Granlund and Montgomery 1994, N = 31 bits); a division by a
+// run-time divisor is some 40 dependent instructions, in front of the first load of every workgroup.
+struct Divisor {
+    uint32_t magic;  // 0: the divisor is 1
+    int shift;
+};
+inline Divisor make_divisor(int d) {
+    if (d == 1) return {0u, 0};
+    int l = 0;
+    while (((int64_t)1 << l) < d) ++l;
+    return {(uint32_t)(((uint64_t)1 << (31 + l)) / (uint64_t)d + 1), l - 1};
+}
+__device__ __forceinline__ int divide(int n, Divisor d) {
+    return d.magic == 0 ? n : (int)((uint32_t)(((uint64_t)(uint32_t)n * d.magic) >> 32) >> d.shift);
+}
+
 struct GemmArgs {
     const uint8_t* q_hi;
     const uint8_t* q_lo;
@@ -128,6 +144,9 @@ struct GemmArgs {
     int stages_hi, stages_lo;
     int tiles_m, tiles_n;
     int bands;   // > 0: token tiles to a band in the order of tile_of_block, tiles_n without padding tiles
+    int last;    // ... and to the last band
+    int patches; // 1: the order of whole patches
+    Divisor by_band, by_rows, by_last;  // tiles of a band; of a column of a band, a patch or the grid; of a column of the last band
     int swiglu;  // 1: channels 2c and 2c+1 are the gate and the up row of feature c; y[m, c] = silu(gate) * up
 };
 
@@ -273,28 +292,43 @@ __device__ __forceinline__ void buffer_load_to_lds_16B(__amdgpu_buffer_rsrc_t rs
 // 4096 30.7 / 31.6.  A column of padding tiles in a multiple of eight, runs with it / bands without, whole calls: 2500 x 2048 ->
 // 3200, 520 tiles of which 500 are its own, 35.4 / 27.9, 8192 x 1024 -> 640 29.0 / 27.6; 14 of 18 such shapes equal.  (Bands of 4 and of 16 throughout: within 3 %, mostly slower.)
 constexpr int kBand = 8;
-__host__ __device__ inline bool whole_patches(int tiles_m, int tiles_n) {
+inline bool whole_patches(int tiles_m, int tiles_n) {
     return tiles_m % 8 == 0 && tiles_n % 8 == 0 && (int64_t)tiles_m * tiles_n % 512 == 0;
 }
+// what tile_of_block divides by (tiles_m, tiles_n and bands are set)
+inline void set_tile_order(GemmArgs& a) {
+    a.last = 0;
+    a.by_band = a.by_last = {0u, 0};
+    if (a.bands) {
+        a.last = a.tiles_m % a.bands ? a.tiles_m % a.bands : a.bands;
+        a.by_band = make_divisor(a.bands * a.tiles_n);
+        a.by_last = make_divisor(a.last);
+    }
+    a.patches = !a.bands && whole_patches(a.tiles_m, a.tiles_n) ? 1 : 0;
+    a.by_rows = make_divisor(a.bands ? a.bands : a.patches ? a.tiles_m >> 3 : a.tiles_m);
+}
 __device__ __forceinline__ void tile_of_block(const GemmArgs& a, int& tm, int& tn) {
+    // what the first loads need beside the tile: asked for together with what the order needs, not in a second trip
+    asm volatile("" ::"s"(a.q_hi), "s"(a.q_lo), "s"(a.ld_hi), "s"(a.ld_lo), "s"(a.packed), "s"(a.L.group_bytes), "s"(a.L.N),
+                 "s"(a.M), "s"(a.stages_hi), "s"(a.stages_lo));
     const int total = a.tiles_m * a.tiles_n;
     const int id = blockIdx.x, xcd = id & 7, k = id >> 3;
     if (a.bands) {
         const int rest = total & 7;
         const int lin = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + k;
-        const int band = lin / (a.bands * a.tiles_n), in_band = lin - band * a.bands * a.tiles_n;
-        const int left = a.tiles_m - a.bands * band, height = left < a.bands ? left : a.bands;
-        tn = in_band / height;
-        tm = a.bands * band + (in_band - tn * height);
-    } else if (whole_patches(a.tiles_m, a.tiles_n)) {
+        const int band = divide(lin, a.by_band), in_band = lin - band * a.bands * a.tiles_n;
+        const bool whole = a.tiles_m - a.bands * band >= a.bands;
+        tn = divide(in_band, whole ? a.by_rows : a.by_last);
+        tm = a.bands * band + (in_band - tn * (whole ? a.bands : a.last));
+    } else if (a.patches) {
         const int patch = (k >> 6) * 8 + xcd, within = k & 63;
-        const int patches_m = a.tiles_m >> 3;
-        tm = (patch % patches_m) * 8 + (within & 7);
-        tn = (patch / patches_m) * 8 + (within >> 3);
+        const int column = divide(patch, a.by_rows);
+        tm = (patch - column * (a.tiles_m >> 3)) * 8 + (within & 7);
+        tn = column * 8 + (within >> 3);
     } else {
         const int lin = xcd * (total >> 3) + k;
-        tn = lin / a.tiles_m;
-        tm = lin % a.tiles_m;
+        tn = divide(lin, a.by_rows);
+        tm = lin - tn * a.tiles_m;
     }
 }
 
@@ -381,34 +415,36 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
     const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
 
     // ---- epilogue constants -> LDS ---------------------------------------------
-    // These are the oldest loads of their waves, so the first wait for a stage
-    // covers them.  Token rows past M repeat the last row (never stored).
+    // Asked for behind the first stages, which the products wait for, and there long before the
+    // last stage is.  Token rows past M repeat the last row (never stored).
     // (a load to LDS places an active lane's bytes at the base plus 16 x its lane number)
-    if (wave == 0) {
-        if (lane < 32) {
-            load_to_lds_16B((lane < 16 ? sw_hi : sw_lo) + n0 + (lane & 15) * 8, lds + kMetaOff + kMetaSwHi);
-            if (asym) load_to_lds_16B(even_sum + a.L.n_pad + n0 + lane * 4, lds + kMetaOff + kMetaWsumHi);
-        }
-    } else if (wave == 1) {
-        if (lane < 32) {
-            load_to_lds_16B(even_sum + n0 + lane * 4, lds + kMetaOff + kMetaEven);
-            if (asym) load_to_lds_16B(even_sum + 2 * a.L.n_pad + n0 + lane * 4, lds + kMetaOff + kMetaWsumLo);
-        }
-    } else {
+    auto load_constants = [&]() __attribute__((always_inline)) {
+        if (wave == 0) {
+            if (lane < 32) {
+                load_to_lds_16B((lane < 16 ? sw_hi : sw_lo) + n0 + (lane & 15) * 8, lds + kMetaOff + kMetaSwHi);
+                if (asym) load_to_lds_16B(even_sum + a.L.n_pad + n0 + lane * 4, lds + kMetaOff + kMetaWsumHi);
+            }
+        } else if (wave == 1) {
+            if (lane < 32) {
+                load_to_lds_16B(even_sum + n0 + lane * 4, lds + kMetaOff + kMetaEven);
+                if (asym) load_to_lds_16B(even_sum + 2 * a.L.n_pad + n0 + lane * 4, lds + kMetaOff + kMetaWsumLo);
+            }
+        } else {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            int64_t m = m0 + h * 64 + lane;
-            m = m < a.M ? m : a.M - 1;
-            if (wave == 2) {
-                if (S_hi > 0) load_to_lds_4B(a.s_hi + m, lds + kMetaOff + kMetaSHi + h * 256);
-                if (S_lo > 0) load_to_lds_4B(a.s_lo + m, lds + kMetaOff + kMetaSLo + h * 256);
-            } else {
-                if (S_lo > 0) load_to_lds_4B(a.lo_sum + m, lds + kMetaOff + kMetaLoSum + h * 256);
-                if (asym && S_hi > 0) load_to_lds_4B(a.c_hi + m, lds + kMetaOff + kMetaCHi + h * 256);
-                if (asym && S_lo > 0) load_to_lds_4B(a.c_lo + m, lds + kMetaOff + kMetaCLo + h * 256);
+            for (int h = 0; h < 2; ++h) {
+                int64_t m = m0 + h * 64 + lane;
+                m = m < a.M ? m : a.M - 1;
+                if (wave == 2) {
+                    if (S_hi > 0) load_to_lds_4B(a.s_hi + m, lds + kMetaOff + kMetaSHi + h * 256);
+                    if (S_lo > 0) load_to_lds_4B(a.s_lo + m, lds + kMetaOff + kMetaSLo + h * 256);
+                } else {
+                    if (S_lo > 0) load_to_lds_4B(a.lo_sum + m, lds + kMetaOff + kMetaLoSum + h * 256);
+                    if (asym && S_hi > 0) load_to_lds_4B(a.c_hi + m, lds + kMetaOff + kMetaCHi + h * 256);
+                    if (asym && S_lo > 0) load_to_lds_4B(a.c_lo + m, lds + kMetaOff + kMetaCLo + h * 256);
+                }
             }
         }
-    }
+    };
 
     // ---- global -> LDS copy --------------------------------------------------
     // One load instruction fills one block: lane l fetches row l / 4, piece
@@ -420,13 +456,13 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
     // scalar offset that depends on the stage alone.
     uint32_t a_voff_hi[2], a_voff_lo[2], b_voff[2];
     {
+        const int rows = (int)min(a.M - m0, (int64_t)(1 << 20));  // of this tile and those below it
         const int r = lane >> 2, kc = (lane & 3) ^ (lane >> 4);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            int64_t row = (wave * 2 + h) * 16 + r;
-            row = m0 + row < a.M ? row : a.M - 1 - m0;
-            a_voff_hi[h] = (uint32_t)(row * a.ld_hi + kc * 16);
-            a_voff_lo[h] = (uint32_t)(row * a.ld_lo + kc * 16);
+            const int row = min((wave * 2 + h) * 16 + r, rows - 1);
+            a_voff_hi[h] = (uint32_t)row * (uint32_t)a.ld_hi + kc * 16;
+            a_voff_lo[h] = (uint32_t)row * (uint32_t)a.ld_lo + kc * 16;
         }
         b_voff[0] = r * kRowBytes + kc * 16;
         b_voff[1] = b_voff[0] + (uint32_t)a.L.group_bytes;
@@ -465,13 +501,15 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
     // acc[j][i]: channels 16 j.., tokens 16 i.. of the wave tile.  Lane l holds
     // token (l % 16) and, in element v, channel 4 (l / 16) + v.
     v4i acc_hi[4][4], acc_lo[4][4];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            acc_hi[j][i] = (v4i){0, 0, 0, 0};
-            acc_lo[j][i] = (v4i){0, 0, 0, 0};
-        }
+            for (int i = 0; i < 4; ++i) {
+                acc_hi[j][i] = (v4i){0, 0, 0, 0};
+                acc_lo[j][i] = (v4i){0, 0, 0, 0};
+            }
+    };
 
     // The tile that a loop does not touch stays where it is, in accumulation
     // registers: stating so in every stage keeps the register allocator from
@@ -625,6 +663,15 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
         const int ahead = S < kPrefetch ? S : kPrefetch;
         for (int i = 0; i < ahead; ++i)
             static_for<kLoadsPerStage>([&](auto k) __attribute__((always_inline)) { issue_load(k, i, i); });
+        // The rest of the preparations behind the first loads: in front of them they took 1400 of the 51000 clocks of 2048 x
+        // 4096 -> 4096.  With the order of the tiles by multiplications and one trip for the arguments, us: that layer 29.9 ->
+        // 29.5, 1500 x 1024 -> 4096 13.35 -> 13.0.  (The fp8 kernel, which has several rounds of tiles, gains nothing by it.)
+        __builtin_amdgcn_sched_barrier(0);
+        load_constants();
+        clear();
+        park(acc_hi);
+        park(acc_lo);
+        __builtin_amdgcn_sched_barrier(0);
         wait_stage_and_barrier(ahead - 1);  // stage 0 (and the epilogue constants) have landed everywhere
         static_for<8>([&](auto k) __attribute__((always_inline)) { read_frag(k, p0, a_off, b_off); });
 

@@ -111,41 +111,43 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
     const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
     const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
 
-    // ---- epilogue constants -> LDS (the oldest loads of their waves) ------------
+    // ---- epilogue constants -> LDS, behind the first stages' loads ------------
     // Token rows past M repeat the last row (never stored).
-    if (half != 0) {
-        // the first ring's wavefronts fetch them
-    } else if (wave == 0) {
-        if (lane < 32) {
-            load_to_lds_16B((lane < 16 ? sw_hi : sw_lo) + n0 + (lane & 15) * 8, lds + kMetaOff64 + kMetaSwHi);
-            if (asym) load_to_lds_16B(even_sum + a.L.n_pad + n0 + lane * 4, lds + kMetaOff64 + kMetaWsumHi);
-        }
-    } else if (wave == 1) {
-        if (lane < 32) {
-            load_to_lds_16B(even_sum + n0 + lane * 4, lds + kMetaOff64 + kMetaEven);
-            if (asym) load_to_lds_16B(even_sum + 2 * a.L.n_pad + n0 + lane * 4, lds + kMetaOff64 + kMetaWsumLo);
-        }
-    } else {
-        int64_t m = m0 + lane;
-        m = m < a.M ? m : a.M - 1;
-        if (wave == 2) {
-            if (any_hi) load_to_lds_4B(a.s_hi + m, lds + kMetaOff64 + kMetaSHi);
-            if (any_lo) load_to_lds_4B(a.s_lo + m, lds + kMetaOff64 + kMetaSLo);
+    auto load_constants = [&]() __attribute__((always_inline)) {
+        if (half != 0) {
+            // the first ring's wavefronts fetch them
+        } else if (wave == 0) {
+            if (lane < 32) {
+                load_to_lds_16B((lane < 16 ? sw_hi : sw_lo) + n0 + (lane & 15) * 8, lds + kMetaOff64 + kMetaSwHi);
+                if (asym) load_to_lds_16B(even_sum + a.L.n_pad + n0 + lane * 4, lds + kMetaOff64 + kMetaWsumHi);
+            }
+        } else if (wave == 1) {
+            if (lane < 32) {
+                load_to_lds_16B(even_sum + n0 + lane * 4, lds + kMetaOff64 + kMetaEven);
+                if (asym) load_to_lds_16B(even_sum + 2 * a.L.n_pad + n0 + lane * 4, lds + kMetaOff64 + kMetaWsumLo);
+            }
         } else {
-            if (any_lo) load_to_lds_4B(a.lo_sum + m, lds + kMetaOff64 + kMetaLoSum);
-            if (asym && any_hi) load_to_lds_4B(a.c_hi + m, lds + kMetaOff64 + kMetaCHi);
-            if (asym && any_lo) load_to_lds_4B(a.c_lo + m, lds + kMetaOff64 + kMetaCLo);
+            int64_t m = m0 + lane;
+            m = m < a.M ? m : a.M - 1;
+            if (wave == 2) {
+                if (any_hi) load_to_lds_4B(a.s_hi + m, lds + kMetaOff64 + kMetaSHi);
+                if (any_lo) load_to_lds_4B(a.s_lo + m, lds + kMetaOff64 + kMetaSLo);
+            } else {
+                if (any_lo) load_to_lds_4B(a.lo_sum + m, lds + kMetaOff64 + kMetaLoSum);
+                if (asym && any_hi) load_to_lds_4B(a.c_hi + m, lds + kMetaOff64 + kMetaCHi);
+                if (asym && any_lo) load_to_lds_4B(a.c_lo + m, lds + kMetaOff64 + kMetaCLo);
+            }
         }
-    }
+    };
 
     // ---- global -> LDS copy: wave w copies A block w and B blocks 2w, 2w+1 of each stage ----
     uint32_t a_voff_hi, a_voff_lo, b_voff[2];
     {
+        const int rows = (int)min(a.M - m0, (int64_t)(1 << 20));  // of this tile and those below it
         const int r = lane >> 2, kc = (lane & 3) ^ (lane >> 4);
-        int64_t row = wave * 16 + r;
-        row = m0 + row < a.M ? row : a.M - 1 - m0;
-        a_voff_hi = (uint32_t)(row * a.ld_hi + kc * 16);
-        a_voff_lo = (uint32_t)(row * a.ld_lo + kc * 16);
+        const int row = min(wave * 16 + r, rows - 1);
+        a_voff_hi = (uint32_t)row * (uint32_t)a.ld_hi + kc * 16;
+        a_voff_lo = (uint32_t)row * (uint32_t)a.ld_lo + kc * 16;
         b_voff[0] = r * kRowBytes + kc * 16;
         b_voff[1] = b_voff[0] + (uint32_t)a.L.group_bytes;
     }
@@ -181,13 +183,15 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
 
     // ---- accumulators: acc[j][i]: channels 16 j.., tokens 16 i.. of the wave tile ----
     v4i acc_hi[4][2], acc_lo[4][2];
+    auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            acc_hi[j][i] = (v4i){0, 0, 0, 0};
-            acc_lo[j][i] = (v4i){0, 0, 0, 0};
-        }
+            for (int i = 0; i < 2; ++i) {
+                acc_hi[j][i] = (v4i){0, 0, 0, 0};
+                acc_lo[j][i] = (v4i){0, 0, 0, 0};
+            }
+    };
     auto park = [&](v4i (&acc)[4][2]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -321,6 +325,14 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
         const int ahead = S < kPrefetch64 ? S : kPrefetch64;
         for (int i = 0; i < ahead; ++i)
             static_for<kLoadsPerStage64>([&](auto k) __attribute__((always_inline)) { issue_load(k, i, i); });
+        // the rest of the preparations behind the first loads, as in the wide kernel (us: 512 x 4096 -> 4096 12.4 -> 12.1, 512 x
+        // 14336 -> 4096 37.3 -> 36.9, 100 x 1024 -> 14336 8.27 -> 7.92, one ring 1024 x 4096 -> 4096 19.4 -> 19.2)
+        __builtin_amdgcn_sched_barrier(0);
+        load_constants();
+        clear();
+        park(acc_hi);
+        park(acc_lo);
+        __builtin_amdgcn_sched_barrier(0);
         wait_stages_and_barrier<kLoadsPerStage64, kPrefetch64 - 1>(ahead - 1);  // stage 0 and the constants have landed
         static_for<6>([&](auto k) __attribute__((always_inline)) { read_frag(k, p0, a_off, b_off); });
 
