@@ -102,6 +102,8 @@ __device__ __forceinline__ void take_channel_consts(EpilogueConsts& c, const Cha
     c.ev[2] = h.even.z;
     c.ev[3] = h.even.w;
 }
+// The two parts that the chunked kernel asks for at different times.  (The kernels for at most 16 tokens keep one function for
+// both: made of these two, 4 x 8192 -> 28672 took 25.65 instead of 25.50 us with its quantizer.)
 __device__ __forceinline__ void load_token_consts(EpilogueConsts& c, const DecodeArgs& a, int tok) {
     const bool has_hi = a.L.r > 0, has_lo = a.L.K - a.L.r > 0;
     c.sth = has_hi ? a.s_hi[tok] : 0.f;
@@ -122,9 +124,23 @@ __device__ __forceinline__ void load_channel_consts(EpilogueConsts& c, const Dec
     }
 }
 __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
+    const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
+    const int32_t* wsum_hi = even_sum + a.L.n_pad;
+    const int32_t* wsum_lo = even_sum + 2 * a.L.n_pad;
+    const bool has_hi = a.L.r > 0, has_lo = a.L.K - a.L.r > 0;
+    const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
     EpilogueConsts c;
-    load_token_consts(c, a, tok);
-    load_channel_consts(c, a, n);
+    c.sth = has_hi ? a.s_hi[tok] : 0.f;
+    c.stl = has_lo ? a.s_lo[tok] : 0.f;
+    c.ca = has_lo ? a.lo_sum[tok] : 0;
+    c.cth = (asym && has_hi) ? a.c_hi[tok] : 0.f;
+    c.ctl = (asym && has_lo) ? a.c_lo[tok] : 0.f;
+    take_channel_consts(c, load_channel_consts(a, n));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        c.wsh[v] = asym ? wsum_hi[n + v] : 0;
+        c.wsl[v] = asym ? wsum_lo[n + v] : 0;
+    }
     return c;
 }
 
