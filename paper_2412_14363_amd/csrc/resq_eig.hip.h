@@ -135,9 +135,10 @@ constexpr int kEigSmallCols = 2;  // columns of Vt per workgroup
 // and the sine |a01| / (h cos).  A root, a quotient and a root, us (the columns of Vt two in both): n = 128 1208 / 1206, 100 922 / 904,
 // 64 371 / 351, 32 157 / 142, 8 30.9 / 28.4.  (The hardware's approximate roots are not enough: the
 // signs of some vectors then come out otherwise.)  Squares below 1e-280 are no turn: roots of what has lost digits there
-// would not give an orthogonal one.
+// would not give an orthogonal one.  (Two comparisons, not one with the larger bound, which would drop
+// a NaN: with one on the diagonal the first comparison fails, the pair is not turned and no vector becomes NaN.)
 __device__ __forceinline__ bool eig_turns(double a00, double a11, double a01) {
-    return a01 * a01 > fmax(kEigSkip * kEigSkip * fabs(a00 * a11), 1e-280);
+    return a01 * a01 > kEigSkip * kEigSkip * fabs(a00 * a11) && a01 * a01 > 1e-280;
 }
 __device__ __forceinline__ double2 eig_rotation(double a00, double a11, double a01) {
     const double d = a11 - a00, q = 2.0 * a01;

@@ -311,6 +311,23 @@ def test_sym_eig_small_orders_rank_and_scale(rq, K, scale):
     assert np.abs(c64 @ p - p * lam).max() <= 1e-6 * lam_ref[0]
 
 
+# A NaN on the diagonal turns no pair: at order 2 the other value and both vectors come out; in larger matrices it
+# reaches every value (but no angle), so all share the first place, and what is written of the vectors is finite.
+@pytest.mark.parametrize("K,at", [(2, 0), (2, 1), (4, 0), (34, 33), (128, 64)])
+def test_sym_eig_nan_on_the_diagonal(rq, K, at):
+    g = torch.Generator().manual_seed(K + at)
+    x = torch.randn(2 * K + 3, K, generator=g, dtype=torch.float64)
+    c = (x.T @ x).float()
+    c[at, at] = float("nan")
+    lam, p = torch.full((K,), 7.0, device="cuda"), torch.full((K, K), 7.0, device="cuda")
+    rq.resq_sym_eig_static(c.cuda(), lam, p)
+    lam, p = lam.cpu(), p.cpu()
+    assert int(lam.isnan().sum()) == 1 and not p.isnan().any()
+    if K == 2:
+        assert torch.equal(lam[~lam.isnan()], c[1 - at, 1 - at].reshape(1))
+        assert torch.equal(p.abs().sum(0), torch.ones(2)) and torch.equal(p.abs().sum(1), torch.ones(2))
+
+
 # Outputs on the memory of c, at orders on both sides of the single-launch kernel's limit.  Its workgroups do not
 # wait for each other, so such calls go through the workspace, which they leave written.
 @pytest.mark.parametrize("K", [2, 8, 10, 64, 126, 128, 130])
