@@ -102,39 +102,22 @@ __device__ __forceinline__ void take_channel_consts(EpilogueConsts& c, const Cha
     c.ev[2] = h.even.z;
     c.ev[3] = h.even.w;
 }
-// The two parts that the chunked kernel asks for at different times.  (The kernels for at most 16 tokens keep one function for
-// both: made of these two, 4 x 8192 -> 28672 took 25.65 instead of 25.50 us with its quantizer.)
 __device__ __forceinline__ void load_token_consts(EpilogueConsts& c, const DecodeArgs& a, int tok) {
     const bool has_hi = a.L.r > 0, has_lo = a.L.K - a.L.r > 0;
-    c.sth = has_hi ? a.s_hi[tok] : 0.f;
-    c.stl = has_lo ? a.s_lo[tok] : 0.f;
-    c.ca = has_lo ? a.lo_sum[tok] : 0;
-    c.cth = a.c_hi ? a.c_hi[tok] : 0.f;   // (null where there is no such group, see gemm_mixed_impl)
-    c.ctl = a.c_lo ? a.c_lo[tok] : 0.f;
-}
-__device__ __forceinline__ void load_channel_consts(EpilogueConsts& c, const DecodeArgs& a, int64_t n) {
-    const int32_t* wsum_hi = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 8 * a.L.n_pad);
-    const int32_t* wsum_lo = wsum_hi + a.L.n_pad;
     const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
-    take_channel_consts(c, load_channel_consts(a, n));
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-        c.wsh[v] = asym ? wsum_hi[n + v] : 0;
-        c.wsl[v] = asym ? wsum_lo[n + v] : 0;
-    }
-}
-__device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
-    const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
-    const int32_t* wsum_hi = even_sum + a.L.n_pad;
-    const int32_t* wsum_lo = even_sum + 2 * a.L.n_pad;
-    const bool has_hi = a.L.r > 0, has_lo = a.L.K - a.L.r > 0;
-    const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
-    EpilogueConsts c;
     c.sth = has_hi ? a.s_hi[tok] : 0.f;
     c.stl = has_lo ? a.s_lo[tok] : 0.f;
     c.ca = has_lo ? a.lo_sum[tok] : 0;
     c.cth = (asym && has_hi) ? a.c_hi[tok] : 0.f;
     c.ctl = (asym && has_lo) ? a.c_lo[tok] : 0.f;
+}
+__device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs& a, int tok, int64_t n) {
+    const int32_t* even_sum = reinterpret_cast<const int32_t*>(a.packed + a.L.scale_off + 4 * a.L.n_pad);
+    const int32_t* wsum_hi = even_sum + a.L.n_pad;
+    const int32_t* wsum_lo = even_sum + 2 * a.L.n_pad;
+    const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
+    EpilogueConsts c;
+    load_token_consts(c, a, tok);
     take_channel_consts(c, load_channel_consts(a, n));
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -142,6 +125,40 @@ __device__ __forceinline__ EpilogueConsts load_epilogue_consts(const DecodeArgs&
         c.wsl[v] = asym ? wsum_lo[n + v] : 0;
     }
     return c;
+}
+
+// The channels' part of a whole group in one register of a wavefront, for gemm_stream_kernel, which holds it through the stream:
+// lanes 0 .. 7 hold the group's 16 high weight scales, 8 .. 15 the low ones, 16 .. 31 even_sum, and with asymmetric codes 32 .. 47
+// wsum_hi, 48 .. 63 wsum_lo.  (A lane's own part is 12 registers, 20 with asymmetric codes: with them the instances for one token
+// group have 136 to 144 registers instead of 122 to 127, more than the 128 with which two workgroups fit a compute unit, and
+// launches of more than 256 workgroups take two rounds: us, own part / this / asked for behind the stream, 48 x 4096 -> 18432
+// 20.3 / 16.8 / 17.1, 616 x 5056 -> 796 14.7 / 11.5 / 11.9, 880 x 7488 -> 270 15.0 / 11.6 / 12.5, 196 x 896 -> 4950 11.7 / 9.8 /
+// 9.9; of 256 workgroups or fewer, 62 shapes drawn, 0.949 / 0.948 / 1 of the time.)
+__device__ __forceinline__ uint32_t load_group_consts(const DecodeArgs& a, int group, int lane) {
+    const uint32_t sel = lane >> 4, at = lane & 15;
+    const uint32_t before = sel == 0 ? (at < 8 ? 0 : 2) : 4 * sel;   // bytes a channel in front of this lane's array
+    const uint64_t offset = (uint64_t)before * (uint32_t)a.L.n_pad + (uint64_t)(uint32_t)group * (sel == 0 ? 32 : 64) +
+                            (sel == 0 ? at & 7 : at) * 4;
+    return sel < 2 || a.c_hi || a.c_lo ? *reinterpret_cast<const uint32_t*>(a.packed + a.L.scale_off + offset) : 0u;
+}
+// ... and each lane's four channels out of it (all lanes of the wavefront take part)
+__device__ __forceinline__ void take_group_consts(EpilogueConsts& c, const DecodeArgs& a, uint32_t held, int lane) {
+    int quad = lane >> 4;
+    asm volatile("" : "+v"(quad));   // or the places are worked out in front of the stream and held through it
+    auto of = [&](int lane0, int each, int v) __attribute__((always_inline)) {
+        return (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (lane0 + each * quad + v), (int)held);
+    };
+    ChannelConsts h;
+    h.sw_hi = make_uint2(of(0, 2, 0), of(0, 2, 1));
+    h.sw_lo = make_uint2(of(8, 2, 0), of(8, 2, 1));
+    h.even = make_int4(of(16, 4, 0), of(16, 4, 1), of(16, 4, 2), of(16, 4, 3));
+    take_channel_consts(c, h);
+    const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        c.wsh[v] = asym ? (int)of(32, 4, v) : 0;   // (left unset, they are eight registers through the stream)
+        c.wsl[v] = asym ? (int)of(48, 4, v) : 0;
+    }
 }
 
 // barrier of the workgroup for what lies in LDS: loads from memory stay in flight
@@ -761,7 +778,8 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const Decod
         const bool live = group < a.groups;
         const uint4* wp = weights_of(group);
         const int64_t n0 = (int64_t)(live ? group : 0) * 16 + (lane >> 4) * 4;
-        if (part == 0) load_channel_consts(ec[0], a, n0);
+        uint32_t channels = 0;
+        if (part == 0) channels = load_group_consts(a, live ? group : 0, lane);
         if (set != (int)blockIdx.x) {
             __syncthreads();  // every wavefront is done with the LDS buffers of the previous set
             fetch_chunk(0, 0);
@@ -943,16 +961,17 @@ __global__ __launch_bounds__(kDecodeThreads) void gemm_stream_kernel(const Decod
         }
         ask(set + gridDim.x);
         if (!live || part != 0) continue;  // the barriers of the next set are reached all the same
+        EpilogueConsts k;
+        take_group_consts(k, a, channels, lane);
 #pragma unroll
         for (int g = 0; g < TG; ++g) {
             const int tok = g * 16 + (lane & 15);
-            EpilogueConsts c = ec[0];   // the channels' part
-            c.sth = ec[g].sth;
-            c.stl = ec[g].stl;
-            c.cth = ec[g].cth;
-            c.ctl = ec[g].ctl;
-            c.ca = ec[g].ca;
-            if (tok < M) stream_epilogue<DBG>(a, tok0 + tok, n0, c, acc_hi[g], acc_lo[g]);
+            k.sth = ec[g].sth;
+            k.stl = ec[g].stl;
+            k.cth = ec[g].cth;
+            k.ctl = ec[g].ctl;
+            k.ca = ec[g].ca;
+            if (tok < M) stream_epilogue<DBG>(a, tok0 + tok, n0, k, acc_hi[g], acc_lo[g]);
             __builtin_amdgcn_sched_barrier(0);  // one token group at a time: keeps the registers few
         }
     }

@@ -13,8 +13,8 @@ OBJDUMP = shutil.which("llvm-objdump", path="/opt/rocm/llvm/bin") or shutil.whic
 
 
 @pytest.fixture(scope="module")
-def kernels(tmp_path_factory):
-    """name -> instructions of every kernel with matrix instructions in assembly"""
+def code_object(tmp_path_factory):
+    """the library's own gfx950 code, as a file"""
     if not OBJDUMP:
         pytest.skip("no llvm-objdump")
     data = build.ensure_built().read_bytes()
@@ -28,6 +28,13 @@ def kernels(tmp_path_factory):
         at += 24 + length
     path = tmp_path_factory.mktemp("code") / "gfx950.co"
     path.write_bytes(code)
+    return path
+
+
+@pytest.fixture(scope="module")
+def kernels(code_object):
+    """name -> instructions of every kernel with matrix instructions in assembly"""
+    path = code_object
     symbols = subprocess.run([OBJDUMP, "-t", str(path)], capture_output=True, text=True, check=True).stdout
     names = sorted(set(re.findall(r"\s(_Z\w*(?:gemm_mixed_\w*kernel|project_split_wide_kernel)\w*)$", symbols, re.M)))
     text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--disassemble-symbols=" + ",".join(names), str(path)],
@@ -81,3 +88,18 @@ def test_operands_are_ready_two_states_before_a_product(kernels):
                 assert not late, (name, late, i)
             elif m.startswith("v_"):
                 written = written[-3:] + [(state, registers(ops[0]), i)]
+
+
+def test_stream_kernels_of_one_token_group_leave_room_for_a_second_workgroup(code_object):
+    """Launches of more than 256 workgroups count on two to a compute unit: 8 wavefronts each, so 4 on a SIMD, 128 registers
+    of 512, and no spills.  (With eight runs to a group LDS holds one workgroup anyway.)"""
+    notes = subprocess.run([re.sub("objdump$", "readelf", OBJDUMP), "--notes", str(code_object)], capture_output=True, text=True,
+                           check=True).stdout
+    found = {}
+    for entry in notes.split("- .agpr_count:")[1:]:
+        name = re.search(r"\.name:\s+(\S+)", entry)[1]
+        if m := re.search(r"gemm_stream_kernelILb0ELi1ELi([124])ELb([01])E", name):
+            found[m.groups()] = tuple(int(re.search(r"\.%s:\s+(\d+)" % key, entry)[1])
+                                      for key in ("vgpr_count", "vgpr_spill_count", "private_segment_fixed_size"))
+    assert len(found) == 6, found
+    assert all(count <= 128 and not spilled and not scratch for count, spilled, scratch in found.values()), found
