@@ -318,6 +318,11 @@ STREAM_PLAN_SHAPES = [
     ((60, 520, 16400, 64), (1, 4, 1)),
 ]
 
+# ... and shapes of more than 256 sets of eight channel groups, so that workgroups take a second set, for every number of token
+# groups; of the last set one group or seven are there
+SECOND_SET_SHAPES = [((12, 4352, 32900, 512), (1, 1, 1)), ((20, 520, 32900, 64), (1, 2, 1)), ((40, 2200, 33000, 256), (1, 4, 1)),
+                     ((60, 520, 32900, 0), (1, 4, 1))]
+
 
 def test_gemm_mixed_plan():
     plan = binding.resq_gemm_mixed_plan
@@ -337,9 +342,10 @@ def test_gemm_mixed_plan():
     assert plan(1025, 1024, 4096, 512) == (3, 0, 2)            # above 1024 tokens always tiled
     assert plan(1025, 4096, 4096, 512) == (2, 0, 0)            # more than 512 tiles of 64 tokens: 128 x 128 tiles
     assert plan(65, 14336, 4096, 512) == (3, 0, 2)             # a wide layer: tiles from 65 tokens on
-    for shape, want in STREAM_PLAN_SHAPES:
+    for shape, want in STREAM_PLAN_SHAPES + SECOND_SET_SHAPES:
         M, K, N, r = shape
         assert plan(M, N, K, r) == want, shape
+    assert all((shape[2] + 15) // 16 > 8 * 256 for shape, _ in SECOND_SET_SHAPES)
     f = binding.lib().resq_gemm_mixed_plan
     import ctypes
     a, b, c = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()

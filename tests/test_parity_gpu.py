@@ -589,6 +589,19 @@ def test_layer_every_token_group_and_run_count(oracle, rq, M, K, N, r):
     check_layer(oracle, rq, x, w, r, ldy_extra=8 if N % 4 == 0 else 3)
 
 
+def _second_set_shapes():
+    from test_boundary_cpu import SECOND_SET_SHAPES
+    return [shape for shape, _ in SECOND_SET_SHAPES]
+
+
+@pytest.mark.parametrize("M,K,N,r", _second_set_shapes())
+@pytest.mark.parametrize("asym", [False, True])
+def test_layer_second_set_of_a_workgroup(oracle, rq, M, K, N, r, asym):
+    # the chunked kernel's loop over sets: weights carried over the epilogue, constants and codes fetched anew
+    x, w = wl.random_small_case(M * 41 + K + N, M, K, N, r, outliers="first4")
+    (check_layer_asym if asym else check_layer)(oracle, rq, x, w, r, ldy_extra=3)
+
+
 def test_layer_batched_decode_full_size(oracle, rq):
     # the decode workload's layer with 64 tokens in flight; every accumulator and output
     s = wl.decode_shape(64)
