@@ -1025,8 +1025,8 @@ static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int swee
                                 int64_t ldp, void* workspace, void* stream) {
     const int n = (int)K;
     // one launch on LDS while the matrix and a slice of the vectors fit there, up to 128 columns:
-    // 1.1 to 1.35 ms at n = 128 against 6.9 to 10.5 in two launches a round, by the sweeps that the matrix
-    // needs (0.15 / 1.69 ms at n = 32, 0.39 / 4.9 at 64).  Not where an output lies on c: its workgroups all read c at their start and write p and
+    // 1.1 to 1.32 ms at n = 128 against 6.9 to 10.5 in two launches a round, by the sweeps that the matrix
+    // needs (0.13 to 0.15 / 1.69 ms at n = 32, 0.31 to 0.35 / 4.9 at 64).  Not where an output lies on c: its workgroups all read c at their start and write p and
     // eigvals at their end, in no order among each other; the workspace takes a copy of c first.
     if (n <= kEigSmallMax && !blocks_overlap(c, K, 4 * ldc, 4 * K, p, K, 4 * ldp, 4 * K) &&
         !blocks_overlap(c, K, 4 * ldc, 4 * K, eigvals, 1, 4 * K, 4 * K)) {
@@ -1039,7 +1039,7 @@ static int sym_eig_on_workspace(const float* c, int64_t ldc, int64_t K, int swee
             hipFuncSetAttribute(reinterpret_cast<const void*>(eig_small_kernel),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, small_lds) != hipSuccess)
             return RESQ_ERR_HIP;
-        launch(eig_small_kernel, dim3((unsigned)((n + kEigSmallCols - 1) / kEigSmallCols)), dim3(kEigSmallThreads),
+        launch(eig_small_kernel, dim3((unsigned)(n / kEigSmallCols)), dim3(kEigSmallThreads),
                small_lds, static_cast<hipStream_t>(stream), c, ldc, n, sweeps, eigvals, p, ldp);
         return launch_status();
     }

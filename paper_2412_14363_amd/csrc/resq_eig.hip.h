@@ -108,13 +108,13 @@ __global__ void eig_rotations_kernel(EigPlan e, int sweep, int round) {
 // the 2 x 2 block of two pairs lie in four planes: no bank is met twice.
 //
 // The vectors do not fit beside the matrix, but column j of Vt is rotated
-// independently of every other column: each of the n / 2 workgroups repeats
+// independently of every other column: each of the n / kEigSmallCols workgroups repeats
 // the iteration on the matrix (same arithmetic, same decisions) and carries two
 // columns of Vt, so that the workgroups never talk to each other.  (Eight columns are a tenth of the traffic of a workgroup's LDS,
 // which bounds a round of the large orders: n = 128 1267 us with eight, 1234 with four, 1208 with two.)
 //
 // One barrier a round.  Wavefront 0 is a round ahead: it turns the blocks that the diagonal blocks of the NEXT round
-// come from, and computes that round's angles, a chain of fp64 roots and quotients, while the others turn the matrix
+// come from, and computes that round's angles, a chain of two fp64 roots, while the others turn the matrix
 // by this round's and, two of them, the vectors.  (With the angles of a round between two barriers, 900 of 2870
 // clocks were theirs alone.)  What bounds a round of n = 128 now is LDS, 8 elements and 4 numbers of rotations a block, about
 // 1650 of 2050 clocks; of n = 64 and less the chain of wavefront 0.  Measured and not taken: two neighbouring rows of blocks to a wavefront, half of their elements handed
@@ -122,12 +122,14 @@ __global__ void eig_rotations_kernel(EigPlan e, int sweep, int round) {
 // vector instructions), n known to the compiler (14 % slower at 128: it joins reads of two planes into one
 // instruction, on the same banks), a thread's blocks loaded together (4 % slower).
 //
-// Measured, 12 sweeps allowed, two launches a round / two barriers a round / this kernel: n = 128 9.9 to 10.5 / 1.79 / 1.21 to 1.28 ms on a
-// covariance with a spectrum that decays by e^-6, - / 1.50 / 1.10 on that of Gaussian rows, which
-// converges in fewer sweeps; n = 100 - / 1.11 / 0.90, n = 64 4.9 / 0.58 / 0.35, n = 34 - / 0.22 / 0.15, n = 32 1.69 / 0.19 / 0.14.
+// Measured, 12 sweeps allowed, two launches a round / two barriers a round / this kernel: n = 128 9.9 to 10.5 / 1.79 / 1.20 to 1.32 ms on
+// covariances with a spectrum that decays by e^-6 (11 or 12 sweeps of 127 rounds, 0.86 us a round), - / 1.50 / 1.10 on that of
+// Gaussian rows (10 sweeps); n = 100 - / 1.11 / 0.89 (with eight columns of the vectors to a workgroup 0.93), n = 64 4.9 / 0.58 /
+// 0.35, n = 34 - / 0.22 / 0.15, n = 32 1.69 / 0.19 / 0.145.
 constexpr int kEigSmallMax = 128;
 constexpr int kEigSmallThreads = 1024;
 constexpr int kEigSmallCols = 2;  // columns of Vt per workgroup
+static_assert(kEigSmallCols == 2, "every workgroup has whole columns only, n being even");
 
 // As eig_rotations_kernel has it, |a01| > 2^-40 sqrt(|a00 a11|) and tan of the smaller angle =
 // sign(tau) / (|tau| + sqrt(1 + tau^2)), tau = (a11 - a00) / (2 a01), in a form with two roots and no quotient in
@@ -185,7 +187,7 @@ __host__ __device__ inline int eig_small_units(int half) { return (half + 1) >> 
 // doubles of one of the two buffers: the four planes, the diagonal blocks (three numbers each)
 // and a place that nothing reads; even, so that what lies behind is 16-byte aligned
 __host__ __device__ inline int eig_small_buf(int half) { return 4 * eig_small_units(half) * half + 3 * half + (half & 1) + 2; }
-// bytes of LDS: both buffers, both buffers of the Vt slice [n][8], cosines and sines of two rounds, two flags
+// bytes of LDS: both buffers, both buffers of the Vt slice [n][kEigSmallCols], cosines and sines of two rounds, two flags
 __host__ __device__ inline int eig_small_lds_bytes(int n) {
     return (2 * eig_small_buf(n / 2) + 2 * n * kEigSmallCols + 2 * n) * (int)sizeof(double) + 2 * (int)sizeof(int);
 }
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
     extern __shared__ __attribute__((aligned(16))) double lds[];
     const int half = n >> 1, units = eig_small_units(half), plane = units * half, bufsz = eig_small_buf(half);
     const int diag = 4 * plane;                        // a00[half], a11[half], a01[half] of the pairs
-    double* vt = lds + 2 * bufsz;                      // [2][n][8]: columns j0 .. j0 + 7 of Vt, rows by slot: half x + k
+    double* vt = lds + 2 * bufsz;                      // [2][n][kEigSmallCols]: columns of Vt from j0 on, rows by slot: half x + k
     double2* cs = reinterpret_cast<double2*>(vt + 2 * n * kEigSmallCols);  // [2][half]
     int* flag = reinterpret_cast<int*>(cs + n);        // [2]: does the round rotate anything
     const int t = threadIdx.x, lane = t & 63;
@@ -296,7 +298,7 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
         move(k1, x1);
         wr[1][0] = lk_on && half > 1 ? at(k0, x0, k1, x1) : unused;
     }
-    // wavefronts 8 .. 15: two rows of one column of Vt
+    // wavefronts 8 and 9, the first n threads: two rows of one column of Vt
     const int vk = (t - kEigSmallThreads / 2) / kEigSmallCols, vc = t & (kEigSmallCols - 1);
     const bool v_on = wave >= kWaves / 2 && vk < half;
     int vw[2];
@@ -410,7 +412,7 @@ __global__ __launch_bounds__(kEigSmallThreads) void eig_small_kernel(const float
     __syncthreads();
     for (int idx = t; idx < n * kEigSmallCols; idx += kEigSmallThreads) {
         const int col = idx / n, s = idx % n;
-        if (j0 + col < n) p[(int64_t)(j0 + col) * ldp + rank[s]] = (float)vt[((s & 1) * half + (s >> 1)) * kEigSmallCols + col];
+        p[(int64_t)(j0 + col) * ldp + rank[s]] = (float)vt[((s & 1) * half + (s >> 1)) * kEigSmallCols + col];
     }
 }
 

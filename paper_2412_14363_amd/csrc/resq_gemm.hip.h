@@ -49,7 +49,7 @@
 // the next stage's activation fragments in place behind the last products
 // that read their predecessors.  High stages multiply the fragments as read.  The
 // epilogue's per-channel and per-token constants (2.5 KiB, 4.5 KiB with
-// asymmetric codes) are fetched into LDS by the first loads of the kernel.
+// asymmetric codes) are fetched into LDS behind the loads of the first stages.
 //
 // The low group.  A lane's 16 packed bytes hold 32 codes, and each nibble is
 // widened to an int8 operand with one AND.  In an activation byte the low
@@ -92,7 +92,7 @@ constexpr int kPrefetch = kNumBuf - 1;  // stages requested ahead of the one bei
 constexpr int kLoadsPerStage = (kBM + kBN) / kRowsPerBlock / 4;  // per wavefront: 4 (two activation blocks, two weight blocks)
 constexpr int kOutRowBytes = kBN * 2 + 16;  // one tile row of bf16 in LDS, padded
 // After the stage buffers: the tile's per-channel and per-token constants of the
-// epilogue, copied there by the first loads of the kernel.
+// epilogue, which nothing reads before the last barrier in front of it.
 constexpr int kMetaOff = kNumBuf * kStageBytes;
 constexpr int kMetaSwHi = 0;       // fp16 [128] high-group weight scales
 constexpr int kMetaSwLo = 256;     // fp16 [128] low-group weight scales
@@ -415,8 +415,9 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
     const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
 
     // ---- epilogue constants -> LDS ---------------------------------------------
-    // Asked for behind the first stages, which the products wait for, and there long before the
-    // last stage is.  Token rows past M repeat the last row (never stored).
+    // Asked for behind the first stages, which the products wait for.  They have landed where stage S - 2 has waited for
+    // every load in flight; all wavefronts may rely on it behind the barrier of that wait.  Token rows past M repeat the
+    // last row (never stored).
     // (a load to LDS places an active lane's bytes at the base plus 16 x its lane number)
     auto load_constants = [&]() __attribute__((always_inline)) {
         if (wave == 0) {
@@ -672,7 +673,9 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_mixed_kernel(const GemmA
         park(acc_hi);
         park(acc_lo);
         __builtin_amdgcn_sched_barrier(0);
-        wait_stage_and_barrier(ahead - 1);  // stage 0 (and the epilogue constants) have landed everywhere
+        // Stage 0 has landed everywhere.  (The constants, up to six loads of a wavefront, are younger and not counted: the
+        // wait holds for that many loads of the next stages as well.)
+        wait_stage_and_barrier(ahead - 1);
         static_for<8>([&](auto k) __attribute__((always_inline)) { read_frag(k, p0, a_off, b_off); });
 
         // widening of a low stage's fragments: one AND over a fragment each

@@ -112,7 +112,8 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
     const bool asym = a.c_hi != nullptr || a.c_lo != nullptr;
 
     // ---- epilogue constants -> LDS, behind the first stages' loads ------------
-    // Token rows past M repeat the last row (never stored).
+    // Landed where the first ring's stage S - 2 has waited for every load in flight, for all wavefronts behind the barrier
+    // of that wait.  Token rows past M repeat the last row (never stored).
     auto load_constants = [&]() __attribute__((always_inline)) {
         if (half != 0) {
             // the first ring's wavefronts fetch them
@@ -333,7 +334,7 @@ __global__ __launch_bounds__(kGemmThreads * KS, KS == 1 ? 2 : 1) void gemm_mixed
         park(acc_hi);
         park(acc_lo);
         __builtin_amdgcn_sched_barrier(0);
-        wait_stages_and_barrier<kLoadsPerStage64, kPrefetch64 - 1>(ahead - 1);  // stage 0 and the constants have landed
+        wait_stages_and_barrier<kLoadsPerStage64, kPrefetch64 - 1>(ahead - 1);  // stage 0 has landed (see the wide kernel)
         static_for<6>([&](auto k) __attribute__((always_inline)) { read_frag(k, p0, a_off, b_off); });
 
         using YES = std::true_type;

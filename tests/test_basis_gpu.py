@@ -275,7 +275,7 @@ def test_sym_eig_order_two(rq, c, sweeps):
 
 
 # orders that take the single-launch kernel (at most 128): the smallest, odd and even numbers of
-# pairs, one more column than a slice of the vectors holds, and the first order beyond it
+# pairs, the largest, and the first order beyond it
 @pytest.mark.parametrize("K", [2, 4, 6, 18, 30, 32, 62, 98, 122, 126, 128, 130])
 def test_sym_eig_small_orders(rq, K):
     g = torch.Generator().manual_seed(K)
