@@ -479,7 +479,9 @@ static GemmPlan plan_gemm(int64_t M, const WeightLayout& L) {
         // Estimate per (token groups, runs): 1.9 us + rounds of 256 workgroups x (a fixed part + a
         // cost per 1 KiB block of a run), never less than one pass over the weights at 6 TB/s.
         // The constants are a least-squares fit to a sweep of all pairs over seven layer shapes and
-        // M = 24..512 (on which this choice is the measured best or within 1 % of it).
+        // M = 24..512, of kernels 0.5 to 1 us slower than the present ones.  With these the choice is within 1 % of the best
+        // on 67 of those 70 layers and on 60 of 70 drawn ones; on launches of more than 256 workgroups of one token group
+        // it is up to 77 % off (48 x 8008 -> 21726 44.3 us, (4, 1) 25.0), the second round being estimated too cheap.
         static const double kFixed[3][4] = {{1.46, 1.88, 0.31, 3.0}, {3.23, 4.72, 0.0, 0.0}, {4.62, 0.0, 0.0, 0.0}};
         static const double kPerBlock[3][4] = {{0.139, 0.146, 0.250, 0.45}, {0.170, 0.194, 0.0, 0.0}, {0.257, 0.0, 0.0, 0.0}};
         const double pass_us = (double)L.total_bytes / 6.0e6;
@@ -511,7 +513,8 @@ static GemmPlan plan_gemm(int64_t M, const WeightLayout& L) {
     const int64_t tiles64 = ((M + kBM64 - 1) / kBM64) * ((L.N + kBN - 1) / kBN);
     const bool narrow = tiles64 <= 512;
     const int rings = narrow ? (tiles64 <= 256 ? 2 : 1) : 0;
-    bool streaming = M <= kStreamMaxM;  // (measured: the streaming kernel is ahead or equal there on every shape)
+    // (measured ahead or equal there on the seven shapes of that sweep; not on all: 43 x 2272 -> 16876 12.3 us, tiles 9.3)
+    bool streaming = M <= kStreamMaxM;
     if (!streaming && tg != 0) {
         if (narrow) {
             // Fits to the sweep (within 10 %).  One ring: a workgroup alone on its compute unit
